@@ -17,8 +17,10 @@
 #include "common.h"
 #include "dense_path.h"
 #include "dispatch.h"
+#include "few_tokens.h"
 #include "gather.h"
 #include "gemm_nt.h"
+#include "router.h"
 #include "scatter.h"
 #include "select.h"
 #include "small_groups.h"
@@ -124,6 +126,14 @@ bool use_dense(const meft_shape& s) {
          C <= kMaxLdsC;
 }
 
+// The forward of a few tokens (few_tokens.h): as many entries as one workgroup looks through, and on average at most
+// two 16-token tiles per block.  Such a forward leaves nothing in the workspace for the backward.
+bool few_tokens(const meft_shape& s) {
+  const int64_t n_ent = (int64_t)s.T * s.top_e;
+  return n_ent <= kFewEntries && n_ent <= (int64_t)32 * s.n_blocks && s.top_e <= kFewMaxE && s.top_k <= kTopkEmitLds &&
+         (int64_t)s.top_e * s.block_size <= kMaxLdsC;
+}
+
 int round64(int v) { return (v + 63) & ~63; }
 // Block-dense path: groups of at most this many tokens go to the per-pair kernels of small_groups.h (0: none).  The
 // tile schedule knows the small groups only where it deals the groups out longest first.
@@ -144,6 +154,7 @@ int tile_bound(const meft_shape& s, int tn) {
 }
 
 constexpr int kRouterSplitMax = 4;
+constexpr int64_t kRouteTiledMin = 4096 * 64;   // token-block pairs from which the tiled router contraction is used
 
 struct RouteWs {
   float* p;
@@ -639,24 +650,82 @@ void launch_neu(const char* name, const NeuArgs& a, hipStream_t st) {
 
 using namespace meft;
 
+// the few-token forward: scores, then selection and value sum
+template <typename T>
+static meft_status launch_few(const meft_shape& s, const void* h, const void* K, const void* V, const int32_t* block_idx, void* out,
+                       int32_t* idx, float* act, float* sc, hipStream_t st, hipEvent_t wait_v) {
+  const int n_ent = s.T * s.top_e, C = s.top_e * s.block_size;
+  const int by_block = s.n_blocks <= n_ent ? 1 : 0, rows = by_block ? s.n_blocks : n_ent;
+  const T *hh = static_cast<const T*>(h), *kk = static_cast<const T*>(K), *vv = static_cast<const T*>(V);
+  // two 16-neuron tiles per workgroup (they share the loads of h) where that leaves a workgroup for every compute unit
+#define FS(NA) MEFT_LAUNCH("few_score", (few_score_kernel<T, NA>), dim3((s.block_size + 16 * (NA) - 1) / (16 * (NA)), rows), dim3(64 * kFewWaves), 0, st, hh, kk, block_idx, n_ent, s.top_e, s.n_blocks, s.block_size, s.d, by_block, sc)
+  if (rows * ((s.block_size + 31) / 32) >= kPersistentWgs) FS(2);
+  else FS(1);
+#undef FS
+  if (wait_v && hipStreamWaitEvent(st, wait_v, 0) != hipSuccess) return MEFT_ERR_DEVICE;
+  T* o = static_cast<T*>(out);
+  // 512 columns per workgroup, 128 where that leaves compute units without one
+  const bool wide = (int64_t)s.T * ((s.d + 511) / 512) >= kPersistentWgs;
+  const int cols = wide ? 512 : 128;
+  const dim3 grid(out ? (s.d + cols - 1) / cols : 1, s.T);
+#define FO3(KPT, FULL, CL) MEFT_LAUNCH("few_out", (few_out_kernel<T, KPT, FULL, CL>), grid, dim3(256), 0, st, sc, block_idx, vv, C, s.block_size, s.top_e, s.top_k, s.n_blocks, s.d, idx, act, o)
+#define FO2(KPT, FULL) do { if (wide) FO3(KPT, FULL, 64); else FO3(KPT, FULL, 16); } while (0)
+#define FO(KPT) do { if (C == 256 * (KPT)) FO2(KPT, true); else FO2(KPT, false); } while (0)
+  if (C <= 256 * 4) FO(4);
+  else if (C <= 256 * 8) FO(8);
+  else if (C <= 256 * 16) FO(16);
+  else if (C <= 256 * 32) FO(32);
+  else FO(48);
+#undef FO
+#undef FO2
+#undef FO3
+  return launch_status();
+}
+
+// Partial router scores without LDS tiles; returns the number of slices of the hidden dimension (at most
+// kRouterSplitMax).
+template <typename T>
+static int launch_route_part(const meft_shape& s, const void* h, const void* Wg, float* p, hipStream_t st) {
+  const T *hh = static_cast<const T*>(h), *ww = static_cast<const T*>(Wg);
+  const int steps = (int)(((int64_t)s.d * sizeof(T) + 63) / 64);
+  // a slice of at least four 64-byte steps per wave: one batch of loads
+  const int want = steps / (4 * kRouteWaves), n_part = want < 1 ? 1 : (want > kRouterSplitMax ? kRouterSplitMax : want);
+#define RP(NA, TT) MEFT_LAUNCH("route_part", (route_part_kernel<T, NA, TT>), dim3((s.n_blocks + 16 * (NA) - 1) / (16 * (NA)), (s.T + 16 * (TT) - 1) / (16 * (TT)), n_part), dim3(64 * kRouteWaves), 0, st, hh, ww, s.T, s.d, s.n_blocks, p)
+  // one 16-block tile per workgroup for the few tokens that would leave the chip idle, else four (they share the
+  // loads of h), and two token tiles (they share the loads of the router) once that still fills it
+  const int64_t wg = (int64_t)((s.T + 15) / 16) * ((s.n_blocks + 63) / 64) * n_part;
+  if (wg < kPersistentWgs / 4) RP(1, 1);
+  else if (wg < 2 * kPersistentWgs) RP(4, 1);
+  else RP(4, 2);
+#undef RP
+  return n_part;
+}
+
 // Router scores (as up to kRouterSplitMax partial sums over slices of the hidden dimension, in `p`) and the top-e
 // selection over their sum.
 static meft_status route_impl(const meft_shape& s, const void* h, const void* Wg, const float* bias,
                               int32_t* block_idx, float* block_score, float* p, hipStream_t st) {
   int n_part = 1;
-  if (s.dtype == MEFT_BF16 && s.d % kTK == 0) {
+  // The tiled contraction takes bf16 problems that fill the chip with its 128-token tiles.  Measured at d = 4096 and
+  // 64 blocks, this launch tiled / untiled: 13.1 / 3.4 us (1 token), 18.0 / 8.8 us (777); 8192 tokens: 20.3 us tiled,
+  // where the untiled one re-reads h and the router too often.
+  if (s.dtype == MEFT_BF16 && s.d % kTK == 0 && (int64_t)s.T * s.n_blocks > kRouteTiledMin) {
     const int kt = s.d / kTK;
     n_part = kt % 4 == 0 ? 4 : (kt % 2 == 0 ? 2 : 1);
     ProbRouter pr{static_cast<const uint16_t*>(h), static_cast<const uint16_t*>(Wg), p, s.T, s.d, s.n_blocks, n_part};
     set_gemm_extents(pr, (uint64_t)s.T * s.d * 2, (uint64_t)s.n_blocks * s.d * 2);
     launch_gemm_mfma("router_gemm", pr, n_part * ((s.T + ProbRouter::kTM - 1) / ProbRouter::kTM) * ((s.n_blocks + kTN - 1) / kTN), st);
   } else {
-    GemmNTArgs a{};
-    a.A = h; a.Bm = Wg; a.C = p; a.perm = nullptr; a.group_off = nullptr; a.tile_off = nullptr;
-    a.n_groups = 1; a.M = s.T; a.Ng = s.n_blocks; a.Kdim = s.d; a.lda = s.d; a.ldb = s.d; a.ldc = s.n_blocks;
-    a.e = 1;
-    launch_gemm_nt(s, a, (s.T + kGemmBM - 1) / kGemmBM, (s.T + kGemmF32BM - 1) / kGemmF32BM, "router_gemm", st);
+    n_part = s.dtype == MEFT_BF16 ? launch_route_part<bf16_t>(s, h, Wg, p, st) : launch_route_part<float>(s, h, Wg, p, st);
   }
+  const size_t stride = (size_t)s.T * s.n_blocks;
+#define PK(Z) MEFT_LAUNCH("route_pick", (route_pick_kernel<Z>), dim3((s.T + 3) / 4), dim3(256), 0, st, p, n_part, stride, bias, s.T, s.n_blocks, s.top_e, block_idx, block_score)
+  if (s.n_blocks <= 64) PK(1);
+  else if (s.n_blocks <= 128) PK(2);
+  else if (s.n_blocks <= 256) PK(4);
+  else if (s.n_blocks <= 1024) PK(16);
+  else
+#undef PK
   MEFT_LAUNCH("route_topk", route_topk_kernel, dim3(s.T), dim3(64), (size_t)s.n_blocks * 4, st, p, n_part,
               (size_t)s.T * s.n_blocks, bias,
               s.n_blocks, s.top_e, block_idx, block_score);
@@ -672,6 +741,11 @@ static meft_status fwd_impl(const meft_shape& s, const void* h, const void* K, c
   const int C = s.top_e * s.block_size;
   const int BM = s.dtype == MEFT_BF16 ? kGemmBM : kGemmF32BM;
 
+  if (few_tokens(s)) {
+    if (wait_k && hipStreamWaitEvent(st, wait_k, 0) != hipSuccess) return MEFT_ERR_DEVICE;
+    return s.dtype == MEFT_BF16 ? launch_few<bf16_t>(s, h, K, V, block_idx, out, idx, act, w.sc, st, wait_v)
+                                : launch_few<float>(s, h, K, V, block_idx, out, idx, act, w.sc, st, wait_v);
+  }
   const bool dense = use_dense(s);
   MEFT_LAUNCH("sort_blocks", sort_blocks_kernel, dim3((s.T + 255) / 256), dim3(256), 0, st, block_idx, s.T,
               s.top_e, s.n_blocks, w.sblk);
@@ -753,7 +827,7 @@ static meft_status bwd_impl(const meft_shape& s, const void* h, const void* K, c
                    *vv = static_cast<const uint16_t*>(V), *gg = static_cast<const uint16_t*>(dOut);
     // With MEFT_FLAG_REUSE_FWD the dispatch tables and the activation rows A' are the ones the forward of this step
     // left in the workspace; otherwise they are rebuilt from (idx, act).
-    const bool reuse = (s.flags & MEFT_FLAG_REUSE_FWD) != 0;
+    const bool reuse = (s.flags & MEFT_FLAG_REUSE_FWD) != 0 && !few_tokens(s);
     if (!reuse) {
       MEFT_LAUNCH("blocks_from_idx", blocks_from_idx_kernel, dim3(s.T), dim3(64), (size_t)((s.n_blocks + 31) / 32) * 4,
                   st, idx, s.top_k, s.N, s.block_size, s.n_blocks, s.top_e, w.sblk);

@@ -7,7 +7,7 @@
 namespace meft {
 
 // ---------------------------------------------------------------------------------------------
-// Top-e blocks (Algorithm 1: tau <- TopK(p, number of experts)).  One wave per token.  The row of
+// Top-e blocks of more than 1024 blocks (router.h has the kernel for fewer).  One wave per token.  The row of
 // B scores sits in LDS as ordered keys; e rounds of a wave-wide arg-max, the winner is retired
 // by zeroing its key (a live key is never 0 for finite scores).  Output order: score descending,
 // block id ascending.  The scores may arrive as n_part partial sums, part_stride floats apart.
@@ -169,26 +169,22 @@ constexpr int kTopkEmitLds = 1024;   // selections per token that go through LDS
 // at eight); with more keys per thread as many as hold them without spilling.
 constexpr int topk_waves(int kpt) { return kpt <= 16 ? 7 : (kpt <= 32 ? 4 : 2); }
 
-template <int KPT, bool kFull>   // kFull: C == 256 * KPT, every position holds a candidate
-__global__ __launch_bounds__(256, topk_waves(KPT)) void topk_select_reg_kernel(const float* __restrict__ sc,
-                                                              const int32_t* __restrict__ sblk, int C, int bs,
-                                                              int e, int k, int32_t* __restrict__ idx,
-                                                              float* __restrict__ act,
-                                                              const int32_t* __restrict__ slot_of_ent, int bsp,
-                                                              uint16_t* __restrict__ Ap) {
-  __shared__ int s_hist[256];
-  __shared__ int s_w[4];
-  __shared__ uint32_t s_prefix;
-  __shared__ int s_need;
-  __shared__ int s_done;
+struct TopkLds {
+  int hist[256];
+  int w[4];
+  uint32_t prefix;
+  int need;
+  int done;
   // staging for the outputs: the sweep reaches a selected position in a few lanes at a time, and that many nearly
   // empty global stores would cost more than everything before them
-  __shared__ int s_idx[kTopkEmitLds];
-  __shared__ float s_act[kTopkEmitLds];
-  const int t = blockIdx.x, tid = threadIdx.x;
-  const float* row = sc + (size_t)t * C;
-  const int p0 = tid * KPT;
-  uint32_t key[KPT];   // 0 for positions beyond C: below every real key, never selected
+  int idx[kTopkEmitLds];
+  float act[kTopkEmitLds];
+};
+
+// The thread's keys: order keys of the positions p0 .. p0 + KPT - 1 of the row, 0 for positions beyond C (below every
+// real key, never selected).
+template <int KPT>
+__device__ __forceinline__ void topk_load_keys(const float* __restrict__ row, int C, int p0, uint32_t (&key)[KPT]) {
   if ((C & 3) == 0 && (KPT & 3) == 0) {
 #pragma unroll
     for (int z = 0; z < KPT; z += 4) {
@@ -203,13 +199,20 @@ __global__ __launch_bounds__(256, topk_waves(KPT)) void topk_select_reg_kernel(c
 #pragma unroll
     for (int z = 0; z < KPT; ++z) key[z] = p0 + z < C ? order_key(row[p0 + z]) : 0u;
   }
-  if (tid == 0) { s_prefix = 0u; s_need = k; s_done = 0; }
+}
+
+// The selection's threshold: every key above `thr` is selected, and the first `need` positions that equal it.
+template <int KPT, bool kFull>
+__device__ __forceinline__ void topk_threshold(const uint32_t (&key)[KPT], int C, int p0, int k, TopkLds& s, uint32_t& thr,
+                                               int& need_eq) {
+  const int tid = threadIdx.x;
+  if (tid == 0) { s.prefix = 0u; s.need = k; s.done = 0; }
   __syncthreads();
 
   for (int shift = 24; shift >= 0; shift -= 8) {
-    s_hist[tid] = 0;
+    s.hist[tid] = 0;
     __syncthreads();
-    const uint32_t prefix = s_prefix;
+    const uint32_t prefix = s.prefix;
     const uint32_t himask = shift == 24 ? 0u : (0xFFFFFFFFu << (shift + 8));
     // A thread adds a run of equal digits with one atomic (that takes most of the same-address conflicts out of the
     // first pass).  Written without nested branches: a run ends where a matching key has another digit; the first
@@ -221,38 +224,43 @@ __global__ __launch_bounds__(256, topk_waves(KPT)) void topk_select_reg_kernel(c
       const bool m = (kFull || p0 + z < C) && (key[z] & himask) == prefix;
       const uint32_t dgt = (key[z] >> shift) & 255u;
       const bool start = m && dgt != cur;
-      if (start) atomicAdd(&s_hist[cur], cnt);
+      if (start) atomicAdd(&s.hist[cur], cnt);
       cnt = (start ? 0 : cnt) + (m ? 1 : 0);
       cur = start ? dgt : cur;
     }
-    atomicAdd(&s_hist[cur], cnt);
+    atomicAdd(&s.hist[cur], cnt);
     __syncthreads();
     // thread `tid` owns digit 255 - tid, so that an exclusive scan counts the larger digits
     const int digit = 255 - tid;
-    const int h = s_hist[digit];
+    const int h = s.hist[digit];
     int tot;
-    const int above = block_excl_scan_256(h, s_w, tot);
-    const int need = s_need;
+    const int above = block_excl_scan_256(h, s.w, tot);
+    const int need = s.need;
     __syncthreads();
     if (above < need && need <= above + h) {
       const uint32_t found = prefix | ((uint32_t)digit << shift);
       if (h == need - above && shift > 0 && found != 0u) {
         // every key with these leading digits is selected: "greater than found - 1" says the same as a threshold
         // with all digits known, and the remaining passes are not needed (the usual case after three passes)
-        s_prefix = found - 1u;
-        s_need = 0;
-        s_done = 1;
+        s.prefix = found - 1u;
+        s.need = 0;
+        s.done = 1;
       } else {
-        s_prefix = found;
-        s_need = need - above;
+        s.prefix = found;
+        s.need = need - above;
       }
     }
     __syncthreads();
-    if (s_done) break;
+    if (s.done) break;
   }
-  const uint32_t thr = s_prefix;
-  const int need = s_need;  // how many keys equal to thr are selected
+  thr = s.prefix;
+  need_eq = s.need;  // how many keys equal to thr are selected
+}
 
+// Number of keys above the threshold and of keys equal to it at the positions before this thread's.
+template <int KPT, bool kFull>
+__device__ __forceinline__ void topk_counts_before(const uint32_t (&key)[KPT], int C, int p0, uint32_t thr, TopkLds& s,
+                                                   int& gt_before, int& eq_before) {
   int ngt = 0, neq = 0;
 #pragma unroll
   for (int z = 0; z < KPT; ++z) {
@@ -260,35 +268,62 @@ __global__ __launch_bounds__(256, topk_waves(KPT)) void topk_select_reg_kernel(c
     neq += (kFull || p0 + z < C) && key[z] == thr;
   }
   int tot;
-  const int packed = block_excl_scan_256(ngt | (neq << 16), s_w, tot);  // C <= 12288 < 2^15
-  int gt_before = packed & 0xFFFF, eq_before = packed >> 16;
-  uint32_t sel = 0u;   // bit z: position p0 + z is selected (KPT <= 32 bits used per word)
-  uint32_t sel_hi = 0u;
+  const int packed = block_excl_scan_256(ngt | (neq << 16), s.w, tot);  // C <= 12288 < 2^15
+  gt_before = packed & 0xFFFF;
+  eq_before = packed >> 16;
+}
+
+// The selected (position, key) pairs of the output slots base .. base + kTopkEmitLds - 1 into the staging arrays, and
+// which of the thread's positions are selected (bit z of sel, z - 32 of sel_hi: position p0 + z).
+template <int KPT, bool kFull>
+__device__ __forceinline__ void topk_stage(const uint32_t (&key)[KPT], int C, int p0, uint32_t thr, int need, int gt_before,
+                                           int eq_before, int base, TopkLds& s, uint32_t& sel, uint32_t& sel_hi) {
+  int gt_run = gt_before, eq_run = eq_before;
+#pragma unroll
+  for (int z = 0; z < KPT; ++z) {
+    const bool in = kFull || p0 + z < C;
+    const bool gt = key[z] > thr, eq = in && key[z] == thr;
+    if (gt || (eq && eq_run < need)) {
+      const int slot = gt_run + min(eq_run, need) - base;  // selected positions before this one
+      if ((unsigned)slot < (unsigned)kTopkEmitLds) {
+        s.idx[slot] = p0 + z;
+        s.act[slot] = __uint_as_float(key[z]);
+      }
+      if (z < 32) sel |= 1u << z; else sel_hi |= 1u << (z - 32);
+    }
+    gt_run += gt;
+    eq_run += eq;
+  }
+}
+
+template <int KPT, bool kFull>   // kFull: C == 256 * KPT, every position holds a candidate
+__global__ __launch_bounds__(256, topk_waves(KPT)) void topk_select_reg_kernel(const float* __restrict__ sc,
+                                                              const int32_t* __restrict__ sblk, int C, int bs,
+                                                              int e, int k, int32_t* __restrict__ idx,
+                                                              float* __restrict__ act,
+                                                              const int32_t* __restrict__ slot_of_ent, int bsp,
+                                                              uint16_t* __restrict__ Ap) {
+  __shared__ TopkLds s;
+  const int t = blockIdx.x, tid = threadIdx.x;
+  const int p0 = tid * KPT;
+  uint32_t key[KPT];
+  topk_load_keys<KPT>(sc + (size_t)t * C, C, p0, key);
+  uint32_t thr;
+  int need;
+  topk_threshold<KPT, kFull>(key, C, p0, k, s, thr, need);
+  int gt_before, eq_before;
+  topk_counts_before<KPT, kFull>(key, C, p0, thr, s, gt_before, eq_before);
+  uint32_t sel = 0u, sel_hi = 0u;
   const int q0 = p0 / bs, r0 = p0 - q0 * bs;   // block entry and row of the thread's first position
   // The selected (position, key) pairs go to their output slots through LDS, kTopkEmitLds slots at a time (one round
   // unless top_k is larger than that); the write-out turns a position into a neuron number and a key into max(score, 0).
   for (int base = 0; base < k; base += kTopkEmitLds) {
-    int gt_run = gt_before, eq_run = eq_before;
-#pragma unroll
-    for (int z = 0; z < KPT; ++z) {
-      const bool in = kFull || p0 + z < C;
-      const bool gt = key[z] > thr, eq = in && key[z] == thr;
-      if (gt || (eq && eq_run < need)) {
-        const int slot = gt_run + min(eq_run, need) - base;  // selected positions before this one
-        if ((unsigned)slot < (unsigned)kTopkEmitLds) {
-          s_idx[slot] = p0 + z;
-          s_act[slot] = __uint_as_float(key[z]);
-        }
-        if (z < 32) sel |= 1u << z; else sel_hi |= 1u << (z - 32);
-      }
-      gt_run += gt;
-      eq_run += eq;
-    }
+    topk_stage<KPT, kFull>(key, C, p0, thr, need, gt_before, eq_before, base, s, sel, sel_hi);
     __syncthreads();
     const int n_out = min(k - base, kTopkEmitLds);
     for (int j = tid; j < n_out; j += 256) {
-      const int i = s_idx[j], q = i / bs;
-      const float v = key_to_float(__float_as_uint(s_act[j]));
+      const int i = s.idx[j], q = i / bs;
+      const float v = key_to_float(__float_as_uint(s.act[j]));
       idx[(size_t)t * k + base + j] = sblk[(size_t)t * e + q] * bs + (i - q * bs);
       act[(size_t)t * k + base + j] = v > 0.f ? v : 0.f;
     }
