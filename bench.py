@@ -65,7 +65,8 @@ def kernel_models(cfg, n_touched):
         "dK_gemm": dict(bound="hbm", flop=pair, bytes=act + P * 8.0 + rows, dense_flop=dense),
         # the sum of a token's per-block partial rows is part of the value / dh stage: its compulsory bytes are
         # already counted there (the partial rows themselves are traffic the design adds)
-        "reduce_parts": dict(bound="hbm", flop=0.0, bytes=0.0),
+        "out_rows": dict(bound="hbm", flop=0.0, bytes=0.0),
+        "dh_rows": dict(bound="hbm", flop=0.0, bytes=0.0),
     }
     # whole step: h, dOut, K, V read once; out, dh and the touched rows of dK, dV written once; idx / act both ways
     m["_step"] = dict(bound="hbm", flop=2.0 * T * B * d + dense + 5 * pair,
@@ -82,7 +83,7 @@ STAGE_SYMBOL = {
     "dV_gemm": ("gemm_mfma_kernel<ProbNeuTN<256>, true>", "gemm_mfma_kernel<ProbNeuTN<128>, true>"),
     "dK_gemm": ("gemm_mfma_kernel<ProbNeuTN<256>, true>", "gemm_mfma_kernel<ProbNeuTN<128>, true>"),
     "topk_select": ("topk_select_reg_kernel<16, true>", "topk_select_reg_kernel<32, true>", "topk_select_reg_kernel<4, true>"),
-    "reduce_parts": "reduce_parts_kernel<2>",
+    "out_rows": "token_rows_kernel<2, false>", "dh_rows": "token_rows_kernel<2, false>",
 }
 GATHER_SCATTER = ("value_gemm", "dact_gemm", "dh_gemm", "dV_gemm", "dK_gemm", "gather_fwd", "gather_bwd", "seg_reduce")
 

@@ -99,14 +99,17 @@ __device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long v)
   return v;
 }
 
-// inclusive prefix sum across the wave
+// inclusive prefix sum across the wave: DPP moves (row shifts, then the rows' totals broadcast), which stay in the vector
+// unit; through LDS permutes a scan takes about 700 cycles, most of a selection pass or of a dispatch table
 __device__ __forceinline__ int wave_incl_scan(int v) {
-  const int lane = threadIdx.x & (kWave - 1);
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    const int w = __shfl_up(v, o, kWave);
-    if (lane >= o) v += w;
-  }
+#define MEFT_DPP_ADD(ctrl, rows) v += __builtin_amdgcn_update_dpp(0, v, ctrl, rows, 0xF, false)
+  MEFT_DPP_ADD(0x111, 0xF);   // row_shr:1
+  MEFT_DPP_ADD(0x112, 0xF);   // row_shr:2
+  MEFT_DPP_ADD(0x114, 0xF);   // row_shr:4
+  MEFT_DPP_ADD(0x118, 0xF);   // row_shr:8
+  MEFT_DPP_ADD(0x142, 0xA);   // row_bcast:15 into rows 1 and 3
+  MEFT_DPP_ADD(0x143, 0xC);   // row_bcast:31 into rows 2 and 3
+#undef MEFT_DPP_ADD
   return v;
 }
 

@@ -16,6 +16,7 @@
 #pragma once
 #include "gemm_mfma.h"
 #include "select.h"
+#include "small_groups.h"
 
 namespace meft {
 
@@ -299,14 +300,16 @@ __global__ __launch_bounds__(64) void blocks_from_idx_kernel(const int32_t* __re
 // After fill_groups: slot -> token (padded by kSlotPad valid entries) and entry -> slot.
 __global__ __launch_bounds__(256) void slot_maps_kernel(const int32_t* __restrict__ perm,
                                                         const int32_t* __restrict__ group_off, int n_groups, int e,
+                                                        const int32_t* __restrict__ sblk, int small_rows,
                                                         int32_t* __restrict__ tok_of_slot,
                                                         int32_t* __restrict__ slot_of_ent) {
   const int n_slots = group_off[n_groups];
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i < n_slots) {
     const int ent = perm[i];
+    const int b = sblk[ent];
     tok_of_slot[i] = ent / e;
-    slot_of_ent[ent] = i;
+    slot_of_ent[ent] = group_off[b + 1] - group_off[b] <= small_rows ? (i | kSmallSlot) : i;
   } else if (i < n_slots + kSlotPad) {
     tok_of_slot[i] = 0;
   }
@@ -341,46 +344,51 @@ __global__ __launch_bounds__(256) void act_rows_kernel(const int32_t* __restrict
   for (int w = tid; w < words; w += 256) {
     const int q = w / wpr, c = w - q * wpr;
     if (sblk[(size_t)t * e + q] < 0) continue;   // fewer than e blocks in use: no slot
-    reinterpret_cast<u32x4*>(Ap + (size_t)slot_of_ent[t * e + q] * bsp)[c] = s4[w];
+    reinterpret_cast<u32x4*>(Ap + (size_t)(slot_of_ent[t * e + q] & ~kSmallSlot) * bsp)[c] = s4[w];
   }
 }
 
-// out[t, :] = sum over the token's entries of part[slot(entry), :] (bf16 partials, fp32 sum), rounded to bf16.
-template <int NV>
-__global__ __launch_bounds__(256) void reduce_parts_kernel(const uint16_t* __restrict__ part,
-                                                           const int32_t* __restrict__ sblk,
-                                                           const int32_t* __restrict__ slot_of_ent, int d, int e,
-                                                           uint16_t* __restrict__ out) {
-  const int t = blockIdx.x, tid = threadIdx.x, nthr = blockDim.x;
-  float acc[NV][8];
-#pragma unroll
-  for (int v = 0; v < NV; ++v)
-#pragma unroll
-    for (int c = 0; c < 8; ++c) acc[v][c] = 0.f;
-  for (int q = 0; q < e; ++q) {
-    if (sblk[(size_t)t * e + q] < 0) continue;
-    const bf16_t* row = reinterpret_cast<const bf16_t*>(part) + (size_t)slot_of_ent[t * e + q] * d;
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-      const int col = (tid + v * nthr) * 8;
-      if (col < d) {
-        float x[8];
-        Vec8<bf16_t>::load(row + col, x);
-#pragma unroll
-        for (int c = 0; c < 8; ++c) acc[v][c] += x[c];
-      }
-    }
+// out[t, :] or dh[t, :] of every token (token_rows_body); with dvdk workers in front (backward): the dV and dK rows of the
+// small groups, which do not depend on them.  Dynamic LDS: k pairs.
+struct SmallDvdk {
+  int n_wg, nx, ny;      // workgroups in front of the tokens' (0: none), nx x ny workers
+  const bf16_t *h, *dOut;
+  const float *act, *ds32;
+  const int32_t *small_grp, *small_cnt, *group_off, *tok_of_slot;
+  bf16_t *dK, *dV;
+};
+
+template <int NV, bool kSplit>
+__global__ __launch_bounds__(256) void token_rows_kernel(TokenRows a, SmallDvdk s) {
+  extern __shared__ int2 s_pairs[];
+  __shared__ int s_blk[kTokenRowsBlocks];
+  __shared__ int s_w[4];
+  __shared__ float s_red[kSplit ? 3 : 1][kSplit ? kSmallCols : 1];
+  const int w = blockIdx.x;
+  if (w < s.n_wg) {
+    small_dvdk_body(w % s.nx, w / s.nx, s.ny, s.h, s.dOut, a.idx, s.act, s.ds32, s.small_grp, s.small_cnt, s.group_off,
+                    s.tok_of_slot, a.d, a.k, a.N, a.bs, s.dK, s.dV);
+    return;
   }
-#pragma unroll
-  for (int v = 0; v < NV; ++v) {
-    const int col = (tid + v * nthr) * 8;
-    if (col < d) Vec8<bf16_t>::store(reinterpret_cast<bf16_t*>(out) + (size_t)t * d + col, acc[v]);
+  if constexpr (kSplit) {
+    const int chunks = (a.d + kSmallCols - 1) / kSmallCols, z = w - s.n_wg;
+    token_rows_split_body(a, z / chunks, z % chunks, s_pairs, s_blk, s_w, s_red);
+  } else {
+    token_rows_body<NV>(a, w - s.n_wg, s_pairs, s_blk, s_w);
   }
 }
 
-// touched = ascending ids with flag > 0, in two launches over chunks of kFlagChunk flags:
-// per-chunk counts, then every chunk sums the counts before it and writes its ids in order.
+__global__ __launch_bounds__(256) void small_dvdk_kernel(TokenRows a, SmallDvdk s) {   // no dh wanted
+  const int w = blockIdx.x;
+  small_dvdk_body(w % s.nx, w / s.nx, s.ny, s.h, s.dOut, a.idx, s.act, s.ds32, s.small_grp, s.small_cnt, s.group_off,
+                  s.tok_of_slot, a.d, a.k, a.N, a.bs, s.dK, s.dV);
+}
+
+// touched = ascending ids with flag > 0, in chunks of kFlagChunk flags: a workgroup of 256 threads counts the flags
+// before its chunk itself (they come out of L2; a launch for the counts costs more up to kFlagCountMax flags), or takes
+// the chunk counts that count_flags_kernel left, and writes its ids in order.
 constexpr int kFlagChunk = 2048;
+constexpr int kFlagCountMax = 1 << 17;
 
 __global__ __launch_bounds__(256) void count_flags_kernel(const int32_t* __restrict__ flag, int N,
                                                           int32_t* __restrict__ chunk_cnt) {
@@ -395,16 +403,25 @@ __global__ __launch_bounds__(256) void count_flags_kernel(const int32_t* __restr
   if (threadIdx.x == 0) chunk_cnt[blockIdx.x] = tot;
 }
 
-__global__ __launch_bounds__(256) void compact_flags_kernel(const int32_t* __restrict__ flag, int N,
-                                                            const int32_t* __restrict__ chunk_cnt,
-                                                            int32_t* __restrict__ touched,
-                                                            int32_t* __restrict__ n_touched) {
-  __shared__ int s_w[4];
+// chunk_cnt == nullptr: no counts were taken
+__device__ __forceinline__ void compact_flags_body(const int32_t* __restrict__ flag, int N,
+                                                   const int32_t* __restrict__ chunk_cnt, int chunk, int n_chunks,
+                                                   int32_t* __restrict__ touched, int32_t* __restrict__ n_touched,
+                                                   int* s_w) {
   int before = 0;
-  for (int c = threadIdx.x; c < (int)blockIdx.x; c += 256) before += chunk_cnt[c];
+  if (chunk_cnt != nullptr) {
+    for (int c = threadIdx.x; c < chunk; c += 256) before += chunk_cnt[c];
+  } else {
+    const i32x4* f4 = reinterpret_cast<const i32x4*>(flag);
+#pragma unroll 8
+    for (int c = threadIdx.x; c < chunk * (kFlagChunk / 4); c += 256) {
+      const i32x4 v = f4[c];
+      before += (v.x > 0) + (v.y > 0) + (v.z > 0) + (v.w > 0);
+    }
+  }
   int base;
   block_excl_scan_256(before, s_w, base);   // base = number of touched ids in earlier chunks
-  const int j0 = blockIdx.x * kFlagChunk + threadIdx.x * (kFlagChunk / 256);
+  const int j0 = chunk * kFlagChunk + threadIdx.x * (kFlagChunk / 256);
   int f = 0;
 #pragma unroll
   for (int z = 0; z < kFlagChunk / 256; ++z)
@@ -414,7 +431,26 @@ __global__ __launch_bounds__(256) void compact_flags_kernel(const int32_t* __res
 #pragma unroll
   for (int z = 0; z < kFlagChunk / 256; ++z)
     if (j0 + z < N && flag[j0 + z] > 0) touched[pos++] = j0 + z;
-  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 255) *n_touched = base + tot;
+  if (chunk == n_chunks - 1 && threadIdx.x == 255) *n_touched = base + tot;
+}
+
+// What the backward does before its contractions: workgroups 0 .. n_chunks - 1 write the touched list, the others
+// (nx x kSmallPairSplit workers, 0: none) the activation gradients of the small groups' pairs.  Dynamic LDS: k ints.
+__global__ __launch_bounds__(256) void bwd_head_kernel(const int32_t* __restrict__ flag, int N,
+                                                       const int32_t* __restrict__ chunk_cnt, int n_chunks,
+                                                       int32_t* __restrict__ touched, int32_t* __restrict__ n_touched,
+                                                       int nx, const bf16_t* __restrict__ V,
+                                                       const bf16_t* __restrict__ dOut, const int32_t* __restrict__ idx,
+                                                       const float* __restrict__ act, const int2* __restrict__ small_ent,
+                                                       const int32_t* __restrict__ small_cnt,
+                                                       const int32_t* __restrict__ tok_of_slot, int d, int k, int bs,
+                                                       float* __restrict__ ds32) {
+  extern __shared__ int s_list[];
+  __shared__ int s_w[4];
+  const int w = blockIdx.x;
+  if (w < n_chunks) compact_flags_body(flag, N, chunk_cnt, w, n_chunks, touched, n_touched, s_w);
+  else small_ds_body((w - n_chunks) % nx, nx, (w - n_chunks) / nx, s_list, s_w, V, dOut, idx, act, small_ent, small_cnt,
+                     tok_of_slot, d, k, N, bs, ds32);
 }
 
 }  // namespace meft

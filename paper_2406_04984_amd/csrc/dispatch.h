@@ -1,11 +1,20 @@
-// (token, block) dispatch in three passes over the entries, for up to 1024 blocks and 2^20 entries: the grouping of
-// the T * top_e entries by block that the grouped GEMMs work from.  Entry i = t * top_e + q holds block sblk[i] (or
-// -1); slots are the entries sorted by block, entries of one block in ascending entry (= token) order:
+// (token, block) dispatch: the grouping of the T * top_e (token, block) entries by block that the grouped GEMMs work
+// from.  Entry i = t * top_e + q holds block sblk[i] (or -1), the blocks of a token ascending; slots are the entries
+// sorted by block, entries of one block in ascending entry (= token) order:
 //   perm[slot] = entry, group_off[b] = first slot of block b, cnt[b] = its entries, tile_off = prefix of
 //   ceil(cnt / BM), and on the matrix-core path tok_of_slot, slot_of_ent and the per-XCD tile schedule.
-// A chunk is 1024 consecutive entries, one per thread.  Pass 1 counts the entries of every block per chunk, pass 2
-// (one workgroup) turns the counts into offsets and deals the groups to the XCDs, pass 3 places the entries.  The
-// rank of an entry inside its wave comes from ballots over the distinct blocks of the wave, the rest from prefix
+// slot_of_ent carries kSmallSlot where the entry's group is one of at most small_rows tokens (small_groups.h).
+//
+// Up to 1024 blocks and 2^20 entries this takes two launches over chunks of whole tokens, at most 1024 entries each:
+//   dispatch_count   sorts every token's blocks, counts the entries of every block per chunk, and clears what the
+//                    forward or backward needs cleared;
+//   dispatch_place   every workgroup adds the chunk counts up for itself (a few thousand integers out of L2 cost less
+//                    than a launch) and places its chunk's entries, while one more workgroup writes the tables and
+//                    deals the groups to the XCDs, which is a serial chain.
+// Against four launches (sort, count, one workgroup that scans and deals, place): 41 -> 24 us at 8192 x 4 entries and 64
+// blocks, 67 -> 30 us at 4096 x 8 and 256.  Where the chunk counts are too many for every workgroup to add up (more than kDispScanMax), one workgroup
+// does it in a launch of its own in between.
+// The rank of an entry inside its wave comes from ballots over the distinct blocks of the wave, the rest from prefix
 // sums, so the order is the entry order and nothing depends on the timing of atomics.
 // (Shapes beyond these limits use count_blocks / fill_groups / slot_maps / build_sched, which scan the entries
 // once per block.)
@@ -18,6 +27,8 @@ namespace meft {
 
 constexpr int kDispMaxBlocks = 1024;    // LDS: 16 waves x n_blocks counters
 constexpr int kDispMaxChunks = 1024;
+constexpr int kDispScanBlocks = 512;    // dispatch_place adds up the chunk counts itself up to this many blocks
+constexpr int kDispScanMax = 32768;     // and this many counts
 
 // Rank of this lane's entry among the entries of the same block in its wave, in lane (= entry) order; lane
 // `leader of the block` also writes the block's count in the wave to row[block] (row zeroed by the caller).
@@ -27,7 +38,7 @@ __device__ __forceinline__ int wave_block_ranks(int b, int* row) {
   unsigned long long todo = __ballot(b >= 0);
   while (todo) {   // wave-uniform: one round per distinct block of the wave
     const int leader = __ffsll(todo) - 1;
-    const int b0 = __shfl(b, leader, 64);
+    const int b0 = __builtin_amdgcn_readlane(b, leader);
     const unsigned long long m = __ballot(b == b0);
     if (b == b0) rank = __popcll(m & ((1ull << lane) - 1ull));
     if (lane == leader) row[b0] = __popcll(m);
@@ -36,90 +47,156 @@ __device__ __forceinline__ int wave_block_ranks(int b, int* row) {
   return rank;
 }
 
-__device__ __forceinline__ int dispatch_block_of(const int32_t* __restrict__ sblk, int i, int n_ent, int n_blocks) {
-  const int b = i < n_ent ? sblk[i] : -1;
-  return (unsigned)b < (unsigned)n_blocks ? b : -1;
-}
-
-// pass 1: H[chunk][b] = entries of block b in the chunk.  Dynamic LDS: 16 * n_blocks ints.
-__global__ __launch_bounds__(1024) void dispatch_count_kernel(const int32_t* __restrict__ sblk, int n_ent,
-                                                              int n_blocks, int32_t* __restrict__ H) {
+// pass 1: H[chunk][b] = entries of block b in the chunk.  kSort: `in` holds the token's blocks in any order, ids are
+// clamped and written to sblk ascending; otherwise `in` is sblk (-1: no entry).  `epc` entries per chunk (whole
+// tokens).  Also zeroes clear[0 .. clear_words).  Dynamic LDS: 16 * n_blocks ints.
+template <bool kSort>
+__global__ __launch_bounds__(1024) void dispatch_count_kernel(const int32_t* __restrict__ in, int n_ent, int e, int epc,
+                                                              int n_blocks, int32_t* __restrict__ sblk,
+                                                              int32_t* __restrict__ H, int32_t* __restrict__ clear,
+                                                              size_t clear_words) {
   extern __shared__ int s_cnt[];   // [16 waves][n_blocks]
+  __shared__ int s_in[kSort ? 1024 : 1], s_out[kSort ? 1024 : 1];
   const int tid = threadIdx.x, w = tid >> 6, c = blockIdx.x;
+  for (size_t i = (size_t)c * 1024 + tid; i < clear_words; i += (size_t)gridDim.x * 1024) clear[i] = 0;
   for (int i = tid; i < 16 * n_blocks; i += 1024) s_cnt[i] = 0;
+  const int i = c * epc + tid;
+  const bool live = tid < epc && i < n_ent;
+  int b = live ? in[i] : -1;
+  if constexpr (kSort) {
+    b = live ? clampi(b, 0, n_blocks - 1) : -1;
+    s_in[tid] = b;
+    __syncthreads();
+    if (live) {
+      const int q = tid % e, base = tid - q;
+      int r = 0;
+      for (int z = 0; z < e; ++z) {
+        const int bz = s_in[base + z];
+        r += (bz < b || (bz == b && z < q)) ? 1 : 0;
+      }
+      s_out[base + r] = b;
+    }
+    __syncthreads();
+    if (live) { b = s_out[tid]; sblk[i] = b; }
+  } else {
+    b = (unsigned)b < (unsigned)n_blocks ? b : -1;
+    __syncthreads();
+  }
+  wave_block_ranks(b, s_cnt + w * n_blocks);
   __syncthreads();
-  wave_block_ranks(dispatch_block_of(sblk, c * 1024 + tid, n_ent, n_blocks), s_cnt + w * n_blocks);
-  __syncthreads();
-  for (int b = tid; b < n_blocks; b += 1024) {
+  for (int bb = tid; bb < n_blocks; bb += 1024) {
     int run = 0;
 #pragma unroll
-    for (int ww = 0; ww < 16; ++ww) run += s_cnt[ww * n_blocks + b];
-    H[(size_t)c * n_blocks + b] = run;
+    for (int ww = 0; ww < 16; ++ww) run += s_cnt[ww * n_blocks + bb];
+    H[(size_t)c * n_blocks + bb] = run;
   }
 }
 
-// pass 2, one workgroup: H[chunk][b] becomes the number of entries of block b in the chunks before; cnt, group_off,
-// tile_off; with grp != nullptr also the tile schedule; with small_ent != nullptr the lists of the small groups.
+// What the dispatch leaves besides perm and the slot maps.
+struct DispatchTables {
+  int32_t *cnt, *group_off, *tile_off;
+  int BM;                 // rows per tile of tile_off
+  int cap;                // tile schedule: entries per XCD
+  int2* grp;              // nullptr: no tile schedule
+  int* len;
+  int small_rows;
+  int2* small_ent;        // nullptr: no lists of small groups
+  int32_t *small_grp, *small_cnt;
+};
+
+// Entries of block tid (0 beyond n_blocks) -> all the tables.  Executed by one whole workgroup of 1024 threads.
+__device__ __forceinline__ void dispatch_tables(const DispatchTables& t, int rows, int n_blocks, int* s_w) {
+  const int tid = threadIdx.x;
+  int all_g, all_t;
+  const int go = block_excl_scan_1024(rows, s_w, all_g);
+  const int to = block_excl_scan_1024((rows + t.BM - 1) / t.BM, s_w, all_t);
+  if (tid < n_blocks) { t.cnt[tid] = rows; t.group_off[tid] = go; t.tile_off[tid] = to; }
+  if (tid == 0) { t.group_off[n_blocks] = all_g; t.tile_off[n_blocks] = all_t; }
+  if (t.small_ent != nullptr) {
+    small_lists_body(rows, go, n_blocks, t.small_rows, t.small_ent, t.small_grp, t.small_cnt, s_w);
+  }
+  if (t.grp != nullptr) build_sched_body(rows, n_blocks, t.cap, t.grp, t.len, kTMTok, t.small_rows);   // (no barrier after it)
+}
+
+// Between the passes where the counts are many, one workgroup: H[chunk][b] becomes the number of entries of block b in
+// the chunks before; the tables.
 __global__ __launch_bounds__(1024) void dispatch_scan_kernel(int32_t* __restrict__ H, int n_chunks, int n_blocks,
-                                                             int BM, int32_t* __restrict__ cnt,
-                                                             int32_t* __restrict__ group_off,
-                                                             int32_t* __restrict__ tile_off, int cap,
-                                                             int2* __restrict__ grp, int* __restrict__ len,
-                                                             int sched_tile_m, int small_rows,
-                                                             int2* __restrict__ small_ent,
-                                                             int32_t* __restrict__ small_grp,
-                                                             int32_t* __restrict__ small_cnt) {
+                                                             DispatchTables t) {
   __shared__ int s_w[16];
   const int tid = threadIdx.x;   // = block, n_blocks <= 1024
   int tot = 0;
   if (tid < n_blocks) {
     // sixteen independent loads at a time: the serial part is the additions, not the memory latency
     for (int c0 = 0; c0 < n_chunks; c0 += 16) {
-      int t[16];
+      int v[16];
 #pragma unroll
-      for (int j = 0; j < 16; ++j) t[j] = c0 + j < n_chunks ? H[(size_t)(c0 + j) * n_blocks + tid] : 0;
+      for (int j = 0; j < 16; ++j) v[j] = c0 + j < n_chunks ? H[(size_t)(c0 + j) * n_blocks + tid] : 0;
 #pragma unroll
       for (int j = 0; j < 16; ++j) {
         if (c0 + j < n_chunks) H[(size_t)(c0 + j) * n_blocks + tid] = tot;
-        tot += t[j];
+        tot += v[j];
       }
     }
-    cnt[tid] = tot;
   }
-  int all_g, all_t;
-  const int go = block_excl_scan_1024(tot, s_w, all_g);
-  const int to = block_excl_scan_1024((tot + BM - 1) / BM, s_w, all_t);
-  if (tid < n_blocks) { group_off[tid] = go; tile_off[tid] = to; }
-  if (tid == 0) { group_off[n_blocks] = all_g; tile_off[n_blocks] = all_t; }
-  if (grp != nullptr) {
-    __syncthreads();   // group_off is read back below
-    build_sched_body(group_off, n_blocks, cap, grp, len, sched_tile_m, small_rows);
-  }
-  if (small_ent != nullptr) {
-    __syncthreads();   // group_off is read back; s_w is free again
-    small_lists_body(group_off, n_blocks, small_rows, small_ent, small_grp, small_cnt, s_w);
-  }
+  dispatch_tables(t, tot, n_blocks, s_w);
 }
 
-// pass 3: perm, and with tok_of_slot != nullptr the slot maps (tok_of_slot padded by `pad` valid entries).
+// pass 2: perm, and with tok_of_slot != nullptr the slot maps (tok_of_slot padded by `pad` valid entries).
+// kScan: H holds the chunk counts, every workgroup adds them up, and workgroup number n_chunks writes the tables; lg =
+// log2 of the power of two at or above n_blocks.  Otherwise H and the tables come from dispatch_scan_kernel.
 // Dynamic LDS: 16 * n_blocks ints.
-__global__ __launch_bounds__(1024) void dispatch_place_kernel(const int32_t* __restrict__ sblk, int n_ent,
-                                                              int n_blocks, int e, const int32_t* __restrict__ H,
-                                                              const int32_t* __restrict__ group_off,
+template <bool kScan>
+__global__ __launch_bounds__(1024) void dispatch_place_kernel(const int32_t* __restrict__ sblk, int n_ent, int e, int epc,
+                                                              int n_blocks, int lg, int n_chunks,
+                                                              const int32_t* __restrict__ H, DispatchTables tab,
                                                               int32_t* __restrict__ perm,
                                                               int32_t* __restrict__ tok_of_slot,
                                                               int32_t* __restrict__ slot_of_ent, int pad) {
   extern __shared__ int s_cnt[];   // [16 waves][n_blocks]
+  __shared__ int s_w[16];
+  __shared__ int s_tot[kScan ? kDispScanBlocks : 1], s_first[kScan ? kDispScanBlocks : 1];
   const int tid = threadIdx.x, w = tid >> 6, c = blockIdx.x;
-  for (int i = tid; i < 16 * n_blocks; i += 1024) s_cnt[i] = 0;
+  const int i = c * epc + tid;
+  int b = c < n_chunks && tid < epc && i < n_ent ? sblk[i] : -1;
+  b = (unsigned)b < (unsigned)n_blocks ? b : -1;
+  if constexpr (kScan) {
+    if (tid < n_blocks) { s_tot[tid] = 0; s_first[tid] = 0; }
+    __syncthreads();
+    const int bb = tid & ((1 << lg) - 1), parts = 1024 >> lg;
+    if (bb < n_blocks) {
+      int tot = 0, before = 0;
+      for (int ch = tid >> lg; ch < n_chunks; ch += parts) {
+        const int v = H[(size_t)ch * n_blocks + bb];
+        tot += v;
+        before += ch < c ? v : 0;
+      }
+      atomicAdd(&s_tot[bb], tot);
+      atomicAdd(&s_first[bb], before);
+    }
+    __syncthreads();
+    const int rows = tid < n_blocks ? s_tot[tid] : 0;
+    if (c == n_chunks) {
+      if (tok_of_slot != nullptr && tid < pad) {
+        int all = 0;   // entries in all (those of block -1 have no slot)
+        for (int z = 0; z < n_blocks; ++z) all += s_tot[z];
+        tok_of_slot[all + tid] = 0;
+      }
+      dispatch_tables(tab, rows, n_blocks, s_w);
+      return;
+    }
+    int all;
+    const int go = block_excl_scan_1024(rows, s_w, all);
+    if (tid < n_blocks) s_first[tid] += go;
+  }
+  for (int z = tid; z < 16 * n_blocks; z += 1024) s_cnt[z] = 0;
   __syncthreads();
-  const int i = c * 1024 + tid;
-  const int b = dispatch_block_of(sblk, i, n_ent, n_blocks);
   const int rank = wave_block_ranks(b, s_cnt + w * n_blocks);
   __syncthreads();
   // per block: first slot of wave 0's entries, then the exclusive prefix over the waves
   for (int bb = tid; bb < n_blocks; bb += 1024) {
-    int run = group_off[bb] + H[(size_t)c * n_blocks + bb];
+    int run;
+    if constexpr (kScan) run = s_first[bb];
+    else run = tab.group_off[bb] + H[(size_t)c * n_blocks + bb];
 #pragma unroll
     for (int ww = 0; ww < 16; ++ww) {
       const int t = s_cnt[ww * n_blocks + bb];
@@ -132,11 +209,14 @@ __global__ __launch_bounds__(1024) void dispatch_place_kernel(const int32_t* __r
     const int slot = s_cnt[w * n_blocks + b] + rank;
     perm[slot] = i;
     if (tok_of_slot != nullptr) {
+      int rows;
+      if constexpr (kScan) rows = s_tot[b];
+      else rows = tab.cnt[b];
       tok_of_slot[slot] = i / e;
-      slot_of_ent[i] = slot;
+      slot_of_ent[i] = rows <= tab.small_rows ? (slot | kSmallSlot) : slot;
     }
   }
-  if (tok_of_slot != nullptr && c == 0 && tid < pad) tok_of_slot[group_off[n_blocks] + tid] = 0;
+  if (!kScan && tok_of_slot != nullptr && c == 0 && tid < pad) tok_of_slot[tab.group_off[n_blocks] + tid] = 0;
 }
 
 }  // namespace meft

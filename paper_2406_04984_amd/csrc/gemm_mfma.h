@@ -877,66 +877,140 @@ constexpr int kSchedLenInts = 2 * kXcd + 1;
 
 constexpr int kSchedSortMax = 1024;   // up to this many groups are dealt out longest first; more: round-robin
 
-// Executed by one whole workgroup of 1024 threads.
-__device__ __forceinline__ void build_sched_body(const int32_t* __restrict__ group_off, int n_groups, int cap,
-                                                 int2* __restrict__ grp, int* __restrict__ len, int tile_m,
-                                                 int small_rows) {
+// v[i] of a small wave-uniform array, i different per lane
+__device__ __forceinline__ int key_of_lane(const int (&v)[kXcd], int i) {
+  int r = v[0];
+#pragma unroll
+  for (int z = 1; z < kXcd; ++z) r = i == z ? v[z] : r;
+  return r;
+}
+
+// Executed by one whole workgroup of 1024 threads; rows = number of tokens of group threadIdx.x (0 beyond n_groups).
+// n_groups <= kSchedSortMax.
+__device__ __forceinline__ void build_sched_body(int rows, int n_groups, int cap, int2* __restrict__ grp,
+                                                 int* __restrict__ len, int tile_m, int small_rows) {
   __shared__ int s_rows[kSchedSortMax];
   __shared__ int s_order[kSchedSortMax];
   __shared__ int s_sorted[kSchedSortMax];
   const int tid = threadIdx.x;
+  __syncthreads();   // the arrays may still be read from an earlier use
+  if (tid < n_groups) s_rows[tid] = rows;
+  const int n_full = __syncthreads_count(rows > 0);   // non-empty groups; also orders the writes above
+  if (tid < n_groups) {
+    int rank = 0;   // position in the order (rows descending, group id ascending): a permutation
+#pragma unroll 8
+    for (int g = 0; g < n_groups; ++g) {
+      const int r = s_rows[g];
+      rank += (r > rows || (r == rows && g < tid)) ? 1 : 0;
+    }
+    s_order[rank] = tid;
+    s_sorted[rank] = rows;
+  }
+  __syncthreads();
+  // Fewer non-empty groups than XCDs: a deal of whole groups would leave XCDs idle.  Then every list holds every
+  // group, len[kXcd] says so, and XCD x takes the tiles x, x + 8, ... of each group (locate_token_tile).
+  const bool split = n_full < kXcd;
+  if (tid == 0) len[kXcd] = split ? 1 : 0;
+  if (tid >= 64) return;
+  const int lane = tid;
+  if (split) {
+    if (lane < kXcd) {
+      int tiles = 0, n_big = 0;
+      for (int i = 0; i < n_full; ++i) {
+        grp[(size_t)lane * cap + i] = make_int2(s_order[i], tiles);
+        n_big += s_sorted[i] > small_rows ? 1 : 0;
+        tiles += (s_sorted[i] + tile_m - 1) / tile_m;
+      }
+      grp[(size_t)lane * cap + n_full] = make_int2(-1, tiles);
+      len[lane] = n_full;
+      len[kXcd + 1 + lane] = n_big;
+    }
+    return;
+  }
+  // The deal of the groups of more than 64 rows is sequential; lanes 0..7 each keep one XCD's load (in units of 64 rows
+  // plus a constant per group) as load * 8 + lane, a three-step DPP butterfly finds the least loaded XCD (ties to the
+  // lower one), and the loop does nothing else: 64 groups at a time come out of a register by lane reads and their XCDs
+  // go into one by lane writes.  List positions and tile numbers follow in parallel.
+  int n_deal = 0;
+  for (int i0 = 0; i0 < n_full; i0 += 64) n_deal += __popcll(__ballot(i0 + lane < n_full && s_sorted[min(i0 + lane, n_full - 1)] > 64));
+  int key = lane < kXcd ? lane : 0x7FFFFFFF;
+  int nx[kXcd], tx[kXcd], bx[kXcd];   // per XCD: list length, tiles, groups of more than small_rows tokens
+#pragma unroll
+  for (int x = 0; x < kXcd; ++x) nx[x] = tx[x] = bx[x] = 0;
+  for (int i0 = 0; i0 < n_deal; i0 += 64) {
+    const int m = min(64, n_deal - i0), at = min(i0 + lane, n_deal - 1);
+    const int r = s_sorted[at], g = s_order[at];
+    const int inc = (((r + 63) >> 6) + 2) << 3;
+    int xcd = -1;
+    for (int i = 0; i < m; ++i) {
+      int k = key;
+      k = min(k, __builtin_amdgcn_update_dpp(k, k, 0xB1, 0xF, 0xF, false));    // quad_perm [1,0,3,2]
+      k = min(k, __builtin_amdgcn_update_dpp(k, k, 0x4E, 0xF, 0xF, false));    // quad_perm [2,3,0,1]
+      k = min(k, __builtin_amdgcn_update_dpp(k, k, 0x141, 0xF, 0xF, false));   // row_half_mirror
+      const int x = __builtin_amdgcn_readfirstlane(k) & (kXcd - 1);
+      key += lane == x ? __builtin_amdgcn_readlane(inc, i) : 0;
+      xcd = lane == i ? x : xcd;
+    }
+    const int t = (r + tile_m - 1) / tile_m;
+#pragma unroll
+    for (int x = 0; x < kXcd; ++x) {
+      const bool mine = xcd == x;
+      const unsigned long long mask = __ballot(mine);
+      const int incl = wave_incl_scan(mine ? t : 0);
+      if (mine)
+        grp[(size_t)x * cap + nx[x] + __popcll(mask & ((1ull << lane) - 1ull))] = make_int2(g, tx[x] + incl - t);
+      nx[x] += __popcll(mask);
+      tx[x] += __builtin_amdgcn_readlane(incl, 63);
+      bx[x] += __popcll(__ballot(mine && r > small_rows));
+    }
+  }
+  // The groups of at most 64 rows all weigh the same (3) and have one tile, so the same deal has a closed form: XCD x
+  // takes its j-th one (from 0) when the least load is load[x] + 3 j, and that is group number
+  // sum over y of #{j' : (load[y] + 3 j', y) < (load[x] + 3 j, x)} of the rest.
+  const int n_eq = n_full - n_deal;
+  int load[kXcd];
+#pragma unroll
+  for (int x = 0; x < kXcd; ++x) load[x] = __builtin_amdgcn_readlane(key, x) >> 3;
+  const int x = lane & (kXcd - 1), my_load = key_of_lane(load, x), my_n = key_of_lane(nx, x), my_t = key_of_lane(tx, x);
+  for (int j0 = 0; j0 < n_eq; j0 += 8) {
+    const int j = j0 + (lane >> 3), k = my_load + 3 * j;
+    int rank = 0;
+#pragma unroll
+    for (int y = 0; y < kXcd; ++y) {
+      const int v = k - load[y] + (y < x ? 1 : 0);
+      rank += v > 0 ? (v + 2) / 3 : 0;
+    }
+    const bool valid = rank < n_eq;
+    bool big = false;
+    if (valid) {
+      grp[(size_t)x * cap + my_n + j] = make_int2(s_order[n_deal + rank], my_t + j);
+      big = s_sorted[n_deal + rank] > small_rows;
+    }
+    const unsigned long long mv = __ballot(valid), mb = __ballot(big);
+    if (!mv) break;
+#pragma unroll
+    for (int y = 0; y < kXcd; ++y) {
+      const unsigned long long my = 0x0101010101010101ull << y;
+      const int c = __popcll(mv & my);
+      nx[y] += c;
+      tx[y] += c;
+      bx[y] += __popcll(mb & my);
+    }
+  }
+  if (lane < kXcd) {
+    const int n = key_of_lane(nx, lane);
+    grp[(size_t)lane * cap + n] = make_int2(-1, key_of_lane(tx, lane));
+    len[lane] = n;
+    len[kXcd + 1 + lane] = key_of_lane(bx, lane);
+  }
+}
+
+__global__ __launch_bounds__(1024) void build_sched_kernel(const int32_t* __restrict__ group_off, int n_groups,
+                                                           int cap, int2* __restrict__ grp, int* __restrict__ len,
+                                                           int tile_m, int small_rows) {
+  const int tid = threadIdx.x;
   if (n_groups <= kSchedSortMax) {
-    int rows = 0;
-    if (tid < n_groups) { rows = group_off[tid + 1] - group_off[tid]; s_rows[tid] = rows; }
-    const int n_full = __syncthreads_count(rows > 0);   // non-empty groups; also orders the writes above
-    if (tid < n_groups) {
-      int rank = 0;   // position in the order (rows descending, group id ascending): a permutation
-      for (int g = 0; g < n_groups; ++g) {
-        const int r = s_rows[g];
-        rank += (r > rows || (r == rows && g < tid)) ? 1 : 0;
-      }
-      s_order[rank] = tid;
-      s_sorted[rank] = rows;
-    }
-    __syncthreads();
-    // Fewer non-empty groups than XCDs: a deal of whole groups would leave XCDs idle.  Then every list holds every
-    // group, len[kXcd] says so, and XCD x takes the tiles x, x + 8, ... of each group (locate_token_tile).
-    const bool split = n_full < kXcd;
-    if (tid == 0) len[kXcd] = split ? 1 : 0;
-    if (tid < 64) {
-      // the deal itself is sequential; lanes 0..7 of the first wave each keep one XCD's work, list length and tile
-      // count, and a three-step DPP butterfly finds the least loaded XCD (ties to the lower one)
-      const int lane = tid;
-      int load = 0, n = 0, tiles = 0, n_big = 0;
-      for (int i = 0; i < n_full; ++i) {   // descending order: the non-empty groups come first
-        const int g = s_order[i], r = s_sorted[i];
-        if (split) {
-          if (lane < kXcd) {
-            grp[(size_t)lane * cap + n] = make_int2(g, tiles);
-            n += 1;
-            n_big += r > small_rows ? 1 : 0;
-            tiles += (r + tile_m - 1) / tile_m;
-          }
-          continue;
-        }
-        int key = lane < kXcd ? ((load << 3) | lane) : 0x7FFFFFFF;
-        key = min(key, __builtin_amdgcn_update_dpp(key, key, 0xB1, 0xF, 0xF, false));    // quad_perm [1,0,3,2]
-        key = min(key, __builtin_amdgcn_update_dpp(key, key, 0x4E, 0xF, 0xF, false));    // quad_perm [2,3,0,1]
-        key = min(key, __builtin_amdgcn_update_dpp(key, key, 0x141, 0xF, 0xF, false));   // row_half_mirror
-        if (lane == (key & (kXcd - 1))) {   // true in one of the lanes 0..7 only: the higher lanes hold 0x7FFFFFFF
-          grp[(size_t)lane * cap + n] = make_int2(g, tiles);
-          n += 1;
-          n_big += r > small_rows ? 1 : 0;
-          tiles += (r + tile_m - 1) / tile_m;
-          load += (r + 63) / 64 + 2;
-        }
-      }
-      if (lane < kXcd) {
-        grp[(size_t)lane * cap + n] = make_int2(-1, tiles);
-        len[lane] = n;
-        len[kXcd + 1 + lane] = n_big;
-      }
-    }
+    build_sched_body(tid < n_groups ? group_off[tid + 1] - group_off[tid] : 0, n_groups, cap, grp, len, tile_m, small_rows);
   } else if (tid < kXcd) {
     const int x = tid;
     if (x == 0) len[kXcd] = 0;
@@ -951,12 +1025,6 @@ __device__ __forceinline__ void build_sched_body(const int32_t* __restrict__ gro
     len[x] = n;
     len[kXcd + 1 + x] = n;   // unsorted lists: no group counts as small (the host passes small_rows = 0 here)
   }
-}
-
-__global__ __launch_bounds__(1024) void build_sched_kernel(const int32_t* __restrict__ group_off, int n_groups,
-                                                           int cap, int2* __restrict__ grp, int* __restrict__ len,
-                                                           int tile_m, int small_rows) {
-  build_sched_body(group_off, n_groups, cap, grp, len, tile_m, small_rows);
 }
 
 // big_only: walk only the groups of more than small_rows tokens (the prefix of every list that the second set of

@@ -166,11 +166,13 @@ struct RouteWs {
   }
 };
 
-// the three-pass dispatch (dispatch.h) covers up to 1024 blocks and 2^20 entries
-bool fast_dispatch(const meft_shape& s) {
-  const int64_t n_ent = (int64_t)s.T * s.top_e;
-  return s.n_blocks <= kDispMaxBlocks && (n_ent + 1023) / 1024 <= kDispMaxChunks;
+// the dispatch over chunks of whole tokens, at most 1024 entries each (dispatch.h): up to 1024 blocks and 1024 chunks
+int disp_chunk_entries(const meft_shape& s) { return 1024 / s.top_e * s.top_e; }   // n_blocks <= 1024 only
+int disp_chunks(const meft_shape& s) {
+  const int epc = disp_chunk_entries(s);
+  return (int)(((int64_t)s.T * s.top_e + epc - 1) / epc);
 }
+bool fast_dispatch(const meft_shape& s) { return s.n_blocks <= kDispMaxBlocks && disp_chunks(s) <= kDispMaxChunks; }
 
 // index structures of the (token, block) dispatch, common to forward and backward
 struct DispatchWs {
@@ -192,7 +194,7 @@ struct DispatchWs {
     slot_of_ent = c.take<int32_t>(n_ent);
     sched_len = c.take<int32_t>(kSchedLenInts);   // list lengths per XCD, the split flag, lengths without small groups
     sched_pairs = c.take<int2>((size_t)kXcd * sched_cap(s));
-    chunk_hist = c.take<int32_t>(fast_dispatch(s) ? ((n_ent + 1023) / 1024) * (size_t)s.n_blocks : 0);
+    chunk_hist = c.take<int32_t>(fast_dispatch(s) ? (size_t)disp_chunks(s) * s.n_blocks : 0);
     const size_t small = (size_t)small_rows_of(s);
     small_ent = c.take<int2>(small ? small * s.n_blocks : 0);
     small_grp = c.take<int32_t>(small ? (size_t)s.n_blocks : 0);
@@ -206,6 +208,8 @@ struct DenseWs : DispatchWs {
   int32_t *flag = nullptr, *chunk_cnt = nullptr;
   uint16_t *zrow = nullptr, *Ap = nullptr, *DS = nullptr, *part = nullptr;
   float* ds32 = nullptr;   // activation gradients of the pairs of small groups, [T, top_k]
+  // the touched flags and the row of zeros start from zero (adjacent in the workspace)
+  size_t clear_words() const { return (size_t)(reinterpret_cast<char*>(Ap) - reinterpret_cast<char*>(flag)) / 4; }
   void carve_dense(const meft_shape& s, Carver& c) {
     carve(s, c);
     const size_t n_ent = (size_t)s.T * s.top_e;
@@ -530,29 +534,55 @@ void launch_gemm_mfma(const char* name, const P& prob, int grid, hipStream_t st)
   }
 }
 
-// (token, block) dispatch from sorted per-token block lists: groups, slot maps, XCD tile schedule
-void launch_dispatch(const meft_shape& s, const DispatchWs& w, int BM, bool dense, bool want_sched, hipStream_t st) {
+// (token, block) dispatch: groups, slot maps, XCD tile schedule; with block_idx the per-token block lists are sorted
+// first (otherwise w.sblk holds them).  `clear`: words set to zero on the way.
+void launch_dispatch(const meft_shape& s, const DispatchWs& w, const int32_t* block_idx, int BM, bool dense, bool want_sched,
+                     int32_t* clear, size_t clear_words, hipStream_t st) {
   const int n_ent = s.T * s.top_e;
   const int small = dense ? small_rows_of(s) : 0;
   if (fast_dispatch(s)) {
-    const int n_chunks = (n_ent + 1023) / 1024;
+    const int epc = disp_chunk_entries(s), n_chunks = disp_chunks(s);
     const size_t lds = (size_t)16 * s.n_blocks * sizeof(int);
-    MEFT_LAUNCH("dispatch_count", dispatch_count_kernel, dim3(n_chunks), dim3(1024), lds, st, w.sblk, n_ent,
-                s.n_blocks, w.chunk_hist);
-    MEFT_LAUNCH("dispatch_scan", dispatch_scan_kernel, dim3(1), dim3(1024), 0, st, w.chunk_hist, n_chunks,
-                s.n_blocks, BM, w.cnt, w.group_off, w.tile_off, sched_cap(s), want_sched ? w.sched_pairs : nullptr,
-                w.sched_len, kTMTok, small, small ? w.small_ent : nullptr, w.small_grp, w.small_cnt);
-    MEFT_LAUNCH("dispatch_place", dispatch_place_kernel, dim3(n_chunks), dim3(1024), lds, st, w.sblk, n_ent,
-                s.n_blocks, s.top_e, w.chunk_hist, w.group_off, w.perm, dense ? w.tok_of_slot : nullptr,
-                w.slot_of_ent, kSlotPad);
+    static std::once_flag configured;   // 64 KB of counters at 1024 blocks, and the static arrays
+    std::call_once(configured, [] {
+      const int most = 16 * kDispMaxBlocks * (int)sizeof(int);
+      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&dispatch_count_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize, most);
+      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&dispatch_count_kernel<false>), hipFuncAttributeMaxDynamicSharedMemorySize, most);
+      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&dispatch_place_kernel<false>), hipFuncAttributeMaxDynamicSharedMemorySize, most);
+    });
+    if (block_idx)
+      MEFT_LAUNCH("dispatch_count", dispatch_count_kernel<true>, dim3(n_chunks), dim3(1024), lds, st, block_idx, n_ent,
+                  s.top_e, epc, s.n_blocks, w.sblk, w.chunk_hist, clear, clear_words);
+    else
+      MEFT_LAUNCH("dispatch_count", dispatch_count_kernel<false>, dim3(n_chunks), dim3(1024), lds, st, w.sblk, n_ent,
+                  s.top_e, epc, s.n_blocks, nullptr, w.chunk_hist, clear, clear_words);
+    const DispatchTables tab{w.cnt, w.group_off, w.tile_off, BM, sched_cap(s), want_sched ? w.sched_pairs : nullptr,
+                             w.sched_len, small, small ? w.small_ent : nullptr, w.small_grp, w.small_cnt};
+    int32_t* tok = dense ? w.tok_of_slot : nullptr;
+    int lg = 0;
+    while ((1 << lg) < s.n_blocks) ++lg;
+    if (s.n_blocks <= kDispScanBlocks && (int64_t)n_chunks * s.n_blocks <= kDispScanMax) {
+      MEFT_LAUNCH("dispatch_place", dispatch_place_kernel<true>, dim3(n_chunks + 1), dim3(1024), lds, st, w.sblk, n_ent,
+                  s.top_e, epc, s.n_blocks, lg, n_chunks, w.chunk_hist, tab, w.perm, tok, w.slot_of_ent, kSlotPad);
+    } else {
+      MEFT_LAUNCH("dispatch_scan", dispatch_scan_kernel, dim3(1), dim3(1024), 0, st, w.chunk_hist, n_chunks, s.n_blocks, tab);
+      MEFT_LAUNCH("dispatch_place", dispatch_place_kernel<false>, dim3(n_chunks), dim3(1024), lds, st, w.sblk, n_ent,
+                  s.top_e, epc, s.n_blocks, lg, n_chunks, w.chunk_hist, tab, w.perm, tok, w.slot_of_ent, kSlotPad);
+    }
     return;
   }
+  if (clear_words)
+    MEFT_LAUNCH("fill_i32", fill_i32_kernel, dim3((unsigned)((clear_words + 255) / 256)), dim3(256), 0, st, clear,
+                clear_words, 0);
+  if (block_idx)
+    MEFT_LAUNCH("sort_blocks", sort_blocks_kernel, dim3((s.T + 255) / 256), dim3(256), 0, st, block_idx, s.T, s.top_e,
+                s.n_blocks, w.sblk);
   MEFT_LAUNCH("count_blocks", count_blocks_kernel, dim3(s.n_blocks), dim3(1024), 0, st, w.sblk, n_ent, w.cnt);
   MEFT_LAUNCH("fill_groups", fill_groups_kernel, dim3(s.n_blocks), dim3(1024), 0, st, w.sblk, n_ent, w.cnt,
               s.n_blocks, BM, w.group_off, w.tile_off, w.perm);
   if (dense) {
     MEFT_LAUNCH("slot_maps", slot_maps_kernel, dim3((n_ent + kSlotPad + 255) / 256), dim3(256), 0, st, w.perm, w.group_off,
-                s.n_blocks, s.top_e, w.tok_of_slot, w.slot_of_ent);
+                s.n_blocks, s.top_e, w.sblk, small, w.tok_of_slot, w.slot_of_ent);
   }
   if (want_sched) {
     MEFT_LAUNCH("build_sched", build_sched_kernel, dim3(1), dim3(1024), 0, st, w.group_off, s.n_blocks,
@@ -564,54 +594,52 @@ void launch_dispatch(const meft_shape& s, const DispatchWs& w, int BM, bool dens
   }
 }
 
-void launch_reduce_parts(const meft_shape& s, const uint16_t* part, const DispatchWs& w, void* out, hipStream_t st) {
+// Launch widths of the work on the lists of small groups: enough workgroups for the lists of a skewed batch to be taken
+// in one pass, few enough that a launch on a batch without small groups costs next to nothing.
+constexpr int kSmallEntGrid = 256, kSmallGrpGrid = 128;
+
+// The tokens' rows of out (W = V, coef = act) or dh (W = K, coef = ds) from the entries' partial rows and the pairs of
+// the small groups; `dv`: the dV / dK work of the small groups, or none.
+void launch_token_rows(const char* name, const meft_shape& s, const uint16_t* part, const DispatchWs& w, const void* W,
+                       const int32_t* idx, const float* coef, void* out, const SmallDvdk& dv, hipStream_t st) {
+  const TokenRows a{part, w.sblk, w.slot_of_ent, idx, coef, static_cast<const bf16_t*>(W), s.d, s.top_e, s.top_k, s.N,
+                    s.block_size, static_cast<bf16_t*>(out)};
+  const size_t lds = small_rows_of(s) ? (size_t)s.top_k * sizeof(int2) : 0;   // up to 96 KB
+  static std::once_flag configured;
+  std::call_once(configured, [] {
+    const void* k[] = {reinterpret_cast<const void*>(&token_rows_kernel<1, true>), reinterpret_cast<const void*>(&token_rows_kernel<1, false>),
+                       reinterpret_cast<const void*>(&token_rows_kernel<2, false>), reinterpret_cast<const void*>(&token_rows_kernel<4, false>),
+                       reinterpret_cast<const void*>(&token_rows_kernel<8, false>)};
+    for (const void* f : k) (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsC * (int)sizeof(int2));
+  });
+  const int chunks = (s.d + kSmallCols - 1) / kSmallCols;
+  // few tokens: a workgroup per 512 columns, so that small groups, whose pairs are a chain of row reads, get more waves
+  if (s.T * chunks <= 16 * kPersistentWgs) {
+    MEFT_LAUNCH(name, (token_rows_kernel<1, true>), dim3(dv.n_wg + s.T * chunks), dim3(256), lds, st, a, dv);
+    return;
+  }
   int nthr, nv;
   row_launch(s.d, nthr, nv);
-  uint16_t* o = static_cast<uint16_t*>(out);
-#define RP(NV) MEFT_LAUNCH("reduce_parts", (reduce_parts_kernel<NV>), dim3(s.T), dim3(nthr), 0, st, part, w.sblk, w.slot_of_ent, s.d, s.top_e, o)
+  if (dv.n_wg) { nthr = 256; nv = s.d <= 2048 ? 1 : s.d <= 4096 ? 2 : s.d <= 8192 ? 4 : 8; }   // the dV / dK work takes four waves
+#define RP(NV) MEFT_LAUNCH(name, (token_rows_kernel<NV, false>), dim3(dv.n_wg + s.T), dim3(nthr), lds, st, a, dv)
   switch (nv) { case 1: RP(1); break; case 2: RP(2); break; case 4: RP(4); break; default: RP(8); }
 #undef RP
 }
 
-size_t small_list_bytes(const meft_shape& s) {
-  return (size_t)s.top_k * sizeof(int);   // top_k <= top_e * block_size <= 12288 on the block-dense path
-}
-
-// Launch widths of the kernels that walk the lists of small groups: enough workgroups for the lists of a skewed
-// batch to be taken in one pass, few enough that a launch on a batch without small groups costs next to nothing.
-constexpr int kSmallEntGrid = 1024, kSmallGrpGrid = 128;
-
-// small groups: their rows of `part` as sums of coef * W rows (forward: act and V; backward: ds and K)
-void launch_small_rowsum(const char* name, const meft_shape& s, const DenseWs& w, const void* W, const int32_t* idx,
-                         const float* coef, hipStream_t st) {
-  const int small = small_rows_of(s);
-  if (small == 0) return;
-  const int gx = s.n_blocks * small < kSmallEntGrid ? s.n_blocks * small : kSmallEntGrid;
-  MEFT_LAUNCH(name, small_rowsum_kernel, dim3(gx, (s.d + kSmallCols - 1) / kSmallCols), dim3(256),
-              small_list_bytes(s), st, static_cast<const bf16_t*>(W), idx, coef, w.small_ent, w.small_cnt,
-              w.tok_of_slot, s.d, s.top_k, s.N, s.block_size, reinterpret_cast<bf16_t*>(w.part));
-}
-
-// backward, small groups: the activation gradients of their pairs
-void launch_small_ds(const meft_shape& s, const DenseWs& w, const void* V, const void* dOut, const int32_t* idx,
-                     const float* act, hipStream_t st) {
-  const int small = small_rows_of(s);
-  if (small == 0) return;
-  const int gx = s.n_blocks * small < kSmallEntGrid ? s.n_blocks * small : kSmallEntGrid;
-  MEFT_LAUNCH("small_ds", small_ds_kernel, dim3(gx, kSmallPairSplit), dim3(256), small_list_bytes(s), st,
-              static_cast<const bf16_t*>(V), static_cast<const bf16_t*>(dOut), idx, act, w.small_ent, w.small_cnt,
-              w.tok_of_slot, s.d, s.top_k, s.N, s.block_size, w.ds32);
-}
-
-// backward, small groups: the dV and dK rows of their blocks
-void launch_small_dvdk(const meft_shape& s, const DenseWs& w, const void* h, const void* dOut, const int32_t* idx,
-                       const float* act, void* dK, void* dV, hipStream_t st) {
-  if (small_rows_of(s) == 0) return;
-  const int gx = s.n_blocks < kSmallGrpGrid ? s.n_blocks : kSmallGrpGrid;
-  MEFT_LAUNCH("small_dvdk", small_dvdk_kernel, dim3((s.block_size + kSmallRowChunk - 1) / kSmallRowChunk, gx),
-              dim3(256), 0, st, static_cast<const bf16_t*>(h), static_cast<const bf16_t*>(dOut), idx, act, w.ds32,
-              w.small_grp, w.small_cnt, w.group_off, w.tok_of_slot, s.d, s.top_k, s.N, s.block_size,
-              static_cast<bf16_t*>(dK), static_cast<bf16_t*>(dV));
+// touched list, and in the same launch (small: w holds lists of small groups) the activation gradients of their pairs
+void launch_bwd_head(const meft_shape& s, const int32_t* flag, int32_t* chunk_cnt, int32_t* touched, int32_t* n_touched,
+                     const DenseWs* w, const void* V, const void* dOut, const int32_t* idx, const float* act,
+                     hipStream_t st) {
+  const int n_chunks = (s.N + kFlagChunk - 1) / kFlagChunk;
+  const bool counts = s.N > kFlagCountMax;
+  if (counts)
+    MEFT_LAUNCH("count_flags", count_flags_kernel, dim3(n_chunks), dim3(256), 0, st, flag, s.N, chunk_cnt);
+  const int small = w ? small_rows_of(s) : 0;
+  const int nx = s.n_blocks * small < kSmallEntGrid ? s.n_blocks * small : kSmallEntGrid;
+  MEFT_LAUNCH("bwd_head", bwd_head_kernel, dim3(n_chunks + nx * kSmallPairSplit), dim3(256), small ? (size_t)s.top_k * 4 : 0, st,
+              flag, s.N, counts ? chunk_cnt : nullptr, n_chunks, touched, n_touched, nx, static_cast<const bf16_t*>(V),
+              static_cast<const bf16_t*>(dOut), idx, act, w ? w->small_ent : nullptr, w ? w->small_cnt : nullptr,
+              w ? w->tok_of_slot : nullptr, s.d, s.top_k, s.block_size, w ? w->ds32 : nullptr);
 }
 
 // Tile rows of the dV / dK contractions: 256 where that computes no more padded rows of the block than 128 would
@@ -747,10 +775,8 @@ static meft_status fwd_impl(const meft_shape& s, const void* h, const void* K, c
                                 : launch_few<float>(s, h, K, V, block_idx, out, idx, act, w.sc, st, wait_v);
   }
   const bool dense = use_dense(s);
-  MEFT_LAUNCH("sort_blocks", sort_blocks_kernel, dim3((s.T + 255) / 256), dim3(256), 0, st, block_idx, s.T,
-              s.top_e, s.n_blocks, w.sblk);
   const bool mfma_scores = dense || use_mfma_scores(s);
-  launch_dispatch(s, w, BM, dense, mfma_scores, st);
+  launch_dispatch(s, w, block_idx, BM, dense, mfma_scores, dense ? w.flag : nullptr, dense ? w.clear_words() : 0, st);
   const int bsp = round64(s.block_size);
   const TokenSched sched{w.sched_pairs, w.sched_len, sched_cap(s), sched_max_tiles(s)};
   const uint16_t *hh = static_cast<const uint16_t*>(h), *kk = static_cast<const uint16_t*>(K),
@@ -774,7 +800,7 @@ static meft_status fwd_impl(const meft_shape& s, const void* h, const void* K, c
   if (C <= kMaxLdsC) {
     // keys in registers, the smallest per-thread count that covers the C candidates with 256 threads
     uint16_t* ap = dense ? w.Ap : nullptr;
-#define TK2(KPT, FULL) MEFT_LAUNCH("topk_select", (topk_select_reg_kernel<KPT, FULL>), dim3(s.T), dim3(256), 0, st, w.sc, w.sblk, C, s.block_size, s.top_e, s.top_k, idx, act, w.slot_of_ent, bsp, ap)
+#define TK2(KPT, FULL) MEFT_LAUNCH("topk_select", (topk_select_reg_kernel<KPT, FULL>), dim3(s.T), dim3(256), 0, st, w.sc, w.sblk, C, s.block_size, s.top_e, s.top_k, idx, act, w.slot_of_ent, bsp, ap, dense ? w.flag : nullptr)
 #define TK(KPT) do { if (C == 256 * (KPT)) TK2(KPT, true); else TK2(KPT, false); } while (0)
     if (C <= 256 * 4) TK(4);
     else if (C <= 256 * 8) TK(8);
@@ -804,8 +830,7 @@ static meft_status fwd_impl(const meft_shape& s, const void* h, const void* K, c
     pv.d = s.d; pv.part = w.part; pv.big_only = small_rows_of(s) > 0;
     set_gemm_extents(pv, (uint64_t)n_ent * bsp * 2, (uint64_t)s.N * s.d * 2);
     launch_gemm_mfma("value_gemm", pv, tile_bound(s, (s.d + kTN - 1) / kTN), st);
-    launch_small_rowsum("small_value", s, w, V, idx, act, st);
-    launch_reduce_parts(s, w.part, w, out, st);
+    launch_token_rows("out_rows", s, w.part, w, V, idx, act, out, SmallDvdk{}, st);
   } else if (s.dtype == MEFT_BF16) {
     launch_gather_fwd<bf16_t>(s, V, idx, act, out, st);
   } else {
@@ -831,15 +856,7 @@ static meft_status bwd_impl(const meft_shape& s, const void* h, const void* K, c
     if (!reuse) {
       MEFT_LAUNCH("blocks_from_idx", blocks_from_idx_kernel, dim3(s.T), dim3(64), (size_t)((s.n_blocks + 31) / 32) * 4,
                   st, idx, s.top_k, s.N, s.block_size, s.n_blocks, s.top_e, w.sblk);
-      launch_dispatch(s, w, kGemmBM, true, true, st);
-    }
-    // the flags and the row of zeros start from zero (adjacent in the workspace); 4-byte fill
-    const size_t clear_words = (size_t)(reinterpret_cast<char*>(w.Ap) - reinterpret_cast<char*>(w.flag)) / 4;
-    MEFT_LAUNCH("fill_i32", fill_i32_kernel, dim3((unsigned)((clear_words + 255) / 256)), dim3(256), 0, st, w.flag,
-                clear_words, 0);
-    if (reuse) {
-      MEFT_LAUNCH("mark_idx", mark_idx_kernel, dim3((P + 255) / 256), dim3(256), 0, st, idx, P, s.N, w.flag);
-    } else {
+      launch_dispatch(s, w, nullptr, kGemmBM, true, true, w.flag, w.clear_words(), st);
       // a token's rows take top_e * bsp * 2 bytes of LDS: up to 96 KB where blocks are small and many (the default
       // limit of a launch is 64 KB)
       static std::once_flag act_rows_configured;
@@ -850,12 +867,11 @@ static meft_status bwd_impl(const meft_shape& s, const void* h, const void* K, c
       MEFT_LAUNCH("act_rows", act_rows_kernel, dim3(s.T), dim3(256), (size_t)s.top_e * bsp * 2, st, idx, act, s.top_k,
                   s.N, s.block_size, bsp, s.top_e, w.sblk, w.slot_of_ent, w.Ap, w.flag);
     }
-    const int n_chunks = (s.N + kFlagChunk - 1) / kFlagChunk;
-    MEFT_LAUNCH("count_flags", count_flags_kernel, dim3(n_chunks), dim3(256), 0, st, w.flag, s.N, w.chunk_cnt);
-    MEFT_LAUNCH("compact_flags", compact_flags_kernel, dim3(n_chunks), dim3(256), 0, st, w.flag, s.N, w.chunk_cnt,
-                touched, n_touched);
+    const int small = small_rows_of(s);
+    // (with host-resident V still on its way the small groups' gradients wait for it)
+    launch_bwd_head(s, w.flag, w.chunk_cnt, touched, n_touched, small && !wait_v ? &w : nullptr, V, dOut, idx, act, st);
     const TokenSched sched{w.sched_pairs, w.sched_len, sched_cap(s), sched_max_tiles(s)};
-    const int big_only = small_rows_of(s) > 0;   // the small groups: launch_small_* below
+    const int big_only = small > 0;   // the small groups: computed pair by pair
     const int n_ent = s.T * s.top_e;
     NeuArgs pn{};
     pn.group_off = w.group_off; pn.tok_of_slot = w.tok_of_slot; pn.flag = w.flag;
@@ -872,20 +888,32 @@ static meft_status bwd_impl(const meft_shape& s, const void* h, const void* K, c
     pg.big_only = big_only;
     set_gemm_extents(pg, (uint64_t)s.T * s.d * 2, (uint64_t)s.N * s.d * 2);
     launch_gemm_mfma("dact_gemm", pg, tile_bound(s, (s.block_size + kTN - 1) / kTN), st);
+    if (small && wait_v) launch_bwd_head(s, w.flag, w.chunk_cnt, touched, n_touched, &w, V, dOut, idx, act, st);
     if (wait_k && hipStreamWaitEvent(st, wait_k, 0) != hipSuccess) return MEFT_ERR_DEVICE;
-    launch_small_ds(s, w, V, dOut, idx, act, st);
+    SmallDvdk dv{};
+    if (small) {
+      dv.nx = (s.block_size + kSmallRowChunk - 1) / kSmallRowChunk;
+      dv.ny = s.n_blocks < kSmallGrpGrid ? s.n_blocks : kSmallGrpGrid;
+      dv.n_wg = dv.nx * dv.ny;
+      dv.h = reinterpret_cast<const bf16_t*>(hh); dv.dOut = reinterpret_cast<const bf16_t*>(gg);
+      dv.act = act; dv.ds32 = w.ds32;
+      dv.small_grp = w.small_grp; dv.small_cnt = w.small_cnt; dv.group_off = w.group_off; dv.tok_of_slot = w.tok_of_slot;
+      dv.dK = static_cast<bf16_t*>(dK); dv.dV = static_cast<bf16_t*>(dV);
+    }
     if (dh) {
       ProbTokNC ph{};
       ph.A = w.DS; ph.W = kk; ph.group_off = w.group_off; ph.sched = sched; ph.bs = s.block_size; ph.bsp = bsp;
       ph.d = s.d; ph.part = w.part; ph.big_only = big_only;
       set_gemm_extents(ph, (uint64_t)n_ent * bsp * 2, (uint64_t)s.N * s.d * 2);
       launch_gemm_mfma("dh_gemm", ph, tile_bound(s, (s.d + kTN - 1) / kTN), st);
-      launch_small_rowsum("small_dh", s, w, K, idx, w.ds32, st);
-      launch_reduce_parts(s, w.part, w, dh, st);
+      launch_token_rows("dh_rows", s, w.part, w, K, idx, w.ds32, dh, dv, st);
+    } else if (small) {
+      TokenRows a{};
+      a.idx = idx; a.d = s.d; a.k = s.top_k; a.N = s.N; a.bs = s.block_size;
+      MEFT_LAUNCH("small_dvdk", small_dvdk_kernel, dim3(dv.n_wg), dim3(256), 0, st, a, dv);
     }
     pn.A = w.DS; pn.zrow = -(n_ent + 1); pn.X = hh; pn.G = static_cast<uint16_t*>(dK);
     launch_neu("dK_gemm", pn, st);
-    launch_small_dvdk(s, w, h, dOut, idx, act, dK, dV, st);
     return launch_status();
   }
 
@@ -968,10 +996,7 @@ meft_status meft_union_fwd(const meft_shape* shape, const void* h, const void* K
   MEFT_LAUNCH("fill_i32", fill_i32_kernel, dim3((unsigned)(((size_t)s.N + 255) / 256)), dim3(256), 0, st, w.flag,
               (size_t)s.N, 0);
   MEFT_LAUNCH("mark_idx", mark_idx_kernel, dim3((P + 255) / 256), dim3(256), 0, st, idx, P, s.N, w.flag);
-  const int n_chunks = (s.N + kFlagChunk - 1) / kFlagChunk;
-  MEFT_LAUNCH("count_flags", count_flags_kernel, dim3(n_chunks), dim3(256), 0, st, w.flag, s.N, w.chunk_cnt);
-  MEFT_LAUNCH("compact_flags", compact_flags_kernel, dim3(n_chunks), dim3(256), 0, st, w.flag, s.N, w.chunk_cnt, S,
-              n_S);
+  launch_bwd_head(s, w.flag, w.chunk_cnt, S, n_S, nullptr, nullptr, nullptr, nullptr, nullptr, st);
   union_front(s, g, w, h, K, V, S, n_S, st);
   const TokenSched sched{w.sched_pairs, w.sched_len, sched_cap(g.vs), sched_max_tiles(g.vs)};
   ProbTokNC pv{};
@@ -979,7 +1004,7 @@ meft_status meft_union_fwd(const meft_shape* shape, const void* h, const void* K
   pv.d = s.d; pv.part = w.part;
   set_gemm_extents(pv, (uint64_t)s.T * g.nvb * g.vbs * 2, (uint64_t)g.nvb * g.vbs * s.d * 2);
   launch_gemm_mfma("union_value_gemm", pv, tile_bound(g.vs, (s.d + kTN - 1) / kTN), st);
-  launch_reduce_parts(g.vs, w.part, w, out, st);
+  launch_token_rows("union_out_rows", g.vs, w.part, w, nullptr, nullptr, nullptr, out, SmallDvdk{}, st);
   return launch_status();
 }
 
@@ -1015,7 +1040,7 @@ meft_status meft_union_bwd(const meft_shape* shape, const void* h, const void* K
     ph.d = s.d; ph.part = w.part;
     set_gemm_extents(ph, (uint64_t)s.T * g.nvb * g.vbs * 2, (uint64_t)g.nvb * g.vbs * s.d * 2);
     launch_gemm_mfma("union_dh_gemm", ph, tile_bound(g.vs, (s.d + kTN - 1) / kTN), st);
-    launch_reduce_parts(g.vs, w.part, w, dh, st);
+    launch_token_rows("union_dh_rows", g.vs, w.part, w, nullptr, nullptr, nullptr, dh, SmallDvdk{}, st);
   }
   NeuArgs pn{};
   pn.group_off = w.group_off; pn.tok_of_slot = w.tok_of_slot; pn.flag = w.rowflag;

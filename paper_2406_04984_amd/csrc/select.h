@@ -151,7 +151,8 @@ __global__ __launch_bounds__(1024) void fill_groups_kernel(const int32_t* __rest
 // most-significant-digit radix select (4 passes of 8 bits) finds the key of the k-th largest and how many of its
 // equals still belong; then one ordered sweep emits the selected positions in ascending order: all keys above
 // the threshold, and the first `need` positions that equal it.  With Ap != nullptr it also writes the token's
-// dense activation rows (one per chosen block, slot-major, zero where not selected).
+// dense activation rows (one per chosen block, slot-major, zero where not selected) and marks the selected neurons in
+// `flag` (zero before).
 //
 // The token's keys live in registers: thread `tid` owns the KPT consecutive candidate
 // positions tid*KPT .. tid*KPT + KPT - 1 (256 * KPT >= C), reads them once from global memory and keeps their
@@ -164,10 +165,9 @@ __global__ __launch_bounds__(1024) void fill_groups_kernel(const int32_t* __rest
 // ---------------------------------------------------------------------------------------------
 constexpr int kTopkEmitLds = 1024;   // selections per token that go through LDS in one round
 
-// Waves per SIMD that the register allocation aims at.  Up to 16 keys per thread seven (72 registers): measured
-// best at 16 keys (0.095 ms against 0.102 with the 86 registers the compiler takes unasked, 0.118 at six waves, 0.123
-// at eight); with more keys per thread as many as hold them without spilling.
-constexpr int topk_waves(int kpt) { return kpt <= 16 ? 7 : (kpt <= 32 ? 4 : 2); }
+// Waves per SIMD that the register allocation aims at: the most that hold the keys without spilling.  (16 keys per
+// thread: 91 us at five, 110 at six or seven with a few registers spilled.)
+constexpr int topk_waves(int kpt) { return kpt <= 8 ? 8 : (kpt <= 16 ? 5 : (kpt <= 32 ? 3 : 2)); }
 
 struct TopkLds {
   int hist[256];
@@ -302,7 +302,7 @@ __global__ __launch_bounds__(256, topk_waves(KPT)) void topk_select_reg_kernel(c
                                                               int e, int k, int32_t* __restrict__ idx,
                                                               float* __restrict__ act,
                                                               const int32_t* __restrict__ slot_of_ent, int bsp,
-                                                              uint16_t* __restrict__ Ap) {
+                                                              uint16_t* __restrict__ Ap, int32_t* __restrict__ flag) {
   __shared__ TopkLds s;
   const int t = blockIdx.x, tid = threadIdx.x;
   const int p0 = tid * KPT;
@@ -324,8 +324,10 @@ __global__ __launch_bounds__(256, topk_waves(KPT)) void topk_select_reg_kernel(c
     for (int j = tid; j < n_out; j += 256) {
       const int i = s.idx[j], q = i / bs;
       const float v = key_to_float(__float_as_uint(s.act[j]));
-      idx[(size_t)t * k + base + j] = sblk[(size_t)t * e + q] * bs + (i - q * bs);
+      const int nid = sblk[(size_t)t * e + q] * bs + (i - q * bs);
+      idx[(size_t)t * k + base + j] = nid;
       act[(size_t)t * k + base + j] = v > 0.f ? v : 0.f;
+      if (flag != nullptr) flag[nid] = 1;
     }
     if (base + kTopkEmitLds < k) __syncthreads();   // the next round overwrites the staging arrays
   }
@@ -343,7 +345,7 @@ __global__ __launch_bounds__(256, topk_waves(KPT)) void topk_select_reg_kernel(c
   if (bs % KPT == 0 && (KPT & 7) == 0) {
     // the thread's positions lie in one block's row, 16-byte aligned
     if (p0 < C) {
-      uint16_t* dst = Ap + (size_t)slot_of_ent[(size_t)t * e + q0] * bsp + r0;
+      uint16_t* dst = Ap + (size_t)(slot_of_ent[(size_t)t * e + q0] & 0x7FFFFFFF) * bsp + r0;
 #pragma unroll
       for (int z = 0; z < KPT; z += 8) {
         u32x4 w;
@@ -358,7 +360,7 @@ __global__ __launch_bounds__(256, topk_waves(KPT)) void topk_select_reg_kernel(c
       const int i = p0 + z;
       if (i < C) {
         const int qz = i / bs, rz = i - qz * bs;
-        Ap[(size_t)slot_of_ent[t * e + qz] * bsp + rz] = (uint16_t)f32_to_bf16_bits(a32[z]);
+        Ap[(size_t)(slot_of_ent[t * e + qz] & 0x7FFFFFFF) * bsp + rz] = (uint16_t)f32_to_bf16_bits(a32[z]);
       }
     }
   }
@@ -366,7 +368,7 @@ __global__ __launch_bounds__(256, topk_waves(KPT)) void topk_select_reg_kernel(c
   const int pad = bsp - bs;
   for (int j = tid; j < e * pad; j += 256) {
     const int qz = j / pad, rz = bs + (j - qz * pad);
-    Ap[(size_t)slot_of_ent[t * e + qz] * bsp + rz] = 0;
+    Ap[(size_t)(slot_of_ent[t * e + qz] & 0x7FFFFFFF) * bsp + rz] = 0;
   }
 }
 

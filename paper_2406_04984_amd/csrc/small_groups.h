@@ -3,17 +3,23 @@
 // a group the matrix-core contractions after the selection would read the block's rows of V or K to use the few
 // dozen that the group's tokens selected, and run whole tiles for a few rows.  Groups of at most `small_rows` tokens
 // are therefore left out of those contractions (the tile schedule lists them last; see TokenSched) and handled here
-// pair by pair, through the same intermediate arrays, so that everything downstream is unchanged:
-//   forward   part[slot, :]   = sum over the token's selected neurons j of the block of act * V[j, :]        (Eq. 4)
-//   backward  ds[t, i]        = act > 0 ? dOut[t, :] . V[j, :] : 0;   dhpart[slot, :] = sum ds * K[j, :]
+// pair by pair:
+//   forward   out[t, :]      += sum over the token's selected neurons j of the block of act * V[j, :]        (Eq. 4)
+//   backward  ds[t, i]        = act > 0 ? dOut[t, :] . V[j, :] : 0;   dh[t, :] += sum ds * K[j, :]
 //             dV[j, :], dK[j, :] of the block's touched neurons, the group's tokens summed in ascending order
 // (Section 3.1, last paragraph).  The key scores of a small group still come from the score contraction: every
 // neuron of a routed block has to be scored whatever the group's size (Eq. 6).
 // A pair moves one row of d elements, so these kernels are bound by latency rather than by arithmetic: the work of
 // one entry is spread over many waves (column chunks of 512 elements across workgroups, pairs across the waves of a
 // workgroup), every sum in an order that the launch alone fixes.
-// The entries of the small groups are listed once per dispatch (small_lists_body); workgroup x of a launch takes the
-// entries x, x + gridDim.x, ... of that list, so consecutive workgroups, which go to the XCDs in turn, hold
+// A token's row of out or dh is the sum of its entries' rows; the kernel that forms it (token_rows_body) takes an entry of
+// a large group from `part` and works through the pairs of the others itself, so a small group costs the forward no
+// launch of its own and its part of the row stays in fp32.  The backward's own small-group work shares launches with
+// other work that does not depend on it: the activation gradients with the compaction of the touched list, the dV / dK
+// rows with the dh rows.  (A launch that finds nothing to do costs 4 us: four of them were a fifth of a 2048-token
+// step at d = 1024.)
+// The entries of the small groups are listed once per dispatch (small_lists_body); worker x of a launch takes the
+// entries x, x + workers, ... of that list, so consecutive workgroups, which go to the XCDs in turn, hold
 // consecutive entries and every XCD gets its share of the memory traffic.
 #pragma once
 #include "common.h"
@@ -30,18 +36,41 @@ constexpr int kSmallRowsMax = 16;   // upper limit of small_rows (size of that k
 constexpr int kSmallRows = MEFT_SMALL_ROWS;   // a group of at most this many tokens is small; 0 switches the path off
 constexpr int kSmallCols = 512;     // elements of a row that one wave covers in one step: 64 lanes x 8
 constexpr int kSmallPairSplit = 8;  // workgroups that share the pairs of one entry in small_ds_kernel
+constexpr int kSmallSlot = (int)0x80000000;   // in slot_of_ent: the entry's group is small
 static_assert(kSmallRows >= 0 && kSmallRows <= kSmallRowsMax, "the tables of small_dvdk_kernel hold kSmallRowsMax tokens");
 
+// acc += cf * eight bf16 values
+__device__ __forceinline__ void fma8_bf16(float cf, u32x4 x, float (&acc)[8]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    acc[2 * i] = fmaf(cf, __uint_as_float(x[i] << 16), acc[2 * i]);
+    acc[2 * i + 1] = fmaf(cf, __uint_as_float(x[i] & 0xFFFF0000u), acc[2 * i + 1]);
+  }
+}
+
+// exclusive scan of one 0 / 1 flag per thread over a workgroup of whole waves (at most 256 threads)
+__device__ __forceinline__ int flag_excl_scan(bool v, int* s_wave /*[4]*/, int& total) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  const unsigned long long m = __ballot(v);
+  if (lane == 0) s_wave[w] = __popcll(m);
+  __syncthreads();
+  int base = 0, tot = 0;
+  for (int i = 0; i < nw; ++i) { const int x = s_wave[i]; base += i < w ? x : 0; tot += x; }
+  total = tot;
+  __syncthreads();
+  return base + __popcll(m & ((1ull << lane) - 1ull));
+}
+
 // Positions p (ascending) of the pairs of one token whose neuron lies in block g, into s_list; returns their number.
-// `it` = the token's idx row (any order), k entries.  s_w: 4 ints of scratch.  Called by all 256 threads.
+// `it` = the token's idx row (any order), k entries.  s_w: 4 ints of scratch.  Called by all the threads.
 __device__ __forceinline__ int collect_block_pairs(const int32_t* __restrict__ it, int k, int N, int bs, int g,
                                                    int* s_list, int* s_w) {
   int n = 0;
-  for (int p0 = 0; p0 < k; p0 += 256) {
+  for (int p0 = 0; p0 < k; p0 += blockDim.x) {
     const int p = p0 + (int)threadIdx.x;
-    const int hit = (p < k && clampi(it[p], 0, N - 1) / bs == g) ? 1 : 0;
+    const bool hit = p < k && clampi(it[p], 0, N - 1) / bs == g;
     int tot;
-    const int pos = block_excl_scan_256(hit, s_w, tot);
+    const int pos = flag_excl_scan(hit, s_w, tot);
     if (hit) s_list[n + pos] = p;
     n += tot;
   }
@@ -53,12 +82,10 @@ __device__ __forceinline__ int collect_block_pairs(const int32_t* __restrict__ i
 // small_rows tokens, small_ent[0 .. small_cnt[0]) = (group, slot) of their entries.  The kernels below walk these
 // lists, so that their launches need not cover every (group, token) position.  n_groups <= 1024; executed by one
 // whole workgroup of 1024 threads (s_w: 16 ints of scratch).
-__device__ __forceinline__ void small_lists_body(const int32_t* __restrict__ group_off, int n_groups, int small_rows,
-                                                 int2* __restrict__ small_ent, int32_t* __restrict__ small_grp,
+__device__ __forceinline__ void small_lists_body(int rows, int s0, int n_groups, int small_rows, int2* __restrict__ small_ent, int32_t* __restrict__ small_grp,
                                                  int32_t* __restrict__ small_cnt, int* s_w) {
+  // rows, s0: number of entries and first slot of group threadIdx.x (0 rows beyond n_groups)
   const int tid = threadIdx.x;
-  int s0 = 0, rows = 0;
-  if (tid < n_groups) { s0 = group_off[tid]; rows = group_off[tid + 1] - s0; }
   const bool sm = rows > 0 && rows <= small_rows;
   int tot_e, tot_g;
   const int eo = block_excl_scan_1024(sm ? rows : 0, s_w, tot_e);
@@ -75,97 +102,178 @@ __global__ __launch_bounds__(1024) void small_lists_kernel(const int32_t* __rest
                                                            int32_t* __restrict__ small_grp,
                                                            int32_t* __restrict__ small_cnt) {
   __shared__ int s_w[16];
-  small_lists_body(group_off, n_groups, small_rows, small_ent, small_grp, small_cnt, s_w);
+  const int tid = threadIdx.x, s0 = tid < n_groups ? group_off[tid] : 0;
+  small_lists_body(tid < n_groups ? group_off[tid + 1] - s0 : 0, s0, n_groups, small_rows, small_ent, small_grp, small_cnt,
+                   s_w);
 }
 
-// part[slot, c0 : c0 + 512] = sum over the entry's pairs of coef[t, p] * W[j, c0 : c0 + 512], c0 = 512 * blockIdx.y
-// (W = V, coef = act: the forward's partial output row; W = K, coef = ds: the partial dh row).  Wave w takes the pairs
-// w, w + 4, ... of the list; the four partial sums are added in wave order.  Dynamic LDS: k ints.
-__global__ __launch_bounds__(256) void small_rowsum_kernel(const bf16_t* __restrict__ W,
-                                                           const int32_t* __restrict__ idx,
-                                                           const float* __restrict__ coef,
-                                                           const int2* __restrict__ small_ent,
-                                                           const int32_t* __restrict__ small_cnt,
-                                                           const int32_t* __restrict__ tok_of_slot, int d, int k,
-                                                           int N, int bs, bf16_t* __restrict__ part) {
-  extern __shared__ int s_list[];
-  __shared__ int s_w[4];
-  __shared__ float s_red[3][kSmallCols];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int col = blockIdx.y * kSmallCols + lane * 8;
-  const bool live = col < d;
-  const int n_ent = small_cnt[0];
-  for (int e = blockIdx.x; e < n_ent; e += gridDim.x) {
-    const int g = small_ent[e].x, slot = small_ent[e].y, t = tok_of_slot[slot];
-    const int32_t* it = idx + (size_t)t * k;
-    const float* ct = coef + (size_t)t * k;
-    const int n = collect_block_pairs(it, k, N, bs, g, s_list, s_w);
-    float acc[8];
+// The rows of one token: row[t, :] = sum over its entries of large groups of part[slot, :] (bf16), plus sum over its
+// pairs of small groups of coef[t, p] * W[j, :] (W = V, coef = act: out; W = K, coef = ds: dh); fp32 sums, large groups in
+// ascending block order first, then the pairs in list order.  One workgroup per token, thread tid owns the columns
+// (tid + v * blockDim.x) * 8.  s_list: k pairs, s_blk: kTokenRowsBlocks ints.
+constexpr int kTokenRowsBlocks = 64;
+
+struct TokenRows {
+  const uint16_t* part;
+  const int32_t *sblk, *slot_of_ent, *idx;
+  const float* coef;
+  const bf16_t* W;
+  int d, e, k, N, bs;
+  bf16_t* out;
+};
+
+// the token's pairs of small groups, ascending, into s_list: neuron, coefficient
+__device__ __forceinline__ int collect_small_pairs(const TokenRows& a, int t, int2* s_list, int* s_blk, int* s_w) {
+  const int32_t* it = a.idx + (size_t)t * a.k;
+  const float* ct = a.coef + (size_t)t * a.k;
+  const int nb = min(a.e, kTokenRowsBlocks);
+  for (int q = threadIdx.x; q < nb; q += blockDim.x)
+    s_blk[q] = a.slot_of_ent[(size_t)t * a.e + q] < 0 ? a.sblk[(size_t)t * a.e + q] : -1;
+  __syncthreads();
+  int n = 0;
+  for (int p0 = 0; p0 < a.k; p0 += blockDim.x) {
+    const int p = p0 + (int)threadIdx.x;
+    bool hit = false;
+    int j = 0;
+    float cf = 0.f;
+    if (p < a.k) {
+      j = clampi(it[p], 0, a.N - 1);
+      cf = ct[p];
+      const int b = j / a.bs;
+      for (int q = 0; q < nb; ++q) hit |= s_blk[q] == b;
+      for (int q = nb; q < a.e; ++q)
+        hit |= a.sblk[(size_t)t * a.e + q] == b && a.slot_of_ent[(size_t)t * a.e + q] < 0;
+    }
+    int tot;
+    const int pos = flag_excl_scan(hit, s_w, tot);
+    if (hit) s_list[n + pos] = make_int2(j, __float_as_int(cf));
+    n += tot;
+  }
+  __syncthreads();
+  return n;
+}
+
+template <int NV>
+__device__ __forceinline__ void token_rows_body(const TokenRows& a, int t, int2* s_list, int* s_blk, int* s_w) {
+  const int tid = threadIdx.x, nthr = blockDim.x, d = a.d;
+  float acc[NV][8];
 #pragma unroll
-    for (int c = 0; c < 8; ++c) acc[c] = 0.f;
-    constexpr int U = 4;
-    int q = wave;
-    for (; q + 4 * (U - 1) < n; q += 4 * U) {
-      float x[U][8], a[U];
+  for (int v = 0; v < NV; ++v)
+#pragma unroll
+    for (int c = 0; c < 8; ++c) acc[v][c] = 0.f;
+  bool small = false;
+  for (int q = 0; q < a.e; ++q) {
+    if (a.sblk[(size_t)t * a.e + q] < 0) continue;
+    const int slot = a.slot_of_ent[(size_t)t * a.e + q];
+    if (slot < 0) { small = true; continue; }
+    const bf16_t* row = reinterpret_cast<const bf16_t*>(a.part) + (size_t)slot * d;
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      const int col = (tid + v * nthr) * 8;
+      if (col < d) {
+        float x[8];
+        Vec8<bf16_t>::load(row + col, x);
+#pragma unroll
+        for (int c = 0; c < 8; ++c) acc[v][c] += x[c];
+      }
+    }
+  }
+  if (small) {   // the same in every thread
+    const int n = collect_small_pairs(a, t, s_list, s_blk, s_w);
+    constexpr int U = NV == 1 ? 16 : NV == 2 ? 8 : NV == 4 ? 4 : 2;   // rows in flight
+    for (int q0 = 0; q0 < n; q0 += U) {
+      u32x4 x[U][NV];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int p = s_list[q + 4 * u];
-        a[u] = ct[p];
-        if (live) Vec8<bf16_t>::load(W + (size_t)clampi(it[p], 0, N - 1) * d + col, x[u]);
+        const bf16_t* row = a.W + (size_t)s_list[min(q0 + u, n - 1)].x * d;
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+          const int col = (tid + v * nthr) * 8;
+          if (col < d) x[u][v] = *reinterpret_cast<const u32x4*>(row + col);
+        }
       }
-      if (live) {
 #pragma unroll
-        for (int u = 0; u < U; ++u)
+      for (int u = 0; u < U; ++u) {
+        if (q0 + u < n) {
+          const float cf = __int_as_float(s_list[q0 + u].y);
 #pragma unroll
-          for (int c = 0; c < 8; ++c) acc[c] = fmaf(a[u], x[u][c], acc[c]);
-      }
-    }
-    for (; q < n; q += 4) {
-      const int p = s_list[q];
-      const float a = ct[p];
-      if (live) {
-        float x[8];
-        Vec8<bf16_t>::load(W + (size_t)clampi(it[p], 0, N - 1) * d + col, x);
-#pragma unroll
-        for (int c = 0; c < 8; ++c) acc[c] = fmaf(a, x[c], acc[c]);
+          for (int v = 0; v < NV; ++v)
+            if ((tid + v * nthr) * 8 < d) fma8_bf16(cf, x[u][v], acc[v]);
+        }
       }
     }
-    if (wave > 0) {
+  }
 #pragma unroll
-      for (int c = 0; c < 8; ++c) s_red[wave - 1][lane * 8 + c] = acc[c];
+  for (int v = 0; v < NV; ++v) {
+    const int col = (tid + v * nthr) * 8;
+    if (col < d) Vec8<bf16_t>::store(a.out + (size_t)t * d + col, acc[v]);
+  }
+}
+
+// The same for few tokens: a workgroup of four waves per (token, 512 columns); the entries and the pairs are dealt to the
+// waves, whose sums are added in wave order.
+__device__ __forceinline__ void token_rows_split_body(const TokenRows& a, int t, int chunk, int2* s_list, int* s_blk,
+                                                      int* s_w, float (&s_red)[3][kSmallCols]) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, d = a.d;
+  const int col = chunk * kSmallCols + lane * 8;
+  const bool live = col < d;
+  float acc[8];
+#pragma unroll
+  for (int c = 0; c < 8; ++c) acc[c] = 0.f;
+  bool small = false;
+  for (int q = 0; q < a.e; ++q) {
+    if (a.sblk[(size_t)t * a.e + q] < 0) continue;
+    const int slot = a.slot_of_ent[(size_t)t * a.e + q];
+    if (slot < 0) { small = true; continue; }
+    if ((q & 3) == wave && live) {
+      float x[8];
+      Vec8<bf16_t>::load(reinterpret_cast<const bf16_t*>(a.part) + (size_t)slot * d + col, x);
+#pragma unroll
+      for (int c = 0; c < 8; ++c) acc[c] += x[c];
     }
-    __syncthreads();
-    if (wave == 0 && live) {
+  }
+  if (small) {
+    const int n = collect_small_pairs(a, t, s_list, s_blk, s_w);
+    constexpr int U = 8;
+    for (int q0 = wave; q0 < n && live; q0 += 4 * U) {
+      u32x4 x[U];
 #pragma unroll
-      for (int w = 0; w < 3; ++w)
+      for (int u = 0; u < U; ++u)
+        x[u] = *reinterpret_cast<const u32x4*>(a.W + (size_t)s_list[min(q0 + 4 * u, n - 1)].x * d + col);
 #pragma unroll
-        for (int c = 0; c < 8; ++c) acc[c] += s_red[w][lane * 8 + c];
-      Vec8<bf16_t>::store(part + (size_t)slot * d + col, acc);
+      for (int u = 0; u < U; ++u)
+        if (q0 + 4 * u < n) fma8_bf16(__int_as_float(s_list[q0 + 4 * u].y), x[u], acc);
     }
-    __syncthreads();   // s_list and s_red are reused by the next entry
+  }
+  if (wave > 0) Vec8<float>::store(&s_red[wave - 1][lane * 8], acc);
+  __syncthreads();
+  if (wave == 0 && live) {
+#pragma unroll
+    for (int w = 0; w < 3; ++w)
+#pragma unroll
+      for (int c = 0; c < 8; ++c) acc[c] += s_red[w][lane * 8 + c];
+    Vec8<bf16_t>::store(a.out + (size_t)t * d + col, acc);
   }
 }
 
 // backward: ds32[t * k + p] = act > 0 ? dOut[t, :] . V[j, :] : 0 for the pairs of the entry; one wave per pair, the
-// entry's pairs dealt to the 4 * kSmallPairSplit waves of the workgroups blockIdx.y = 0 .. kSmallPairSplit - 1.
-// Dynamic LDS: k ints.
-__global__ __launch_bounds__(256) void small_ds_kernel(const bf16_t* __restrict__ V, const bf16_t* __restrict__ dOut,
+// entry's pairs dealt to the 4 * kSmallPairSplit waves of the workers with the same wx and wy = 0 .. kSmallPairSplit - 1.
+// s_list: k ints.
+__device__ __forceinline__ void small_ds_body(int wx, int nx, int wy, int* s_list, int* s_w, const bf16_t* __restrict__ V, const bf16_t* __restrict__ dOut,
                                                        const int32_t* __restrict__ idx, const float* __restrict__ act,
                                                        const int2* __restrict__ small_ent,
                                                        const int32_t* __restrict__ small_cnt,
                                                        const int32_t* __restrict__ tok_of_slot, int d, int k, int N,
                                                        int bs, float* __restrict__ ds32) {
-  extern __shared__ int s_list[];
-  __shared__ int s_w[4];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int n_ent = small_cnt[0];
-  for (int e = blockIdx.x; e < n_ent; e += gridDim.x) {
+  for (int e = wx; e < n_ent; e += nx) {
     const int g = small_ent[e].x, t = tok_of_slot[small_ent[e].y];
     const int32_t* it = idx + (size_t)t * k;
     const float* at = act + (size_t)t * k;
     const int n = collect_block_pairs(it, k, N, bs, g, s_list, s_w);
     const bf16_t* grow = dOut + (size_t)t * d;
-    for (int q = blockIdx.y * 4 + wave; q < n; q += 4 * kSmallPairSplit) {
+    for (int q = wy * 4 + wave; q < n; q += 4 * kSmallPairSplit) {
       const int p = s_list[q];
       const bf16_t* vrow = V + (size_t)clampi(it[p], 0, N - 1) * d;
       float dot = 0.f;
@@ -186,7 +294,7 @@ __global__ __launch_bounds__(256) void small_ds_kernel(const bf16_t* __restrict_
 
 // backward: dV and dK rows of a small group's block.  Only this group's tokens select neurons of its block, so the
 // touched rows of the block are exactly the rows some token of the group selected.  The chunk of kSmallRowChunk
-// neurons is the fast launch index (blockIdx.x), so that the chunks of one group, whose work is alike, go to the
+// neurons is the fast launch index (wx), so that the chunks of one group, whose work is alike, go to the
 // XCDs in turn whatever the sizes of the groups.  Per (group, chunk): tables in LDS say which tokens of the group
 // select each neuron of the chunk, with which activation and activation gradient; the (selected neuron, 512 columns)
 // pieces are dealt to the four waves, and a neuron's rows are summed over the group's tokens in ascending slot
@@ -211,7 +319,7 @@ __device__ __forceinline__ void small_dvdk_piece(const bf16_t* __restrict__ h, c
   }
 }
 
-__global__ __launch_bounds__(256) void small_dvdk_kernel(const bf16_t* __restrict__ h, const bf16_t* __restrict__ dOut,
+__device__ __forceinline__ void small_dvdk_body(int wx, int wy, int ny, const bf16_t* __restrict__ h, const bf16_t* __restrict__ dOut,
                                                          const int32_t* __restrict__ idx, const float* __restrict__ act,
                                                          const float* __restrict__ ds32,
                                                          const int32_t* __restrict__ small_grp,
@@ -226,9 +334,9 @@ __global__ __launch_bounds__(256) void small_dvdk_kernel(const bf16_t* __restric
   __shared__ int s_nrows;
   static_assert(kSmallRowChunk <= 64, "one lane of the first wave per neuron of the chunk");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int r0 = blockIdx.x * kSmallRowChunk;   // first neuron of the chunk, inside the block
+  const int r0 = wx * kSmallRowChunk;   // first neuron of the chunk, inside the block
   const int n_grp = small_cnt[1];
-  for (int e = blockIdx.y; e < n_grp; e += gridDim.y) {
+  for (int e = wy; e < n_grp; e += ny) {
     const int g = small_grp[e];
     const int slot0 = group_off[g], rows = min(group_off[g + 1] - slot0, kSmallRowsMax);   // (at most small_rows)
     for (int z = tid; z < kSmallRowChunk * kSmallRowsMax; z += 256) (&s_tok[0][0])[z] = -1;
