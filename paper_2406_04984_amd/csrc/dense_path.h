@@ -15,6 +15,7 @@
 // A'[slot, r] = bf16(act) where neuron r of the block is selected by the slot's token, else 0.
 #pragma once
 #include "gemm_mfma.h"
+#include "gemm_tile.h"
 #include "select.h"
 #include "small_groups.h"
 
@@ -70,26 +71,27 @@ struct ProbRouter {
 
 // Token-major, B contiguous along k: rows = tokens of the group (gathered through perm), columns =
 // the block's neurons.  What is written depends on MODE:
-//   kTokScores: key scores, fp32, by entry.
+//   kTokScores: key scores, fp32, by entry;  kTokSlotScores: the same, slot-major.
 //   kTokMasked: the activation gradient, masked by A' > 0, bf16, slot-major (DS').
 //   kTokRelu:   ReLU of the scores (Eq. 2 without a selection: the batch-union evaluation of Algorithm 1), bf16,
 //               written through the same pointer.
-constexpr int kTokScores = 0, kTokMasked = 1, kTokRelu = 2;
+constexpr int kTokScores = 0, kTokMasked = 1, kTokRelu = 2, kTokSlotScores = 3;
+constexpr bool tok_fp32_out(int mode) { return mode == kTokScores || mode == kTokSlotScores; }
 
 template <int MODE>
 struct ProbTokKC {
-  static constexpr int kTM = kTMTok, kSA = MEFT_TOK_SA, kSB = MEFT_TOK_SB, kCW = 4;
+  static constexpr int kTM = kTMTok, kSA = 3, kSB = 3, kCW = 4;
   static constexpr int kLoaders = 2;
   static constexpr bool kAMC = false;
   static constexpr bool kBNC = false;
   static constexpr bool kRowIdsInMemory = false;
   const uint16_t* X;          // h (scores) or dOut (activation gradient), [T, d]
   const uint16_t* W;          // K or V, [N, d]
-  const int32_t* perm; const int32_t* group_off;
+  const int32_t* perm; const int32_t* tok_of_slot;
   TokenSched sched;
   int big_only;               // 1: the groups of at most small_rows tokens are left to the per-pair kernels
   int e, bs, bsp, d;
-  float* sc;                  // kTokScores: [T*e, bs]
+  float* sc;                  // kTokScores, kTokSlotScores: [T*e, bs]
   const uint16_t* Ap;         // kTokMasked: A' [slots, bsp]
   uint16_t* DS;               // kTokMasked / kTokRelu: [slots, bsp]; columns bs..bsp are written as zeros
   uint32_t a_bytes, b_bytes; bool buf;
@@ -97,7 +99,7 @@ struct ProbTokKC {
   __device__ const uint16_t* b_base() const { return W; }
   __device__ bool locate(int wg, TileCoord& tc) const {
     int mt, nt, rows;
-    if (!locate_token_tile(sched, group_off, wg, (bs + kTN - 1) / kTN, big_only != 0, tc.g, mt, nt, tc.slot0, rows))
+    if (!locate_token_tile(sched, wg, (bs + kTN - 1) / kTN, big_only != 0, tc.g, mt, nt, tc.slot0, rows))
       return false;
     tc.m0 = mt * kTM; tc.n0 = nt * kTN; tc.Mrows = rows; tc.Ncols = bs; tc.nk = d / kTK;
     return true;
@@ -109,16 +111,16 @@ struct ProbTokKC {
   __device__ const uint16_t* b_row(const TileCoord& tc, int n) const {
     return W + ((size_t)tc.g * bs + (n < bs ? n : bs - 1)) * d;
   }
-  __device__ int out_cols(const TileCoord&) const { return MODE == kTokScores ? bs : bsp; }
+  __device__ int out_cols(const TileCoord&) const { return tok_fp32_out(MODE) ? bs : bsp; }
   // scores: the row's entry number + 1; otherwise 1 for a row of the group
   __device__ int row_tag(const TileCoord& tc, int m) const {
     if (m >= tc.Mrows) return 0;
     return MODE == kTokScores ? perm[tc.slot0 + m] + 1 : 1;
   }
   static constexpr bool kRowsLinear = MODE != kTokScores;   // the score rows go by entry
-  __device__ int out_ld(const TileCoord&) const { return bsp; }
+  __device__ int out_ld(const TileCoord&) const { return MODE == kTokSlotScores ? bs : bsp; }
   __device__ size_t row_off(const TileCoord& tc, int tag, int m) const {
-    return MODE == kTokScores ? (size_t)(tag - 1) * bs : (size_t)(tc.slot0 + m) * bsp;
+    return MODE == kTokScores ? (size_t)(tag - 1) * bs : (size_t)(tc.slot0 + m) * out_ld(tc);
   }
   // kTokMasked: the two activations of A' that decide whether the two gradient values are kept
   static constexpr bool kAux = MODE == kTokMasked;
@@ -126,7 +128,7 @@ struct ProbTokKC {
     const int mm = m < tc.Mrows ? m : tc.Mrows - 1, nn = n < bsp ? n : bsp - 2;
     return *reinterpret_cast<const uint32_t*>(Ap + (size_t)(tc.slot0 + mm) * bsp + nn);
   }
-  static constexpr bool kOutBf16 = MODE != kTokScores;
+  static constexpr bool kOutBf16 = !tok_fp32_out(MODE);
   __device__ void store2(size_t at, int n, float v0, float v1, uint32_t) const {   // kTokScores
     if ((bs & 1) == 0) {   // rows are 8-byte aligned and n + 1 < bs whenever n < bs
       if (n < bs) *reinterpret_cast<f32x2_hw*>(sc + at) = f32x2_hw{v0, v1};
@@ -137,6 +139,9 @@ struct ProbTokKC {
   }
   __device__ void store_pk(size_t at, int n, uint32_t pk, uint32_t mk) const {   // kTokMasked, kTokRelu
     if (n >= bsp) return;   // bsp is even: n + 1 < bsp
+    *reinterpret_cast<uint32_t*>(DS + at) = keep(pk, n, mk);
+  }
+  __device__ uint32_t keep(uint32_t pk, int n, uint32_t mk) const {
     // a half is kept where the deciding value is positive: sign bit clear and not zero
     uint32_t keep = 0u;
     if constexpr (MODE == kTokMasked) {
@@ -148,21 +153,20 @@ struct ProbTokKC {
       if (n < bs && (pk & 0x7FFFu) != 0u && (pk & 0x8000u) == 0u) keep |= 0xFFFFu;
       if (n + 1 < bs && (pk & 0x7FFF0000u) != 0u && (pk & 0x80000000u) == 0u) keep |= 0xFFFF0000u;
     }
-    *reinterpret_cast<uint32_t*>(DS + at) = pk & keep;
+    return pk & keep;
   }
 };
 
 // Token-major, B contiguous along n: part[slot, :] = A[slot, 0:bs] . W_b   (W = V: forward value sum;
 // W = K: dh).  A is slot-major [slots, bsp] with zero padding in columns bs..bsp.
 struct ProbTokNC {
-  static constexpr int kTM = kTMTok, kSA = MEFT_TOK_SA, kSB = MEFT_TOK_SB, kCW = 4;
+  static constexpr int kTM = kTMTok, kSA = 3, kSB = 3, kCW = 4;
   static constexpr int kLoaders = 4;   // measured: 0.375 -> 0.339 ms (value sum) against two
   static constexpr bool kAMC = false;
   static constexpr bool kBNC = true;
   static constexpr bool kRowIdsInMemory = false;
   const uint16_t* A;          // A' or DS'
   const uint16_t* W;          // V or K, [N, d]
-  const int32_t* group_off;
   TokenSched sched;
   int big_only;               // 1: the groups of at most small_rows tokens are left to the per-pair kernels
   int bs, bsp, d;
@@ -172,7 +176,7 @@ struct ProbTokNC {
   __device__ const uint16_t* b_base() const { return W; }
   __device__ bool locate(int wg, TileCoord& tc) const {
     int mt, nt, rows;
-    if (!locate_token_tile(sched, group_off, wg, (d + kTN - 1) / kTN, big_only != 0, tc.g, mt, nt, tc.slot0, rows))
+    if (!locate_token_tile(sched, wg, (d + kTN - 1) / kTN, big_only != 0, tc.g, mt, nt, tc.slot0, rows))
       return false;
     tc.m0 = mt * kTM; tc.n0 = nt * kTN; tc.Mrows = rows; tc.Ncols = d; tc.nk = bsp / kTK;
     return true;
@@ -213,7 +217,7 @@ struct ProbNeuTN {
   const uint16_t* A;          // [slots, bsp]
   int zrow;                   // number of a row of bsp zeros, counted from A's row 0 (it lies before A: negative)
   const uint16_t* X;          // [T, d]
-  const int32_t* group_off; const int32_t* tok_of_slot;
+  const int32_t* tok_of_slot;
   const int32_t* flag;        // [N] > 0 where some token selected the neuron
   TokenSched sched;           // only the group lists are used: every group has the same number of tiles
   int big_only;               // 1: the groups of at most small_rows tokens are left to the per-pair kernels
@@ -236,9 +240,10 @@ struct ProbNeuTN {
       w = local - gi * (tm * tn);
     }
     if (gi >= as_const(sched.len)[big_only ? kXcd + 1 + x : x]) return false;
-    tc.g = as_const(sched.grp)[(size_t)x * sched.cap + gi].x;
-    tc.slot0 = as_const(group_off)[tc.g];
-    const int rows = as_const(group_off)[tc.g + 1] - tc.slot0;   // > 0: the lists hold non-empty groups only
+    const auto* ent = as_const(sched.grp) + (size_t)x * sched.cap + gi;
+    tc.g = ent->x;
+    tc.slot0 = ent->y;
+    const int rows = ent->z;   // > 0: the lists hold non-empty groups only
     // m tiles vary fastest: the tiles that share the gathered rows of one n tile run together
     tc.m0 = (w % tm) * kTM; tc.n0 = (w / tm) * kTN; tc.Mrows = bs; tc.Ncols = d; tc.nk = round_up64(rows) / kTK;
     tc.aux = rows;
@@ -260,6 +265,40 @@ struct ProbNeuTN {
   __device__ size_t row_off(const TileCoord& tc, int, int m) const { return ((size_t)tc.g * bs + m) * d; }
   static constexpr bool kOutBf16 = true;
   __device__ void store_pk(size_t at, int, uint32_t pk, uint32_t) const { *reinterpret_cast<uint32_t*>(G + at) = pk; }
+};
+
+// ---- the same problems for gemm_tile_kernel -----------------------------------------------------
+template <int MODE, int TM, int TN>
+struct TileTokKC : ProbTokKC<MODE> {
+  using Base = ProbTokKC<MODE>;
+  static constexpr int kTM = TM, kTNt = TN;
+  static constexpr bool kAIds = true;
+  uint32_t o_bytes;
+  __device__ void* out_base() const { return tok_fp32_out(MODE) ? static_cast<void*>(Base::sc) : static_cast<void*>(Base::DS); }
+  __device__ int tiles_n() const { return (Base::bs + TN - 1) / TN; }
+  __device__ void coord(int mt, int nt, TileCoord& tc) const {
+    tc.m0 = mt * TM; tc.n0 = nt * TN; tc.Mrows = tc.aux; tc.Ncols = Base::bs; tc.nk = Base::d / kTK;
+  }
+  __device__ const int32_t* a_ids(const TileCoord& tc) const { return Base::tok_of_slot + tc.slot0 + tc.m0; }
+  __device__ int a_ld() const { return Base::d; }
+  __device__ int b_row0(const TileCoord& tc) const { return tc.g * Base::bs; }
+  __device__ int b_ld() const { return Base::d; }
+};
+
+template <int TM, int TN>
+struct TileTokNC : ProbTokNC {
+  static constexpr int kTM = TM, kTNt = TN;
+  static constexpr bool kAIds = false;
+  uint32_t o_bytes;
+  __device__ void* out_base() const { return part; }
+  __device__ uint32_t keep(uint32_t pk, int, uint32_t) const { return pk; }
+  __device__ int tiles_n() const { return (d + TN - 1) / TN; }
+  __device__ void coord(int mt, int nt, TileCoord& tc) const {
+    tc.m0 = mt * TM; tc.n0 = nt * TN; tc.Mrows = tc.aux; tc.Ncols = d; tc.nk = bsp / kTK;
+  }
+  __device__ int a_ld() const { return bsp; }
+  __device__ int b_row0(const TileCoord& tc) const { return tc.g * bs; }
+  __device__ int b_rows(const TileCoord&) const { return bs; }
 };
 
 // ---- helper kernels ----------------------------------------------------------------------------

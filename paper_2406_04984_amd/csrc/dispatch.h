@@ -97,7 +97,8 @@ struct DispatchTables {
   int32_t *cnt, *group_off, *tile_off;
   int BM;                 // rows per tile of tile_off
   int cap;                // tile schedule: entries per XCD
-  int2* grp;              // nullptr: no tile schedule
+  int4* grp;              // nullptr: no tile schedule
+  int2* tiles;
   int* len;
   int small_rows;
   int2* small_ent;        // nullptr: no lists of small groups
@@ -115,7 +116,7 @@ __device__ __forceinline__ void dispatch_tables(const DispatchTables& t, int row
   if (t.small_ent != nullptr) {
     small_lists_body(rows, go, n_blocks, t.small_rows, t.small_ent, t.small_grp, t.small_cnt, s_w);
   }
-  if (t.grp != nullptr) build_sched_body(rows, n_blocks, t.cap, t.grp, t.len, kTMTok, t.small_rows);   // (no barrier after it)
+  if (t.grp != nullptr) build_sched_body(rows, go, n_blocks, t.cap, t.grp, t.tiles, t.len, t.small_rows);   // (no barrier after it)
 }
 
 // Between the passes where the counts are many, one workgroup: H[chunk][b] becomes the number of entries of block b in

@@ -59,15 +59,10 @@
 namespace meft {
 
 constexpr int kTN = 256, kTK = 64;
-#ifndef MEFT_TOK_TM
-#define MEFT_TOK_TM 128
-#define MEFT_TOK_SA 3
-#define MEFT_TOK_SB 3
-#endif
 #ifndef MEFT_NEU_TM
 #define MEFT_NEU_TM 256
 #endif
-constexpr int kTMTok = MEFT_TOK_TM;    // tile rows of the token-major problems (groups of tokens against a block's rows)
+constexpr int kTMTok = 128;            // tile rows of the token-major problems (groups of tokens against a block's rows)
 constexpr int kTMNeu = 128;            // tile rows of the router
 constexpr int kTMNeuW = MEFT_NEU_TM;   // largest tile rows of the neuron-major problems (dV, dK): 256; 128 rules the larger tile out
 constexpr int kBSlotElems = kTN * kTK;                         // one B slot: 32 KB
@@ -854,8 +849,8 @@ __global__ __launch_bounds__(gemm_threads<P>(), 1) void gemm_mfma_kernel(P p, in
 
 // ---- tile schedule shared by the grouped problems ----------------------------------------------
 // Every non-empty group (block of neurons with its tokens) is given to one XCD; XCD x works through its list
-// in order.  grp[x][i] = (group, number of m tiles -- of tile_m rows -- of the groups before it in this list); an end entry
-// (-1, total m tiles) closes the list.  Inside a group the m tiles vary fastest, so that the tiles that share a
+// in order.  grp[x][i] = (group, first slot, rows, number of 128-row m tiles of the groups before it in this list); an
+// end entry (-1, ., ., total m tiles) closes the list.  tiles[x][i] counts the m tiles in 64 and in 128 rows.  Inside a group the m tiles vary fastest, so that the tiles that share a
 // B panel (one n tile of the group's block) run at the same time and the panel is read from HBM once.
 //
 // Groups differ in size (the router does not balance them), so they are dealt out longest first, each to the
@@ -867,7 +862,8 @@ __global__ __launch_bounds__(gemm_threads<P>(), 1) void gemm_mfma_kernel(P p, in
 // second set of list lengths counts only the larger groups in front of them: a problem that leaves the small groups
 // to the per-pair kernels (small_groups.h) walks that prefix of the same lists.
 struct TokenSched {
-  const int2* grp;       // [kXcd][cap]
+  const int4* grp;       // [kXcd][cap]: group, its first slot, its rows, 128-row m tiles of the groups before it
+  const int2* tiles;     // [kXcd][cap]: 64-row and 128-row m tiles of the groups before it
   const int* len;        // [kXcd] number of groups in the list; [kXcd]: 1 = every list holds every group (split);
                          // [kXcd + 1 + x]: groups of more than small_rows tokens in XCD x's list (a prefix of it)
   int cap;               // entries per XCD (n_groups + 1)
@@ -885,16 +881,23 @@ __device__ __forceinline__ int key_of_lane(const int (&v)[kXcd], int i) {
   return r;
 }
 
-// Executed by one whole workgroup of 1024 threads; rows = number of tokens of group threadIdx.x (0 beyond n_groups).
-// n_groups <= kSchedSortMax.
-__device__ __forceinline__ void build_sched_body(int rows, int n_groups, int cap, int2* __restrict__ grp,
-                                                 int* __restrict__ len, int tile_m, int small_rows) {
+__device__ __forceinline__ void sched_entry(int4* __restrict__ grp, int2* __restrict__ tiles, size_t at, int g, int slot0,
+                                            int rows, int t64, int t128) {
+  grp[at] = make_int4(g, slot0, rows, t128);
+  tiles[at] = make_int2(t64, t128);
+}
+
+// Executed by one whole workgroup of 1024 threads; rows, slot0 = number of tokens and first slot of group threadIdx.x
+// (0 rows beyond n_groups).  n_groups <= kSchedSortMax.
+__device__ __forceinline__ void build_sched_body(int rows, int slot0, int n_groups, int cap, int4* __restrict__ grp,
+                                                 int2* __restrict__ tiles, int* __restrict__ len, int small_rows) {
   __shared__ int s_rows[kSchedSortMax];
+  __shared__ int s_slot[kSchedSortMax];
   __shared__ int s_order[kSchedSortMax];
   __shared__ int s_sorted[kSchedSortMax];
   const int tid = threadIdx.x;
   __syncthreads();   // the arrays may still be read from an earlier use
-  if (tid < n_groups) s_rows[tid] = rows;
+  if (tid < n_groups) { s_rows[tid] = rows; s_slot[tid] = slot0; }
   const int n_full = __syncthreads_count(rows > 0);   // non-empty groups; also orders the writes above
   if (tid < n_groups) {
     int rank = 0;   // position in the order (rows descending, group id ascending): a permutation
@@ -915,13 +918,15 @@ __device__ __forceinline__ void build_sched_body(int rows, int n_groups, int cap
   const int lane = tid;
   if (split) {
     if (lane < kXcd) {
-      int tiles = 0, n_big = 0;
+      int t64 = 0, t128 = 0, n_big = 0;
       for (int i = 0; i < n_full; ++i) {
-        grp[(size_t)lane * cap + i] = make_int2(s_order[i], tiles);
-        n_big += s_sorted[i] > small_rows ? 1 : 0;
-        tiles += (s_sorted[i] + tile_m - 1) / tile_m;
+        const int g = s_order[i], r = s_sorted[i];
+        sched_entry(grp, tiles, (size_t)lane * cap + i, g, s_slot[g], r, t64, t128);
+        n_big += r > small_rows ? 1 : 0;
+        t64 += (r + 63) >> 6;
+        t128 += (r + 127) >> 7;
       }
-      grp[(size_t)lane * cap + n_full] = make_int2(-1, tiles);
+      sched_entry(grp, tiles, (size_t)lane * cap + n_full, -1, 0, 0, t64, t128);
       len[lane] = n_full;
       len[kXcd + 1 + lane] = n_big;
     }
@@ -934,9 +939,9 @@ __device__ __forceinline__ void build_sched_body(int rows, int n_groups, int cap
   int n_deal = 0;
   for (int i0 = 0; i0 < n_full; i0 += 64) n_deal += __popcll(__ballot(i0 + lane < n_full && s_sorted[min(i0 + lane, n_full - 1)] > 64));
   int key = lane < kXcd ? lane : 0x7FFFFFFF;
-  int nx[kXcd], tx[kXcd], bx[kXcd];   // per XCD: list length, tiles, groups of more than small_rows tokens
+  int nx[kXcd], sx[kXcd], tx[kXcd], bx[kXcd];   // per XCD: list length, tiles of 64 and of 128 rows, groups > small_rows
 #pragma unroll
-  for (int x = 0; x < kXcd; ++x) nx[x] = tx[x] = bx[x] = 0;
+  for (int x = 0; x < kXcd; ++x) nx[x] = sx[x] = tx[x] = bx[x] = 0;
   for (int i0 = 0; i0 < n_deal; i0 += 64) {
     const int m = min(64, n_deal - i0), at = min(i0 + lane, n_deal - 1);
     const int r = s_sorted[at], g = s_order[at];
@@ -951,16 +956,18 @@ __device__ __forceinline__ void build_sched_body(int rows, int n_groups, int cap
       key += lane == x ? __builtin_amdgcn_readlane(inc, i) : 0;
       xcd = lane == i ? x : xcd;
     }
-    const int t = (r + tile_m - 1) / tile_m;
+    const int u = (r + 63) >> 6, t = (r + 127) >> 7;
 #pragma unroll
     for (int x = 0; x < kXcd; ++x) {
       const bool mine = xcd == x;
       const unsigned long long mask = __ballot(mine);
-      const int incl = wave_incl_scan(mine ? t : 0);
+      const int iu = wave_incl_scan(mine ? u : 0), it = wave_incl_scan(mine ? t : 0);
       if (mine)
-        grp[(size_t)x * cap + nx[x] + __popcll(mask & ((1ull << lane) - 1ull))] = make_int2(g, tx[x] + incl - t);
+        sched_entry(grp, tiles, (size_t)x * cap + nx[x] + __popcll(mask & ((1ull << lane) - 1ull)), g, s_slot[g], r,
+                    sx[x] + iu - u, tx[x] + it - t);
       nx[x] += __popcll(mask);
-      tx[x] += __builtin_amdgcn_readlane(incl, 63);
+      sx[x] += __builtin_amdgcn_readlane(iu, 63);
+      tx[x] += __builtin_amdgcn_readlane(it, 63);
       bx[x] += __popcll(__ballot(mine && r > small_rows));
     }
   }
@@ -971,7 +978,8 @@ __device__ __forceinline__ void build_sched_body(int rows, int n_groups, int cap
   int load[kXcd];
 #pragma unroll
   for (int x = 0; x < kXcd; ++x) load[x] = __builtin_amdgcn_readlane(key, x) >> 3;
-  const int x = lane & (kXcd - 1), my_load = key_of_lane(load, x), my_n = key_of_lane(nx, x), my_t = key_of_lane(tx, x);
+  const int x = lane & (kXcd - 1), my_load = key_of_lane(load, x), my_n = key_of_lane(nx, x), my_u = key_of_lane(sx, x),
+            my_t = key_of_lane(tx, x);
   for (int j0 = 0; j0 < n_eq; j0 += 8) {
     const int j = j0 + (lane >> 3), k = my_load + 3 * j;
     int rank = 0;
@@ -983,8 +991,9 @@ __device__ __forceinline__ void build_sched_body(int rows, int n_groups, int cap
     const bool valid = rank < n_eq;
     bool big = false;
     if (valid) {
-      grp[(size_t)x * cap + my_n + j] = make_int2(s_order[n_deal + rank], my_t + j);
-      big = s_sorted[n_deal + rank] > small_rows;
+      const int g = s_order[n_deal + rank], r = s_sorted[n_deal + rank];
+      sched_entry(grp, tiles, (size_t)x * cap + my_n + j, g, s_slot[g], r, my_u + j, my_t + j);
+      big = r > small_rows;
     }
     const unsigned long long mv = __ballot(valid), mb = __ballot(big);
     if (!mv) break;
@@ -993,35 +1002,38 @@ __device__ __forceinline__ void build_sched_body(int rows, int n_groups, int cap
       const unsigned long long my = 0x0101010101010101ull << y;
       const int c = __popcll(mv & my);
       nx[y] += c;
+      sx[y] += c;
       tx[y] += c;
       bx[y] += __popcll(mb & my);
     }
   }
   if (lane < kXcd) {
     const int n = key_of_lane(nx, lane);
-    grp[(size_t)lane * cap + n] = make_int2(-1, key_of_lane(tx, lane));
+    sched_entry(grp, tiles, (size_t)lane * cap + n, -1, 0, 0, key_of_lane(sx, lane), key_of_lane(tx, lane));
     len[lane] = n;
     len[kXcd + 1 + lane] = key_of_lane(bx, lane);
   }
 }
 
 __global__ __launch_bounds__(1024) void build_sched_kernel(const int32_t* __restrict__ group_off, int n_groups,
-                                                           int cap, int2* __restrict__ grp, int* __restrict__ len,
-                                                           int tile_m, int small_rows) {
+                                                           int cap, int4* __restrict__ grp, int2* __restrict__ tiles,
+                                                           int* __restrict__ len, int small_rows) {
   const int tid = threadIdx.x;
   if (n_groups <= kSchedSortMax) {
-    build_sched_body(tid < n_groups ? group_off[tid + 1] - group_off[tid] : 0, n_groups, cap, grp, len, tile_m, small_rows);
+    const int s0 = tid < n_groups ? group_off[tid] : 0;
+    build_sched_body(tid < n_groups ? group_off[tid + 1] - s0 : 0, s0, n_groups, cap, grp, tiles, len, small_rows);
   } else if (tid < kXcd) {
     const int x = tid;
     if (x == 0) len[kXcd] = 0;
-    int n = 0, tiles = 0;
+    int n = 0, t64 = 0, t128 = 0;
     for (int g = x; g < n_groups; g += kXcd) {
-      const int rows = group_off[g + 1] - group_off[g];
+      const int s0 = group_off[g], rows = group_off[g + 1] - s0;
       if (rows == 0) continue;
-      grp[(size_t)x * cap + n++] = make_int2(g, tiles);
-      tiles += (rows + tile_m - 1) / tile_m;
+      sched_entry(grp, tiles, (size_t)x * cap + n++, g, s0, rows, t64, t128);
+      t64 += (rows + 63) >> 6;
+      t128 += (rows + 127) >> 7;
     }
-    grp[(size_t)x * cap + n] = make_int2(-1, tiles);
+    sched_entry(grp, tiles, (size_t)x * cap + n, -1, 0, 0, t64, t128);
     len[x] = n;
     len[kXcd + 1 + x] = n;   // unsorted lists: no group counts as small (the host passes small_rows = 0 here)
   }
@@ -1029,7 +1041,7 @@ __global__ __launch_bounds__(1024) void build_sched_kernel(const int32_t* __rest
 
 // big_only: walk only the groups of more than small_rows tokens (the prefix of every list that the second set of
 // lengths describes)
-__device__ __forceinline__ bool locate_token_tile(const TokenSched& s, const int32_t* group_off, int wg, int tn,
+__device__ __forceinline__ bool locate_token_tile(const TokenSched& s, int wg, int tn,
                                                    bool big_only, int& g, int& mt, int& nt, int& slot0, int& rows) {
   const int x = wg & (kXcd - 1), local = wg >> 3;
   const int n = as_const(s.len)[big_only ? kXcd + 1 + x : x];
@@ -1038,34 +1050,34 @@ __device__ __forceinline__ bool locate_token_tile(const TokenSched& s, const int
     // split lists (fewer than 8 entries): XCD x takes the tiles x, x + 8, ... of every group, m tiles fastest
     int rest = local;
     for (int i = 0; i < n; ++i) {
-      const int tm = list[i + 1].y - list[i].y, all = tm * tn;
+      const int tm = list[i + 1].w - list[i].w, all = tm * tn;
       const int mine = all > x ? (all - x + kXcd - 1) / kXcd : 0;
       if (rest < mine) {
         const int w = x + kXcd * rest;
         g = list[i].x;
         nt = w / tm;
         mt = w - nt * tm;
-        slot0 = as_const(group_off)[g];
-        rows = as_const(group_off)[g + 1] - slot0;
+        slot0 = list[i].y;
+        rows = list[i].z;
         return true;
       }
       rest -= mine;
     }
     return false;
   }
-  if (n == 0 || local >= list[n].y * tn) return false;
-  int lo = 0, hi = n;  // list[lo].y * tn <= local < list[hi].y * tn
+  if (n == 0 || local >= list[n].w * tn) return false;
+  int lo = 0, hi = n;  // list[lo].w * tn <= local < list[hi].w * tn
   while (hi - lo > 1) {
     const int mid = (lo + hi) >> 1;
-    if (list[mid].y * tn <= local) lo = mid; else hi = mid;
+    if (list[mid].w * tn <= local) lo = mid; else hi = mid;
   }
   g = list[lo].x;
-  const int tm = list[lo + 1].y - list[lo].y;
-  const int w = local - list[lo].y * tn;
+  const int tm = list[lo + 1].w - list[lo].w;
+  const int w = local - list[lo].w * tn;
   nt = w / tm;
   mt = w - nt * tm;
-  slot0 = as_const(group_off)[g];
-  rows = as_const(group_off)[g + 1] - slot0;
+  slot0 = list[lo].y;
+  rows = list[lo].z;
   return true;
 }
 

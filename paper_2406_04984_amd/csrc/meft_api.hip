@@ -179,7 +179,8 @@ struct DispatchWs {
   int32_t* chunk_hist = nullptr;   // three-pass dispatch: [chunks][n_blocks]
   int32_t *sblk = nullptr, *cnt = nullptr, *group_off = nullptr, *tile_off = nullptr, *perm = nullptr,
           *tok_of_slot = nullptr, *slot_of_ent = nullptr, *sched_len = nullptr;
-  int2* sched_pairs = nullptr;
+  int4* sched_pairs = nullptr;
+  int2* sched_tiles = nullptr;
   // the groups of at most small_rows_of(s) tokens and their entries (small_groups.h), and the two list lengths
   int2* small_ent = nullptr;
   int32_t *small_grp = nullptr, *small_cnt = nullptr;
@@ -193,7 +194,8 @@ struct DispatchWs {
     tok_of_slot = c.take<int32_t>(n_ent + kSlotPad);   // padded: see kSlotPad
     slot_of_ent = c.take<int32_t>(n_ent);
     sched_len = c.take<int32_t>(kSchedLenInts);   // list lengths per XCD, the split flag, lengths without small groups
-    sched_pairs = c.take<int2>((size_t)kXcd * sched_cap(s));
+    sched_pairs = c.take<int4>((size_t)kXcd * sched_cap(s));
+    sched_tiles = c.take<int2>((size_t)kXcd * sched_cap(s));
     chunk_hist = c.take<int32_t>(fast_dispatch(s) ? (size_t)disp_chunks(s) * s.n_blocks : 0);
     const size_t small = (size_t)small_rows_of(s);
     small_ent = c.take<int2>(small ? small * s.n_blocks : 0);
@@ -506,11 +508,12 @@ std::atomic<int> g_force_global_loads{[] {
   return (env && env[0] == '1') ? 1 : 0;
 }()};
 
+constexpr uint64_t kBufLimit = 0xFFFF0000ull;   // bytes that a buffer resource's 32-bit offsets reach
+
 template <class P>
 void set_gemm_extents(P& p, uint64_t a_bytes, uint64_t b_bytes) {
-  constexpr uint64_t kLimit = 0xFFFF0000ull;
   const bool forced_global = g_force_global_loads.load(std::memory_order_relaxed) != 0;
-  p.buf = !forced_global && a_bytes < kLimit && b_bytes < kLimit;
+  p.buf = !forced_global && a_bytes < kBufLimit && b_bytes < kBufLimit;
   p.a_bytes = p.buf ? (uint32_t)a_bytes : 0u;
   p.b_bytes = p.buf ? (uint32_t)b_bytes : 0u;
 }
@@ -533,6 +536,52 @@ void launch_gemm_mfma(const char* name, const P& prob, int grid, hipStream_t st)
     MEFT_LAUNCH(name, (gemm_mfma_kernel<P, false>), dim3(launch), dim3(gemm_threads<P>()), gemm_lds_bytes<P>(), st, prob, grid);
   }
 }
+
+template <class P>
+void launch_gemm_tile(const char* name, const P& prob, int64_t tiles, hipStream_t st) {
+  static std::once_flag configured;
+  std::call_once(configured, [] {
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_tile_kernel<P>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                              gemm_tile_lds<P>());
+  });
+  const int bound = (int)(tiles < (int64_t)INT32_MAX ? tiles : (int64_t)INT32_MAX);
+  const int launch = bound < 2 * kPersistentWgs ? bound : 2 * kPersistentWgs;   // two workgroups per compute unit
+  MEFT_LAUNCH(name, gemm_tile_kernel<P>, dim3(launch), dim3(256), gemm_tile_lds<P>(), st, prob, bound);
+}
+
+// Whether a token-major contraction over `cols` output columns runs on small tiles.  What a compute unit's time goes by
+// is the kilobytes per k tile it takes into LDS: 48 for each of its 128 x 256 tiles, 24 for each 64 x 128 tile; large
+// tiles come in whole rounds of one per compute unit, small ones two at a time.  Groups are taken to be alike, each
+// with half a tile to spare.
+bool small_tiles(const meft_shape& s, int cols) {
+  const int64_t n_ent = (int64_t)s.T * s.top_e, groups = s.n_blocks < n_ent ? s.n_blocks : n_ent;
+  const int64_t large = (n_ent / kTMTok + (groups + 1) / 2) * ((cols + kTN - 1) / kTN);
+  const int64_t small = (n_ent / 64 + (groups + 1) / 2) * ((cols + 127) / 128);
+  const int64_t cost_large = (large + kPersistentWgs - 1) / kPersistentWgs * kPersistentWgs * 48;
+  return (small < kPersistentWgs ? kPersistentWgs : small) * 24 < cost_large;
+}
+
+// Fills in a token-major policy's fields and launches it with the tiles that suit the problem.
+template <class Large, class Small, class F>
+void launch_tok(const char* name, const meft_shape& s, int cols, uint64_t a_bytes, uint64_t b_bytes, uint64_t o_bytes, F&& fill,
+                hipStream_t st) {
+  Small q{};
+  set_gemm_extents(q, a_bytes, b_bytes);
+  if (q.buf && o_bytes < kBufLimit && (s.block_size & 1) == 0 && small_tiles(s, cols)) {
+    q.o_bytes = (uint32_t)o_bytes;
+    fill(q);
+    const int64_t m_tiles = (int64_t)s.T * s.top_e / Small::kTM + s.n_blocks;
+    launch_gemm_tile(name, q, kXcd * m_tiles * ((cols + Small::kTNt - 1) / Small::kTNt), st);
+    return;
+  }
+  Large p{};
+  set_gemm_extents(p, a_bytes, b_bytes);
+  fill(p);
+  launch_gemm_mfma(name, p, tile_bound(s, (cols + kTN - 1) / kTN), st);
+}
+template <int MODE> using TokKCLarge = ProbTokKC<MODE>;
+template <int MODE> using TokKCSmall = TileTokKC<MODE, 64, 128>;
+using TokNCSmall = TileTokNC<64, 128>;
 
 // (token, block) dispatch: groups, slot maps, XCD tile schedule; with block_idx the per-token block lists are sorted
 // first (otherwise w.sblk holds them).  `clear`: words set to zero on the way.
@@ -557,7 +606,7 @@ void launch_dispatch(const meft_shape& s, const DispatchWs& w, const int32_t* bl
       MEFT_LAUNCH("dispatch_count", dispatch_count_kernel<false>, dim3(n_chunks), dim3(1024), lds, st, w.sblk, n_ent,
                   s.top_e, epc, s.n_blocks, nullptr, w.chunk_hist, clear, clear_words);
     const DispatchTables tab{w.cnt, w.group_off, w.tile_off, BM, sched_cap(s), want_sched ? w.sched_pairs : nullptr,
-                             w.sched_len, small, small ? w.small_ent : nullptr, w.small_grp, w.small_cnt};
+                             w.sched_tiles, w.sched_len, small, small ? w.small_ent : nullptr, w.small_grp, w.small_cnt};
     int32_t* tok = dense ? w.tok_of_slot : nullptr;
     int lg = 0;
     while ((1 << lg) < s.n_blocks) ++lg;
@@ -586,7 +635,7 @@ void launch_dispatch(const meft_shape& s, const DispatchWs& w, const int32_t* bl
   }
   if (want_sched) {
     MEFT_LAUNCH("build_sched", build_sched_kernel, dim3(1), dim3(1024), 0, st, w.group_off, s.n_blocks,
-                sched_cap(s), w.sched_pairs, w.sched_len, kTMTok, small);
+                sched_cap(s), w.sched_pairs, w.sched_tiles, w.sched_len, small);
   }
   if (small) {
     MEFT_LAUNCH("small_lists", small_lists_kernel, dim3(1), dim3(1024), 0, st, w.group_off, s.n_blocks, small,
@@ -650,7 +699,7 @@ int neu_tile_rows(int block_rows) {
 // One weight-gradient contraction (dV: A = A', X = dOut; dK: A = DS', X = h) over the groups of a tile schedule
 struct NeuArgs {
   const uint16_t* A; int zrow; const uint16_t* X; uint16_t* G;
-  const int32_t *group_off, *tok_of_slot, *flag;
+  const int32_t *tok_of_slot, *flag;
   TokenSched sched;
   int big_only, n_groups, bs, bsp, d;
   uint64_t a_bytes, x_bytes;   // bytes readable from the lowest address of either operand
@@ -660,7 +709,7 @@ template <int TM>
 void launch_neu_tm(const char* name, const NeuArgs& a, hipStream_t st) {
   ProbNeuTN<TM> pn{};
   pn.A = a.A; pn.zrow = a.zrow; pn.X = a.X; pn.G = a.G;
-  pn.group_off = a.group_off; pn.tok_of_slot = a.tok_of_slot; pn.flag = a.flag;
+  pn.tok_of_slot = a.tok_of_slot; pn.flag = a.flag;
   pn.sched = a.sched; pn.big_only = a.big_only; pn.bs = a.bs; pn.bsp = a.bsp; pn.d = a.d;
   set_gemm_extents(pn, a.a_bytes, a.x_bytes);
   // every listed group has the same tiles; in the worst case one XCD holds all groups
@@ -778,16 +827,23 @@ static meft_status fwd_impl(const meft_shape& s, const void* h, const void* K, c
   const bool mfma_scores = dense || use_mfma_scores(s);
   launch_dispatch(s, w, block_idx, BM, dense, mfma_scores, dense ? w.flag : nullptr, dense ? w.clear_words() : 0, st);
   const int bsp = round64(s.block_size);
-  const TokenSched sched{w.sched_pairs, w.sched_len, sched_cap(s), sched_max_tiles(s)};
+  const TokenSched sched{w.sched_pairs, w.sched_tiles, w.sched_len, sched_cap(s), sched_max_tiles(s)};
   const uint16_t *hh = static_cast<const uint16_t*>(h), *kk = static_cast<const uint16_t*>(K),
                  *vv = static_cast<const uint16_t*>(V);
   if (wait_k && hipStreamWaitEvent(st, wait_k, 0) != hipSuccess) return MEFT_ERR_DEVICE;
   if (mfma_scores) {
-    ProbTokKC<kTokScores> ps{};
-    ps.X = hh; ps.W = kk; ps.perm = w.perm; ps.group_off = w.group_off; ps.sched = sched;
-    ps.e = s.top_e; ps.bs = s.block_size; ps.bsp = bsp; ps.d = s.d; ps.sc = w.sc;
-    set_gemm_extents(ps, (uint64_t)s.T * s.d * 2, (uint64_t)s.N * s.d * 2);
-    launch_gemm_mfma("score_gemm", ps, tile_bound(s, (s.block_size + kTN - 1) / kTN), st);
+    auto fill = [&](auto& ps) {
+      ps.X = hh; ps.W = kk; ps.perm = w.perm; ps.tok_of_slot = w.tok_of_slot; ps.sched = sched;
+      ps.e = s.top_e; ps.bs = s.block_size; ps.bsp = bsp; ps.d = s.d; ps.sc = w.sc;
+    };
+    if (dense) {
+      launch_tok<TokKCLarge<kTokSlotScores>, TokKCSmall<kTokSlotScores>>("score_gemm", s, s.block_size, (uint64_t)s.T * s.d * 2, (uint64_t)s.N * s.d * 2, (uint64_t)n_ent * s.block_size * 4, fill, st);
+    } else {
+      ProbTokKC<kTokScores> ps{};
+      set_gemm_extents(ps, (uint64_t)s.T * s.d * 2, (uint64_t)s.N * s.d * 2);
+      fill(ps);
+      launch_gemm_mfma("score_gemm", ps, tile_bound(s, (s.block_size + kTN - 1) / kTN), st);
+    }
   } else {
     GemmNTArgs a{};
     a.A = h; a.Bm = K; a.C = w.sc; a.perm = w.perm; a.group_off = w.group_off; a.tile_off = w.tile_off;
@@ -825,11 +881,10 @@ static meft_status fwd_impl(const meft_shape& s, const void* h, const void* K, c
   if (wait_v && hipStreamWaitEvent(st, wait_v, 0) != hipSuccess) return MEFT_ERR_DEVICE;
   if (!out) return launch_status();   // selection only
   if (dense) {
-    ProbTokNC pv{};
-    pv.A = w.Ap; pv.W = vv; pv.group_off = w.group_off; pv.sched = sched; pv.bs = s.block_size; pv.bsp = bsp;
-    pv.d = s.d; pv.part = w.part; pv.big_only = small_rows_of(s) > 0;
-    set_gemm_extents(pv, (uint64_t)n_ent * bsp * 2, (uint64_t)s.N * s.d * 2);
-    launch_gemm_mfma("value_gemm", pv, tile_bound(s, (s.d + kTN - 1) / kTN), st);
+    launch_tok<ProbTokNC, TokNCSmall>("value_gemm", s, s.d, (uint64_t)n_ent * bsp * 2, (uint64_t)s.N * s.d * 2, (uint64_t)n_ent * s.d * 2, [&](auto& pv) {
+      pv.A = w.Ap; pv.W = vv; pv.sched = sched; pv.bs = s.block_size; pv.bsp = bsp;
+      pv.d = s.d; pv.part = w.part; pv.big_only = small_rows_of(s) > 0;
+    }, st);
     launch_token_rows("out_rows", s, w.part, w, V, idx, act, out, SmallDvdk{}, st);
   } else if (s.dtype == MEFT_BF16) {
     launch_gather_fwd<bf16_t>(s, V, idx, act, out, st);
@@ -870,11 +925,11 @@ static meft_status bwd_impl(const meft_shape& s, const void* h, const void* K, c
     const int small = small_rows_of(s);
     // (with host-resident V still on its way the small groups' gradients wait for it)
     launch_bwd_head(s, w.flag, w.chunk_cnt, touched, n_touched, small && !wait_v ? &w : nullptr, V, dOut, idx, act, st);
-    const TokenSched sched{w.sched_pairs, w.sched_len, sched_cap(s), sched_max_tiles(s)};
+    const TokenSched sched{w.sched_pairs, w.sched_tiles, w.sched_len, sched_cap(s), sched_max_tiles(s)};
     const int big_only = small > 0;   // the small groups: computed pair by pair
     const int n_ent = s.T * s.top_e;
     NeuArgs pn{};
-    pn.group_off = w.group_off; pn.tok_of_slot = w.tok_of_slot; pn.flag = w.flag;
+    pn.tok_of_slot = w.tok_of_slot; pn.flag = w.flag;
     pn.sched = sched; pn.big_only = big_only; pn.n_groups = s.n_blocks; pn.bs = s.block_size; pn.bsp = bsp; pn.d = s.d;
     pn.a_bytes = (uint64_t)(1 + 2 * (uint64_t)n_ent) * bsp * 2; pn.x_bytes = (uint64_t)s.T * s.d * 2;
     // dV first: it needs neither K nor V (so it also runs while host-resident K, V are still on their way), and it
@@ -882,12 +937,11 @@ static meft_status bwd_impl(const meft_shape& s, const void* h, const void* K, c
     pn.A = w.Ap; pn.zrow = -1; pn.X = gg; pn.G = static_cast<uint16_t*>(dV);
     launch_neu("dV_gemm", pn, st);
     if (wait_v && hipStreamWaitEvent(st, wait_v, 0) != hipSuccess) return MEFT_ERR_DEVICE;
-    ProbTokKC<kTokMasked> pg{};
-    pg.X = gg; pg.W = vv; pg.perm = w.perm; pg.group_off = w.group_off; pg.sched = sched;
-    pg.e = s.top_e; pg.bs = s.block_size; pg.bsp = bsp; pg.d = s.d; pg.Ap = w.Ap; pg.DS = w.DS;
-    pg.big_only = big_only;
-    set_gemm_extents(pg, (uint64_t)s.T * s.d * 2, (uint64_t)s.N * s.d * 2);
-    launch_gemm_mfma("dact_gemm", pg, tile_bound(s, (s.block_size + kTN - 1) / kTN), st);
+    launch_tok<TokKCLarge<kTokMasked>, TokKCSmall<kTokMasked>>("dact_gemm", s, s.block_size, (uint64_t)s.T * s.d * 2, (uint64_t)s.N * s.d * 2, (uint64_t)n_ent * bsp * 2, [&](auto& pg) {
+      pg.X = gg; pg.W = vv; pg.perm = w.perm; pg.tok_of_slot = w.tok_of_slot; pg.sched = sched;
+      pg.e = s.top_e; pg.bs = s.block_size; pg.bsp = bsp; pg.d = s.d; pg.Ap = w.Ap; pg.DS = w.DS;
+      pg.big_only = big_only;
+    }, st);
     if (small && wait_v) launch_bwd_head(s, w.flag, w.chunk_cnt, touched, n_touched, &w, V, dOut, idx, act, st);
     if (wait_k && hipStreamWaitEvent(st, wait_k, 0) != hipSuccess) return MEFT_ERR_DEVICE;
     SmallDvdk dv{};
@@ -901,11 +955,10 @@ static meft_status bwd_impl(const meft_shape& s, const void* h, const void* K, c
       dv.dK = static_cast<bf16_t*>(dK); dv.dV = static_cast<bf16_t*>(dV);
     }
     if (dh) {
-      ProbTokNC ph{};
-      ph.A = w.DS; ph.W = kk; ph.group_off = w.group_off; ph.sched = sched; ph.bs = s.block_size; ph.bsp = bsp;
-      ph.d = s.d; ph.part = w.part; ph.big_only = big_only;
-      set_gemm_extents(ph, (uint64_t)n_ent * bsp * 2, (uint64_t)s.N * s.d * 2);
-      launch_gemm_mfma("dh_gemm", ph, tile_bound(s, (s.d + kTN - 1) / kTN), st);
+      launch_tok<ProbTokNC, TokNCSmall>("dh_gemm", s, s.d, (uint64_t)n_ent * bsp * 2, (uint64_t)s.N * s.d * 2, (uint64_t)n_ent * s.d * 2, [&](auto& ph) {
+        ph.A = w.DS; ph.W = kk; ph.sched = sched; ph.bs = s.block_size; ph.bsp = bsp;
+        ph.d = s.d; ph.part = w.part; ph.big_only = big_only;
+      }, st);
       launch_token_rows("dh_rows", s, w.part, w, K, idx, w.ds32, dh, dv, st);
     } else if (small) {
       TokenRows a{};
@@ -947,7 +1000,7 @@ static void union_front(const meft_shape& s, const UnionGeom& g, const UnionWs& 
   MEFT_LAUNCH("union_maps", union_maps_kernel, dim3((unsigned)((n_thr + 255) / 256)), dim3(256), 0, st, n_S, g.cap,
               s.T, g.vbs, g.nvb, w.sblk, w.perm, w.tok_of_slot, w.slot_of_ent, w.group_off, w.rowflag);
   MEFT_LAUNCH("build_sched", build_sched_kernel, dim3(1), dim3(1024), 0, st, w.group_off, g.nvb, sched_cap(g.vs),
-              w.sched_pairs, w.sched_len, kTMTok, 0);
+              w.sched_pairs, w.sched_tiles, w.sched_len, 0);
   // the row of zeros that pads the contraction over tokens in the weight-gradient GEMMs (vbs % 64 == 0)
   MEFT_LAUNCH("fill_i32", fill_i32_kernel, dim3((g.vbs / 2 + 255) / 256), dim3(256), 0, st,
               reinterpret_cast<int32_t*>(w.zrow), (size_t)g.vbs / 2, 0);
@@ -956,13 +1009,12 @@ static void union_front(const meft_shape& s, const UnionGeom& g, const UnionWs& 
               S, n_S, g.cap, s.N, s.d, g.vbs, w.Kc);
   MEFT_LAUNCH("gather_rows", gather_rows_kernel, dim3(rows_grid), dim3(256), 0, st, static_cast<const uint16_t*>(V),
               S, n_S, g.cap, s.N, s.d, g.vbs, w.Vc);
-  const TokenSched sched{w.sched_pairs, w.sched_len, sched_cap(g.vs), sched_max_tiles(g.vs)};
-  ProbTokKC<kTokRelu> pr{};
-  pr.X = static_cast<const uint16_t*>(h); pr.W = w.Kc; pr.perm = w.perm; pr.group_off = w.group_off;
-  pr.sched = sched; pr.e = g.nvb; pr.bs = g.vbs; pr.bsp = g.vbs; pr.d = s.d;
-  pr.DS = w.Ap;
-  set_gemm_extents(pr, (uint64_t)s.T * s.d * 2, (uint64_t)n_rows * s.d * 2);
-  launch_gemm_mfma("union_score_gemm", pr, tile_bound(g.vs, (g.vbs + kTN - 1) / kTN), st);
+  const TokenSched sched{w.sched_pairs, w.sched_tiles, w.sched_len, sched_cap(g.vs), sched_max_tiles(g.vs)};
+  launch_tok<TokKCLarge<kTokRelu>, TokKCSmall<kTokRelu>>("union_score_gemm", g.vs, g.vbs, (uint64_t)s.T * s.d * 2, (uint64_t)n_rows * s.d * 2, (uint64_t)s.T * g.nvb * g.vbs * 2, [&](auto& pr) {
+    pr.X = static_cast<const uint16_t*>(h); pr.W = w.Kc; pr.perm = w.perm; pr.tok_of_slot = w.tok_of_slot;
+    pr.sched = sched; pr.e = g.nvb; pr.bs = g.vbs; pr.bsp = g.vbs; pr.d = s.d;
+    pr.DS = w.Ap;
+  }, st);
 }
 
 extern "C" {
@@ -998,12 +1050,11 @@ meft_status meft_union_fwd(const meft_shape* shape, const void* h, const void* K
   MEFT_LAUNCH("mark_idx", mark_idx_kernel, dim3((P + 255) / 256), dim3(256), 0, st, idx, P, s.N, w.flag);
   launch_bwd_head(s, w.flag, w.chunk_cnt, S, n_S, nullptr, nullptr, nullptr, nullptr, nullptr, st);
   union_front(s, g, w, h, K, V, S, n_S, st);
-  const TokenSched sched{w.sched_pairs, w.sched_len, sched_cap(g.vs), sched_max_tiles(g.vs)};
-  ProbTokNC pv{};
-  pv.A = w.Ap; pv.W = w.Vc; pv.group_off = w.group_off; pv.sched = sched; pv.bs = g.vbs; pv.bsp = g.vbs;
-  pv.d = s.d; pv.part = w.part;
-  set_gemm_extents(pv, (uint64_t)s.T * g.nvb * g.vbs * 2, (uint64_t)g.nvb * g.vbs * s.d * 2);
-  launch_gemm_mfma("union_value_gemm", pv, tile_bound(g.vs, (s.d + kTN - 1) / kTN), st);
+  const TokenSched sched{w.sched_pairs, w.sched_tiles, w.sched_len, sched_cap(g.vs), sched_max_tiles(g.vs)};
+  launch_tok<ProbTokNC, TokNCSmall>("union_value_gemm", g.vs, s.d, (uint64_t)s.T * g.nvb * g.vbs * 2, (uint64_t)g.nvb * g.vbs * s.d * 2, (uint64_t)s.T * g.nvb * s.d * 2, [&](auto& pv) {
+    pv.A = w.Ap; pv.W = w.Vc; pv.sched = sched; pv.bs = g.vbs; pv.bsp = g.vbs;
+    pv.d = s.d; pv.part = w.part;
+  }, st);
   launch_token_rows("union_out_rows", g.vs, w.part, w, nullptr, nullptr, nullptr, out, SmallDvdk{}, st);
   return launch_status();
 }
@@ -1027,23 +1078,21 @@ meft_status meft_union_bwd(const meft_shape* shape, const void* h, const void* K
   MEFT_API_LOCK();
   clear_stale_error();
   union_front(s, g, w, h, K, V, S, n_S, st);
-  const TokenSched sched{w.sched_pairs, w.sched_len, sched_cap(g.vs), sched_max_tiles(g.vs)};
+  const TokenSched sched{w.sched_pairs, w.sched_tiles, w.sched_len, sched_cap(g.vs), sched_max_tiles(g.vs)};
   const uint16_t *hh = static_cast<const uint16_t*>(h), *gg = static_cast<const uint16_t*>(dOut);
-  ProbTokKC<kTokMasked> pg{};
-  pg.X = gg; pg.W = w.Vc; pg.perm = w.perm; pg.group_off = w.group_off; pg.sched = sched;
-  pg.e = g.nvb; pg.bs = g.vbs; pg.bsp = g.vbs; pg.d = s.d; pg.Ap = w.Ap; pg.DS = w.DS;
-  set_gemm_extents(pg, (uint64_t)s.T * s.d * 2, (uint64_t)g.nvb * g.vbs * s.d * 2);
-  launch_gemm_mfma("union_dact_gemm", pg, tile_bound(g.vs, (g.vbs + kTN - 1) / kTN), st);
+  launch_tok<TokKCLarge<kTokMasked>, TokKCSmall<kTokMasked>>("union_dact_gemm", g.vs, g.vbs, (uint64_t)s.T * s.d * 2, (uint64_t)g.nvb * g.vbs * s.d * 2, (uint64_t)s.T * g.nvb * g.vbs * 2, [&](auto& pg) {
+    pg.X = gg; pg.W = w.Vc; pg.perm = w.perm; pg.tok_of_slot = w.tok_of_slot; pg.sched = sched;
+    pg.e = g.nvb; pg.bs = g.vbs; pg.bsp = g.vbs; pg.d = s.d; pg.Ap = w.Ap; pg.DS = w.DS;
+  }, st);
   if (dh) {
-    ProbTokNC ph{};
-    ph.A = w.DS; ph.W = w.Kc; ph.group_off = w.group_off; ph.sched = sched; ph.bs = g.vbs; ph.bsp = g.vbs;
-    ph.d = s.d; ph.part = w.part;
-    set_gemm_extents(ph, (uint64_t)s.T * g.nvb * g.vbs * 2, (uint64_t)g.nvb * g.vbs * s.d * 2);
-    launch_gemm_mfma("union_dh_gemm", ph, tile_bound(g.vs, (s.d + kTN - 1) / kTN), st);
+    launch_tok<ProbTokNC, TokNCSmall>("union_dh_gemm", g.vs, s.d, (uint64_t)s.T * g.nvb * g.vbs * 2, (uint64_t)g.nvb * g.vbs * s.d * 2, (uint64_t)s.T * g.nvb * s.d * 2, [&](auto& ph) {
+      ph.A = w.DS; ph.W = w.Kc; ph.sched = sched; ph.bs = g.vbs; ph.bsp = g.vbs;
+      ph.d = s.d; ph.part = w.part;
+    }, st);
     launch_token_rows("union_dh_rows", g.vs, w.part, w, nullptr, nullptr, nullptr, dh, SmallDvdk{}, st);
   }
   NeuArgs pn{};
-  pn.group_off = w.group_off; pn.tok_of_slot = w.tok_of_slot; pn.flag = w.rowflag;
+  pn.tok_of_slot = w.tok_of_slot; pn.flag = w.rowflag;
   pn.sched = sched; pn.big_only = 0; pn.n_groups = g.nvb; pn.bs = g.vbs; pn.bsp = g.vbs; pn.d = s.d;
   pn.a_bytes = (1 + 2 * (uint64_t)s.T * g.nvb) * g.vbs * 2; pn.x_bytes = (uint64_t)s.T * s.d * 2;
   pn.A = w.Ap; pn.zrow = -1; pn.X = gg; pn.G = w.dVc;

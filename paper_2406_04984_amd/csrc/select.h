@@ -152,7 +152,7 @@ __global__ __launch_bounds__(1024) void fill_groups_kernel(const int32_t* __rest
 // equals still belong; then one ordered sweep emits the selected positions in ascending order: all keys above
 // the threshold, and the first `need` positions that equal it.  With Ap != nullptr it also writes the token's
 // dense activation rows (one per chosen block, slot-major, zero where not selected) and marks the selected neurons in
-// `flag` (zero before).
+// `flag` (zero before); the scores then come slot-major too.
 //
 // The token's keys live in registers: thread `tid` owns the KPT consecutive candidate
 // positions tid*KPT .. tid*KPT + KPT - 1 (256 * KPT >= C), reads them once from global memory and keeps their
@@ -198,6 +198,44 @@ __device__ __forceinline__ void topk_load_keys(const float* __restrict__ row, in
   } else {
 #pragma unroll
     for (int z = 0; z < KPT; ++z) key[z] = p0 + z < C ? order_key(row[p0 + z]) : 0u;
+  }
+}
+
+// The same where the scores are slot-major: block entry q of the token has its bs scores in row slot[q] of sc.
+template <int KPT>
+__device__ __forceinline__ void topk_load_keys_slots(const float* __restrict__ sc, const int32_t* __restrict__ slot, int bs,
+                                                     int C, int p0, uint32_t (&key)[KPT]) {
+  static_assert((KPT & 3) == 0, "");
+  if (bs % KPT == 0) {   // all of the thread's positions in one row
+    if (p0 < C) {
+      const int q = p0 / bs;
+      const float* row = sc + (size_t)(slot[q] & 0x7FFFFFFF) * bs + (p0 - q * bs);
+#pragma unroll
+      for (int z = 0; z < KPT; z += 4) {
+        const f32x4 v = *reinterpret_cast<const f32x4*>(row + z);
+        key[z] = order_key(v.x); key[z + 1] = order_key(v.y); key[z + 2] = order_key(v.z); key[z + 3] = order_key(v.w);
+      }
+    } else {
+#pragma unroll
+      for (int z = 0; z < KPT; ++z) key[z] = 0u;
+    }
+  } else if ((bs & 3) == 0) {
+#pragma unroll
+    for (int z = 0; z < KPT; z += 4) {
+      if (p0 + z < C) {
+        const int q = (p0 + z) / bs;
+        const f32x4 v = *reinterpret_cast<const f32x4*>(sc + (size_t)(slot[q] & 0x7FFFFFFF) * bs + (p0 + z - q * bs));
+        key[z] = order_key(v.x); key[z + 1] = order_key(v.y); key[z + 2] = order_key(v.z); key[z + 3] = order_key(v.w);
+      } else {
+        key[z] = key[z + 1] = key[z + 2] = key[z + 3] = 0u;
+      }
+    }
+  } else {
+#pragma unroll
+    for (int z = 0; z < KPT; ++z) {
+      const int q = (p0 + z) / bs;
+      key[z] = p0 + z < C ? order_key(sc[(size_t)(slot[q] & 0x7FFFFFFF) * bs + (p0 + z - q * bs)]) : 0u;
+    }
   }
 }
 
@@ -307,7 +345,8 @@ __global__ __launch_bounds__(256, topk_waves(KPT)) void topk_select_reg_kernel(c
   const int t = blockIdx.x, tid = threadIdx.x;
   const int p0 = tid * KPT;
   uint32_t key[KPT];
-  topk_load_keys<KPT>(sc + (size_t)t * C, C, p0, key);
+  if (Ap != nullptr) topk_load_keys_slots<KPT>(sc, slot_of_ent + (size_t)t * e, bs, C, p0, key);
+  else topk_load_keys<KPT>(sc + (size_t)t * C, C, p0, key);
   uint32_t thr;
   int need;
   topk_threshold<KPT, kFull>(key, C, p0, k, s, thr, need);
