@@ -304,7 +304,7 @@ size_t workspace_bytes(const meft_shape& s) {
 // ---- host-resident keys/values: side stream, events, pinned read-back buffer (created on first use) ----
 struct HostKvState {
   hipStream_t side = nullptr;
-  hipEvent_t ev_entry = nullptr, ev_cnt = nullptr, ev_k = nullptr, ev_v = nullptr;
+  hipEvent_t ev_entry = nullptr, ev_cnt = nullptr, ev_k = nullptr, ev_v = nullptr, ev_dv = nullptr, ev_out = nullptr;
   int32_t* host_cnt = nullptr;
   bool ready = false;
 };
@@ -313,7 +313,7 @@ HostKvState g_hkv;
 bool hostkv_init() {
   if (g_hkv.ready) return true;
   if (hipStreamCreateWithFlags(&g_hkv.side, hipStreamNonBlocking) != hipSuccess) return false;
-  hipEvent_t* evs[4] = {&g_hkv.ev_entry, &g_hkv.ev_cnt, &g_hkv.ev_k, &g_hkv.ev_v};
+  hipEvent_t* evs[6] = {&g_hkv.ev_entry, &g_hkv.ev_cnt, &g_hkv.ev_k, &g_hkv.ev_v, &g_hkv.ev_dv, &g_hkv.ev_out};
   for (hipEvent_t* e : evs)
     if (hipEventCreateWithFlags(e, hipEventDisableTiming) != hipSuccess) return false;
   if (hipHostMalloc(reinterpret_cast<void**>(&g_hkv.host_cnt), (size_t)kMaxBlocks * sizeof(int32_t), hipHostMallocDefault) !=
@@ -346,8 +346,8 @@ StageSlot* stage_slot(const void* ws, bool create) {
 }
 
 // Reads the per-block entry counts back (the host blocks until the work queued on `st` so far has produced them),
-// then copies the blocks that some token uses from the pinned host matrices to their device copies on the side
-// stream: `first` before `second`, each followed by its event.
+// then copies the blocks that some token uses, in runs of neighbouring blocks, from the pinned host matrices to their
+// device copies on the side stream: `first` before `second`, each followed by its event.
 meft_status hostkv_fetch(const meft_shape& s, const int32_t* cnt_dev, const void* first_host, char* first_dev,
                          hipEvent_t first_ev, const void* second_host, char* second_dev, hipEvent_t second_ev,
                          hipStream_t st) {
@@ -360,11 +360,14 @@ meft_status hostkv_fetch(const meft_shape& s, const int32_t* cnt_dev, const void
   char* dev[2] = {first_dev, second_dev};
   hipEvent_t ev[2] = {first_ev, second_ev};
   for (int m = 0; m < 2; ++m) {
-    for (int b = 0; b < s.n_blocks; ++b) {
+    for (int b = 0; b < s.n_blocks; ++b) {   // neighbouring blocks in use travel in one copy
       if (k.host_cnt[b] <= 0) continue;
+      int n = 1;
+      while (b + n < s.n_blocks && k.host_cnt[b + n] > 0) ++n;
       if (hipMemcpyAsync(dev[m] + (size_t)b * block_bytes, static_cast<const char*>(host[m]) + (size_t)b * block_bytes,
-                         block_bytes, hipMemcpyHostToDevice, k.side) != hipSuccess)
+                         (size_t)n * block_bytes, hipMemcpyHostToDevice, k.side) != hipSuccess)
         return MEFT_ERR_DEVICE;
+      b += n - 1;
     }
     if (hipEventRecord(ev[m], k.side) != hipSuccess) return MEFT_ERR_DEVICE;
   }
@@ -894,11 +897,22 @@ static meft_status fwd_impl(const meft_shape& s, const void* h, const void* K, c
   return launch_status();
 }
 
-// Backward on device-resident K, V, dK, dV.  wait_v / wait_k as in fwd_impl.
+// Writes the touched rows of a gradient matrix in device staging to the host matrix.
+static void launch_rows_to_host(const meft_shape& s, const int32_t* touched, const int32_t* n_touched, const void* src,
+                                void* dst, hipStream_t st) {
+  const int n_rows = s.N < s.T * s.top_k ? s.N : s.T * s.top_k;
+  const int vec = s.d * (s.dtype == MEFT_BF16 ? 2 : 4) / 16;
+  MEFT_LAUNCH("rows_to_host", rows_to_host_kernel, dim3(n_rows), dim3(256), 0, st, touched, n_touched,
+              static_cast<const u32x4*>(src), static_cast<u32x4*>(dst), vec);
+}
+
+// Backward on device-resident K, V, dK, dV.  wait_v / wait_k as in fwd_impl.  dV_host: not null where dV is staging for
+// that host matrix; its rows then leave on the side stream as soon as they are complete, under the rest of the backward
+// (the caller waits for g_hkv.ev_out).
 static meft_status bwd_impl(const meft_shape& s, const void* h, const void* K, const void* V, const int32_t* idx,
                             const float* act, const void* dOut, void* dh, void* dK, void* dV, int32_t* touched,
                             int32_t* n_touched, const BwdWs& w, hipStream_t st, hipEvent_t wait_k,
-                            hipEvent_t wait_v) {
+                            hipEvent_t wait_v, void* dV_host) {
   const int P = s.T * s.top_k;
 
   if (use_dense(s)) {
@@ -936,14 +950,6 @@ static meft_status bwd_impl(const meft_shape& s, const void* h, const void* K, c
     // gathers the same dOut rows as the activation-gradient GEMM that follows it
     pn.A = w.Ap; pn.zrow = -1; pn.X = gg; pn.G = static_cast<uint16_t*>(dV);
     launch_neu("dV_gemm", pn, st);
-    if (wait_v && hipStreamWaitEvent(st, wait_v, 0) != hipSuccess) return MEFT_ERR_DEVICE;
-    launch_tok<TokKCLarge<kTokMasked>, TokKCSmall<kTokMasked>>("dact_gemm", s, s.block_size, (uint64_t)s.T * s.d * 2, (uint64_t)s.N * s.d * 2, (uint64_t)n_ent * bsp * 2, [&](auto& pg) {
-      pg.X = gg; pg.W = vv; pg.perm = w.perm; pg.tok_of_slot = w.tok_of_slot; pg.sched = sched;
-      pg.e = s.top_e; pg.bs = s.block_size; pg.bsp = bsp; pg.d = s.d; pg.Ap = w.Ap; pg.DS = w.DS;
-      pg.big_only = big_only;
-    }, st);
-    if (small && wait_v) launch_bwd_head(s, w.flag, w.chunk_cnt, touched, n_touched, &w, V, dOut, idx, act, st);
-    if (wait_k && hipStreamWaitEvent(st, wait_k, 0) != hipSuccess) return MEFT_ERR_DEVICE;
     SmallDvdk dv{};
     if (small) {
       dv.nx = (s.block_size + kSmallRowChunk - 1) / kSmallRowChunk;
@@ -954,16 +960,38 @@ static meft_status bwd_impl(const meft_shape& s, const void* h, const void* K, c
       dv.small_grp = w.small_grp; dv.small_cnt = w.small_cnt; dv.group_off = w.group_off; dv.tok_of_slot = w.tok_of_slot;
       dv.dK = static_cast<bf16_t*>(dK); dv.dV = static_cast<bf16_t*>(dV);
     }
+    auto launch_small_dvdk = [&]() {
+      TokenRows a{};
+      a.idx = idx; a.d = s.d; a.k = s.top_k; a.N = s.N; a.bs = s.block_size;
+      MEFT_LAUNCH("small_dvdk", small_dvdk_kernel, dim3(dv.n_wg), dim3(256), 0, st, a, dv);
+      dv.n_wg = 0;
+    };
+    auto dv_to_host = [&]() -> bool {   // dV is complete in its staging
+      if (small) launch_small_dvdk();
+      if (hipEventRecord(g_hkv.ev_dv, st) != hipSuccess || hipStreamWaitEvent(g_hkv.side, g_hkv.ev_dv, 0) != hipSuccess) return false;
+      launch_rows_to_host(s, touched, n_touched, dV, dV_host, g_hkv.side);
+      return hipEventRecord(g_hkv.ev_out, g_hkv.side) == hipSuccess;
+    };
+    if (dV_host && !(small && wait_v) && !dv_to_host()) return MEFT_ERR_DEVICE;
+    if (wait_v && hipStreamWaitEvent(st, wait_v, 0) != hipSuccess) return MEFT_ERR_DEVICE;
+    launch_tok<TokKCLarge<kTokMasked>, TokKCSmall<kTokMasked>>("dact_gemm", s, s.block_size, (uint64_t)s.T * s.d * 2, (uint64_t)s.N * s.d * 2, (uint64_t)n_ent * bsp * 2, [&](auto& pg) {
+      pg.X = gg; pg.W = vv; pg.perm = w.perm; pg.tok_of_slot = w.tok_of_slot; pg.sched = sched;
+      pg.e = s.top_e; pg.bs = s.block_size; pg.bsp = bsp; pg.d = s.d; pg.Ap = w.Ap; pg.DS = w.DS;
+      pg.big_only = big_only;
+    }, st);
+    if (small && wait_v) {
+      launch_bwd_head(s, w.flag, w.chunk_cnt, touched, n_touched, &w, V, dOut, idx, act, st);
+      if (dV_host && !dv_to_host()) return MEFT_ERR_DEVICE;
+    }
+    if (wait_k && hipStreamWaitEvent(st, wait_k, 0) != hipSuccess) return MEFT_ERR_DEVICE;
     if (dh) {
       launch_tok<ProbTokNC, TokNCSmall>("dh_gemm", s, s.d, (uint64_t)n_ent * bsp * 2, (uint64_t)s.N * s.d * 2, (uint64_t)n_ent * s.d * 2, [&](auto& ph) {
         ph.A = w.DS; ph.W = kk; ph.sched = sched; ph.bs = s.block_size; ph.bsp = bsp;
         ph.d = s.d; ph.part = w.part; ph.big_only = big_only;
       }, st);
       launch_token_rows("dh_rows", s, w.part, w, K, idx, w.ds32, dh, dv, st);
-    } else if (small) {
-      TokenRows a{};
-      a.idx = idx; a.d = s.d; a.k = s.top_k; a.N = s.N; a.bs = s.block_size;
-      MEFT_LAUNCH("small_dvdk", small_dvdk_kernel, dim3(dv.n_wg), dim3(256), 0, st, a, dv);
+    } else if (dv.n_wg) {
+      launch_small_dvdk();
     }
     pn.A = w.DS; pn.zrow = -(n_ent + 1); pn.X = hh; pn.G = static_cast<uint16_t*>(dK);
     launch_neu("dK_gemm", pn, st);
@@ -988,6 +1016,10 @@ static meft_status bwd_impl(const meft_shape& s, const void* h, const void* K, c
               w.pair_list, w.pair_sorted);
   if (s.dtype == MEFT_BF16) launch_seg_reduce<bf16_t>(s, w, touched, n_touched, act, h, dOut, dK, dV, n_seg, st);
   else launch_seg_reduce<float>(s, w, touched, n_touched, act, h, dOut, dK, dV, n_seg, st);
+  if (dV_host) {
+    launch_rows_to_host(s, touched, n_touched, dV, dV_host, st);
+    if (hipEventRecord(g_hkv.ev_out, st) != hipSuccess) return MEFT_ERR_DEVICE;
+  }
   return launch_status();
 }
 
@@ -1255,7 +1287,7 @@ meft_status meft_sparse_bwd(const meft_shape* shape, const void* h, const void* 
     return launch_status();
   }
   if (!(s.flags & MEFT_FLAG_HOST_KV))
-    return bwd_impl(s, h, K, V, idx, act, dOut, dh, dK, dV, touched, n_touched, w, st, nullptr, nullptr);
+    return bwd_impl(s, h, K, V, idx, act, dOut, dh, dK, dV, touched, n_touched, w, st, nullptr, nullptr, nullptr);
 
   // K, V, dK, dV in pinned host memory: fetch the blocks that hold a selected neuron (V first: the activation
   // gradient needs it before dh needs K), compute into device staging, then write the touched rows back.
@@ -1264,7 +1296,7 @@ meft_status meft_sparse_bwd(const meft_shape* shape, const void* h, const void* 
   if (s.flags & MEFT_FLAG_KEEP_STAGED) {
     // the forward of this step left the blocks in use in the workspace, and its copies are ordered before
     // anything enqueued here (the forward made `st` wait for them)
-    rc = bwd_impl(s, h, hw.Kd, hw.Vd, idx, act, dOut, dh, hw.dKd, hw.dVd, touched, n_touched, w, st, nullptr, nullptr);
+    rc = bwd_impl(s, h, hw.Kd, hw.Vd, idx, act, dOut, dh, hw.dKd, hw.dVd, touched, n_touched, w, st, nullptr, nullptr, dV);
   } else {
   if (hipEventRecord(g_hkv.ev_entry, st) != hipSuccess || hipStreamWaitEvent(g_hkv.side, g_hkv.ev_entry, 0) != hipSuccess)
     return MEFT_ERR_DEVICE;
@@ -1276,15 +1308,11 @@ meft_status meft_sparse_bwd(const meft_shape* shape, const void* h, const void* 
               cnt_tmp);
   if ((rc = hostkv_fetch(s, cnt_tmp, V, hw.Vd, g_hkv.ev_v, K, hw.Kd, g_hkv.ev_k, st)) != MEFT_OK) return rc;
   rc = bwd_impl(s, h, hw.Kd, hw.Vd, idx, act, dOut, dh, hw.dKd, hw.dVd, touched, n_touched, w, st, g_hkv.ev_k,
-                g_hkv.ev_v);
+                g_hkv.ev_v, dV);
   }
   if (rc != MEFT_OK) return rc;
-  const int n_rows = s.N < s.T * s.top_k ? s.N : s.T * s.top_k;
-  const int vec = s.d * (s.dtype == MEFT_BF16 ? 2 : 4) / 16;
-  MEFT_LAUNCH("rows_to_host", rows_to_host_kernel, dim3(n_rows), dim3(256), 0, st, touched, n_touched,
-              reinterpret_cast<const u32x4*>(hw.dVd), reinterpret_cast<u32x4*>(dV), vec);
-  MEFT_LAUNCH("rows_to_host", rows_to_host_kernel, dim3(n_rows), dim3(256), 0, st, touched, n_touched,
-              reinterpret_cast<const u32x4*>(hw.dKd), reinterpret_cast<u32x4*>(dK), vec);
+  launch_rows_to_host(s, touched, n_touched, hw.dKd, dK, st);
+  if (hipStreamWaitEvent(st, g_hkv.ev_out, 0) != hipSuccess) return MEFT_ERR_DEVICE;
   return launch_status();
 }
 
