@@ -78,16 +78,23 @@ struct Vec8<bf16_t> {
 };
 
 // ---- wave-level reductions -----------------------------------------------------------------
+// sum over the wave, in every lane: DPP moves inside the rows of 16 lanes, then two lane permutes
 __device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-  return v;
+#define MEFT_DPP_ADDF(ctrl) v += __builtin_amdgcn_update_dpp(0.f, v, ctrl, 0xF, 0xF, false)
+  MEFT_DPP_ADDF(0xB1);    // quad_perm [1,0,3,2]
+  MEFT_DPP_ADDF(0x4E);    // quad_perm [2,3,0,1]
+  MEFT_DPP_ADDF(0x141);   // row_half_mirror
+  MEFT_DPP_ADDF(0x140);   // row_mirror
+#undef MEFT_DPP_ADDF
+  v += __shfl_xor(v, 16, kWave);
+  return v + __shfl_xor(v, 32, kWave);
 }
 
-__device__ __forceinline__ int wave_sum_i(int v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-  return v;
+// orders a wave's own LDS accesses (writes by some lanes, then reads by others) without a workgroup barrier
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 __device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long v) {

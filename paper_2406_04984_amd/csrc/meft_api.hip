@@ -247,25 +247,30 @@ size_t seg_multi_chunks(const meft_shape& s) { return 2 * (((size_t)s.T * s.top_
 struct BwdWs : DenseWs {
   // gather path
   float* ds;
-  int32_t *cnt_n, *cursor, *seg_off, *pair_list, *pair_sorted, *work_off, *multi_off;
+  int32_t *cnt_n, *seg_off, *pair_list, *pair_sorted, *totals;   // pair_sorted also holds the pairs' places (pair_count)
+  PairSums* sums;
+  SegWork* work;     // at most one chunk per touched neuron plus one per kSegChunk pairs
+  int4* multi;       // neurons of more than one chunk
   float* seg_part;   // fp32 chunk sums of the neurons with more than kSegChunk pairs: [chunk][dV | dK][d]
   size_t bytes;
   BwdWs(const meft_shape& s, void* ws) {
     Carver c(ws);
     const size_t P = (size_t)s.T * s.top_k;
-    ds = nullptr; cnt_n = cursor = seg_off = pair_list = pair_sorted = work_off = multi_off = nullptr; seg_part = nullptr;
+    ds = nullptr; cnt_n = seg_off = pair_list = pair_sorted = totals = nullptr; seg_part = nullptr;
+    sums = nullptr; work = nullptr; multi = nullptr;
     if (use_dense(s)) {
       carve_dense(s, c);
     } else {
       ds = c.take<float>(P);
-      cnt_n = c.take<int32_t>(s.N);     // cnt_n and cursor are adjacent: cleared by one fill
-      cursor = c.take<int32_t>(s.N);
+      cnt_n = c.take<int32_t>(s.N);
       seg_off = c.take<int32_t>((size_t)s.N + 1);
       pair_list = c.take<int32_t>(P);
       pair_sorted = c.take<int32_t>(P);
+      totals = c.take<int32_t>(3);
+      sums = c.take<PairSums>(s.N > kScanSelfMax ? (size_t)(s.N + kScanChunk - 1) / kScanChunk : 0);
       const size_t n_seg = (size_t)s.N < P ? (size_t)s.N : P;
-      work_off = c.take<int32_t>(n_seg + 1);
-      multi_off = c.take<int32_t>(n_seg + 1);
+      work = c.take<SegWork>(n_seg + P / kSegChunk + 1);
+      multi = c.take<int4>(P / kSegChunk + 1);
       seg_part = c.take<float>(seg_multi_chunks(s) * 2 * (size_t)s.d);
     }
     bytes = c.off;
@@ -465,38 +470,44 @@ void launch_gather_fwd(const meft_shape& s, const void* V, const int32_t* idx, c
 #undef GF
 }
 
+// (also clears clear[0 .. n_clear))
 template <typename T>
 void launch_gather_bwd(const meft_shape& s, const void* K, const void* V, const void* dOut, const int32_t* idx,
-                       const float* act, float* ds, void* dh, hipStream_t st) {
-  int nthr, nv;
-  row_launch(s.d, nthr, nv);
+                       const float* act, float* ds, void* dh, int32_t* clear, size_t n_clear, hipStream_t st) {
   const T *k = static_cast<const T*>(K), *v = static_cast<const T*>(V), *g = static_cast<const T*>(dOut);
   T* o = static_cast<T*>(dh);
+  // a wave per pair holds dOut's and dh's rows in fp32 and one row each of V and K: up to 4096 bf16 or 2048 fp32 columns
+  const int cols = (s.d + 511) / 512;
+#define GW(NV) MEFT_LAUNCH("gather_bwd", (gather_bwd_wave_kernel<T, NV>), dim3(s.T), dim3(256), 0, st, k, v, g, idx, act, s.d, s.top_k, s.N, ds, o, clear, n_clear)
+  if (cols <= 1) { GW(1); return; }
+  if (cols <= 2) { GW(2); return; }
+  if (cols <= 4) { GW(4); return; }
+  if constexpr (sizeof(T) == 2) {
+    if (cols <= 8) { GW(8); return; }
+  }
+#undef GW
+  MEFT_LAUNCH("fill_i32", fill_i32_kernel, dim3((unsigned)((n_clear + 255) / 256)), dim3(256), 0, st, clear, n_clear, 0);
+  int nthr, nv;
+  row_launch(s.d, nthr, nv);
 #define GB(NV, PB) MEFT_LAUNCH("gather_bwd", (gather_bwd_kernel<T, NV, PB>), dim3(s.T), dim3(nthr), 0, st, k, v, g, idx, act, s.d, s.top_k, s.N, ds, o)
-  switch (nv) { case 1: GB(1, 8); break; case 2: GB(2, 8); break; case 4: GB(4, 4); break; default: GB(8, 2); }
+  if (nv <= 2) GB(2, 8); else if (nv == 4) GB(4, 4); else GB(8, 2);
 #undef GB
 }
 
 template <typename T>
-void launch_seg_reduce(const meft_shape& s, const BwdWs& w, const int32_t* touched, const int32_t* n_touched,
-                       const float* act, const void* h, const void* dOut, void* dK, void* dV, int grid,
-                       hipStream_t st) {
-  int nthr, nv;
-  row_launch(s.d, nthr, nv);
+void launch_seg_reduce(const meft_shape& s, const BwdWs& w, const float* act, const void* h, const void* dOut, void* dK,
+                       void* dV, hipStream_t st) {
   const T *hh = static_cast<const T*>(h), *g = static_cast<const T*>(dOut);
   T *pk = static_cast<T*>(dK), *pv = static_cast<T*>(dV);
-  // one workgroup per chunk: at most one chunk per touched neuron plus one per kSegChunk pairs
-  const int64_t work = (int64_t)grid + ((int64_t)s.T * s.top_k) / kSegChunk;
-  const int finish = grid < 4096 ? grid : 4096;
-#define SR(NV)                                                                                                        \
-  do {                                                                                                                \
-    MEFT_LAUNCH("seg_reduce", (seg_reduce_kernel<T, NV>), dim3((unsigned)work), dim3(nthr), 0, st, touched, n_touched, \
-                w.seg_off, w.work_off, w.multi_off, w.pair_sorted, act, w.ds, hh, g, s.d, s.top_k, pk, pv, w.seg_part); \
-    MEFT_LAUNCH("seg_finish", (seg_finish_kernel<T, NV>), dim3(finish), dim3(nthr), 0, st, touched, n_touched,        \
-                w.work_off, w.multi_off, w.seg_part, s.d, pk, pv);                                                     \
-  } while (0)
-  switch (nv) { case 1: SR(1); break; case 2: SR(2); break; case 4: SR(4); break; default: SR(8); }
-#undef SR
+  const int64_t P = (int64_t)s.T * s.top_k, n_seg = s.N < P ? s.N : P;
+  // four chunks per workgroup: at most one chunk per touched neuron plus one per kSegChunk pairs
+  const int64_t groups = (n_seg + P / kSegChunk + 3) / 4;
+  MEFT_LAUNCH("seg_reduce", seg_reduce_kernel<T>, dim3((unsigned)(groups * ((s.d + 511) / 512))), dim3(256), 0, st, w.work,
+              w.totals, w.pair_list, w.pair_sorted, act, w.ds, hh, g, s.d, s.top_k, (int)groups, pk, pv, w.seg_part);
+  if (s.T > kSegChunk) {   // a neuron of more than one chunk takes that many tokens
+    const int finish = (int)(P / kSegChunk < 4096 ? P / kSegChunk + 1 : 4096);
+    MEFT_LAUNCH("seg_finish", seg_finish_kernel<T>, dim3(finish), dim3(256), 0, st, w.multi, w.totals, w.seg_part, s.d, pk, pv);
+  }
 }
 
 
@@ -1000,22 +1011,22 @@ static meft_status bwd_impl(const meft_shape& s, const void* h, const void* K, c
 
   if (wait_v && hipStreamWaitEvent(st, wait_v, 0) != hipSuccess) return MEFT_ERR_DEVICE;
   if (wait_k && hipStreamWaitEvent(st, wait_k, 0) != hipSuccess) return MEFT_ERR_DEVICE;
-  if (s.dtype == MEFT_BF16) launch_gather_bwd<bf16_t>(s, K, V, dOut, idx, act, w.ds, dh, st);
-  else launch_gather_bwd<float>(s, K, V, dOut, idx, act, w.ds, dh, st);
+  if (s.dtype == MEFT_BF16) launch_gather_bwd<bf16_t>(s, K, V, dOut, idx, act, w.ds, dh, w.cnt_n, s.N, st);
+  else launch_gather_bwd<float>(s, K, V, dOut, idx, act, w.ds, dh, w.cnt_n, s.N, st);
 
-  const size_t n_clear = (size_t)(w.cursor - w.cnt_n) + s.N;  // cnt, its padding, cursor
-  MEFT_LAUNCH("fill_i32", fill_i32_kernel, dim3((unsigned)((n_clear + 255) / 256)), dim3(256), 0, st, w.cnt_n,
-              n_clear, 0);
-  MEFT_LAUNCH("pair_count", pair_count_kernel, dim3((P + 255) / 256), dim3(256), 0, st, idx, P, s.N, w.cnt_n);
-  MEFT_LAUNCH("pair_scan", pair_scan_kernel, dim3(1), dim3(1024), 0, st, w.cnt_n, s.N, w.seg_off, touched,
-              n_touched, w.work_off, w.multi_off);
+  MEFT_LAUNCH("pair_count", pair_count_kernel, dim3((P + 255) / 256), dim3(256), 0, st, idx, P, s.N, w.cnt_n, w.pair_sorted);
+  const int n_chunks = (s.N + kScanChunk - 1) / kScanChunk;
+  if (w.sums && s.N > kScanSelfMax)
+    MEFT_LAUNCH("pair_sums", pair_sums_kernel, dim3(n_chunks), dim3(256), 0, st, w.cnt_n, s.N, w.sums);
+  MEFT_LAUNCH("pair_scan", pair_scan_kernel, dim3(n_chunks), dim3(256), 0, st, w.cnt_n, s.N,
+              s.N > kScanSelfMax ? w.sums : nullptr, w.seg_off, touched, n_touched, w.work, w.multi, w.totals);
   MEFT_LAUNCH("pair_fill", pair_fill_kernel, dim3((P + 255) / 256), dim3(256), 0, st, idx, P, s.N, w.seg_off,
-              w.cursor, w.pair_list);
-  const int n_seg = s.N < P ? s.N : P;  // upper bound on the number of touched neurons
-  MEFT_LAUNCH("seg_sort", seg_sort_kernel, dim3(n_seg), dim3(256), 0, st, touched, n_touched, w.seg_off,
-              w.pair_list, w.pair_sorted);
-  if (s.dtype == MEFT_BF16) launch_seg_reduce<bf16_t>(s, w, touched, n_touched, act, h, dOut, dK, dV, n_seg, st);
-  else launch_seg_reduce<float>(s, w, touched, n_touched, act, h, dOut, dK, dV, n_seg, st);
+              w.pair_sorted, w.pair_list);
+  if (s.T > kSegChunk)   // segments of more than one chunk
+    MEFT_LAUNCH("seg_sort", seg_sort_kernel, dim3(P / kSegChunk < 512 ? P / kSegChunk + 1 : 512), dim3(256), 0, st, w.multi,
+                w.totals, w.seg_off, w.pair_list, w.pair_sorted);
+  if (s.dtype == MEFT_BF16) launch_seg_reduce<bf16_t>(s, w, act, h, dOut, dK, dV, st);
+  else launch_seg_reduce<float>(s, w, act, h, dOut, dK, dV, st);
   if (dV_host) {
     launch_rows_to_host(s, touched, n_touched, dV, dV_host, st);
     if (hipEventRecord(g_hkv.ev_out, st) != hipSuccess) return MEFT_ERR_DEVICE;
