@@ -76,6 +76,7 @@ struct LaunchScope {
 // ---- shape checks ---------------------------------------------------------------------------
 constexpr int kMaxD = 16384, kMaxBlocks = 16384;
 constexpr int kMaxC = 1 << 22;      // candidates per token (top_e * block_size)
+constexpr int kBoundMinC = 4096;    // few out of more candidates than this: topk_select_bound_kernel
 constexpr int kMaxLdsC = 12288;     // up to here the top-k selection keeps a token's keys in LDS
 
 meft_status check_shape(const meft_shape* s) {
@@ -867,7 +868,10 @@ static meft_status fwd_impl(const meft_shape& s, const void* h, const void* K, c
     const int nb_used = s.n_blocks < n_ent ? s.n_blocks : n_ent;
     launch_gemm_nt(s, a, n_ent / kGemmBM + nb_used, n_ent / kGemmF32BM + nb_used, "score_gemm", st);
   }
-  if (C <= kMaxLdsC) {
+  if (!dense && s.top_k <= kBoundMaxK && C > kBoundMinC && C <= 1024 * 64) {
+    MEFT_LAUNCH("topk_select_bound", topk_select_bound_kernel, dim3(s.T), dim3(1024), 0, st, w.sc, w.sblk, C, s.block_size,
+                s.top_e, s.top_k, idx, act);
+  } else if (C <= kMaxLdsC) {
     // keys in registers, the smallest per-thread count that covers the C candidates with 256 threads
     uint16_t* ap = dense ? w.Ap : nullptr;
 #define TK2(KPT, FULL) MEFT_LAUNCH("topk_select", (topk_select_reg_kernel<KPT, FULL>), dim3(s.T), dim3(256), 0, st, w.sc, w.sblk, C, s.block_size, s.top_e, s.top_k, idx, act, w.slot_of_ent, bsp, ap, dense ? w.flag : nullptr)

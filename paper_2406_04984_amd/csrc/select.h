@@ -412,6 +412,158 @@ __global__ __launch_bounds__(256, topk_waves(KPT)) void topk_select_reg_kernel(c
 }
 
 // ---------------------------------------------------------------------------------------------
+// Selection of few out of many (k <= kBoundMaxK, C <= 65536; the ablation without key experts picks 256 of 65536): 1024
+// threads per token.  The k-th largest of the 1024 threads' own maxima is a lower bound of the k-th largest key, and a tight one: with 4 k <= 1024 about 1.15 k keys of independent scores
+// reach it.  Its leading 16 bits come from two histogram passes over one value per thread; a second sweep over
+// the scores puts the keys that reach it into a list in LDS, and the list is ranked by counting (key descending, position ascending), which gives the selection and
+// its order exactly.  A list that does not fit (many equal keys) leaves the token to histogram passes over all its keys.
+// Two sweeps with few registers, so that two tokens share a compute unit, beat one with the keys held (343 us).
+// Against those passes for every token (64 keys per thread into a histogram of which a handful of bins are hit, and
+// reads of which a wave touches 64 lines at a time): 637 -> 210 us at 2048 tokens x 65536.
+// ---------------------------------------------------------------------------------------------
+constexpr int kBoundMaxK = 256, kBoundList = 2048;
+
+// Threshold among keys that `each` calls its argument with (0: none; four at a time), 1024 threads: keys above thr are
+// selected and `need` equal ones; only the digits down to last_shift are found (the rest of thr is 0).
+template <class F>
+__device__ __forceinline__ void topk_threshold_1024(F&& each, int k, int* s_hist, int* s_w, uint32_t* s_prefix, int* s_need,
+                                                    int last_shift, uint32_t& thr, int& need_eq) {
+  const int tid = threadIdx.x;
+  if (tid == 0) { *s_prefix = 0u; *s_need = k; }
+  __syncthreads();
+  for (int shift = 24; shift >= last_shift; shift -= 8) {
+    if (tid < 256) s_hist[tid] = 0;
+    __syncthreads();
+    const uint32_t prefix = *s_prefix;
+    const uint32_t himask = shift == 24 ? 0u : (0xFFFFFFFFu << (shift + 8));
+    each([&](uint32_t key) {
+      if (key != 0u && (key & himask) == prefix) atomicAdd(&s_hist[(key >> shift) & 255u], 1);
+    });
+    __syncthreads();
+    // thread `tid` < 256 owns digit 255 - tid, so that an exclusive scan counts the larger digits
+    const int digit = 255 - tid;
+    const int h = tid < 256 ? s_hist[digit] : 0;
+    int tot;
+    const int above = block_excl_scan_1024(h, s_w, tot);
+    const int need = *s_need;
+    __syncthreads();
+    if (tid < 256 && above < need && need <= above + h) {
+      *s_prefix = prefix | ((uint32_t)digit << shift);
+      *s_need = need - above;
+    }
+    __syncthreads();
+  }
+  thr = *s_prefix;
+  need_eq = *s_need;
+}
+
+__global__ __launch_bounds__(1024, 8) void topk_select_bound_kernel(const float* __restrict__ sc,
+                                                                    const int32_t* __restrict__ sblk, int C, int bs, int e,
+                                                                    int k, int32_t* __restrict__ idx,
+                                                                    float* __restrict__ act) {
+  __shared__ int s_hist[256];
+  __shared__ int s_w[16];
+  __shared__ uint32_t s_prefix;
+  __shared__ int s_need, s_n;
+  __shared__ unsigned long long s_list[kBoundList];   // key << 32 | ~position: larger = earlier in the selection
+  __shared__ int s_pos[kBoundMaxK];
+  __shared__ uint32_t s_key[kBoundMaxK];
+  const int t = blockIdx.x, tid = threadIdx.x;
+  const float* row = sc + (size_t)t * C;
+  // The thread's positions: 4096 q + 4 tid + 0 .. 3.  (C >= 4096: every thread has a score.)
+  const int full = (C & 3) == 0 ? C : 0;   // up to here in 16-byte loads
+  float top = -__builtin_inff();
+  auto sweep = [&](auto&& f) {
+#pragma unroll 4
+    for (int p0 = tid * 4; p0 < full; p0 += 4096) {
+      const f32x4 v = *reinterpret_cast<const f32x4*>(row + p0);
+      f(p0, v.x); f(p0 + 1, v.y); f(p0 + 2, v.z); f(p0 + 3, v.w);
+    }
+    for (int p0 = full + tid * 4; p0 < C; p0 += 4096) {
+#pragma unroll
+      for (int z = 0; z < 4; ++z)
+        if (p0 + z < C) f(p0 + z, row[p0 + z]);
+    }
+  };
+  sweep([&](int, float v) { top = fmaxf(top, v); });
+  if (tid == 0) s_n = 0;
+  const uint32_t top_key = order_key(top);
+  uint32_t bound;
+  int need;
+  topk_threshold_1024([&](auto&& f) { f(top_key); }, k, s_hist, s_w, &s_prefix, &s_need, 16, bound, need);
+  const float lo = bound >= 0x00800000u ? key_to_float(bound) : -__builtin_inff();   // (below: the keys of no finite score)
+  sweep([&](int p, float v) {
+    if (v >= lo) {
+      const int at = atomicAdd(&s_n, 1);
+      if (at < kBoundList) s_list[at] = ((unsigned long long)order_key(v) << 32) | (uint32_t)~p;
+    }
+  });
+  __syncthreads();
+  int n_list = s_n;
+  __syncthreads();
+  if (n_list > kBoundList) {
+    // The same in every thread, and rare: the exact threshold over the scores in memory, then only what it selects is
+    // listed: the keys above it (fewer than k) and the first `need` positions that equal it.
+    auto four = [&](int p0, uint32_t (&v)[4]) {
+#pragma unroll
+      for (int z = 0; z < 4; ++z) v[z] = p0 + z < C ? order_key(row[p0 + z]) : 0u;
+    };
+    uint32_t thr;
+    topk_threshold_1024([&](auto&& f) {
+      for (int p0 = tid * 4; p0 < C; p0 += 4096) {
+        uint32_t v[4];
+        four(p0, v);
+#pragma unroll
+        for (int z = 0; z < 4; ++z) f(v[z]);
+      }
+    }, k, s_hist, s_w, &s_prefix, &s_need, 0, thr, need);
+    if (tid == 0) s_n = 0;
+    __syncthreads();
+    int taken = 0;   // equal ones at earlier positions
+    for (int base = 0; base < C; base += 4096) {
+      uint32_t v[4];
+      four(base + tid * 4, v);
+      int eq = 0;
+#pragma unroll
+      for (int z = 0; z < 4; ++z) eq += v[z] == thr;
+      int tot;
+      int before = taken + block_excl_scan_1024(eq, s_w, tot);
+#pragma unroll
+      for (int z = 0; z < 4; ++z) {
+        if (v[z] > thr || (v[z] == thr && before < need))
+          s_list[atomicAdd(&s_n, 1)] = ((unsigned long long)v[z] << 32) | (uint32_t)~(base + tid * 4 + z);
+        before += v[z] == thr;
+      }
+      taken += tot;
+    }
+    __syncthreads();
+    n_list = s_n;
+  }
+  // rank by counting; the selected ones go to s_pos, s_key
+  for (int i = tid; i < n_list; i += 1024) {
+    const unsigned long long me = s_list[i];
+    int r = 0;
+#pragma unroll 8
+    for (int z = 0; z < n_list; ++z) r += s_list[z] > me;
+    if (r < k) {
+      s_pos[r] = (int)~(uint32_t)me;
+      s_key[r] = (uint32_t)(me >> 32);
+    }
+  }
+  __syncthreads();
+  if (tid < k) {
+    const int i = s_pos[tid];
+    int slot = 0;   // selected positions before this one
+#pragma unroll 8
+    for (int z = 0; z < k; ++z) slot += s_pos[z] < i;
+    const int q = i / bs;
+    const float v = key_to_float(s_key[tid]);
+    idx[(size_t)t * k + slot] = sblk[(size_t)t * e + q] * bs + (i - q * bs);
+    act[(size_t)t * k + slot] = v > 0.f ? v : 0.f;
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
 // The register-resident selection for 12288 < C <= 65536 candidates: 1024 threads per token, thread `tid` owns
 // the KPT consecutive positions from tid*KPT (1024 * KPT >= C).  Same passes as above; no dense activation rows
 // (shapes this large do not take the matrix-core path).
