@@ -493,7 +493,7 @@ __global__ __launch_bounds__(1024, 8) void topk_select_bound_kernel(const float*
   topk_threshold_1024([&](auto&& f) { f(top_key); }, k, s_hist, s_w, &s_prefix, &s_need, 16, bound, need);
   const float lo = bound >= 0x00800000u ? key_to_float(bound) : -__builtin_inff();   // (below: the keys of no finite score)
   sweep([&](int p, float v) {
-    if (v >= lo) {
+    if (!(v < lo)) {   // NaNs are listed too: their keys decide, as in every other selection
       const int at = atomicAdd(&s_n, 1);
       if (at < kBoundList) s_list[at] = ((unsigned long long)order_key(v) << 32) | (uint32_t)~p;
     }
@@ -501,7 +501,7 @@ __global__ __launch_bounds__(1024, 8) void topk_select_bound_kernel(const float*
   __syncthreads();
   int n_list = s_n;
   __syncthreads();
-  if (n_list > kBoundList) {
+  if (n_list > kBoundList || n_list < k) {   // (never fewer than k, unless a maximum was not a number)
     // The same in every thread, and rare: the exact threshold over the scores in memory, then only what it selects is
     // listed: the keys above it (fewer than k) and the first `need` positions that equal it.
     auto four = [&](int p0, uint32_t (&v)[4]) {

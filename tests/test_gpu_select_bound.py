@@ -38,3 +38,17 @@ def test_more_equal_keys_than_the_list_holds(N):
     s = t.h @ t.K[:2].T
     best = (s[3:, 1] > s[3:, 0]).astype(int)
     assert (g["idx"][3:] == best[:, None] + 2 * np.arange(100)[None]).all()
+
+
+def test_scores_that_are_no_numbers():
+    from tests import parity as P
+    N, k = 5000, 100
+    t = synth.make_inputs(synth.small_case(T=6, d=64, n_blocks=1, block_size=N, top_e=1, top_k=k, dtype="f32", seed=8300))
+    ref = P.run_gpu(t)["idx"]
+    t.h[1] = np.nan            # every score of the token
+    t.K[[7, 1999, 4321]] = np.nan   # three scores of every token: they rank above the numbers, or all of them below
+    idx = P.run_gpu(t)["idx"]
+    assert (idx >= 0).all() and (idx < N).all() and (np.diff(idx, axis=1) > 0).all()
+    for i in (0, 2, 3, 4, 5):
+        rest = np.setdiff1d(idx[i], [7, 1999, 4321])
+        assert len(rest) in (k, k - 3) and np.isin(rest, ref[i]).sum() >= k - 3
