@@ -505,7 +505,7 @@ void launch_seg_reduce(const meft_shape& s, const BwdWs& w, const float* act, co
   const int64_t groups = (n_seg + P / kSegChunk + 3) / 4;
   MEFT_LAUNCH("seg_reduce", seg_reduce_kernel<T>, dim3((unsigned)(groups * ((s.d + 511) / 512))), dim3(256), 0, st, w.work,
               w.totals, w.pair_list, w.pair_sorted, act, w.ds, hh, g, s.d, s.top_k, (int)groups, pk, pv, w.seg_part);
-  if (s.T > kSegChunk) {   // a neuron of more than one chunk takes that many tokens
+  if (P > kSegChunk) {
     const int finish = (int)(P / kSegChunk < 4096 ? P / kSegChunk + 1 : 4096);
     MEFT_LAUNCH("seg_finish", seg_finish_kernel<T>, dim3(finish), dim3(256), 0, st, w.multi, w.totals, w.seg_part, s.d, pk, pv);
   }
@@ -1026,7 +1026,7 @@ static meft_status bwd_impl(const meft_shape& s, const void* h, const void* K, c
               s.N > kScanSelfMax ? w.sums : nullptr, w.seg_off, touched, n_touched, w.work, w.multi, w.totals);
   MEFT_LAUNCH("pair_fill", pair_fill_kernel, dim3((P + 255) / 256), dim3(256), 0, st, idx, P, s.N, w.seg_off,
               w.pair_sorted, w.pair_list);
-  if (s.T > kSegChunk)   // segments of more than one chunk
+  if (P > kSegChunk)   // else no segment of more than one chunk (a token's ids may repeat where they were clamped)
     MEFT_LAUNCH("seg_sort", seg_sort_kernel, dim3(P / kSegChunk < 512 ? P / kSegChunk + 1 : 512), dim3(256), 0, st, w.multi,
                 w.totals, w.seg_off, w.pair_list, w.pair_sorted);
   if (s.dtype == MEFT_BF16) launch_seg_reduce<bf16_t>(s, w, act, h, dOut, dK, dV, st);

@@ -41,3 +41,18 @@ def test_without_dh():
     n = int(layer.n_touched.item())
     assert torch.equal(touched[:n], layer.touched[:n])
     assert torch.equal(dK, layer.dK) and torch.equal(dV, layer.dV) and bool((layer.dh == 7.0).all())
+
+
+def test_an_id_repeated_within_its_tokens():
+    """Ids beyond the last neuron are clamped to it, so that a neuron may get more pairs than there are tokens."""
+    import torch
+    from tests import parity as P
+    t = synth.make_inputs(synth.small_case(T=100, d=64, n_blocks=2, block_size=40, top_e=2, top_k=20, dtype="f32", seed=7300))
+    layer = P.DeviceLayer(t)
+    layer.step()
+    layer.idx[:, 10:] = 80 + 5
+    layer.bwd()
+    torch.cuda.synchronize()
+    act, dOut = layer.act.double(), layer.dOut.double()
+    want = act[:, 10:].sum(1) @ dOut + ((layer.idx[:, :10] == 79) * act[:, :10]).sum(1) @ dOut
+    assert torch.allclose(layer.dV[79].double(), want, rtol=1e-4, atol=1e-4 * float(want.abs().max()))
