@@ -41,7 +41,8 @@ __device__ __forceinline__ void mma16_rows(const char* const (&pa)[NA], const ch
     u32x4 a[U][NA], b[U][NB];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      // beyond the row or the range: any valid address; the A values are then replaced by zeros
+      // beyond the row or the range: any valid address; both values are then replaced by zeros (one of them an infinity
+      // would make the product of the other's zero NaN)
       const int off = (s + u) * 64 + q16;
       const int at = off < row_bytes ? off : 0;
 #pragma unroll
@@ -53,11 +54,14 @@ __device__ __forceinline__ void mma16_rows(const char* const (&pa)[NA], const ch
     for (int u = 0; u < U; ++u) {
       const bool in = s + u < s1 && (s + u) * 64 + q16 < row_bytes;
       const u32x4 zero = {0u, 0u, 0u, 0u};
+      u32x4 bv[NB];
+#pragma unroll
+      for (int j = 0; j < NB; ++j) bv[j] = in ? b[u][j] : zero;
 #pragma unroll
       for (int i = 0; i < NA; ++i) {
         const u32x4 av = in ? a[u][i] : zero;
 #pragma unroll
-        for (int j = 0; j < NB; ++j) acc[i][j] = Mma16<T>::step(av, b[u][j], acc[i][j]);
+        for (int j = 0; j < NB; ++j) acc[i][j] = Mma16<T>::step(av, bv[j], acc[i][j]);
       }
     }
   }
