@@ -37,15 +37,34 @@ __device__ __forceinline__ void static_for(F&& f) {
   }
 }
 
-template <int OFF>
-__device__ __forceinline__ void lds_read16(u32x4& v, uint32_t addr) {
-  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFF));
+// The LDS reads of one k16 step (one A fragment, two B fragments) with the wait for them, in one asm statement: through
+// builtins the compiler orders every LDS read behind all outstanding global -> LDS loads, and the outputs of a read
+// without its wait would count as written while they are on their way.
+template <int OFFA, int OFFB0, int OFFB1>
+__device__ __forceinline__ void lds_read_kc3(u32x4& a, u32x4& b0, u32x4& b1, uint32_t xa, uint32_t xb) {
+  asm volatile(
+      "ds_read_b128 %0, %3 offset:%5\n\t"
+      "ds_read_b128 %1, %4 offset:%6\n\t"
+      "ds_read_b128 %2, %4 offset:%7\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(a), "=&v"(b0), "=&v"(b1)
+      : "v"(xa), "v"(xb), "n"(OFFA), "n"(OFFB0), "n"(OFFB1)
+      : "memory");
 }
-// transposing read: low and high k half of one fragment
-template <int OFF>
-__device__ __forceinline__ void lds_read_tr(u32x2& lo, u32x2& hi, uint32_t alo, uint32_t ahi) {
-  asm volatile("ds_read_b64_tr_b16 %0, %2 offset:%4\n\tds_read_b64_tr_b16 %1, %3 offset:%4"
-               : "=&v"(lo), "=&v"(hi) : "v"(alo), "v"(ahi), "n"(OFF));
+// the B fragments by transposing reads, low and high k half each
+template <int OFFA, int OFFB>
+__device__ __forceinline__ void lds_read_nc3(u32x4& a, u32x2 (&b)[4], uint32_t xa, uint32_t b0lo, uint32_t b0hi, uint32_t b1lo,
+                                             uint32_t b1hi) {
+  asm volatile(
+      "ds_read_b128 %0, %5 offset:%10\n\t"
+      "ds_read_b64_tr_b16 %1, %6 offset:%11\n\t"
+      "ds_read_b64_tr_b16 %2, %7 offset:%11\n\t"
+      "ds_read_b64_tr_b16 %3, %8 offset:%11\n\t"
+      "ds_read_b64_tr_b16 %4, %9 offset:%11\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(a), "=&v"(b[0]), "=&v"(b[1]), "=&v"(b[2]), "=&v"(b[3])
+      : "v"(xa), "v"(b0lo), "v"(b0hi), "v"(b1lo), "v"(b1hi), "n"(OFFA), "n"(OFFB)
+      : "memory");
 }
 
 // Chunk swizzle of row k of an operand that is contiguous along its own index, COLS elements per row (chunks of 16 B):
@@ -278,45 +297,29 @@ __global__ __launch_bounds__(256, 2) void gemm_tile_kernel(P p, int n_tiles_boun
   Frags f0, f1;
   f32x16 acc[MI][NJ];
   int slot = 0;
-  auto read_frags = [&](auto ks_tag, Frags& f) {   // issue only; see wait_frags
+  static_assert(MI == 1 && NJ == 2, "read_frags");
+  auto read_frags = [&](auto ks_tag, Frags& f) {
     constexpr int KS = decltype(ks_tag)::value;
     const uint32_t soa = (uint32_t)slot * (kASlot * 2), sob = (uint32_t)slot * (kBSlot * 2);
-    static_for<MI>([&](auto i_tag) {
-      constexpr int i = decltype(i_tag)::value;
-      lds_read16<i * 32 * kTK * 2>(f.a[i], xa[KS] + soa);
-    });
-    static_for<NJ>([&](auto j_tag) {
-      constexpr int j = decltype(j_tag)::value;
-      if constexpr (P::kBNC) {
-        u32x2 lo, hi;
-        lds_read_tr<KS * 16 * TN * 2>(lo, hi, xb[j] + sob, xbh[j] + sob);
-        f.b[j] = u32x4{lo.x, lo.y, hi.x, hi.y};
-      } else {
-        lds_read16<j * 32 * kTK * 2>(f.b[j], xb[KS] + sob);
-      }
-    });
+    if constexpr (P::kBNC) {
+      u32x2 b[4];
+      lds_read_nc3<0, KS * 16 * TN * 2>(f.a[0], b, xa[KS] + soa, xb[0] + sob, xbh[0] + sob, xb[1] + sob, xbh[1] + sob);
+      f.b[0] = u32x4{b[0].x, b[0].y, b[1].x, b[1].y};
+      f.b[1] = u32x4{b[2].x, b[2].y, b[3].x, b[3].y};
+    } else {
+      lds_read_kc3<0, 0, 32 * kTK * 2>(f.a[0], f.b[0], f.b[1], xa[KS] + soa, xb[KS] + sob);
+    }
   };
-  auto wait_frags = [&](Frags& f) {
-    if constexpr (MI == 1 && NJ == 1)
-      asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f.a[0]), "+v"(f.b[0]));
-    else if constexpr (MI == 1)
-      asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f.a[0]), "+v"(f.b[0]), "+v"(f.b[1]));
-    else
-      asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f.a[0]), "+v"(f.a[1]), "+v"(f.b[0]), "+v"(f.b[1]));
-  };
-  static_assert(MI <= 2 && NJ <= 2 && NJ >= MI, "wait_frags");
 #define MEFT_FENCE() __builtin_amdgcn_sched_barrier(0)
-  auto mma = [&](auto zero_tag, const Frags& f) {
-    static_for<MI * NJ>([&](auto n_tag) {
-      constexpr int i = decltype(n_tag)::value / NJ, j = decltype(n_tag)::value % NJ;
-      const bf16x8 av = __builtin_bit_cast(bf16x8, f.a[i]), bv = __builtin_bit_cast(bf16x8, f.b[j]);
-      if constexpr (decltype(zero_tag)::value) {
-        const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, zero, 0, 0, 0);
-      } else {
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, acc[i][j], 0, 0, 0);
-      }
-    });
+  auto mma = [&](auto zero_tag, auto j_tag, const Frags& f) {
+    constexpr int j = decltype(j_tag)::value;
+    const bf16x8 av = __builtin_bit_cast(bf16x8, f.a[0]), bv = __builtin_bit_cast(bf16x8, f.b[j]);
+    if constexpr (decltype(zero_tag)::value) {
+      const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      acc[0][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, zero, 0, 0, 0);
+    } else {
+      acc[0][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, acc[0][j], 0, 0, 0);
+    }
     MEFT_FENCE();
   };
 #define KS(n) std::integral_constant<int, n> {}
@@ -326,20 +329,20 @@ __global__ __launch_bounds__(256, 2) void gemm_tile_kernel(P p, int n_tiles_boun
   constexpr int kStores = 8 * MI * NJ;
   int since = 2;   // k tiles since the last stores
   auto k_tile = [&](auto first) {
-    read_frags(KS(1), f1); MEFT_FENCE(); mma(first, f0); wait_frags(f1);
-    read_frags(KS(2), f0); MEFT_FENCE(); mma(std::false_type{}, f1); wait_frags(f0);
-    read_frags(KS(3), f1); MEFT_FENCE(); mma(std::false_type{}, f0); wait_frags(f1);
+    mma(first, KS(0), f0); mma(first, KS(1), f0); read_frags(KS(1), f1); MEFT_FENCE();
+    mma(std::false_type{}, KS(0), f1); mma(std::false_type{}, KS(1), f1); read_frags(KS(2), f0); MEFT_FENCE();
+    mma(std::false_type{}, KS(0), f0); mma(std::false_type{}, KS(1), f0); read_frags(KS(3), f1); MEFT_FENCE();
     if (since < 2) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(NL + kStores) : "memory");
     else asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(NL) : "memory");
     ++since;
     MEFT_FENCE();
     slot = slot == 2 ? 0 : slot + 1;
-    read_frags(KS(0), f0); MEFT_FENCE();
+    mma(std::false_type{}, KS(0), f1);
     static_for<NL>([&](auto n) { request(n); });
     MEFT_FENCE();
-    mma(std::false_type{}, f1);
+    mma(std::false_type{}, KS(1), f1);
     advance();
-    wait_frags(f0);
+    read_frags(KS(0), f0);
     MEFT_FENCE();
   };
 
@@ -351,7 +354,6 @@ __global__ __launch_bounds__(256, 2) void gemm_tile_kernel(P p, int n_tiles_boun
   }
   asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * NL) : "memory");   // the first k tile has landed
   read_frags(KS(0), f0);
-  wait_frags(f0);
   MEFT_FENCE();
 
   int wg = wg0;
