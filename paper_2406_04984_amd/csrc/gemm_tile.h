@@ -12,13 +12,14 @@
 // they move fewer bytes per flop and win (value sum of the latter: 52 against 71 us).
 //
 // Schedule of one k tile (four k16 steps):
-//   step 0..2   matrix instructions of the step, LDS reads of the step after it in their shadow
-//   wait        own LDS reads, and own requests of the next k tile (the ones of the k tile after that may be on their
-//               way); barrier: everyone is past this k tile's slot, and the next k tile's has landed
-//   step 3      matrix instructions, LDS reads of the next k tile's step 0, the requests of the k tile three ahead into
-//               the slot just released
-// The requests run on across tiles.  Fragment reads are asm, with the wait in an asm statement of its own that ties the
-// registers: through builtins the compiler orders every LDS read behind all outstanding global -> LDS loads.
+//   step 0..2   matrix instructions of the step, then the LDS reads of the step after it, whose latency passes under them
+//   wait        own requests of the next k tile (the ones of the k tile after that may be on their way); barrier:
+//               everyone is past this k tile's slot (every LDS read has been waited for where it was issued), and the
+//               next k tile's has landed
+//   step 3      matrix instructions, the requests of the k tile three ahead into the slot just released, LDS reads of
+//               the next k tile's step 0
+// The requests run on across tiles.  Fragment reads are asm: through builtins the compiler orders every LDS read behind
+// all outstanding global -> LDS loads.
 // A request never branches: what must not be read (rows beyond the group, contraction indices beyond the end, a k tile
 // beyond the stream) gets an offset outside the buffer, which loads zeros without touching memory.
 #pragma once

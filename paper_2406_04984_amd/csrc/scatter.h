@@ -1,7 +1,7 @@
 // Backward weight gradients without floating-point atomics: the (token, neuron) pairs are grouped
 // by neuron (counting sort; integer atomics only decide positions, and every group is then put in
 // ascending pair order, i.e. ascending token), and the group is summed in that fixed order, in chunks of
-// kSegChunk pairs (one workgroup each; the chunk sums of a long group are added in chunk order):
+// kSegChunk pairs (a wave per chunk and 512 columns; the chunk sums of a long group are added in chunk order):
 //   dV[j,:] = sum act * dOut[t,:],  dK[j,:] = sum ds * h[t,:].
 // Only touched rows are written.
 #pragma once
@@ -87,8 +87,8 @@ __global__ void pair_count_kernel(const int32_t* __restrict__ idx, int P, int N,
   if (p < P) pos[p] = atomicAdd(&cnt[clampi(idx[p], 0, N - 1)], 1);
 }
 
-// A neuron's pairs are summed in chunks of kSegChunk consecutive pairs, one workgroup per chunk, so that a neuron that
-// very many tokens selected does not leave one workgroup with all of its pairs.
+// A neuron's pairs are summed in chunks of kSegChunk consecutive pairs, so that a neuron that very many tokens selected does
+// not leave one wave with all of its pairs.
 constexpr int kSegChunk = 256;
 
 // What one chunk is: neuron, first pair in the grouped list, number of pairs, and its row in the buffer of partial sums
