@@ -267,6 +267,18 @@ struct ProbNeuTN {
   __device__ void store_pk(size_t at, int, uint32_t pk, uint32_t) const { *reinterpret_cast<uint32_t*>(G + at) = pk; }
 };
 
+// The same with an output row number + 1 in every entry of `flag` (0: not stored): batch-union evaluation, whose compacted
+// gradients go to their neurons' rows without a pass of their own.
+template <int TM>
+struct ProbNeuTNRows : ProbNeuTN<TM> {
+  using Base = ProbNeuTN<TM>;
+  __device__ int row_tag(const TileCoord& tc, int m) const {
+    return m < Base::bs ? Base::flag[(size_t)tc.g * Base::bs + m] : 0;
+  }
+  static constexpr bool kRowsLinear = false;
+  __device__ size_t row_off(const TileCoord&, int tag, int) const { return (size_t)(tag - 1) * Base::d; }
+};
+
 // ---- the same problems for gemm_tile_kernel -----------------------------------------------------
 template <int MODE, int TM, int TN>
 struct TileTokKC : ProbTokKC<MODE> {

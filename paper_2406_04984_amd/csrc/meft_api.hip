@@ -401,8 +401,8 @@ bool union_geom(const meft_shape& s, UnionGeom& g) {
 }
 
 struct UnionWs : DispatchWs {
-  int32_t *flag, *chunk_cnt, *rowflag;
-  uint16_t *Kc, *Vc, *dKc, *dVc, *zrow, *Ap, *DS, *part;
+  int32_t *flag, *chunk_cnt, *rowtag;
+  uint16_t *Kc, *Vc, *zrow, *Ap, *DS, *part;
   size_t bytes;
   UnionWs(const meft_shape& s, const UnionGeom& g, void* ws) {
     Carver c(ws);
@@ -410,11 +410,9 @@ struct UnionWs : DispatchWs {
     const size_t n_ent = (size_t)s.T * g.nvb, rows = (size_t)g.nvb * g.vbs;
     chunk_cnt = c.take<int32_t>((size_t)(s.N + kFlagChunk - 1) / kFlagChunk);
     flag = c.take<int32_t>(s.N);
-    rowflag = c.take<int32_t>(rows);
+    rowtag = c.take<int32_t>(rows);
     Kc = c.take<uint16_t>(rows * s.d);
     Vc = c.take<uint16_t>(rows * s.d);
-    dKc = c.take<uint16_t>(rows * s.d);
-    dVc = c.take<uint16_t>(rows * s.d);
     zrow = c.take<uint16_t>((size_t)g.vbs * (1 + 2 * n_ent));   // one piece: row of zeros, A', DS' (see BwdWs)
     Ap = zrow ? zrow + g.vbs : nullptr;
     DS = zrow ? Ap + n_ent * g.vbs : nullptr;
@@ -720,9 +718,10 @@ struct NeuArgs {
   uint64_t a_bytes, x_bytes;   // bytes readable from the lowest address of either operand
 };
 
-template <int TM>
+template <class P>
 void launch_neu_tm(const char* name, const NeuArgs& a, hipStream_t st) {
-  ProbNeuTN<TM> pn{};
+  constexpr int TM = P::kTM;
+  P pn{};
   pn.A = a.A; pn.zrow = a.zrow; pn.X = a.X; pn.G = a.G;
   pn.tok_of_slot = a.tok_of_slot; pn.flag = a.flag;
   pn.sched = a.sched; pn.big_only = a.big_only; pn.bs = a.bs; pn.bsp = a.bsp; pn.d = a.d;
@@ -732,9 +731,10 @@ void launch_neu_tm(const char* name, const NeuArgs& a, hipStream_t st) {
   launch_gemm_mfma(name, pn, (int)(tiles < (int64_t)INT32_MAX ? tiles : (int64_t)INT32_MAX), st);
 }
 
+template <template <int> class P = ProbNeuTN>
 void launch_neu(const char* name, const NeuArgs& a, hipStream_t st) {
-  if (neu_tile_rows(a.bs) == 256) launch_neu_tm<256>(name, a, st);
-  else launch_neu_tm<128>(name, a, st);
+  if (neu_tile_rows(a.bs) == 256) launch_neu_tm<P<256>>(name, a, st);
+  else launch_neu_tm<P<128>>(name, a, st);
 }
 
 }  // namespace
@@ -1044,18 +1044,14 @@ static void union_front(const meft_shape& s, const UnionGeom& g, const UnionWs& 
                         const void* V, const int32_t* S, const int32_t* n_S, hipStream_t st) {
   const size_t n_slots = (size_t)g.nvb * s.T, n_rows = (size_t)g.nvb * g.vbs;
   const size_t n_thr = (n_slots + kSlotPad) > n_rows ? (n_slots + kSlotPad) : n_rows;
-  MEFT_LAUNCH("union_maps", union_maps_kernel, dim3((unsigned)((n_thr + 255) / 256)), dim3(256), 0, st, n_S, g.cap,
-              s.T, g.vbs, g.nvb, w.sblk, w.perm, w.tok_of_slot, w.slot_of_ent, w.group_off, w.rowflag);
+  MEFT_LAUNCH("union_maps", union_maps_kernel, dim3((unsigned)((n_thr + 255) / 256)), dim3(256), 0, st, S, n_S, g.cap,
+              s.N, s.T, g.vbs, g.nvb, w.sblk, w.perm, w.tok_of_slot, w.slot_of_ent, w.group_off, w.rowtag,
+              reinterpret_cast<int32_t*>(w.zrow));   // (vbs % 64 == 0)
   MEFT_LAUNCH("build_sched", build_sched_kernel, dim3(1), dim3(1024), 0, st, w.group_off, g.nvb, sched_cap(g.vs),
               w.sched_pairs, w.sched_tiles, w.sched_len, 0);
-  // the row of zeros that pads the contraction over tokens in the weight-gradient GEMMs (vbs % 64 == 0)
-  MEFT_LAUNCH("fill_i32", fill_i32_kernel, dim3((g.vbs / 2 + 255) / 256), dim3(256), 0, st,
-              reinterpret_cast<int32_t*>(w.zrow), (size_t)g.vbs / 2, 0);
   const int rows_grid = (int)(n_rows < 4096 ? n_rows : 4096);
-  MEFT_LAUNCH("gather_rows", gather_rows_kernel, dim3(rows_grid), dim3(256), 0, st, static_cast<const uint16_t*>(K),
-              S, n_S, g.cap, s.N, s.d, g.vbs, w.Kc);
-  MEFT_LAUNCH("gather_rows", gather_rows_kernel, dim3(rows_grid), dim3(256), 0, st, static_cast<const uint16_t*>(V),
-              S, n_S, g.cap, s.N, s.d, g.vbs, w.Vc);
+  MEFT_LAUNCH("gather_rows", gather_rows_kernel, dim3(rows_grid, 2), dim3(256), 0, st, static_cast<const uint16_t*>(K),
+              static_cast<const uint16_t*>(V), S, n_S, g.cap, s.N, s.d, g.vbs, w.Kc, w.Vc);
   const TokenSched sched{w.sched_pairs, w.sched_tiles, w.sched_len, sched_cap(g.vs), sched_max_tiles(g.vs)};
   launch_tok<TokKCLarge<kTokRelu>, TokKCSmall<kTokRelu>>("union_score_gemm", g.vs, g.vbs, (uint64_t)s.T * s.d * 2, (uint64_t)n_rows * s.d * 2, (uint64_t)s.T * g.nvb * g.vbs * 2, [&](auto& pr) {
     pr.X = static_cast<const uint16_t*>(h); pr.W = w.Kc; pr.perm = w.perm; pr.tok_of_slot = w.tok_of_slot;
@@ -1139,18 +1135,14 @@ meft_status meft_union_bwd(const meft_shape* shape, const void* h, const void* K
     launch_token_rows("union_dh_rows", g.vs, w.part, w, nullptr, nullptr, nullptr, dh, SmallDvdk{}, st);
   }
   NeuArgs pn{};
-  pn.tok_of_slot = w.tok_of_slot; pn.flag = w.rowflag;
+  pn.tok_of_slot = w.tok_of_slot; pn.flag = w.rowtag;
   pn.sched = sched; pn.big_only = 0; pn.n_groups = g.nvb; pn.bs = g.vbs; pn.bsp = g.vbs; pn.d = s.d;
   pn.a_bytes = (1 + 2 * (uint64_t)s.T * g.nvb) * g.vbs * 2; pn.x_bytes = (uint64_t)s.T * s.d * 2;
-  pn.A = w.Ap; pn.zrow = -1; pn.X = gg; pn.G = w.dVc;
-  launch_neu("union_dV_gemm", pn, st);
-  pn.A = w.DS; pn.zrow = -(s.T * g.nvb + 1); pn.X = hh; pn.G = w.dKc;
-  launch_neu("union_dK_gemm", pn, st);
-  const int rows_grid = g.cap < 4096 ? g.cap : 4096;
-  MEFT_LAUNCH("scatter_rows", scatter_rows_kernel, dim3(rows_grid), dim3(256), 0, st, w.dVc, S, n_S, s.N, s.d, g.cap,
-              static_cast<uint16_t*>(dV));
-  MEFT_LAUNCH("scatter_rows", scatter_rows_kernel, dim3(rows_grid), dim3(256), 0, st, w.dKc, S, n_S, s.N, s.d, g.cap,
-              static_cast<uint16_t*>(dK));
+  pn.A = w.Ap; pn.zrow = -1; pn.X = gg; // the gradients are written to the rows of S directly: a pass over the compacted ones took 2 x 24 us at 16384 rows x 2048
+  pn.G = static_cast<uint16_t*>(dV);
+  launch_neu<ProbNeuTNRows>("union_dV_gemm", pn, st);
+  pn.A = w.DS; pn.zrow = -(s.T * g.nvb + 1); pn.X = hh; pn.G = static_cast<uint16_t*>(dK);
+  launch_neu<ProbNeuTNRows>("union_dK_gemm", pn, st);
   return launch_status();
 }
 

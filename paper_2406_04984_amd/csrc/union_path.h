@@ -22,14 +22,17 @@ __global__ __launch_bounds__(256) void mark_idx_kernel(const int32_t* __restrict
 // Index structure of the virtual blocks, from the union size U = *n_S (device):
 //   n_real = ceil(U / vbs) blocks hold rows; block g < n_real has all T tokens as its group, slot g*T + t.
 //   entry of token t for block g: t*nvb + g.  Blocks g >= n_real are empty (sblk = -1).
+// rowtag[i] = S[i] + 1: the row that the gradients of compacted row i go to; 0 where there is none.  Also clears zrow.
 // One thread per (block, token) slot of the full nvb x T grid; the small tables are written by workgroup 0.
-__global__ __launch_bounds__(256) void union_maps_kernel(const int32_t* __restrict__ n_S, int cap, int T, int vbs,
-                                                         int nvb,
+__global__ __launch_bounds__(256) void union_maps_kernel(const int32_t* __restrict__ S,
+                                                         const int32_t* __restrict__ n_S, int cap, int N, int T,
+                                                         int vbs, int nvb,
                                                          int32_t* __restrict__ sblk, int32_t* __restrict__ perm,
                                                          int32_t* __restrict__ tok_of_slot,
                                                          int32_t* __restrict__ slot_of_ent,
                                                          int32_t* __restrict__ group_off,
-                                                         int32_t* __restrict__ rowflag) {
+                                                         int32_t* __restrict__ rowtag,
+                                                         int32_t* __restrict__ zrow) {
   const int U = max(0, min(*n_S, cap));   // cap <= nvb * vbs is the capacity of S
   const int n_real = (U + vbs - 1) / vbs;
   const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
@@ -47,7 +50,11 @@ __global__ __launch_bounds__(256) void union_maps_kernel(const int32_t* __restri
   }
   // kSlotPad valid entries behind the last real slot (the GEMMs look row numbers up a little beyond a group)
   if (i >= (long long)n_real * T && i < (long long)n_real * T + kSlotPad) tok_of_slot[i] = 0;
-  if (i < (long long)nvb * vbs) rowflag[i] = i < U ? 1 : 0;   // which compacted rows exist
+  if (i < (long long)nvb * vbs) {
+    const int j = i < U ? S[i] : -1;
+    rowtag[i] = (unsigned)j < (unsigned)N ? j + 1 : 0;
+  }
+  if (i < vbs / 2) zrow[i] = 0;
   if (blockIdx.x == 0) {
     for (int g = threadIdx.x; g <= nvb; g += 256) {
       const int r = g < n_real ? g : n_real;
@@ -56,12 +63,15 @@ __global__ __launch_bounds__(256) void union_maps_kernel(const int32_t* __restri
   }
 }
 
-// dst[i, :] = src[S[i], :] for i < U, zero for U <= i < n_real*vbs (the tail of the last virtual block).
-// One workgroup per compacted row at a time; 16-byte accesses (bf16 rows, d % 8 == 0).
-__global__ __launch_bounds__(256) void gather_rows_kernel(const uint16_t* __restrict__ src,
+// Kc[i, :] = K[S[i], :] and Vc[i, :] = V[S[i], :] for i < U, zero for U <= i < n_real*vbs (the tail of the last virtual
+// block).  One workgroup per compacted row of one of the two (blockIdx.y) at a time; 16-byte accesses (bf16 rows,
+// d % 8 == 0).
+__global__ __launch_bounds__(256) void gather_rows_kernel(const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
                                                           const int32_t* __restrict__ S,
                                                           const int32_t* __restrict__ n_S, int cap, int N, int d,
-                                                          int vbs, uint16_t* __restrict__ dst) {
+                                                          int vbs, uint16_t* __restrict__ Kc, uint16_t* __restrict__ Vc) {
+  const uint16_t* src = blockIdx.y == 0 ? K : V;
+  uint16_t* dst = blockIdx.y == 0 ? Kc : Vc;
   const int U = max(0, min(*n_S, cap));
   const int rows = ((U + vbs - 1) / vbs) * vbs;
   for (int i = blockIdx.x; i < rows; i += gridDim.x) {
@@ -71,21 +81,6 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const uint16_t* __rest
     const u32x4* in = j >= 0 ? reinterpret_cast<const u32x4*>(src + (size_t)j * d) : nullptr;
     const u32x4 zero = {0u, 0u, 0u, 0u};
     for (int c = threadIdx.x; c < d / 8; c += 256) o[c] = in ? in[c] : zero;
-  }
-}
-
-// dst[S[i], :] = src[i, :] for i < U: the compacted gradient rows go to their neurons' rows.
-__global__ __launch_bounds__(256) void scatter_rows_kernel(const uint16_t* __restrict__ src,
-                                                           const int32_t* __restrict__ S,
-                                                           const int32_t* __restrict__ n_S, int N, int d, int cap,
-                                                           uint16_t* __restrict__ dst) {
-  const int U = max(0, min(*n_S, cap));
-  for (int i = blockIdx.x; i < U; i += gridDim.x) {
-    const int j = S[i];
-    if ((unsigned)j >= (unsigned)N) continue;
-    const u32x4* in = reinterpret_cast<const u32x4*>(src + (size_t)i * d);
-    u32x4* o = reinterpret_cast<u32x4*>(dst + (size_t)j * d);
-    for (int c = threadIdx.x; c < d / 8; c += 256) o[c] = in[c];
   }
 }
 

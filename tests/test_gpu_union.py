@@ -143,3 +143,14 @@ def test_full_size_sampled():
     ni = torch.from_numpy(neu.astype(np.int64)).cuda()
     assert P.rel_l2(P.to_host(g["dK"][ni]), dK) <= TOL
     assert P.rel_l2(P.to_host(g["dV"][ni]), dV) <= TOL
+
+
+@pytest.mark.parametrize("T,d,blocks,bs,k", [
+    (37, 320, 10, 64, 8),     # capacity 296: one virtual block of 320 rows, 128-row gradient tiles with a ragged last one
+    (24, 64, 8, 32, 8),       # capacity 192 of 256: one 256-row tile, part of its rows beyond the union, d below a tile
+    (130, 576, 24, 48, 16),   # N = 1152: the second virtual block holds at most 128 rows
+])
+def test_gradient_rows_go_to_the_rows_of_the_union(T, d, blocks, bs, k):
+    # the gradient contractions write to the rows that S names, whichever tile height they run on
+    n = _check_small(synth.small_case(T, d, blocks, bs, 2, k, dtype="bf16", seed=T))
+    assert 0 < n <= min(blocks * bs, T * k)
