@@ -76,7 +76,7 @@ def kernel_models(cfg, n_touched):
 
 # profiler name of the kernel behind each stage label (the rocprofv3 summaries list kernels by symbol)
 STAGE_SYMBOL = {
-    "router_gemm": "gemm_mfma_kernel<ProbRouter, true>", "score_gemm": "gemm_mfma_kernel<ProbTokKC<0>, true>",
+    "router_gemm": "gemm_mfma_kernel<ProbRouter, true>", "score_gemm": ("gemm_mfma_kernel<ProbTokKC<3>, true>", "gemm_mfma_kernel<ProbTokKC<0>, true>"),
     "dact_gemm": "gemm_mfma_kernel<ProbTokKC<1>, true>", "value_gemm": "gemm_mfma_kernel<ProbTokNC, true>",
     "dh_gemm": "gemm_mfma_kernel<ProbTokNC, true>",
     # dV / dK: the tile height is chosen per shape (256 rows where the block fills them, else 128)

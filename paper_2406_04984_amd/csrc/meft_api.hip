@@ -1138,8 +1138,8 @@ meft_status meft_union_bwd(const meft_shape* shape, const void* h, const void* K
   pn.tok_of_slot = w.tok_of_slot; pn.flag = w.rowtag;
   pn.sched = sched; pn.big_only = 0; pn.n_groups = g.nvb; pn.bs = g.vbs; pn.bsp = g.vbs; pn.d = s.d;
   pn.a_bytes = (1 + 2 * (uint64_t)s.T * g.nvb) * g.vbs * 2; pn.x_bytes = (uint64_t)s.T * s.d * 2;
-  pn.A = w.Ap; pn.zrow = -1; pn.X = gg; // the gradients are written to the rows of S directly: a pass over the compacted ones took 2 x 24 us at 16384 rows x 2048
-  pn.G = static_cast<uint16_t*>(dV);
+  // written to the rows of S directly: a pass over compacted gradients took 2 x 24 us at 16384 rows x 2048
+  pn.A = w.Ap; pn.zrow = -1; pn.X = gg; pn.G = static_cast<uint16_t*>(dV);
   launch_neu<ProbNeuTNRows>("union_dV_gemm", pn, st);
   pn.A = w.DS; pn.zrow = -(s.T * g.nvb + 1); pn.X = hh; pn.G = static_cast<uint16_t*>(dK);
   launch_neu<ProbNeuTNRows>("union_dK_gemm", pn, st);
