@@ -24,6 +24,7 @@
 // beyond the stream) gets an offset outside the buffer, which loads zeros without touching memory.
 #pragma once
 #include "gemm_mfma.h"
+#include "tile_div.h"
 
 namespace meft {
 
@@ -83,7 +84,7 @@ __device__ __forceinline__ int nc_key(int k) {
 struct TileFinder {
   int c, g, slot0, rows;   // lane: tiles before the entry (in m tiles), group, its first slot, its rows
   int mts;                 // its m tiles
-  uint32_t inv;            // and floor(2^32 / mts) + 1: w / mts is the high half of w * inv (w * mts < 2^32; mts > 1)
+  uint32_t inv;            // and what tile_div divides by it with
   int first, mine;         // split lists: this XCD's tiles before the entry, and of it
   int b, n, x, tn;
   bool split;
@@ -102,7 +103,7 @@ struct TileFinder {
     g = e.x; slot0 = e.y; rows = e.z;
     c = TM == 64 ? t.x : t.y;
     mts = max(__shfl_down(c, 1, 64) - c, 1);
-    inv = mts > 1 ? 0xFFFFFFFFu / (uint32_t)mts + 1u : 0u;
+    inv = tile_div_inverse((uint32_t)mts);
     if (split) {   // at most 7 groups
       const int all = mts * tn;
       mine = lane < n && all > x ? (all - x + kXcd - 1) / kXcd : 0;
@@ -134,7 +135,7 @@ struct TileFinder {
       w = local - __builtin_amdgcn_readlane(c, i) * tn;
     }
     const int m = __builtin_amdgcn_readlane(mts, i);
-    nt = m > 1 ? (int)__umulhi((uint32_t)w, (uint32_t)__builtin_amdgcn_readlane((int)inv, i)) : w;
+    nt = tile_div(w, m, (uint32_t)__builtin_amdgcn_readlane((int)inv, i));
     mt = w - nt * m;
     tc.g = __builtin_amdgcn_readlane(g, i);
     tc.slot0 = __builtin_amdgcn_readlane(slot0, i);

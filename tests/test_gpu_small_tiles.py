@@ -38,3 +38,36 @@ def test_same_bits_as_large_tiles(kw):
             layer.B.meft_debug_global_loads(False)
     for n in NAMES:
         assert np.array_equal(got[0][n], got[1][n]), n
+
+
+def test_a_group_of_more_than_65536_tiles():
+    """One group of 65537 tiles of 64 rows: the number of a tile times the group's tiles passes 2^32."""
+    import torch
+    from paper_2406_04984_amd import binding as B
+    T, d, bs = 65536 * 64 + 1, 64, 64
+    s = B.make_shape(T, d, 1, bs, 1, 1, "bf16")
+    gen = torch.Generator(device="cuda").manual_seed(6200)
+    bf = dict(dtype=torch.bfloat16, device="cuda")
+    h, dOut = (torch.randn((T, d), generator=gen, **bf) for _ in range(2))
+    K, V = (torch.randn((bs, d), generator=gen, **bf) for _ in range(2))
+    block_idx = torch.zeros((T, 1), dtype=torch.int32, device="cuda")
+    ws = torch.empty((B.meft_workspace_bytes(s),), dtype=torch.uint8, device="cuda")
+    got = []
+    for forced in (False, True):
+        out, dh = torch.zeros((T, d), **bf), torch.zeros((T, d), **bf)
+        idx, act = torch.zeros((T, 1), dtype=torch.int32, device="cuda"), torch.zeros((T, 1), device="cuda")
+        dK, dV = torch.zeros((bs, d), **bf), torch.zeros((bs, d), **bf)
+        touched, n = torch.zeros((bs,), dtype=torch.int32, device="cuda"), torch.zeros((1,), dtype=torch.int32, device="cuda")
+        ws.fill_(0xFF)
+        B.meft_debug_global_loads(forced)
+        try:
+            B.meft_sparse_fwd(s, h, K, V, block_idx, out, idx, act, ws)
+            B.meft_sparse_bwd(s, h, K, V, idx, act, dOut, dh, dK, dV, touched, n, ws)
+            torch.cuda.synchronize()
+        finally:
+            B.meft_debug_global_loads(False)
+        got.append((idx, act, out, dh, dK, dV, touched, n))
+    for x, y in zip(*got):
+        assert torch.equal(x, y)
+    score = h[-64:].float() @ K.float().T
+    assert torch.equal(got[0][0][-64:, 0].long(), score.argmax(1))
