@@ -782,7 +782,7 @@ static int launch_route_part(const meft_shape& s, const void* h, const void* Wg,
   const int steps = (int)(((int64_t)s.d * sizeof(T) + 63) / 64);
   // a slice of at least four 64-byte steps per wave: one batch of loads
   const int want = steps / (4 * kRouteWaves), n_part = want < 1 ? 1 : (want > kRouterSplitMax ? kRouterSplitMax : want);
-#define RP(NA, TT) MEFT_LAUNCH("route_part", (route_part_kernel<T, NA, TT>), dim3((s.n_blocks + 16 * (NA) - 1) / (16 * (NA)), (s.T + 16 * (TT) - 1) / (16 * (TT)), n_part), dim3(64 * kRouteWaves), 0, st, hh, ww, s.T, s.d, s.n_blocks, p)
+#define RP(NA, TT) MEFT_LAUNCH("route_part", (route_part_kernel<T, NA, TT>), dim3((unsigned)((s.n_blocks + 16 * (NA) - 1) / (16 * (NA))) * ((s.T + 16u * (TT) - 1) / (16 * (TT))), 1, n_part), dim3(64 * kRouteWaves), 0, st, hh, ww, s.T, s.d, s.n_blocks, p)
   // one 16-block tile per workgroup for the few tokens that would leave the chip idle, else four (they share the
   // loads of h), and two token tiles (they share the loads of the router) once that still fills it
   const int64_t wg = (int64_t)((s.T + 15) / 16) * ((s.n_blocks + 63) / 64) * n_part;

@@ -10,7 +10,8 @@ constexpr int kRouteWaves = 8;
 // p[part][t][b] = partial score of token t and block b over slice `part` of the hidden dimension.  A workgroup takes 16
 // tokens * TT, 16 blocks * NA and one of the n_part slices, which its eight waves share out again; each multiplies with
 // 16 x 16 matrix-core steps straight from memory, and the waves are added through LDS in order.
-// Grid: (ceil(B / (16 * NA)), ceil(T / (16 * TT)), n_part).
+// Grid: (ceil(B / (16 * NA)) * ceil(T / (16 * TT)), 1, n_part), the blocks fastest (a batch has more token tiles than a
+// launch may have workgroups along y).
 //
 // Used for fp32, and for bf16 as long as the problem is small: what bounds it there is the latency of a compute unit's
 // loads (one compute unit has about a hundred 128-byte lines in flight, so one alone takes 12 us to read the router of
@@ -21,7 +22,8 @@ __global__ __launch_bounds__(64 * kRouteWaves) void route_part_kernel(const T* _
                                                                       int n_tok, int d, int B, float* __restrict__ p) {
   __shared__ __attribute__((aligned(16))) float s_part[kRouteWaves][NA][TT][64][4];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int b0 = blockIdx.x * 16 * NA, t0 = blockIdx.y * 16 * TT;
+  const int b_tiles = (B + 16 * NA - 1) / (16 * NA), t_tile = blockIdx.x / b_tiles;
+  const int b0 = (blockIdx.x - t_tile * b_tiles) * 16 * NA, t0 = t_tile * 16 * TT;
   const int row_bytes = d * (int)sizeof(T);
   const char *pa[NA], *pb[TT];
 #pragma unroll

@@ -1,0 +1,33 @@
+"""Launch shapes of accepted problems against the limits of the device (65536 workgroups along y and z, fewer than 2^32
+threads along x, 1024 threads and 160 KB of LDS per workgroup), at the far ends of what the shape check lets through and
+a batch can hold."""
+import pytest
+
+from tests.hostcalls import record, shape
+
+CASES = [
+    (shape(3_000_000, 8, 8, 1, 1, 1, "f32"), ["route", "fwd", "bwd"]),
+    (shape(10_000_000, 16, 1, 4, 1, 4, "f32"), ["route", "fwd", "bwd"]),
+    (shape(3_000_000, 72, 2, 16, 2, 8, "bf16"), ["route", "fwd", "bwd"]),
+    (shape(4_194_305, 64, 1, 64, 1, 1, "bf16"), ["route", "fwd", "bwd"]),
+    (shape(400_000, 64, 64, 16, 8, 16, "bf16"), ["route", "fwd", "bwd"]),
+    (shape(1, 16384, 16384, 1, 1, 1, "f32"), ["route", "fwd", "bwd"]),
+    (shape(512, 16384, 512, 96, 1, 96, "bf16"), ["route", "fwd", "bwd"]),
+    (shape(70_000, 128, 16384, 8, 3, 5, "f32"), ["route", "fwd", "bwd"]),
+    (shape(500, 64, 1, 4_194_304, 1, 4096, "bf16"), ["route", "fwd", "bwd"]),
+    (shape(100_000, 64, 4, 512, 2, 64, "bf16"), ["union_fwd", "union_bwd"]),
+]
+
+
+@pytest.fixture(scope="module")
+def launches():
+    return [[r for r in rows if r["what"] == "launch"] for rows in record(CASES)]
+
+
+@pytest.mark.parametrize("i", range(len(CASES)), ids=lambda i: "T{}_d{}_N{}_B{}".format(*CASES[i][0][:4]))
+def test_within_the_limits_of_the_device(launches, i):
+    assert launches[i]
+    for r in launches[i]:
+        g, b = r["grid"], r["block"]
+        assert min(g) >= 1 and g[1] <= 65536 and g[2] <= 65536, r
+        assert g[0] * b[0] < 1 << 32 and b[0] * b[1] * b[2] <= 1024 and r["lds"] <= 160 * 1024, r
