@@ -155,7 +155,38 @@ int tile_bound(const meft_shape& s, int tn) {
 }
 
 constexpr int kRouterSplitMax = 4;
-constexpr int64_t kRouteTiledMin = 4096 * 64;   // token-block pairs from which the tiled router contraction is used
+
+// Slices of the hidden dimension in the untiled router contraction (router.h): at least four 64-byte steps per wave of a
+// slice, one batch of loads.
+int route_slices(const meft_shape& s) {
+  const int steps = (int)(((int64_t)s.d * (s.dtype == MEFT_BF16 ? 2 : 4) + 63) / 64), want = steps / (4 * kRouteWaves);
+  return want < 1 ? 1 : (want > kRouterSplitMax ? kRouterSplitMax : want);
+}
+
+// Whether the router contraction runs on LDS tiles: ProbRouter for bf16 rows of whole 64-element k tiles, gemm_nt.h
+// otherwise.  The untiled one wins while the problem is small and then re-reads h (once per 64 blocks) and the router too
+// often.  All times are of the whole route call, us, untiled / tiled.
+bool route_on_tiles(const meft_shape& s) {
+  if (s.dtype == MEFT_BF16 && s.d % kTK == 0) {
+    // d 4096, 64 blocks: 11.0 / 18.6 at 1024 tokens, 20.3 / 20.1 at 4096, 39.1 / 23.5 at 8192; 256 blocks: 22.6 / 23.4 at
+    // 1024, 69.5 / 27.6 at 4096
+    if ((int64_t)s.T * s.n_blocks > 4096 * 64) return true;
+    // Few blocks, long rows: the tiled one wins once its 128-token tiles fill the chip.  8 blocks, 4096 / 8192 tokens: d 4096
+    // 14.2 / 18.6 and 31.2 / 20.6, d 8192 24.4 / 28.4 and 46.7 / 33.5; 32768 tokens: d 2048 50.4 / 42.3.  Below d 2048 the
+    // ring's start outweighs a slice's few k tiles: 28.4 / 32.1 at d 1024.
+    const int kt = s.d / kTK, parts = kt % 4 == 0 ? 4 : (kt % 2 == 0 ? 2 : 1);
+    return s.d >= 2048 && (int64_t)(s.T / 128) * parts >= 160 && (int64_t)s.T * s.d > (int64_t)5 << 22;
+  }
+  // The untiled time goes by tokens x groups of 64 blocks, and by the steps of a row rounded up to whole batches of four
+  // per wave and slice.  64 blocks, 16384 and 65536 tokens: fp32 d 256 26.1 / 25.3 and 87.8 / 50.4, d 768 43 / 57 and 159 /
+  // 112, d 1024 45 / 72 and 176 / 156, d 4096 167 / 279 and 672 / 588 (1024 blocks, 16384 tokens: 2530 / 1957); bf16 d 1000
+  // 19.5 / 25.5 and 65 / 42, d 4104 85 / 68 and 385 / 142 (1024 blocks, 16384 tokens: 1404 / 274).
+  const int es = s.dtype == MEFT_BF16 ? 2 : 4;
+  const int64_t steps = ((int64_t)s.d * es + 63) / 64, slices = (int64_t)route_slices(s) * kRouteWaves;
+  const int64_t per = (steps + slices - 1) / slices, padded = slices * ((per + 3) / 4 * 4);
+  const int64_t reads = (int64_t)s.T * ((s.n_blocks + 63) / 64);
+  return reads * padded > (es == 2 ? 28672 : 49152) * steps;
+}
 
 struct RouteWs {
   float* p;
@@ -779,9 +810,7 @@ static meft_status launch_few(const meft_shape& s, const void* h, const void* K,
 template <typename T>
 static int launch_route_part(const meft_shape& s, const void* h, const void* Wg, float* p, hipStream_t st) {
   const T *hh = static_cast<const T*>(h), *ww = static_cast<const T*>(Wg);
-  const int steps = (int)(((int64_t)s.d * sizeof(T) + 63) / 64);
-  // a slice of at least four 64-byte steps per wave: one batch of loads
-  const int want = steps / (4 * kRouteWaves), n_part = want < 1 ? 1 : (want > kRouterSplitMax ? kRouterSplitMax : want);
+  const int n_part = route_slices(s);
 #define RP(NA, TT) MEFT_LAUNCH("route_part", (route_part_kernel<T, NA, TT>), dim3((unsigned)((s.n_blocks + 16 * (NA) - 1) / (16 * (NA))) * ((s.T + 16u * (TT) - 1) / (16 * (TT))), 1, n_part), dim3(64 * kRouteWaves), 0, st, hh, ww, s.T, s.d, s.n_blocks, p)
   // one 16-block tile per workgroup for the few tokens that would leave the chip idle, else four (they share the
   // loads of h), and two token tiles (they share the loads of the router) once that still fills it
@@ -798,17 +827,20 @@ static int launch_route_part(const meft_shape& s, const void* h, const void* Wg,
 static meft_status route_impl(const meft_shape& s, const void* h, const void* Wg, const float* bias,
                               int32_t* block_idx, float* block_score, float* p, hipStream_t st) {
   int n_part = 1;
-  // The tiled contraction takes bf16 problems that fill the chip with its 128-token tiles.  Measured at d = 4096 and
-  // 64 blocks, this launch tiled / untiled: 13.1 / 3.4 us (1 token), 18.0 / 8.8 us (777); 8192 tokens: 20.3 us tiled,
-  // where the untiled one re-reads h and the router too often.
-  if (s.dtype == MEFT_BF16 && s.d % kTK == 0 && (int64_t)s.T * s.n_blocks > kRouteTiledMin) {
+  if (!route_on_tiles(s)) {
+    n_part = s.dtype == MEFT_BF16 ? launch_route_part<bf16_t>(s, h, Wg, p, st) : launch_route_part<float>(s, h, Wg, p, st);
+  } else if (s.dtype == MEFT_BF16 && s.d % kTK == 0) {
     const int kt = s.d / kTK;
     n_part = kt % 4 == 0 ? 4 : (kt % 2 == 0 ? 2 : 1);
     ProbRouter pr{static_cast<const uint16_t*>(h), static_cast<const uint16_t*>(Wg), p, s.T, s.d, s.n_blocks, n_part};
     set_gemm_extents(pr, (uint64_t)s.T * s.d * 2, (uint64_t)s.n_blocks * s.d * 2);
     launch_gemm_mfma("router_gemm", pr, n_part * ((s.T + ProbRouter::kTM - 1) / ProbRouter::kTM) * ((s.n_blocks + kTN - 1) / kTN), st);
   } else {
-    n_part = s.dtype == MEFT_BF16 ? launch_route_part<bf16_t>(s, h, Wg, p, st) : launch_route_part<float>(s, h, Wg, p, st);
+    GemmNTArgs a{};
+    a.A = h; a.Bm = Wg; a.C = p; a.perm = nullptr; a.group_off = nullptr; a.tile_off = nullptr;
+    a.n_groups = 1; a.M = s.T; a.Ng = s.n_blocks; a.Kdim = s.d; a.lda = s.d; a.ldb = s.d; a.ldc = s.n_blocks;
+    a.e = 1;
+    launch_gemm_nt(s, a, (s.T + kGemmBM - 1) / kGemmBM, (s.T + kGemmF32BM - 1) / kGemmF32BM, "router_gemm", st);
   }
   const size_t stride = (size_t)s.T * s.n_blocks;
 #define PK(Z) MEFT_LAUNCH("route_pick", (route_pick_kernel<Z>), dim3((s.T + 3) / 4), dim3(256), 0, st, p, n_part, stride, bias, s.T, s.n_blocks, s.top_e, block_idx, block_score)

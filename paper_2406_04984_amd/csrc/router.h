@@ -13,10 +13,10 @@ constexpr int kRouteWaves = 8;
 // Grid: (ceil(B / (16 * NA)) * ceil(T / (16 * TT)), 1, n_part), the blocks fastest (a batch has more token tiles than a
 // launch may have workgroups along y).
 //
-// Used for fp32, and for bf16 as long as the problem is small: what bounds it there is the latency of a compute unit's
-// loads (one compute unit has about a hundred 128-byte lines in flight, so one alone takes 12 us to read the router of
-// a 4096 x 64 layer), and the LDS-tiled contraction (ProbRouter) fills too few of them and pays for its ring's start.
-// For large problems the tiled one moves a quarter of the bytes per flop.
+// Used as long as the problem is small (route_on_tiles has the lines): what bounds it there is the latency of a compute
+// unit's loads (one compute unit has about a hundred 128-byte lines in flight, so one alone takes 12 us to read the router
+// of a 4096 x 64 layer), and the LDS-tiled contractions (ProbRouter, gemm_nt.h) fill too few of them and pay for their
+// ring's start.  For large problems the tiled ones move a fraction of the bytes per flop.
 template <typename T, int NA, int TT>
 __global__ __launch_bounds__(64 * kRouteWaves) void route_part_kernel(const T* __restrict__ h, const T* __restrict__ Wg,
                                                                       int n_tok, int d, int B, float* __restrict__ p) {

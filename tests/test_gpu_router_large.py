@@ -1,11 +1,22 @@
-"""The router on more tokens than one launch dimension can count tiles of: every token's choice against torch."""
+"""The router on either side of the lines from which its contraction runs on LDS tiles, and on more tokens than one launch
+dimension can count tiles of: every token's choice against torch."""
 import pytest
 
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("T, d, n_blocks, dtype", [(2_100_003, 8, 5, "f32"), (2_100_003, 24, 2, "bf16")])
-def test_more_token_tiles_than_workgroups_along_y(T, d, n_blocks, dtype):
+SIZES = [
+    (2_100_003, 8, 5, "f32"), (2_100_003, 24, 2, "bf16"),
+    (3072, 512, 1024, "f32"), (3073, 512, 1024, "f32"),
+    (1792, 1000, 1023, "bf16"), (1793, 1000, 1023, "bf16"),
+    (910, 2056, 1024, "bf16"), (911, 2056, 1024, "bf16"),
+    (10240, 2048, 5, "bf16"), (10241, 2048, 5, "bf16"),
+    (20479, 2112, 3, "bf16"), (20480, 2112, 3, "bf16"),
+]
+
+
+@pytest.mark.parametrize("T, d, n_blocks, dtype", SIZES)
+def test_choices_of_all_tokens(T, d, n_blocks, dtype):
     import torch
     from paper_2406_04984_amd import binding as B
     s = B.make_shape(T, d, n_blocks, 16, 1, 4, dtype)
