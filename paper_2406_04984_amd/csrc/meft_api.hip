@@ -847,7 +847,10 @@ static meft_status route_impl(const meft_shape& s, const void* h, const void* Wg
   if (s.n_blocks <= 64) PK(1);
   else if (s.n_blocks <= 128) PK(2);
   else if (s.n_blocks <= 256) PK(4);
-  else if (s.n_blocks <= 1024) PK(16);
+  // beyond 256 blocks the keys take sixteen registers per lane: better for several rounds on few tokens (route call, LDS
+  // keys / registers, 1024 blocks and 2048 tokens: 39.9 / 28.7 us for 16 blocks, 23.4 / 22.2 for 4, 19.1 / 20.7 for 1),
+  // worse once the tokens fill the chip (16384 tokens: 112 / 153, 55 / 104, 40 / 92)
+  else if (s.n_blocks <= 1024 && s.top_e >= 8 && s.T <= 2048) PK(16);
   else
 #undef PK
   MEFT_LAUNCH("route_topk", route_topk_kernel, dim3(s.T), dim3(64), (size_t)s.n_blocks * 4, st, p, n_part,

@@ -7,7 +7,7 @@
 namespace meft {
 
 // ---------------------------------------------------------------------------------------------
-// Top-e blocks of more than 1024 blocks (router.h has the kernel for fewer).  One wave per token.  The row of
+// Top-e blocks of many blocks (router.h has the kernel for few).  One wave per token.  The row of
 // B scores sits in LDS as ordered keys; e rounds of a wave-wide arg-max, the winner is retired
 // by zeroing its key (a live key is never 0 for finite scores).  Output order: score descending,
 // block id ascending.  The scores may arrive as n_part partial sums, part_stride floats apart.

@@ -51,3 +51,11 @@ def test_router(T, n_blocks, dtype):
     cfg = synth.small_case(T=T, d=320, n_blocks=n_blocks, block_size=16, top_e=min(6, n_blocks), top_k=8, dtype=dtype,
                            seed=4300 + n_blocks, zipf_s=0.7)
     P.run_and_compare(cfg).assert_ok()
+
+
+@pytest.mark.parametrize("T", [2048, 2049])
+def test_router_of_many_blocks_and_rounds(T):
+    """Both sides of the line between keys in registers, sixteen per lane, and keys in LDS."""
+    from tests import parity as P
+    cfg = synth.small_case(T=T, d=64, n_blocks=1000, block_size=4, top_e=8, top_k=4, dtype="f32", seed=4400, zipf_s=0.7)
+    P.run_and_compare(cfg).assert_ok()

@@ -51,3 +51,13 @@ def test_large_router_contractions_run_on_tiles():
     for (untiled, tiled, name), a, b in zip(ROUTER, rows[::2], rows[1::2]):
         assert "route_part_kernel" in a[0]["name"], (untiled, a)
         assert name in b[0]["name"], (tiled, b)
+
+
+# The selection with sixteen keys per lane took 153 us where the one with keys in LDS takes 112 (16384 tokens, 1024 blocks,
+# top_e 16), 92 against 40 with top_e 1.
+@pytest.mark.parametrize("T, n_blocks, top_e, name", [
+    (16384, 256, 1, "route_pick_kernel"), (2048, 1024, 8, "route_pick_kernel"), (2049, 1024, 8, "route_topk_kernel"),
+    (2048, 257, 7, "route_topk_kernel"), (100, 1025, 8, "route_topk_kernel")])
+def test_selection_of_blocks(T, n_blocks, top_e, name):
+    rows, = record([(shape(T, 64, n_blocks, 64, top_e, 16, "bf16"), ["route"])])
+    assert [name in r["name"] for r in rows] == [False, True], rows
