@@ -338,9 +338,10 @@ size_t workspace_bytes(const meft_shape& s) {
   return (s.flags & MEFT_FLAG_HOST_KV) ? HostKvWs(s, nullptr).bytes : compute_bytes(s);
 }
 
-// ---- host-resident keys/values: side stream, events, pinned read-back buffer (created on first use) ----
+// ---- host-resident keys/values: side streams, events, pinned read-back buffer (created on first use) ----
 struct HostKvState {
-  hipStream_t side = nullptr;
+  hipStream_t side = nullptr;   // K, V on their way in
+  hipStream_t back = nullptr;   // dV on its way out: on the stream of the copies in it would wait for a later layer's blocks
   hipEvent_t ev_entry = nullptr, ev_cnt = nullptr, ev_k = nullptr, ev_v = nullptr, ev_dv = nullptr, ev_out = nullptr;
   int32_t* host_cnt = nullptr;
   bool ready = false;
@@ -349,10 +350,12 @@ HostKvState g_hkv;
 
 bool hostkv_init() {
   if (g_hkv.ready) return true;
-  if (hipStreamCreateWithFlags(&g_hkv.side, hipStreamNonBlocking) != hipSuccess) return false;
+  hipStream_t* streams[2] = {&g_hkv.side, &g_hkv.back};
+  for (hipStream_t* st : streams)
+    if (!*st && hipStreamCreateWithFlags(st, hipStreamNonBlocking) != hipSuccess) return false;
   hipEvent_t* evs[6] = {&g_hkv.ev_entry, &g_hkv.ev_cnt, &g_hkv.ev_k, &g_hkv.ev_v, &g_hkv.ev_dv, &g_hkv.ev_out};
   for (hipEvent_t* e : evs)
-    if (hipEventCreateWithFlags(e, hipEventDisableTiming) != hipSuccess) return false;
+    if (!*e && hipEventCreateWithFlags(e, hipEventDisableTiming) != hipSuccess) return false;
   if (hipHostMalloc(reinterpret_cast<void**>(&g_hkv.host_cnt), (size_t)kMaxBlocks * sizeof(int32_t), hipHostMallocDefault) !=
       hipSuccess)
     return false;
@@ -957,7 +960,7 @@ static void launch_rows_to_host(const meft_shape& s, const int32_t* touched, con
 }
 
 // Backward on device-resident K, V, dK, dV.  wait_v / wait_k as in fwd_impl.  dV_host: not null where dV is staging for
-// that host matrix; its rows then leave on the side stream as soon as they are complete, under the rest of the backward
+// that host matrix; its rows then leave on a stream of their own as soon as they are complete, under the rest of the backward
 // (the caller waits for g_hkv.ev_out).
 static meft_status bwd_impl(const meft_shape& s, const void* h, const void* K, const void* V, const int32_t* idx,
                             const float* act, const void* dOut, void* dh, void* dK, void* dV, int32_t* touched,
@@ -1018,9 +1021,9 @@ static meft_status bwd_impl(const meft_shape& s, const void* h, const void* K, c
     };
     auto dv_to_host = [&]() -> bool {   // dV is complete in its staging
       if (small) launch_small_dvdk();
-      if (hipEventRecord(g_hkv.ev_dv, st) != hipSuccess || hipStreamWaitEvent(g_hkv.side, g_hkv.ev_dv, 0) != hipSuccess) return false;
-      launch_rows_to_host(s, touched, n_touched, dV, dV_host, g_hkv.side);
-      return hipEventRecord(g_hkv.ev_out, g_hkv.side) == hipSuccess;
+      if (hipEventRecord(g_hkv.ev_dv, st) != hipSuccess || hipStreamWaitEvent(g_hkv.back, g_hkv.ev_dv, 0) != hipSuccess) return false;
+      launch_rows_to_host(s, touched, n_touched, dV, dV_host, g_hkv.back);
+      return hipEventRecord(g_hkv.ev_out, g_hkv.back) == hipSuccess;
     };
     if (dV_host && !(small && wait_v) && !dv_to_host()) return MEFT_ERR_DEVICE;
     if (wait_v && hipStreamWaitEvent(st, wait_v, 0) != hipSuccess) return MEFT_ERR_DEVICE;
