@@ -959,13 +959,19 @@ static void launch_rows_to_host(const meft_shape& s, const int32_t* touched, con
               static_cast<const u32x4*>(src), static_cast<u32x4*>(dst), vec);
 }
 
-// Backward on device-resident K, V, dK, dV.  wait_v / wait_k as in fwd_impl.  dV_host: not null where dV is staging for
-// that host matrix; its rows then leave on a stream of their own as soon as they are complete, under the rest of the backward
-// (the caller waits for g_hkv.ev_out).
+// Where the rows of a dV in device staging go: dst, the host matrix (nullptr: dV is not staging), on `stream`.  On another
+// stream than the backward's they leave as soon as they are complete, under the rest of the backward, and the caller waits
+// for g_hkv.ev_out.
+struct HostRows {
+  void* dst = nullptr;
+  hipStream_t stream = nullptr;
+};
+
+// Backward on device-resident K, V, dK, dV.  wait_v / wait_k as in fwd_impl.
 static meft_status bwd_impl(const meft_shape& s, const void* h, const void* K, const void* V, const int32_t* idx,
                             const float* act, const void* dOut, void* dh, void* dK, void* dV, int32_t* touched,
                             int32_t* n_touched, const BwdWs& w, hipStream_t st, hipEvent_t wait_k,
-                            hipEvent_t wait_v, void* dV_host) {
+                            hipEvent_t wait_v, HostRows dV_rows) {
   const int P = s.T * s.top_k;
 
   if (use_dense(s)) {
@@ -1021,11 +1027,12 @@ static meft_status bwd_impl(const meft_shape& s, const void* h, const void* K, c
     };
     auto dv_to_host = [&]() -> bool {   // dV is complete in its staging
       if (small) launch_small_dvdk();
-      if (hipEventRecord(g_hkv.ev_dv, st) != hipSuccess || hipStreamWaitEvent(g_hkv.back, g_hkv.ev_dv, 0) != hipSuccess) return false;
-      launch_rows_to_host(s, touched, n_touched, dV, dV_host, g_hkv.back);
-      return hipEventRecord(g_hkv.ev_out, g_hkv.back) == hipSuccess;
+      const hipStream_t to = dV_rows.stream;
+      if (to != st && (hipEventRecord(g_hkv.ev_dv, st) != hipSuccess || hipStreamWaitEvent(to, g_hkv.ev_dv, 0) != hipSuccess)) return false;
+      launch_rows_to_host(s, touched, n_touched, dV, dV_rows.dst, to);
+      return to == st || hipEventRecord(g_hkv.ev_out, to) == hipSuccess;
     };
-    if (dV_host && !(small && wait_v) && !dv_to_host()) return MEFT_ERR_DEVICE;
+    if (dV_rows.dst && !(small && wait_v) && !dv_to_host()) return MEFT_ERR_DEVICE;
     if (wait_v && hipStreamWaitEvent(st, wait_v, 0) != hipSuccess) return MEFT_ERR_DEVICE;
     launch_tok<TokKCLarge<kTokMasked>, TokKCSmall<kTokMasked>>("dact_gemm", s, s.block_size, (uint64_t)s.T * s.d * 2, (uint64_t)s.N * s.d * 2, (uint64_t)n_ent * bsp * 2, [&](auto& pg) {
       pg.X = gg; pg.W = vv; pg.perm = w.perm; pg.tok_of_slot = w.tok_of_slot; pg.sched = sched;
@@ -1034,7 +1041,7 @@ static meft_status bwd_impl(const meft_shape& s, const void* h, const void* K, c
     }, st);
     if (small && wait_v) {
       launch_bwd_head(s, w.flag, w.chunk_cnt, touched, n_touched, &w, V, dOut, idx, act, st);
-      if (dV_host && !dv_to_host()) return MEFT_ERR_DEVICE;
+      if (dV_rows.dst && !dv_to_host()) return MEFT_ERR_DEVICE;
     }
     if (wait_k && hipStreamWaitEvent(st, wait_k, 0) != hipSuccess) return MEFT_ERR_DEVICE;
     if (dh) {
@@ -1069,10 +1076,7 @@ static meft_status bwd_impl(const meft_shape& s, const void* h, const void* K, c
                 w.totals, w.seg_off, w.pair_list, w.pair_sorted);
   if (s.dtype == MEFT_BF16) launch_seg_reduce<bf16_t>(s, w, act, h, dOut, dK, dV, st);
   else launch_seg_reduce<float>(s, w, act, h, dOut, dK, dV, st);
-  if (dV_host) {
-    launch_rows_to_host(s, touched, n_touched, dV, dV_host, st);
-    if (hipEventRecord(g_hkv.ev_out, st) != hipSuccess) return MEFT_ERR_DEVICE;
-  }
+  if (dV_rows.dst) launch_rows_to_host(s, touched, n_touched, dV, dV_rows.dst, st);   // complete with dK: nothing to gain
   return launch_status();
 }
 
@@ -1332,16 +1336,21 @@ meft_status meft_sparse_bwd(const meft_shape* shape, const void* h, const void* 
     return launch_status();
   }
   if (!(s.flags & MEFT_FLAG_HOST_KV))
-    return bwd_impl(s, h, K, V, idx, act, dOut, dh, dK, dV, touched, n_touched, w, st, nullptr, nullptr, nullptr);
+    return bwd_impl(s, h, K, V, idx, act, dOut, dh, dK, dV, touched, n_touched, w, st, nullptr, nullptr, HostRows{});
 
   // K, V, dK, dV in pinned host memory: fetch the blocks that hold a selected neuron (V first: the activation
   // gradient needs it before dh needs K), compute into device staging, then write the touched rows back.
   if (!hostkv_init()) return MEFT_ERR_DEVICE;
   HostKvWs hw(s, ws);
+  // Under capture everything stays on the caller's stream: a stream of the library's that joined a capture would stay part
+  // of it until it ends, and other calls' work on that stream would be recorded instead of run.
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  const bool early = use_dense(s) && hipStreamIsCapturing(st, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone;
+  const HostRows dV_rows{dV, early ? g_hkv.back : st};
   if (s.flags & MEFT_FLAG_KEEP_STAGED) {
     // the forward of this step left the blocks in use in the workspace, and its copies are ordered before
     // anything enqueued here (the forward made `st` wait for them)
-    rc = bwd_impl(s, h, hw.Kd, hw.Vd, idx, act, dOut, dh, hw.dKd, hw.dVd, touched, n_touched, w, st, nullptr, nullptr, dV);
+    rc = bwd_impl(s, h, hw.Kd, hw.Vd, idx, act, dOut, dh, hw.dKd, hw.dVd, touched, n_touched, w, st, nullptr, nullptr, dV_rows);
   } else {
   if (hipEventRecord(g_hkv.ev_entry, st) != hipSuccess || hipStreamWaitEvent(g_hkv.side, g_hkv.ev_entry, 0) != hipSuccess)
     return MEFT_ERR_DEVICE;
@@ -1353,12 +1362,12 @@ meft_status meft_sparse_bwd(const meft_shape* shape, const void* h, const void* 
               cnt_tmp);
   if ((rc = hostkv_fetch(s, cnt_tmp, V, hw.Vd, g_hkv.ev_v, K, hw.Kd, g_hkv.ev_k, st)) != MEFT_OK) return rc;
   rc = bwd_impl(s, h, hw.Kd, hw.Vd, idx, act, dOut, dh, hw.dKd, hw.dVd, touched, n_touched, w, st, g_hkv.ev_k,
-                g_hkv.ev_v, dV);
+                g_hkv.ev_v, dV_rows);
   }
-  if (rc != MEFT_OK) return rc;
-  launch_rows_to_host(s, touched, n_touched, hw.dKd, dK, st);
-  if (hipStreamWaitEvent(st, g_hkv.ev_out, 0) != hipSuccess) return MEFT_ERR_DEVICE;
-  return launch_status();
+  if (rc == MEFT_OK) launch_rows_to_host(s, touched, n_touched, hw.dKd, dK, st);
+  // (also after an error: what has been enqueued still reads the workspace and writes dV)
+  if (early && hipStreamWaitEvent(st, g_hkv.ev_out, 0) != hipSuccess) return MEFT_ERR_DEVICE;
+  return rc != MEFT_OK ? rc : launch_status();
 }
 
 meft_status meft_adam_rows(const meft_shape* shape, const meft_adam* hp, void* W, const void* G, float* m,

@@ -25,6 +25,9 @@ static int n_recs;
 static uint64_t next_handle = 0x1000;
 static int32_t counts_value = 1;   /* what a copy to the host delivers in every word */
 
+static int capturing;
+
+void rec_capture(int on) { capturing = on; }
 int rec_count(void) { return n_recs; }
 const rec_t* rec_at(int i) { return &recs[i]; }
 void rec_clear(void) { n_recs = 0; }
@@ -89,6 +92,7 @@ int hipStreamWaitEvent(void* stream, void* e, unsigned flags) {
   r->event = (uint64_t)(uintptr_t)e; r->stream = (uint64_t)(uintptr_t)stream;
   return 0;
 }
+int hipStreamIsCapturing(void* stream, int* status) { (void)stream; *status = capturing; return 0; }
 int hipHostMalloc(void** p, size_t bytes, unsigned flags) { (void)flags; *p = calloc(1, bytes); return *p ? 0 : 2; }
 int hipFuncSetAttribute(const void* f, int attr, int value) { (void)f; (void)attr; (void)value; return 0; }
 int hipGetDevice(int* d) { *d = 0; return 0; }

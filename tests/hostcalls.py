@@ -1,6 +1,7 @@
 """What libmeft asks of the HIP runtime, without a GPU: record([(shape, calls), ...]) makes the calls of the C ABI in a
 process where tests/hip_recorder.c stands in for the runtime, and returns the launches, copies, event records and stream
-waits of each entry, in order.  Addresses are made up; the library does not follow them on the host."""
+waits of each entry, in order.  The call names "capture" and "no_capture" set what the runtime says of the stream from then on.
+Addresses are made up; the library does not follow them on the host."""
 import ctypes
 import json
 import os
@@ -81,7 +82,11 @@ def _main(rec_path):
     for fields, calls in json.load(sys.stdin):
         s = _Shape(*fields)
         rec.rec_clear()
+        rec.rec_capture(0)
         for c in calls:
+            if c.endswith("capture"):
+                rec.rec_capture(int(c == "capture"))
+                continue
             rc = call(s, c)
             assert rc == 0, (fields, c, rc)
         rows = []

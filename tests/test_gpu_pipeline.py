@@ -101,3 +101,33 @@ def test_prestaged_without_a_stage_call_is_refused():
                            layer.ws, check=False)
     assert rc == B.MEFT_ERR_INVALID_ARG
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_captured_backward_on_kept_copies(dtype):
+    """The backward on the forward's kept copies does not block the host, so it can be recorded into a graph; every replay
+    gives the eager gradients, also after another layer's blocks have been fetched in between."""
+    import torch
+    t, other = _layers(2, dtype=dtype)
+    t = synth.Tensors(t.cfg.replace(keep_staged=True), t.h, t.Wg, t.K, t.V, t.dOut, t.bias, t.outlier_channels)
+    ref = P.run_gpu(t)
+    layer, layer2 = P.DeviceLayer(t), P.DeviceLayer(other)
+    layer2.route()
+    layer.fill_grad_sentinel()
+    layer.route()
+    layer.fwd()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        layer.bwd()
+    for rep in range(3):
+        layer2.fwd()
+        layer.dh.fill_(7.0)
+        layer.touched.fill_(-1)
+        layer.fill_grad_sentinel()
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        got = layer.results()
+        for n in ("dh", "dK_bits", "dV_bits", "touched"):
+            assert np.array_equal(ref[n], got[n]), (rep, n)

@@ -29,3 +29,13 @@ def test_gradients_do_not_queue_behind_blocks_on_their_way_in(kw, keep):
     if side:
         last = max(i for i, r in enumerate(rows) if r["what"] == "record" and r["stream"] == side[0])
         assert any(r["what"] == "wait" and r["stream"] == STREAM and r["event"] == rows[last]["event"] for r in rows[last:])
+
+
+@pytest.mark.parametrize("kw", [DENSE, PER_PAIR], ids=["dense", "per_pair"])
+def test_a_captured_backward_keeps_to_its_stream(kw):
+    # the forward of the step ran eagerly; its kept copies make the backward capturable
+    before = len(_calls(kw, HOST_KV | KEEP_STAGED, ["fwd"]))
+    rows = _calls(kw, HOST_KV | KEEP_STAGED, ["fwd", "capture", "bwd", "no_capture"])[before:]
+    assert sum("rows_to_host" in r["name"] for r in rows) == 2
+    assert {r["stream"] for r in rows} == {STREAM}, rows
+    assert not [r for r in rows if r["what"] == "copy"]
