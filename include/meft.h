@@ -83,7 +83,7 @@ typedef enum { MEFT_F32 = 0, MEFT_BF16 = 1 } meft_dtype;
  * was routed to, the backward the blocks that hold a selected neuron, with hipMemcpyAsync on a stream of the
  * library's own, overlapped with the dispatch kernels (K) and with scoring and selection (V); the backward
  * computes dK, dV into device staging and a kernel then writes only the touched rows over the host link (on the matrix-core
- * kernels dV's rows leave on a second stream of the library's, under the rest of the backward; `stream` waits for them).
+ * kernels dV's rows leave on a stream of the library's, under the rest of the backward; `stream` waits for them).
  * The workspace grows by four [N, d] matrices.  Differences from the conventions below, for these calls only:
  * the host blocks once per call until the routing result (which blocks are in use) is known; the library
  * creates two side streams, six events and a small pinned buffer on first use and keeps them; two such calls

@@ -1,6 +1,6 @@
 """Which stream the work of host-resident keys and values goes to, from the calls that the library makes of the HIP runtime
-(tests/hostcalls.py): the copies in on one stream, the gradient rows that leave early on another, so that a later layer's
-blocks and this layer's gradients use the two directions of the link at once."""
+(tests/hostcalls.py): while a later layer's blocks are on their way in, the gradient rows that leave early go on another stream,
+so that both use the link's two directions at once."""
 import pytest
 
 from tests.hostcalls import STREAM, record, shape
