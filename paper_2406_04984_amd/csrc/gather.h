@@ -72,18 +72,22 @@ __global__ __launch_bounds__(256) void gather_fwd_kernel(const T* __restrict__ V
 // pairs w, w + 4, ..., holds its V and K rows in flight together (a pair is one trip to memory, where a workgroup per
 // row has to finish the dot products before it asks for K), and keeps its own sum of dh, added in wave order at the end.
 // No barrier in the loop.  Bound by the rows' reads: at 2048 tokens x 256 pairs x 4096 bf16 (8.6 GB) 1451 -> 1130 us.
-// Also clears clear[0 .. n_clear) for the kernels that follow.  dh may be null.
+// Also clears clear[0 .. n_clear) for the kernels that follow.  dh may be null.  Grid: tokens along x, then y (a launch
+// takes fewer than 2^32 threads along x).
 template <typename T, int NV>
 __global__ __launch_bounds__(256, 2) void gather_bwd_wave_kernel(const T* __restrict__ K, const T* __restrict__ V,
                                                                  const T* __restrict__ dOut,
                                                                  const int32_t* __restrict__ idx,
-                                                                 const float* __restrict__ act, int d, int k, int N,
-                                                                 float* __restrict__ ds, T* __restrict__ dh,
+                                                                 const float* __restrict__ act, int n_tok, int d, int k,
+                                                                 int N, float* __restrict__ ds, T* __restrict__ dh,
                                                                  int32_t* __restrict__ clear, size_t n_clear) {
   __shared__ float s_red[3][NV * 512];
-  const int t = blockIdx.x, lane = threadIdx.x & 63;
+  const size_t tok = (size_t)blockIdx.y * gridDim.x + blockIdx.x;
+  const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  for (size_t i = (size_t)t * 256 + threadIdx.x; i < n_clear; i += (size_t)gridDim.x * 256) clear[i] = 0;
+  for (size_t i = tok * 256 + threadIdx.x; i < n_clear; i += (size_t)gridDim.x * gridDim.y * 256) clear[i] = 0;
+  if (tok >= (size_t)n_tok) return;
+  const int t = (int)tok;
   float g[NV][8], acc[NV][8];
 #pragma unroll
   for (int v = 0; v < NV; ++v) {

@@ -519,8 +519,8 @@ void launch_gather_bwd(const meft_shape& s, const void* K, const void* V, const 
   const T *k = static_cast<const T*>(K), *v = static_cast<const T*>(V), *g = static_cast<const T*>(dOut);
   T* o = static_cast<T*>(dh);
   // a wave per pair holds dOut's and dh's rows in fp32 and one row each of V and K: up to 4096 bf16 or 2048 fp32 columns
-  const int cols = (s.d + 511) / 512;
-#define GW(NV) MEFT_LAUNCH("gather_bwd", (gather_bwd_wave_kernel<T, NV>), dim3(s.T), dim3(256), 0, st, k, v, g, idx, act, s.d, s.top_k, s.N, ds, o, clear, n_clear)
+  const int cols = (s.d + 511) / 512, tx = s.T < (1 << 23) ? s.T : 1 << 23;
+#define GW(NV) MEFT_LAUNCH("gather_bwd", (gather_bwd_wave_kernel<T, NV>), dim3(tx, (s.T + tx - 1) / tx), dim3(256), 0, st, k, v, g, idx, act, s.T, s.d, s.top_k, s.N, ds, o, clear, n_clear)
   if (cols <= 1) { GW(1); return; }
   if (cols <= 2) { GW(2); return; }
   if (cols <= 4) { GW(4); return; }
@@ -544,8 +544,8 @@ void launch_seg_reduce(const meft_shape& s, const BwdWs& w, const float* act, co
   const int64_t P = (int64_t)s.T * s.top_k, n_seg = s.N < P ? s.N : P;
   // four chunks per workgroup: at most one chunk per touched neuron plus one per kSegChunk pairs
   const int64_t groups = (n_seg + P / kSegChunk + 3) / 4;
-  MEFT_LAUNCH("seg_reduce", seg_reduce_kernel<T>, dim3((unsigned)(groups * ((s.d + 511) / 512))), dim3(256), 0, st, w.work,
-              w.totals, w.pair_list, w.pair_sorted, act, w.ds, hh, g, s.d, s.top_k, (int)groups, pk, pv, w.seg_part);
+  MEFT_LAUNCH("seg_reduce", seg_reduce_kernel<T>, dim3((unsigned)groups, (s.d + 511) / 512), dim3(256), 0, st, w.work,
+              w.totals, w.pair_list, w.pair_sorted, act, w.ds, hh, g, s.d, s.top_k, pk, pv, w.seg_part);
   if (P > kSegChunk) {
     const int finish = (int)(P / kSegChunk < 4096 ? P / kSegChunk + 1 : 4096);
     MEFT_LAUNCH("seg_finish", seg_finish_kernel<T>, dim3(finish), dim3(256), 0, st, w.multi, w.totals, w.seg_part, s.d, pk, pv);

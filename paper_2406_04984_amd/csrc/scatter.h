@@ -256,7 +256,7 @@ __global__ __launch_bounds__(256) void seg_sort_kernel(const int4* __restrict__ 
 
 // One chunk of a touched neuron's pairs, summed in ascending pair order (which is ascending token order): dV[j,:] = sum
 // act * dOut[t,:], dK[j,:] = sum ds * h[t,:].  A wave takes (chunk, 512 columns), a workgroup four chunks of the same
-// columns.  The columns are the slow launch index: while a slice of 512 columns is worked through, the slices of h and
+// columns.  The columns are the slow launch index (y): while a slice of 512 columns is worked through, the slices of h and
 // dOut (2 MB each at 2048 bf16 tokens) stay in the L2 of every XCD, and the row reads, of which there is one pair per
 // (token, neuron) pair, no longer go to memory.  A neuron of one chunk gets its rows written here; the chunks of a longer
 // segment leave their fp32 sums in `part` ([chunk][dV | dK][d]), which seg_finish_kernel adds in chunk order.
@@ -268,12 +268,11 @@ __global__ __launch_bounds__(256) void seg_reduce_kernel(const SegWork* __restri
                                                          const int32_t* __restrict__ pair_sorted,
                                                          const float* __restrict__ act, const float* __restrict__ ds,
                                                          const T* __restrict__ h, const T* __restrict__ dOut, int d, int k,
-                                                         int n_groups, T* __restrict__ dK, T* __restrict__ dV,
-                                                         float* __restrict__ part) {
+                                                         T* __restrict__ dK, T* __restrict__ dV, float* __restrict__ part) {
   __shared__ int s_p[4][kSegChunk];
   __shared__ float2 s_c[4][kSegChunk];   // act, ds
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int slice = blockIdx.x / n_groups, wk = (blockIdx.x - slice * n_groups) * 4 + wave;
+  const int slice = blockIdx.y, wk = blockIdx.x * 4 + wave;
   if (wk >= totals[1]) return;   // (no workgroup barrier below: every wave keeps to its own part of LDS)
   const SegWork x = work[wk];
   int* sp = s_p[wave];

@@ -56,3 +56,28 @@ def test_an_id_repeated_within_its_tokens():
     act, dOut = layer.act.double(), layer.dOut.double()
     want = act[:, 10:].sum(1) @ dOut + ((layer.idx[:, :10] == 79) * act[:, :10]).sum(1) @ dOut
     assert torch.allclose(layer.dV[79].double(), want, rtol=1e-4, atol=1e-4 * float(want.abs().max()))
+
+
+def test_more_tokens_than_a_launch_has_along_x():
+    """2^23 + 1 tokens of whole numbers (every sum is exact): the tokens go on along y."""
+    import torch
+    from paper_2406_04984_amd import binding as B
+    T, d, nb, bs = (1 << 23) + 1, 8, 128, 255
+    N = nb * bs
+    s = B.make_shape(T, d, nb, bs, 1, 1, "f32")
+    gen = torch.Generator(device="cuda").manual_seed(7300)
+    h, dOut, K, V = (torch.randint(-3, 4, (n, d), generator=gen, device="cuda").float() for n in (T, T, N, N))
+    idx = torch.randint(0, N, (T, 1), generator=gen, device="cuda", dtype=torch.int32)
+    act = torch.randint(0, 3, (T, 1), generator=gen, device="cuda").float()
+    dh, dK, dV = torch.full((T, d), 7.0, device="cuda"), torch.zeros((N, d), device="cuda"), torch.zeros((N, d), device="cuda")
+    touched, n = torch.zeros((N,), dtype=torch.int32, device="cuda"), torch.zeros((1,), dtype=torch.int32, device="cuda")
+    ws = torch.empty((B.meft_workspace_bytes(s),), dtype=torch.uint8, device="cuda")
+    B.meft_sparse_bwd(s, h, K, V, idx, act, dOut, dh, dK, dV, touched, n, ws)
+    torch.cuda.synchronize()
+    j = idx[:, 0].long()
+    ds = (dOut * V[j]).sum(1, keepdim=True) * (act > 0)
+    assert torch.equal(dh, ds * K[j])
+    assert torch.equal(dV, torch.zeros_like(dV).index_add_(0, j, act * dOut))
+    assert torch.equal(dK, torch.zeros_like(dK).index_add_(0, j, ds * h))
+    ids = torch.unique(j)
+    assert int(n) == len(ids) and torch.equal(touched[:len(ids)].long(), ids)

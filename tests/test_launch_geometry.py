@@ -16,6 +16,8 @@ CASES = [
     (shape(70_000, 128, 16384, 8, 3, 5, "f32"), ["route", "fwd", "bwd"]),
     (shape(500, 64, 1, 4_194_304, 1, 4096, "bf16"), ["route", "fwd", "bwd"]),
     (shape(100_000, 64, 4, 512, 2, 64, "bf16"), ["union_fwd", "union_bwd"]),
+    (shape(20_000_000, 8, 8, 16, 1, 1, "f32"), ["bwd"]),
+    (shape(16_384, 2056, 16_384, 860, 1, 860, "bf16"), ["route", "fwd", "bwd"]),
 ]
 
 
