@@ -26,7 +26,7 @@
 namespace meft {
 
 constexpr int kDispMaxBlocks = 1024;    // LDS: 16 waves x n_blocks counters
-constexpr int kDispMaxChunks = 1024;
+constexpr int kDispMaxEntries = 1 << 20;   // at most 2045 chunks (of 513 entries at top_e 513)
 constexpr int kDispScanBlocks = 512;    // dispatch_place adds up the chunk counts itself up to this many blocks
 constexpr int kDispScanMax = 32768;     // and this many counts
 

@@ -198,13 +198,13 @@ struct RouteWs {
   }
 };
 
-// the dispatch over chunks of whole tokens, at most 1024 entries each (dispatch.h): up to 1024 blocks and 1024 chunks
+// the dispatch over chunks of whole tokens, at most 1024 entries each (dispatch.h): up to 1024 blocks and 2^20 entries
 int disp_chunk_entries(const meft_shape& s) { return 1024 / s.top_e * s.top_e; }   // n_blocks <= 1024 only
 int disp_chunks(const meft_shape& s) {
   const int epc = disp_chunk_entries(s);
   return (int)(((int64_t)s.T * s.top_e + epc - 1) / epc);
 }
-bool fast_dispatch(const meft_shape& s) { return s.n_blocks <= kDispMaxBlocks && disp_chunks(s) <= kDispMaxChunks; }
+bool fast_dispatch(const meft_shape& s) { return s.n_blocks <= kDispMaxBlocks && (int64_t)s.T * s.top_e <= kDispMaxEntries; }
 
 // index structures of the (token, block) dispatch, common to forward and backward
 struct DispatchWs {

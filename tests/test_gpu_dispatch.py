@@ -16,6 +16,7 @@ CASES = [
     dict(T=2000, d=64, n_blocks=31, block_size=16, top_e=1, top_k=4),                     # groups around 64 rows
     dict(T=300, d=64, n_blocks=600, block_size=16, top_e=4, top_k=8),                     # more than 512 blocks
     dict(T=9000, d=64, n_blocks=500, block_size=16, top_e=9, top_k=12, zipf_s=0.8),       # 80 chunks x 500 blocks
+    dict(T=2044, d=64, n_blocks=1024, block_size=16, top_e=513, top_k=130),               # 2044 chunks, just under 2^20 entries
     dict(T=300, d=64, n_blocks=1030, block_size=16, top_e=2, top_k=8),                    # the general path
     dict(T=1500, d=64, n_blocks=140, block_size=1000, top_e=2, top_k=64),                 # 140000 neurons
 ]

@@ -63,3 +63,13 @@ def test_large_router_contractions_run_on_tiles():
 def test_selection_of_blocks(T, n_blocks, top_e, name):
     rows, = record([(shape(T, 64, n_blocks, 64, top_e, 16, "bf16"), ["route"])])
     assert [name in r["name"] for r in rows] == [False, True], rows
+
+
+# Chunks hold whole tokens (1023 entries of 1024 at top_e 3), and the limit is on the entries: counted in chunks, the last
+# thousand below 2^20 entries fell to kernels that scan all entries once per block (2338 instead of 1560 us at 349400 x 3).
+@pytest.mark.parametrize("T, n_blocks, top_e, chunked", [
+    (349_525, 64, 3, True), (349_526, 64, 3, False), (1_048_576, 8, 1, True), (1_048_577, 8, 1, False),
+    (2044, 1024, 513, True), (1_048_576 // 513 + 1, 1024, 513, False)])
+def test_dispatch_in_chunks_up_to_its_limit(T, n_blocks, top_e, chunked):
+    rows, = record([(shape(T, 64, n_blocks, 16, top_e, 8 * top_e, "bf16"), ["fwd"])])
+    assert any("dispatch_place" in r["name"] for r in rows) == chunked, rows
