@@ -400,7 +400,7 @@ __global__ __launch_bounds__(256) void act_rows_kernel(const int32_t* __restrict
 }
 
 // out[t, :] or dh[t, :] of every token (token_rows_body); with dvdk workers in front (backward): the dV and dK rows of the
-// small groups, which do not depend on them.  Dynamic LDS: k pairs.
+// small groups, which do not depend on them.  Dynamic LDS: min(k, kTokenRowsPairs) pairs.
 struct SmallDvdk {
   int n_wg, nx, ny;      // workgroups in front of the tokens' (0: none), nx x ny workers
   const bf16_t *h, *dOut;

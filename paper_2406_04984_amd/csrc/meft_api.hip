@@ -709,14 +709,7 @@ void launch_token_rows(const char* name, const meft_shape& s, const uint16_t* pa
                        const int32_t* idx, const float* coef, void* out, const SmallDvdk& dv, hipStream_t st) {
   const TokenRows a{part, w.sblk, w.slot_of_ent, idx, coef, static_cast<const bf16_t*>(W), s.d, s.top_e, s.top_k, s.N,
                     s.block_size, static_cast<bf16_t*>(out)};
-  const size_t lds = small_rows_of(s) ? (size_t)s.top_k * sizeof(int2) : 0;   // up to 96 KB
-  static std::once_flag configured;
-  std::call_once(configured, [] {
-    const void* k[] = {reinterpret_cast<const void*>(&token_rows_kernel<1, true>), reinterpret_cast<const void*>(&token_rows_kernel<1, false>),
-                       reinterpret_cast<const void*>(&token_rows_kernel<2, false>), reinterpret_cast<const void*>(&token_rows_kernel<4, false>),
-                       reinterpret_cast<const void*>(&token_rows_kernel<8, false>)};
-    for (const void* f : k) (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsC * (int)sizeof(int2));
-  });
+  const size_t lds = small_rows_of(s) ? (size_t)(s.top_k < kTokenRowsPairs ? s.top_k : kTokenRowsPairs) * sizeof(int2) : 0;
   const int chunks = (s.d + kSmallCols - 1) / kSmallCols;
   // few tokens: a workgroup per 512 columns, so that small groups, whose pairs are a chain of row reads, get more waves
   if (s.T * chunks <= 16 * kPersistentWgs) {

@@ -110,8 +110,10 @@ __global__ __launch_bounds__(1024) void small_lists_kernel(const int32_t* __rest
 // The rows of one token: row[t, :] = sum over its entries of large groups of part[slot, :] (bf16), plus sum over its
 // pairs of small groups of coef[t, p] * W[j, :] (W = V, coef = act: out; W = K, coef = ds: dh); fp32 sums, large groups in
 // ascending block order first, then the pairs in list order.  One workgroup per token, thread tid owns the columns
-// (tid + v * blockDim.x) * 8.  s_list: k pairs, s_blk: kTokenRowsBlocks ints.
-constexpr int kTokenRowsBlocks = 64;
+// (tid + v * blockDim.x) * 8.  s_list: min(k, kTokenRowsPairs) pairs, s_blk: kTokenRowsBlocks ints.  The pairs are listed
+// kTokenRowsPairs positions at a time: a list of all of a large top_k (64 KB at 8192) leaves a compute unit too few
+// workgroups for what is otherwise a stream (out rows of 4096 tokens x 8 entries x 4096: 61 us without the list, 104 with).
+constexpr int kTokenRowsBlocks = 64, kTokenRowsPairs = 1024;
 
 struct TokenRows {
   const uint16_t* part;
@@ -122,21 +124,27 @@ struct TokenRows {
   bf16_t* out;
 };
 
-// the token's pairs of small groups, ascending, into s_list: neuron, coefficient
-__device__ __forceinline__ int collect_small_pairs(const TokenRows& a, int t, int2* s_list, int* s_blk, int* s_w) {
-  const int32_t* it = a.idx + (size_t)t * a.k;
-  const float* ct = a.coef + (size_t)t * a.k;
-  const int nb = min(a.e, kTokenRowsBlocks);
-  for (int q = threadIdx.x; q < nb; q += blockDim.x)
+// the token's blocks whose groups are small, into s_blk
+__device__ __forceinline__ void collect_small_blocks(const TokenRows& a, int t, int* s_blk) {
+  for (int q = threadIdx.x; q < min(a.e, kTokenRowsBlocks); q += blockDim.x)
     s_blk[q] = a.slot_of_ent[(size_t)t * a.e + q] < 0 ? a.sblk[(size_t)t * a.e + q] : -1;
   __syncthreads();
+}
+
+// the token's pairs of small groups among its positions first .. first + kTokenRowsPairs - 1, ascending, into s_list: neuron,
+// coefficient.  (The first scan's barriers keep the list until everyone has read the one before.)
+__device__ __forceinline__ int collect_small_pairs(const TokenRows& a, int t, int first, int2* s_list, const int* s_blk,
+                                                   int* s_w) {
+  const int32_t* it = a.idx + (size_t)t * a.k;
+  const float* ct = a.coef + (size_t)t * a.k;
+  const int nb = min(a.e, kTokenRowsBlocks), end = min(a.k, first + kTokenRowsPairs);
   int n = 0;
-  for (int p0 = 0; p0 < a.k; p0 += blockDim.x) {
+  for (int p0 = first; p0 < end; p0 += blockDim.x) {
     const int p = p0 + (int)threadIdx.x;
     bool hit = false;
     int j = 0;
     float cf = 0.f;
-    if (p < a.k) {
+    if (p < end) {
       j = clampi(it[p], 0, a.N - 1);
       cf = ct[p];
       const int b = j / a.bs;
@@ -179,26 +187,29 @@ __device__ __forceinline__ void token_rows_body(const TokenRows& a, int t, int2*
     }
   }
   if (small) {   // the same in every thread
-    const int n = collect_small_pairs(a, t, s_list, s_blk, s_w);
+    collect_small_blocks(a, t, s_blk);
     constexpr int U = NV == 1 ? 16 : NV == 2 ? 8 : NV == 4 ? 4 : 2;   // rows in flight
-    for (int q0 = 0; q0 < n; q0 += U) {
-      u32x4 x[U][NV];
+    for (int p0 = 0; p0 < a.k; p0 += kTokenRowsPairs) {
+      const int n = collect_small_pairs(a, t, p0, s_list, s_blk, s_w);
+      for (int q0 = 0; q0 < n; q0 += U) {
+        u32x4 x[U][NV];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const bf16_t* row = a.W + (size_t)s_list[min(q0 + u, n - 1)].x * d;
+        for (int u = 0; u < U; ++u) {
+          const bf16_t* row = a.W + (size_t)s_list[min(q0 + u, n - 1)].x * d;
 #pragma unroll
-        for (int v = 0; v < NV; ++v) {
-          const int col = (tid + v * nthr) * 8;
-          if (col < d) x[u][v] = *reinterpret_cast<const u32x4*>(row + col);
+          for (int v = 0; v < NV; ++v) {
+            const int col = (tid + v * nthr) * 8;
+            if (col < d) x[u][v] = *reinterpret_cast<const u32x4*>(row + col);
+          }
         }
-      }
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        if (q0 + u < n) {
-          const float cf = __int_as_float(s_list[q0 + u].y);
+        for (int u = 0; u < U; ++u) {
+          if (q0 + u < n) {
+            const float cf = __int_as_float(s_list[q0 + u].y);
 #pragma unroll
-          for (int v = 0; v < NV; ++v)
-            if ((tid + v * nthr) * 8 < d) fma8_bf16(cf, x[u][v], acc[v]);
+            for (int v = 0; v < NV; ++v)
+              if ((tid + v * nthr) * 8 < d) fma8_bf16(cf, x[u][v], acc[v]);
+          }
         }
       }
     }
@@ -233,16 +244,21 @@ __device__ __forceinline__ void token_rows_split_body(const TokenRows& a, int t,
     }
   }
   if (small) {
-    const int n = collect_small_pairs(a, t, s_list, s_blk, s_w);
+    collect_small_blocks(a, t, s_blk);
     constexpr int U = 8;
-    for (int q0 = wave; q0 < n && live; q0 += 4 * U) {
-      u32x4 x[U];
+    int before = 0;   // pairs of the lists before: pair number i of all goes to wave i % 4
+    for (int p0 = 0; p0 < a.k; p0 += kTokenRowsPairs) {
+      const int n = collect_small_pairs(a, t, p0, s_list, s_blk, s_w);
+      for (int q0 = (wave - before) & 3; q0 < n && live; q0 += 4 * U) {
+        u32x4 x[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u)
-        x[u] = *reinterpret_cast<const u32x4*>(a.W + (size_t)s_list[min(q0 + 4 * u, n - 1)].x * d + col);
+        for (int u = 0; u < U; ++u)
+          x[u] = *reinterpret_cast<const u32x4*>(a.W + (size_t)s_list[min(q0 + 4 * u, n - 1)].x * d + col);
 #pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (q0 + 4 * u < n) fma8_bf16(__int_as_float(s_list[q0 + 4 * u].y), x[u], acc);
+        for (int u = 0; u < U; ++u)
+          if (q0 + 4 * u < n) fma8_bf16(__int_as_float(s_list[q0 + 4 * u].y), x[u], acc);
+      }
+      before += n;
     }
   }
   if (wave > 0) Vec8<float>::store(&s_red[wave - 1][lane * 8], acc);

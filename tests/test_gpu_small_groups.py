@@ -103,3 +103,13 @@ def test_backward_without_dh_leaves_it_alone():
     for n in ("idx", "act", "out", "dK_bits", "dV_bits", "touched"):
         assert np.array_equal(ref[n], got[n]), n
     assert bool((layer.dh == 7.0).all())
+
+
+@pytest.mark.parametrize("T, d", [(200, 1024), (4100, 64)], ids=["columns_shared", "token_per_workgroup"])
+def test_lists_of_pairs_in_several_pieces(T, d):
+    # 1500 of 3000 candidates: a token's pairs of small groups (at most two tokens) are listed 1024 positions at a time
+    cfg = synth.small_case(T=T, d=d, n_blocks=60, block_size=1000, top_e=3, top_k=1500, dtype="bf16", seed=1406, zipf_s=2.5,
+                           reuse_fwd=True)
+    g = _check(synth.make_inputs(cfg))
+    sizes = np.bincount(g["block_idx"].ravel(), minlength=cfg.n_blocks)
+    assert ((sizes > 0) & (sizes <= 2)).sum() >= 2, sizes

@@ -73,3 +73,10 @@ def test_selection_of_blocks(T, n_blocks, top_e, name):
 def test_dispatch_in_chunks_up_to_its_limit(T, n_blocks, top_e, chunked):
     rows, = record([(shape(T, 64, n_blocks, 16, top_e, 8 * top_e, "bf16"), ["fwd"])])
     assert any("dispatch_place" in r["name"] for r in rows) == chunked, rows
+
+
+def test_token_rows_keep_their_lists_short():
+    # a list of all of top_k in LDS: 104 us for the rows that took 61 without (4096 tokens x 8 entries x 4096, top_k 8192)
+    rows, = record([(shape(4096, 4096, 16, 1024, 8, 8192, "bf16"), ["fwd", "bwd"])])
+    rows = [r for r in rows if "token_rows" in r["name"]]
+    assert len(rows) == 2 and all(r["lds"] <= 8192 for r in rows), rows
