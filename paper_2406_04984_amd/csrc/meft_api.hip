@@ -703,6 +703,19 @@ void launch_dispatch(const meft_shape& s, const DispatchWs& w, const int32_t* bl
 // in one pass, few enough that a launch on a batch without small groups costs next to nothing.
 constexpr int kSmallEntGrid = 256, kSmallGrpGrid = 128;
 
+// few tokens: a workgroup per (token, 512 columns), so that small groups, whose pairs are a chain of row reads, get more waves
+bool rows_split(const meft_shape& s) { return s.T * ((s.d + kSmallCols - 1) / kSmallCols) <= 16 * kPersistentWgs; }
+
+// Whether the dV / dK rows of the small groups share the launch of the dh rows.  That launch then has four waves per
+// workgroup, of which a token's short row uses as many as it has 512 columns; an idle one costs 0.2 to 0.3 ns, the launch that
+// is saved 4 to 6 us.  One launch / two, us: 37 / 28 at 32768 tokens x 512, 166 / 97 at 100000 x 256, 393 / 166 at 300000 x
+// 64; 20.8 for one at 8192 x 1024, where the rows alone take 18.
+bool dvdk_beside_rows(const meft_shape& s) {
+  int nthr, nv;
+  row_launch(s.d, nthr, nv);
+  return rows_split(s) || (int64_t)s.T * (4 - nthr / 64) <= 16384;
+}
+
 // The tokens' rows of out (W = V, coef = act) or dh (W = K, coef = ds) from the entries' partial rows and the pairs of
 // the small groups; `dv`: the dV / dK work of the small groups, or none.
 void launch_token_rows(const char* name, const meft_shape& s, const uint16_t* part, const DispatchWs& w, const void* W,
@@ -711,8 +724,7 @@ void launch_token_rows(const char* name, const meft_shape& s, const uint16_t* pa
                     s.block_size, static_cast<bf16_t*>(out)};
   const size_t lds = small_rows_of(s) ? (size_t)(s.top_k < kTokenRowsPairs ? s.top_k : kTokenRowsPairs) * sizeof(int2) : 0;
   const int chunks = (s.d + kSmallCols - 1) / kSmallCols;
-  // few tokens: a workgroup per 512 columns, so that small groups, whose pairs are a chain of row reads, get more waves
-  if (s.T * chunks <= 16 * kPersistentWgs) {
+  if (rows_split(s)) {
     MEFT_LAUNCH(name, (token_rows_kernel<1, true>), dim3(dv.n_wg + s.T * chunks), dim3(256), lds, st, a, dv);
     return;
   }
@@ -1051,6 +1063,7 @@ static meft_status bwd_impl(const meft_shape& s, const void* h, const void* K, c
         ph.A = w.DS; ph.W = kk; ph.sched = sched; ph.bs = s.block_size; ph.bsp = bsp;
         ph.d = s.d; ph.part = w.part; ph.big_only = big_only;
       }, st);
+      if (dv.n_wg && !dvdk_beside_rows(s)) launch_small_dvdk();
       launch_token_rows("dh_rows", s, w.part, w, K, idx, w.ds32, dh, dv, st);
     } else if (dv.n_wg) {
       launch_small_dvdk();

@@ -80,3 +80,13 @@ def test_token_rows_keep_their_lists_short():
     rows, = record([(shape(4096, 4096, 16, 1024, 8, 8192, "bf16"), ["fwd", "bwd"])])
     rows = [r for r in rows if "token_rows" in r["name"]]
     assert len(rows) == 2 and all(r["lds"] <= 8192 for r in rows), rows
+
+
+# Gradient rows of small groups in the launch of the dh rows leave most of its waves idle where rows are short and many.
+@pytest.mark.parametrize("T, d, own", [(300_000, 64, True), (32_768, 512, True), (8192, 1024, False), (8193, 1024, True),
+                                       (8192, 4096, False), (2048, 512, False)])
+def test_gradient_rows_of_small_groups_share_a_launch(T, d, own):
+    rows, = record([(shape(T, d, 64, 16, 2, 8, "bf16"), ["bwd"])])
+    rows = [r for r in rows if "token_rows" in r["name"] or "small_dvdk" in r["name"]]
+    assert any("small_dvdk_kernel" in r["name"] for r in rows) == own, rows
+    assert not own or rows[-1]["grid"][0] == T, rows
