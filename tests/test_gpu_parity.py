@@ -128,10 +128,11 @@ def test_selection_larger_than_one_output_staging_round(P, dtype):
     _case(P, T=21, d=64, n_blocks=5, block_size=700, top_e=3, top_k=2049, dtype=dtype, seed=212)    # C = 2100
 
 
-def test_tokens_whose_scores_are_all_equal(P):
+@pytest.mark.parametrize("T", [48, 300], ids=["few_tokens", "block_dense"])
+def test_tokens_whose_scores_are_all_equal(P, T):
     """Zero rows of h give all-zero scores: every digit of every key is the same (the histogram passes see one bin),
     the first top_k candidates are selected and contribute nothing."""
-    cfg = synth.small_case(T=48, d=64, n_blocks=6, block_size=64, top_e=2, top_k=30, dtype="bf16", seed=213)
+    cfg = synth.small_case(T=T, d=64, n_blocks=6, block_size=64, top_e=2, top_k=30, dtype="bf16", seed=213)
     t = synth.make_inputs(cfg)
     t.h[::3] = 0.0
     from oracle import oracle
@@ -201,9 +202,10 @@ def test_empty_batch(P):
     assert int(nt.item()) == 0
 
 
-def test_exact_ties_go_to_the_lower_index(P):
+@pytest.mark.parametrize("T", [64, 200], ids=["few_tokens", "block_dense"])
+def test_exact_ties_go_to_the_lower_index(P, T):
     """Duplicated router rows and duplicated keys give exactly equal scores on both sides."""
-    cfg = synth.small_case(T=64, d=64, n_blocks=8, block_size=32, top_e=3, top_k=20, dtype="bf16", seed=401)
+    cfg = synth.small_case(T=T, d=64, n_blocks=8, block_size=32, top_e=3, top_k=20, dtype="bf16", seed=401)
     t = synth.make_inputs(cfg)
     t.Wg[5] = t.Wg[2]
     t.Wg[7] = t.Wg[2]

@@ -71,10 +71,12 @@ def test_group_sizes_around_the_limit_three_blocks_per_token(reuse):
     assert (sizes[sizes > 0] <= 8).sum() >= 3 and (sizes > 8).sum() >= 3, sizes
 
 
-def test_every_group_is_small():
+@pytest.mark.parametrize("T, n_blocks, reuse", [(96, 40, True), (300, 200, True), (300, 200, False)],
+                         ids=["few_tokens", "reuse_fwd", "rebuild"])
+def test_every_group_is_small(T, n_blocks, reuse):
     # more blocks than tokens per block: no group reaches the matrix cores after the selection
-    cfg = synth.small_case(T=96, d=128, n_blocks=40, block_size=32, top_e=2, top_k=4, dtype="bf16", seed=1403,
-                           reuse_fwd=True)
+    cfg = synth.small_case(T=T, d=128, n_blocks=n_blocks, block_size=32, top_e=2, top_k=4, dtype="bf16", seed=1403,
+                           reuse_fwd=reuse)
     g = _check(synth.make_inputs(cfg))
     assert np.bincount(g["block_idx"].ravel(), minlength=cfg.n_blocks).max() <= 16
 

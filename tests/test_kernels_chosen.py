@@ -1,0 +1,43 @@
+"""That the GPU tests of a kernel reach it: which kernels their shapes launch, from the calls that the library makes of the HIP
+runtime (tests/hostcalls.py)."""
+import pytest
+
+from tests.hostcalls import record, shape
+from tests.test_gpu_select_bound import CASES
+
+
+def _names(calls, flags=0, **kw):
+    rows, = record([(shape(flags=flags, **kw), calls)])
+    return [r["name"] for r in rows if r["what"] == "launch"]
+
+
+def _has(names, kernel):
+    return any(kernel in n for n in names)
+
+
+def test_selection_of_few_out_of_many():
+    kernels = ("few_out", "select_reg", "select_bound", "select_big")
+    got = record([(shape(**kw), ["fwd"]) for _, kw in CASES])
+    for (kernel, kw), rows in zip(CASES, got):
+        names = [r["name"] for r in rows]
+        assert [k for k in kernels if _has(names, k)] == [kernel], (kw, names)
+
+
+@pytest.mark.parametrize("N, T, kernel", [(5000, 6, "few_out"), (5000, 8, "few_out"), (5000, 40, "select_bound"),
+                                          (30001, 8, "select_bound"), (20000, 6, "select_bound")])
+def test_equal_keys_and_scores_that_are_no_numbers(N, T, kernel):
+    assert _has(_names(["fwd"], T=T, d=64, n_blocks=1, block_size=N, top_e=1, top_k=100, dtype="f32"), kernel)
+
+
+@pytest.mark.parametrize("few, kw", [
+    (True, dict(T=48, d=64, n_blocks=6, block_size=64, top_e=2, top_k=30)),      # equal scores
+    (False, dict(T=300, d=64, n_blocks=6, block_size=64, top_e=2, top_k=30)),
+    (True, dict(T=64, d=64, n_blocks=8, block_size=32, top_e=3, top_k=20)),      # ties
+    (False, dict(T=200, d=64, n_blocks=8, block_size=32, top_e=3, top_k=20)),
+    (True, dict(T=96, d=128, n_blocks=40, block_size=32, top_e=2, top_k=4)),     # small groups only
+    (False, dict(T=300, d=128, n_blocks=200, block_size=32, top_e=2, top_k=4))])
+def test_few_tokens_and_block_dense(few, kw):
+    names = _names(["fwd"], dtype="bf16", **kw)
+    assert _has(names, "few_out") == few and _has(names, "select_reg") != few
+    reuse = _names(["bwd"], flags=8, dtype="bf16", **kw)
+    assert _has(reuse, "act_rows") == few      # the few-token forward leaves nothing to reuse
