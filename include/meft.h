@@ -109,11 +109,12 @@ enum {
   /*
    * For meft_sparse_bwd (ignored by the other calls): the meft_sparse_fwd of this step ran on this workspace with
    * this shape and wrote the idx and act that the backward is given, unchanged since, and no other call has used
-   * the workspace in between.  The backward then takes the grouping of the (token, block) entries and the
-   * activation rows from the workspace, where the forward left them, instead of rebuilding both from (idx, act):
-   * same results, about 0.1 ms less at the LLaMA-7B-shaped configuration.  Like MEFT_FLAG_KEEP_STAGED this is an
+   * the workspace in between.  The backward then takes the grouping of the (token, block) entries, the activation rows
+   * and the flags of the touched neurons from the workspace, where the forward left them, instead of rebuilding them from
+   * (idx, act): same results, about 0.1 ms less at the LLaMA-7B-shaped configuration.  Like MEFT_FLAG_KEEP_STAGED this is an
    * exception to "the workspace carries nothing from call to call", and the promise is the caller's: the library
-   * cannot check it.  Shapes that run on the per-pair kernels rebuild nothing and ignore the flag.
+   * cannot check it.  Shapes that run on the per-pair kernels rebuild nothing and ignore the flag; the forward of few
+   * tokens (T * top_e <= 512, and at most 32 * n_blocks) leaves nothing, so there the backward rebuilds all the same.
    */
   MEFT_FLAG_REUSE_FWD = 8u
 };

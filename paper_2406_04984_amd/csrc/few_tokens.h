@@ -8,8 +8,10 @@
 //                of the token's workgroups, it costs less than a launch -- then the selected value rows are summed pair
 //                by pair in fp32 (Eq. 1-4).
 // Both element types.  Measured at the LLaMA-7B-shaped layer (64 blocks of 1024, top_e 4, top_k 256), route and forward
-// together: 1 token 105 -> 24 us, 24 tokens 190 -> 103 us (the keys of the ~50 blocks in use are 0.42 GB, 86 us at the
-// 4.9 TB/s of a copy), against the eleven launches of the block-dense path.
+// together, against the eleven launches of the block-dense path: 1 token 101 -> 23 us with its 35 MB of weights in the caches,
+// 148 -> 68 us on a layer not used before; 24 tokens 196 -> 107 us (the keys of the ~50 blocks in use are 0.42 GB, 91 us at the
+// 4.6 TB/s of a copy).  At the limit, forward alone, 128 tokens of 4 blocks: 248 -> 162 us (129 tokens, on the other path, take
+// 185); 128 tokens of a 64 x 256 x 1024 layer 79 -> 19 (129: 47); 64 tokens of 8 of 64 x 96 x 4096 113 -> 28 (65: 63).
 #pragma once
 #include "mma16.h"
 #include "select.h"

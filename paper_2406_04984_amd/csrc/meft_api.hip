@@ -76,7 +76,10 @@ struct LaunchScope {
 // ---- shape checks ---------------------------------------------------------------------------
 constexpr int kMaxD = 16384, kMaxBlocks = 16384;
 constexpr int kMaxC = 1 << 22;      // candidates per token (top_e * block_size)
-constexpr int kBoundMinC = 4096;    // few out of more candidates than this: topk_select_bound_kernel
+// few out of more candidates than this: topk_select_bound_kernel, whose 1024 threads need four each.  Forward without the
+// value sum, 2048 tokens, registers / bound: 16 of 4160 75 / 60 us, 64 of 4160 78 / 68, 256 of 4160 85 / 82, 256 of 12288
+// 168 / 142.
+constexpr int kBoundMinC = 4096;
 constexpr int kMaxLdsC = 12288;     // up to here the top-k selection keeps a token's keys in LDS
 
 meft_status check_shape(const meft_shape* s) {
@@ -532,7 +535,10 @@ void launch_gather_bwd(const meft_shape& s, const void* K, const void* V, const 
   int nthr, nv;
   row_launch(s.d, nthr, nv);
 #define GB(NV, PB) MEFT_LAUNCH("gather_bwd", (gather_bwd_kernel<T, NV, PB>), dim3(s.T), dim3(nthr), 0, st, k, v, g, idx, act, s.d, s.top_k, s.N, ds, o)
-  if (nv <= 2) GB(2, 8); else if (nv == 4) GB(4, 4); else GB(8, 2);
+  if constexpr (sizeof(T) == 4) {   // bf16 rows of up to 4096 columns are above
+    if (nv <= 2) { GB(2, 8); return; }
+  }
+  if (nv == 4) GB(4, 4); else GB(8, 2);
 #undef GB
 }
 

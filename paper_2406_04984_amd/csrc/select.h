@@ -413,13 +413,14 @@ __global__ __launch_bounds__(256, topk_waves(KPT)) void topk_select_reg_kernel(c
 
 // ---------------------------------------------------------------------------------------------
 // Selection of few out of many (k <= kBoundMaxK, C <= 65536; the ablation without key experts picks 256 of 65536): 1024
-// threads per token.  The k-th largest of the 1024 threads' own maxima is a lower bound of the k-th largest key, and a tight one: with 4 k <= 1024 about 1.15 k keys of independent scores
-// reach it.  Its leading 16 bits come from two histogram passes over one value per thread; a second sweep over
-// the scores puts the keys that reach it into a list in LDS, and the list is ranked by counting (key descending, position ascending), which gives the selection and
-// its order exactly.  A list that does not fit (many equal keys) leaves the token to histogram passes over all its keys.
-// Two sweeps with few registers, so that two tokens share a compute unit, beat one with the keys held (343 us).
+// threads per token.  The k-th largest of the 1024 threads' own maxima is a lower bound of the k-th largest key, and a tight
+// one: with 4 k <= 1024 about 1.15 k keys of independent scores reach it.  Its leading 16 bits come from two histogram passes
+// over one value per thread; a second sweep over the scores puts the keys that reach it into a list in LDS, and the list is
+// ranked by counting (key descending, position ascending), which gives the selection and its order exactly.  A list that
+// does not fit (many equal keys) leaves the token to histogram passes over all its keys.
 // Against those passes for every token (64 keys per thread into a histogram of which a handful of bins are hit, and
-// reads of which a wave touches 64 lines at a time): 637 -> 210 us at 2048 tokens x 65536.
+// reads of which a wave touches 64 lines at a time): 637 -> 191 us at 2048 tokens x 65536.  The two sweeps hold few registers,
+// so that two tokens share a compute unit; one sweep with the keys held took 343 us at that size.
 // ---------------------------------------------------------------------------------------------
 constexpr int kBoundMaxK = 256, kBoundList = 2048;
 

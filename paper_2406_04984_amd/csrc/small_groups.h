@@ -35,9 +35,9 @@ constexpr int kSmallRowChunk = 16;  // neurons per workgroup of the dV / dK kern
 constexpr int kSmallRowsMax = 16;   // upper limit of small_rows (size of that kernel's tables)
 constexpr int kSmallRows = MEFT_SMALL_ROWS;   // a group of at most this many tokens is small; 0 switches the path off
 constexpr int kSmallCols = 512;     // elements of a row that one wave covers in one step: 64 lanes x 8
-constexpr int kSmallPairSplit = 8;  // workgroups that share the pairs of one entry in small_ds_kernel
+constexpr int kSmallPairSplit = 8;  // workgroups that share the pairs of one entry in small_ds_body
 constexpr int kSmallSlot = (int)0x80000000;   // in slot_of_ent: the entry's group is small
-static_assert(kSmallRows >= 0 && kSmallRows <= kSmallRowsMax, "the tables of small_dvdk_kernel hold kSmallRowsMax tokens");
+static_assert(kSmallRows >= 0 && kSmallRows <= kSmallRowsMax, "the tables of small_dvdk_body hold kSmallRowsMax tokens");
 
 // acc += cf * eight bf16 values
 __device__ __forceinline__ void fma8_bf16(float cf, u32x4 x, float (&acc)[8]) {
