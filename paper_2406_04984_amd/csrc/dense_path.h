@@ -409,23 +409,28 @@ struct SmallDvdk {
   bf16_t *dK, *dV;
 };
 
-template <int NV, bool kSplit>
+// kDvdk: such workers may be there.  Without them the form for few tokens holds 63 registers instead of 94, which is eight waves
+// per SIMD instead of five: 175.0 -> 172.7 us for a training step of 2048 tokens, d 1024, 64 blocks of 256.
+template <int NV, bool kSplit, bool kDvdk = true>
 __global__ __launch_bounds__(256) void token_rows_kernel(TokenRows a, SmallDvdk s) {
   extern __shared__ int2 s_pairs[];
   __shared__ int s_blk[kTokenRowsBlocks];
   __shared__ int s_w[4];
   __shared__ float s_red[kSplit ? 3 : 1][kSplit ? kSmallCols : 1];
-  const int w = blockIdx.x;
-  if (w < s.n_wg) {
-    small_dvdk_body(w % s.nx, w / s.nx, s.ny, s.h, s.dOut, a.idx, s.act, s.ds32, s.small_grp, s.small_cnt, s.group_off,
-                    s.tok_of_slot, a.d, a.k, a.N, a.bs, s.dK, s.dV);
-    return;
+  int w = blockIdx.x;
+  if constexpr (kDvdk) {
+    if (w < s.n_wg) {
+      small_dvdk_body(w % s.nx, w / s.nx, s.ny, s.h, s.dOut, a.idx, s.act, s.ds32, s.small_grp, s.small_cnt, s.group_off,
+                      s.tok_of_slot, a.d, a.k, a.N, a.bs, s.dK, s.dV);
+      return;
+    }
+    w -= s.n_wg;
   }
   if constexpr (kSplit) {
-    const int chunks = (a.d + kSmallCols - 1) / kSmallCols, z = w - s.n_wg;
-    token_rows_split_body(a, z / chunks, z % chunks, s_pairs, s_blk, s_w, s_red);
+    const int chunks = (a.d + kSmallCols - 1) / kSmallCols;
+    token_rows_split_body(a, w / chunks, w % chunks, s_pairs, s_blk, s_w, s_red);
   } else {
-    token_rows_body<NV>(a, w - s.n_wg, s_pairs, s_blk, s_w);
+    token_rows_body<NV>(a, w, s_pairs, s_blk, s_w);
   }
 }
 

@@ -731,7 +731,8 @@ void launch_token_rows(const char* name, const meft_shape& s, const uint16_t* pa
   const size_t lds = small_rows_of(s) ? (size_t)(s.top_k < kTokenRowsPairs ? s.top_k : kTokenRowsPairs) * sizeof(int2) : 0;
   const int chunks = (s.d + kSmallCols - 1) / kSmallCols;
   if (rows_split(s)) {
-    MEFT_LAUNCH(name, (token_rows_kernel<1, true>), dim3(dv.n_wg + s.T * chunks), dim3(256), lds, st, a, dv);
+    if (dv.n_wg) MEFT_LAUNCH(name, (token_rows_kernel<1, true, true>), dim3(dv.n_wg + s.T * chunks), dim3(256), lds, st, a, dv);
+    else MEFT_LAUNCH(name, (token_rows_kernel<1, true, false>), dim3(s.T * chunks), dim3(256), lds, st, a, dv);
     return;
   }
   int nthr, nv;
