@@ -170,23 +170,30 @@ int route_slices(const meft_shape& s) {
 // otherwise.  The untiled one wins while the problem is small and then re-reads h (once per 64 blocks) and the router too
 // often.  All times are of the whole route call, us, untiled / tiled.
 bool route_on_tiles(const meft_shape& s) {
+  // 64-byte steps of a row, and the steps the untiled one's waves go through: whole batches of four per wave and slice
+  const int es = s.dtype == MEFT_BF16 ? 2 : 4;
+  const int64_t steps = ((int64_t)s.d * es + 63) / 64, slices = (int64_t)route_slices(s) * kRouteWaves;
+  const int64_t per = (steps + slices - 1) / slices, padded = slices * ((per + 3) / 4 * 4);
   if (s.dtype == MEFT_BF16 && s.d % kTK == 0) {
     // d 4096, 64 blocks: 11.0 / 18.6 at 1024 tokens, 20.3 / 20.1 at 4096, 39.1 / 23.5 at 8192; 256 blocks: 22.6 / 23.4 at
     // 1024, 69.5 / 27.6 at 4096
     if ((int64_t)s.T * s.n_blocks > 4096 * 64) return true;
-    // Few blocks, long rows: the tiled one wins once its 128-token tiles fill the chip.  8 blocks, 4096 / 8192 tokens: d 4096
-    // 14.2 / 18.6 and 31.2 / 20.6, d 8192 24.4 / 28.4 and 46.7 / 33.5; 32768 tokens: d 2048 50.4 / 42.3.  Below d 2048 the
-    // ring's start outweighs a slice's few k tiles: 28.4 / 32.1 at d 1024.
+    // Few blocks, many long rows: by two models in us, fitted to 60 shapes.  Untiled: by the steps, those that are only padding
+    // counted half.  Tiled: the serial k tiles of a slice (one of `parts`; 1 or 2 where d / 64 is no multiple of 4), or h at
+    // the copy rate.  8 blocks: d 4096 14.2 / 18.6 at 4096 tokens, 31.2 / 20.6 at 8192; d 4160 33.6 / 47 at 8192, 78 / 57 at
+    // 20000; d 5120 (160 steps go as 256) 12.7 / 19 at 2048, 29.2 / 21 at 5000; d 8192 24.4 / 28.4 at 4096, 46.7 / 33.5 at
+    // 8192; d 2048 14.0 / 15.0 at 8192, 50.4 / 42.3 at 32768.  Below d 2048 the ring's start outweighs a slice's few k tiles:
+    // 28.4 / 32.1 at d 1024 and 32768 tokens.
+    if (s.d < 2048 || (int64_t)s.T * s.d <= (int64_t)5 << 22) return false;
     const int kt = s.d / kTK, parts = kt % 4 == 0 ? 4 : (kt % 2 == 0 ? 2 : 1);
-    return s.d >= 2048 && (int64_t)(s.T / 128) * parts >= 160 && (int64_t)s.T * s.d > (int64_t)5 << 22;
+    const double untiled = 6.0 + (16.0 + s.n_blocks / 4.0) * 1e-6 * s.T * 0.5 * (double)(steps + padded);
+    const double chain = 9.0 + 0.62 * kt / parts, stream = 6.0 + 2.0 * s.T * (double)s.d / 4.6e6;
+    return untiled > 1.05 * (chain > stream ? chain : stream);
   }
-  // The untiled time goes by tokens x groups of 64 blocks, and by the steps of a row rounded up to whole batches of four
-  // per wave and slice.  64 blocks, 16384 and 65536 tokens: fp32 d 256 26.1 / 25.3 and 87.8 / 50.4, d 768 43 / 57 and 159 /
-  // 112, d 1024 45 / 72 and 176 / 156, d 4096 167 / 279 and 672 / 588 (1024 blocks, 16384 tokens: 2530 / 1957); bf16 d 1000
-  // 19.5 / 25.5 and 65 / 42, d 4104 85 / 68 and 385 / 142 (1024 blocks, 16384 tokens: 1404 / 274).
-  const int es = s.dtype == MEFT_BF16 ? 2 : 4;
-  const int64_t steps = ((int64_t)s.d * es + 63) / 64, slices = (int64_t)route_slices(s) * kRouteWaves;
-  const int64_t per = (steps + slices - 1) / slices, padded = slices * ((per + 3) / 4 * 4);
+  // The untiled time goes by tokens x groups of 64 blocks, and by the steps.  64 blocks, 16384 and 65536 tokens: fp32 d 256
+  // 26.1 / 25.3 and 87.8 / 50.4, d 768 43 / 57 and 159 / 112, d 1024 45 / 72 and 176 / 156, d 4096 167 / 279 and 672 / 588
+  // (1024 blocks, 16384 tokens: 2530 / 1957); bf16 d 1000 19.5 / 25.5 and 65 / 42, d 4104 85 / 68 and 385 / 142 (1024
+  // blocks, 16384 tokens: 1404 / 274).
   const int64_t reads = (int64_t)s.T * ((s.n_blocks + 63) / 64);
   return reads * padded > (es == 2 ? 28672 : 49152) * steps;
 }

@@ -11,7 +11,7 @@ SIZES = [
     (1792, 1000, 1023, "bf16"), (1793, 1000, 1023, "bf16"),
     (910, 2056, 1024, "bf16"), (911, 2056, 1024, "bf16"),
     (10240, 2048, 5, "bf16"), (10241, 2048, 5, "bf16"),
-    (20479, 2112, 3, "bf16"), (20480, 2112, 3, "bf16"),
+    (12000, 2112, 3, "bf16"), (16000, 2112, 3, "bf16"),
 ]
 
 

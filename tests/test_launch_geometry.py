@@ -40,7 +40,11 @@ def test_within_the_limits_of_the_device(launches, i):
 ROUTER = [
     (shape(4096, 4096, 8, 64, 4, 16, "bf16"), shape(8192, 4096, 8, 64, 4, 16, "bf16"), "gemm_mfma_kernel"),
     (shape(4096, 4096, 64, 64, 4, 16, "bf16"), shape(4097, 4096, 64, 64, 4, 16, "bf16"), "gemm_mfma_kernel"),
+    (shape(2048, 5120, 32, 64, 4, 16, "bf16"), shape(5000, 5120, 32, 64, 4, 16, "bf16"), "gemm_mfma_kernel"),
+    (shape(5000, 4224, 8, 64, 4, 16, "bf16"), shape(8192, 4224, 32, 64, 4, 16, "bf16"), "gemm_mfma_kernel"),
+    (shape(8192, 4160, 8, 64, 4, 16, "bf16"), shape(20000, 4160, 8, 64, 4, 16, "bf16"), "gemm_mfma_kernel"),
     (shape(32768, 1024, 8, 64, 4, 16, "bf16"), shape(32768, 2048, 8, 64, 4, 16, "bf16"), "gemm_mfma_kernel"),
+    (shape(12000, 2112, 3, 64, 3, 16, "bf16"), shape(16000, 2112, 3, 64, 3, 16, "bf16"), "gemm_mfma_kernel"),
     (shape(4096, 4104, 64, 64, 4, 16, "bf16"), shape(16384, 4104, 64, 64, 4, 16, "bf16"), "gemm_nt_"),
     (shape(16384, 1000, 64, 64, 4, 16, "bf16"), shape(16384, 1000, 1024, 64, 4, 16, "bf16"), "gemm_nt_"),
     (shape(16384, 1024, 64, 64, 4, 16, "f32"), shape(16384, 1024, 256, 64, 4, 16, "f32"), "gemm_nt_"),
