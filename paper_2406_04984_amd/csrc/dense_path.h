@@ -43,18 +43,21 @@ struct ProbRouter {
   uint32_t a_bytes, b_bytes; bool buf;
   __device__ const uint16_t* a_base() const { return h; }
   __device__ const uint16_t* b_base() const { return Wg; }
-  __device__ bool locate(int wg, TileCoord& tc) const {
+  struct Finder {};
+  __device__ Finder finder(int) const { return {}; }
+  __device__ bool locate(Finder&, int wg, TileCoord& tc) const {
     const int tn = (B + kTN - 1) / kTN;
     const int ks = wg % ksplit, w = wg / ksplit, mt = w / tn;
     tc.g = 0; tc.m0 = mt * kTM; tc.n0 = (w - mt * tn) * kTN; tc.Mrows = T; tc.Ncols = B;
     tc.nk = d / kTK / ksplit; tc.slot0 = 0; tc.aux = ks;
     return tc.m0 < T;
   }
-  __device__ const uint16_t* a_row(const TileCoord& tc, int m) const {
-    return h + (size_t)(m < T ? m : T - 1) * d + (size_t)tc.aux * tc.nk * kTK;
+  static constexpr bool kAIds = false;
+  __device__ const uint16_t* a_row(const TileCoord& tc, int m, int) const {
+    return h + (size_t)m * d + (size_t)tc.aux * tc.nk * kTK;
   }
   __device__ const uint16_t* b_row(const TileCoord& tc, int n) const {
-    return Wg + (size_t)(n < B ? n : B - 1) * d + (size_t)tc.aux * tc.nk * kTK;
+    return Wg + (size_t)n * d + (size_t)tc.aux * tc.nk * kTK;
   }
   __device__ int out_cols(const TileCoord&) const { return B; }
   static constexpr bool kAux = false;
@@ -69,7 +72,7 @@ struct ProbRouter {
   }
 };
 
-// Token-major, B contiguous along k: rows = tokens of the group (gathered through perm), columns =
+// Token-major, B contiguous along k: rows = tokens of the group (gathered through tok_of_slot), columns =
 // the block's neurons.  What is written depends on MODE:
 //   kTokScores: key scores, fp32, by entry;  kTokSlotScores: the same, slot-major.
 //   kTokMasked: the activation gradient, masked by A' > 0, bf16, slot-major (DS').
@@ -97,20 +100,22 @@ struct ProbTokKC {
   uint32_t a_bytes, b_bytes; bool buf;
   __device__ const uint16_t* a_base() const { return X; }
   __device__ const uint16_t* b_base() const { return W; }
-  __device__ bool locate(int wg, TileCoord& tc) const {
-    int mt, nt, rows;
-    if (!locate_token_tile(sched, wg, (bs + kTN - 1) / kTN, big_only != 0, tc.g, mt, nt, tc.slot0, rows))
-      return false;
-    tc.m0 = mt * kTM; tc.n0 = nt * kTN; tc.Mrows = rows; tc.Ncols = bs; tc.nk = d / kTK;
+  using Finder = TileFinder;
+  __device__ Finder finder(int xcd) const {
+    Finder f;
+    f.init<kTM>(sched, xcd, (bs + kTN - 1) / kTN, big_only != 0);
+    return f;
+  }
+  __device__ bool locate(Finder& f, int wg, TileCoord& tc) const {
+    int mt, nt;
+    if (!f.find<kTM>(sched, wg >> 3, mt, nt, tc)) return false;
+    tc.m0 = mt * kTM; tc.n0 = nt * kTN; tc.Mrows = tc.aux; tc.Ncols = bs; tc.nk = d / kTK;
     return true;
   }
-  __device__ const uint16_t* a_row(const TileCoord& tc, int m) const {
-    const int ent = perm[tc.slot0 + (m < tc.Mrows ? m : tc.Mrows - 1)];
-    return X + (size_t)(ent / e) * d;
-  }
-  __device__ const uint16_t* b_row(const TileCoord& tc, int n) const {
-    return W + ((size_t)tc.g * bs + (n < bs ? n : bs - 1)) * d;
-  }
+  static constexpr bool kAIds = true;
+  __device__ const int32_t* a_ids(const TileCoord& tc) const { return tok_of_slot + tc.slot0 + tc.m0; }
+  __device__ const uint16_t* a_row(const TileCoord&, int, int id) const { return X + (size_t)id * d; }
+  __device__ const uint16_t* b_row(const TileCoord& tc, int n) const { return W + ((size_t)tc.g * bs + n) * d; }
   __device__ int out_cols(const TileCoord&) const { return tok_fp32_out(MODE) ? bs : bsp; }
   // scores: the row's entry number + 1; otherwise 1 for a row of the group
   __device__ int row_tag(const TileCoord& tc, int m) const {
@@ -174,16 +179,20 @@ struct ProbTokNC {
   uint32_t a_bytes, b_bytes; bool buf;
   __device__ const uint16_t* a_base() const { return A; }
   __device__ const uint16_t* b_base() const { return W; }
-  __device__ bool locate(int wg, TileCoord& tc) const {
-    int mt, nt, rows;
-    if (!locate_token_tile(sched, wg, (d + kTN - 1) / kTN, big_only != 0, tc.g, mt, nt, tc.slot0, rows))
-      return false;
-    tc.m0 = mt * kTM; tc.n0 = nt * kTN; tc.Mrows = rows; tc.Ncols = d; tc.nk = bsp / kTK;
+  using Finder = TileFinder;
+  __device__ Finder finder(int xcd) const {
+    Finder f;
+    f.init<kTM>(sched, xcd, (d + kTN - 1) / kTN, big_only != 0);
+    return f;
+  }
+  __device__ bool locate(Finder& f, int wg, TileCoord& tc) const {
+    int mt, nt;
+    if (!f.find<kTM>(sched, wg >> 3, mt, nt, tc)) return false;
+    tc.m0 = mt * kTM; tc.n0 = nt * kTN; tc.Mrows = tc.aux; tc.Ncols = d; tc.nk = bsp / kTK;
     return true;
   }
-  __device__ const uint16_t* a_row(const TileCoord& tc, int m) const {
-    return A + (size_t)(tc.slot0 + (m < tc.Mrows ? m : tc.Mrows - 1)) * bsp;
-  }
+  static constexpr bool kAIds = false;
+  __device__ const uint16_t* a_row(const TileCoord& tc, int m, int) const { return A + (size_t)(tc.slot0 + m) * bsp; }
   __device__ int b_row_ids(const TileCoord& tc, int k) const { return tc.g * bs + (k < bs ? k : bs - 1); }
   // the 64 rows from k0 on are consecutive rows of W (no clamping inside the k tile)
   __device__ bool b_rows_linear(const TileCoord&, int k0) const { return k0 + kTK <= bs; }
@@ -226,27 +235,17 @@ struct ProbNeuTN {
   uint32_t a_bytes, b_bytes; bool buf;
   __device__ const uint16_t* a_base() const { return A + (int64_t)zrow * bsp; }   // the row of zeros lies lowest
   __device__ const uint16_t* b_base() const { return X; }
-  __device__ bool locate(int wg, TileCoord& tc) const {
-    const int tm = (bs + kTM - 1) / kTM, tn = (d + kTN - 1) / kTN;
-    const int x = wg & (kXcd - 1), local = wg >> 3;
-    int gi, w;
-    if (as_const(sched.len)[kXcd] != 0) {   // split lists: this XCD takes the tiles x, x + 8, ... of every group
-      const int mine = tm * tn > x ? (tm * tn - x + kXcd - 1) / kXcd : 0;
-      if (mine == 0) return false;
-      gi = local / mine;
-      w = x + kXcd * (local - gi * mine);
-    } else {
-      gi = local / (tm * tn);
-      w = local - gi * (tm * tn);
-    }
-    if (gi >= as_const(sched.len)[big_only ? kXcd + 1 + x : x]) return false;
-    const auto* ent = as_const(sched.grp) + (size_t)x * sched.cap + gi;
-    tc.g = ent->x;
-    tc.slot0 = ent->y;
-    const int rows = ent->z;   // > 0: the lists hold non-empty groups only
+  using Finder = GroupFinder;
+  __device__ Finder finder(int xcd) const {
+    Finder f;
+    f.init(sched, xcd, (bs + kTM - 1) / kTM, (d + kTN - 1) / kTN, big_only != 0);
+    return f;
+  }
+  __device__ bool locate(Finder& f, int wg, TileCoord& tc) const {
+    int mt, nt;
+    if (!f.find(sched, wg >> 3, mt, nt, tc)) return false;
     // m tiles vary fastest: the tiles that share the gathered rows of one n tile run together
-    tc.m0 = (w % tm) * kTM; tc.n0 = (w / tm) * kTN; tc.Mrows = bs; tc.Ncols = d; tc.nk = round_up64(rows) / kTK;
-    tc.aux = rows;
+    tc.m0 = mt * kTM; tc.n0 = nt * kTN; tc.Mrows = bs; tc.Ncols = d; tc.nk = round_up64(tc.aux) / kTK;
     return true;
   }
   __device__ const uint16_t* a_mat() const { return A; }
@@ -284,14 +283,12 @@ template <int MODE, int TM, int TN>
 struct TileTokKC : ProbTokKC<MODE> {
   using Base = ProbTokKC<MODE>;
   static constexpr int kTM = TM, kTNt = TN;
-  static constexpr bool kAIds = true;
   uint32_t o_bytes;
   __device__ void* out_base() const { return tok_fp32_out(MODE) ? static_cast<void*>(Base::sc) : static_cast<void*>(Base::DS); }
   __device__ int tiles_n() const { return (Base::bs + TN - 1) / TN; }
   __device__ void coord(int mt, int nt, TileCoord& tc) const {
     tc.m0 = mt * TM; tc.n0 = nt * TN; tc.Mrows = tc.aux; tc.Ncols = Base::bs; tc.nk = Base::d / kTK;
   }
-  __device__ const int32_t* a_ids(const TileCoord& tc) const { return Base::tok_of_slot + tc.slot0 + tc.m0; }
   __device__ int a_ld() const { return Base::d; }
   __device__ int b_row0(const TileCoord& tc) const { return tc.g * Base::bs; }
   __device__ int b_ld() const { return Base::d; }
@@ -300,7 +297,6 @@ struct TileTokKC : ProbTokKC<MODE> {
 template <int TM, int TN>
 struct TileTokNC : ProbTokNC {
   static constexpr int kTM = TM, kTNt = TN;
-  static constexpr bool kAIds = false;
   uint32_t o_bytes;
   __device__ void* out_base() const { return part; }
   __device__ uint32_t keep(uint32_t pk, int, uint32_t) const { return pk; }

@@ -31,9 +31,10 @@
 //     k-consecutive values of column i of a 4 x 16 block.
 //
 // The k tiles of all the tiles a workgroup works through form ONE stream through the rings: right after the barrier
-// that hands position s to the compute waves, A of position s + kSA - 1 and B of position s + kSB - 1 are requested
-// (the operand with the shorter lead first), whether or not those belong to the next output tile, so the operand
-// pipeline never drains at a tile boundary.  There is exactly one workgroup barrier per k tile of the stream,
+// that hands position s to the compute waves, A and B of position s + kSA - 1 are requested, whether or not that belongs
+// to the next output tile, so the operand pipeline never drains at a tile boundary.  For the same reason nothing at a tile
+// boundary waits for memory: the tile comes out of registers (TileFinder, GroupFinder), gathered row numbers by scalar
+// loads.  There is exactly one workgroup barrier per k tile of the stream,
 // executed by all the waves.  (An extra barrier at the end of every tile, releasing its last stage before the stores
 // so that the loaders request a third k tile during the epilogue, was measured and did not pay.)
 //
@@ -55,6 +56,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "tile_div.h"
 
 namespace meft {
 
@@ -105,18 +107,24 @@ struct TileCoord {
 };
 
 // A problem policy P provides:
-//   static constexpr int kTM, kSA, kSB;                 tile rows (128 or 192) and the slots of the A and B rings
+//   static constexpr int kTM, kSA, kSB;                 tile rows (128 or 192) and the slots of the A and B rings (kSA == kSB)
 //   static constexpr int kLoaders;                      loader waves, 2 or 4
-//   __device__ bool locate(int wg, TileCoord&) const;   false: no tile with id wg, nor with any larger id on
-//                                                       the same XCD (ids wg + 8, wg + 16, ...)
+//   Finder, __device__ Finder finder(int xcd) const;    what a wave of that XCD looks its tiles up with, in registers
+//   __device__ bool locate(Finder&, int wg, TileCoord&) const;   false: no tile with id wg, nor with any larger id on
+//                                                       the same XCD (ids wg + 8, wg + 16, ...).  Called at every tile
+//                                                       boundary of the operand stream: it reads no memory (but for the
+//                                                       next part of a group list that is longer than a wave)
 //   static constexpr bool kAMC;                         A contiguous along m (rows indexed by k)?
-//       false: __device__ const uint16_t* a_row(const TileCoord&, int m) const;    start of row m (clamped)
+//       false: __device__ const uint16_t* a_row(const TileCoord&, int m, int id) const;    start of row m; id = entry m0 + .. of
+//              a_ids where static constexpr bool kAIds is true:
+//              __device__ const int32_t* a_ids(const TileCoord&) const;   row numbers of the rows m0 ..  m0 + kTM - 1 (readable
+//              and valid also beyond the group);  m < Mrows where it is false
 //       true:  __device__ const uint16_t* a_mat() const;                 row 0 of the matrix that holds A,
 //              __device__ int a_cols(const TileCoord&) const;            its row length (a multiple of 8), and
 //              __device__ int a_krow(const TileCoord&, int k) const;     the number of the row that holds contraction
 //              index k (possibly negative; a row of zeros beyond the contraction length)
 //   static constexpr bool kBNC;                         B contiguous along n (rows indexed by k)?
-//       false: __device__ const uint16_t* b_row(const TileCoord&, int n) const;    start of B row n (clamped)
+//       false: __device__ const uint16_t* b_row(const TileCoord&, int n) const;    start of B row n, n < Ncols
 //       true:  __device__ const uint16_t* b_row_ptr(int row) const;   start of B row `row`; rows are
 //              TileCoord::Ncols elements apart;  and, with static constexpr bool kRowIdsInMemory (false where B
 //              is k-contiguous),
@@ -205,7 +213,7 @@ __global__ __launch_bounds__(gemm_threads<P>(), 1) void gemm_mfma_kernel(P p, in
   constexpr int kBRing = SA * kASlotElems;          // element offset of the B ring
   static_assert(kLoaders == 2 || kLoaders == 4 || kLoaders == 8, "waves that load: 2, 4 or 8");
   static_assert((kCW == 4 && (TM == 128 || TM == 192)) || (kCW == 8 && TM == 256), "tile rows: 128, 192 or 256");
-  static_assert(SA >= 2 && SA <= 3 && SB >= 2 && SB <= 3, "ring depths: 2 or 3");
+  static_assert(SA >= 2 && SA <= 3 && SB == SA, "ring depths: 2 or 3, A and B requested for the same positions");
   static_assert(!P::kAMC || TM == 128 || TM == 256, "the m-contiguous A layouts are written for 128 and 256 rows");
   static_assert(!kSelf || (P::kAMC && P::kBNC && SA == 2 && SB == 2 && kCW == 8),
                 "compute waves that load: written for the neuron-major problems with two slots per ring");
@@ -213,8 +221,10 @@ __global__ __launch_bounds__(gemm_threads<P>(), 1) void gemm_mfma_kernel(P p, in
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // locate() answers false only when the workgroup's XCD has no tile with this or any larger id
-  auto next_tile = [&](int wg, TileCoord& t) -> bool { return wg < n_tiles_bound && p.locate(wg, t); };
+  typename P::Finder finder = p.finder(blockIdx.x & (kXcd - 1));
+  auto next_tile = [&](int wg, TileCoord& t) -> bool { return wg < n_tiles_bound && p.locate(finder, wg, t); };
   const int step = gridDim.x;
+  constexpr uint32_t kNowhere = 0xFFFFFFF0u;   // offset outside every buffer: such a load brings zeros and touches no memory
 
   TileCoord tc;
   if (!next_tile(blockIdx.x, tc)) return;   // the same answer in every wave
@@ -225,20 +235,21 @@ __global__ __launch_bounds__(gemm_threads<P>(), 1) void gemm_mfma_kernel(P p, in
     const int lw = kSelf ? wave : wave - kCW;
     constexpr int LA = TM / 8 / kLoaders;    // A wave-loads (1 KB each) per loader and slot: 12, 8, 6 or 4
     constexpr int LB = kTN / 8 / kLoaders;   // B wave-loads (1 KB each) per loader and slot: 16 or 8
-    constexpr int DA = SA - 1, DB = SB - 1;  // positions ahead of the barrier at which A and B are requested
-    constexpr int kAhead = (DA - 1) * LA + (DB - 1) * LB;   // loads that may still be in flight at a barrier
+    constexpr int DA = SA - 1;               // positions ahead of the barrier at which they are requested
+    constexpr int kAhead = (DA - 1) * (LA + LB);   // loads that may still be in flight at a barrier
     static_assert(kAhead <= 63, "partial vmcnt wait out of range");
     const int lr8 = lane >> 3;
     int* idring = reinterpret_cast<int*>(smem + operand_lds_bytes<P>() / 2) + lw * kIdRingSlots * 64;
 
-    // Cursors over one and the same sequence of (tile, k tile) positions: the operand A, the operand B, and (where
-    // they sit in memory) the row numbers of gathered B rows, which run one position ahead of B.
+    // Cursors over one and the same sequence of (tile, k tile) positions: the operands, and (where they sit in memory) the
+    // row numbers of gathered B rows, which run one position ahead.
     struct Cursor {
-      int wg, k, n, slot;
+      int wg, k, n;
       bool ok;
       TileCoord t;
     };
-    Cursor ca{(int)blockIdx.x, 0, 0, 0, true, tc}, cb = ca, cd = ca;
+    Cursor cu{(int)blockIdx.x, 0, 0, true, tc}, cd = cu;
+    int slot = 0;   // ring slot of the next request
     cd.ok = P::kBNC && P::kRowIdsInMemory;
     //   consume: position handed to the compute waves at the next barrier
     int wg_c = blockIdx.x, nk_c = tc.nk;
@@ -264,8 +275,32 @@ __global__ __launch_bounds__(gemm_threads<P>(), 1) void gemm_mfma_kernel(P p, in
     // instruction's scalar offset: the k offset of k-contiguous operands, the row offset of consecutive B rows.
     [[maybe_unused]] uint32_t oa[P::kAMC ? 4 : LA], ob[P::kBNC ? 4 : LB];
     const int half = lane >> 5;
+    // Rows beyond the group are not loaded (buffer loads), or any valid row is.  Gathered row numbers come by scalar loads,
+    // eight per wave-load, of which each lane picks its row's: a vector load here would wait for every operand request on
+    // its way.
+    [[maybe_unused]] auto a_row_start = [&](const TileCoord& t, int i) -> const uint16_t* {
+      if constexpr (P::kAMC) {
+        return nullptr;
+      } else {
+      const int row = (lw * LA + i) * 8 + lr8;
+      int id = 0, m = t.m0 + row;
+      if constexpr (P::kAIds) {
+        const auto* ids = as_const(p.a_ids(t) + (lw * LA + i) * 8);
+        int s[8];
+#pragma unroll
+        for (int z = 0; z < 8; ++z) s[z] = ids[z];
+        const int s01 = (lr8 & 1) ? s[1] : s[0], s23 = (lr8 & 1) ? s[3] : s[2], s45 = (lr8 & 1) ? s[5] : s[4],
+                  s67 = (lr8 & 1) ? s[7] : s[6];
+        const int s03 = (lr8 & 2) ? s23 : s01, s47 = (lr8 & 2) ? s67 : s45;
+        id = (lr8 & 4) ? s47 : s03;
+      } else {
+        m = m < t.Mrows ? m : t.Mrows - 1;
+      }
+      return p.a_row(t, m, id) + (((lane & 7) ^ ((row >> 1) & 7)) << 3);
+      }
+    };
     auto setup_a = [&]() {
-      const TileCoord& t = ca.t;
+      const TileCoord& t = cu.t;
       if constexpr (kBuf) {
         if constexpr (P::kAMC && TM == 256) {
 #pragma unroll
@@ -283,8 +318,8 @@ __global__ __launch_bounds__(gemm_threads<P>(), 1) void gemm_mfma_kernel(P p, in
         } else {
 #pragma unroll
           for (int i = 0; i < LA; ++i) {
-            const int row = (lw * LA + i) * 8 + lr8;
-            oa[i] = byte_off(p.a_row(t, t.m0 + row) + (((lane & 7) ^ ((row >> 1) & 7)) << 3), p.a_base());
+            const uint32_t o = byte_off(a_row_start(t, i), p.a_base());
+            oa[i] = t.m0 + (lw * LA + i) * 8 + lr8 < t.Mrows ? o : kNowhere;
           }
         }
       } else {
@@ -303,15 +338,12 @@ __global__ __launch_bounds__(gemm_threads<P>(), 1) void gemm_mfma_kernel(P p, in
           for (int q = 0; q < 4; ++q) pa[q] = p.a_mat() + (acol - q * 512);
         } else {
 #pragma unroll
-          for (int i = 0; i < LA; ++i) {
-            const int row = (lw * LA + i) * 8 + lr8;
-            pa[i] = p.a_row(t, t.m0 + row) + (((lane & 7) ^ ((row >> 1) & 7)) << 3) - (i & 3) * 512;
-          }
+          for (int i = 0; i < LA; ++i) pa[i] = a_row_start(t, i) - (i & 3) * 512;
         }
       }
     };
     auto setup_b = [&]() {
-      const TileCoord& t = cb.t;
+      const TileCoord& t = cu.t;
       if constexpr (kBuf) {
         if constexpr (P::kBNC) {
 #pragma unroll
@@ -324,8 +356,9 @@ __global__ __launch_bounds__(gemm_threads<P>(), 1) void gemm_mfma_kernel(P p, in
         } else {
 #pragma unroll
           for (int i = 0; i < LB; ++i) {
-            const int row = (lw * LB + i) * 8 + lr8;
-            ob[i] = byte_off(p.b_row(t, t.n0 + row) + (((lane & 7) ^ ((row >> 1) & 7)) << 3), p.b_base());
+            const int row = (lw * LB + i) * 8 + lr8, n = min(t.n0 + row, t.Ncols - 1);
+            const uint32_t o = byte_off(p.b_row(t, n) + (((lane & 7) ^ ((row >> 1) & 7)) << 3), p.b_base());
+            ob[i] = t.n0 + row < t.Ncols ? o : kNowhere;
           }
         }
       } else {
@@ -340,8 +373,8 @@ __global__ __launch_bounds__(gemm_threads<P>(), 1) void gemm_mfma_kernel(P p, in
         } else {
 #pragma unroll
           for (int i = 0; i < LB; ++i) {
-            const int row = (lw * LB + i) * 8 + lr8;
-            pb[i] = p.b_row(t, t.n0 + row) + (((lane & 7) ^ ((row >> 1) & 7)) << 3) - (i & 3) * 512;
+            const int row = (lw * LB + i) * 8 + lr8, n = min(t.n0 + row, t.Ncols - 1);
+            pb[i] = p.b_row(t, n) + (((lane & 7) ^ ((row >> 1) & 7)) << 3) - (i & 3) * 512;
           }
         }
       }
@@ -380,19 +413,18 @@ __global__ __launch_bounds__(gemm_threads<P>(), 1) void gemm_mfma_kernel(P p, in
         if (++cd.k == cd.t.nk) { cd.wg += step; cd.k = 0; cd.ok = next_tile(cd.wg, cd.t); }
       }
     };
-    // one k tile of A into the next slot of the A ring; false: the stream has ended, nothing was requested
-    auto request_a = [&]() -> bool {
-      if (!ca.ok) return false;
-      const TileCoord& t = ca.t;
-      uint16_t* my_a = smem + ca.slot * kASlotElems + lw * LA * 512;   // 512 elements = 1 KB per load
+    // one k tile of A into the next slot of the A ring
+    auto request_a = [&]() {
+      const TileCoord& t = cu.t;
+      uint16_t* my_a = smem + slot * kASlotElems + lw * LA * 512;   // 512 elements = 1 KB per load
       [[maybe_unused]] int a_row_bytes = 0;
       if constexpr (P::kAMC) a_row_bytes = p.a_cols(t) * 2;
       if constexpr (kBuf) {
-        const int k_bytes = ca.k * kTK * 2;
+        const int k_bytes = cu.k * kTK * 2;
 #pragma unroll
         for (int i = 0; i < LA; ++i) {
           if constexpr (P::kAMC) {
-            const int row = p.a_krow(t, ca.k * kTK + (TM == 256 ? 2 * (lw * LA + i) + half : 4 * (lw * LA + i) + (lane >> 4)));
+            const int row = p.a_krow(t, cu.k * kTK + (TM == 256 ? 2 * (lw * LA + i) + half : 4 * (lw * LA + i) + (lane >> 4)));
             MEFT_LOAD_1K_BUF(rsrc_a, oa[i & 3] + (uint32_t)row * (uint32_t)a_row_bytes, 0, my_a, i);
           } else {
             MEFT_LOAD_1K_BUF(rsrc_a, oa[i], k_bytes, my_a, i);
@@ -402,33 +434,25 @@ __global__ __launch_bounds__(gemm_threads<P>(), 1) void gemm_mfma_kernel(P p, in
 #pragma unroll
         for (int i = 0; i < LA; ++i) {
           if constexpr (P::kAMC) {
-            const int row = p.a_krow(t, ca.k * kTK + (TM == 256 ? 2 * (lw * LA + i) + half : 4 * (lw * LA + i) + (lane >> 4)));
+            const int row = p.a_krow(t, cu.k * kTK + (TM == 256 ? 2 * (lw * LA + i) + half : 4 * (lw * LA + i) + (lane >> 4)));
             MEFT_LOAD_1K(reinterpret_cast<const char*>(pa[i & 3]) + (int64_t)row * a_row_bytes, my_a, i);
           } else {
-            MEFT_LOAD_1K(pa[i] + ca.k * kTK, my_a, i);
+            MEFT_LOAD_1K(pa[i] + cu.k * kTK, my_a, i);
           }
         }
       }
-      ++ca.n;
-      ca.slot = ca.slot + 1 == SA ? 0 : ca.slot + 1;
-      if (++ca.k == t.nk) {
-        ca.wg += step; ca.k = 0; ca.ok = next_tile(ca.wg, ca.t);
-        if (ca.ok) setup_a();
-      }
-      return true;
     };
     // one k tile of B into the next slot of the B ring
-    auto request_b = [&]() -> bool {
-      if (!cb.ok) return false;
-      const TileCoord& t = cb.t;
+    auto request_b = [&]() {
+      const TileCoord& t = cu.t;
       // n-contiguous B: ids[i] = number of the B row this lane fetches in its i-th load,
-      // k = 64 * cb.k + 2 * (lw * LB + i) + half
+      // k = 64 * cu.k + 2 * (lw * LB + i) + half
       int ids[LB];
       if constexpr (P::kBNC && P::kRowIdsInMemory) {
         // out of the ring; one asm block with its own wait (through plain loads the compiler would first drain every
         // outstanding operand load)
         const uint32_t a = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)(
-            idring + (cb.n & (kIdRingSlots - 1)) * 64 + 2 * lw * LB + half);
+            idring + (cu.n & (kIdRingSlots - 1)) * 64 + 2 * lw * LB + half);
         if constexpr (LB == 16) {
         asm volatile(
             "ds_read_b32 %0, %16\n\tds_read_b32 %1, %16 offset:8\n\tds_read_b32 %2, %16 offset:16\n\t"
@@ -462,19 +486,19 @@ __global__ __launch_bounds__(gemm_threads<P>(), 1) void gemm_mfma_kernel(P p, in
         }
       } else if constexpr (P::kBNC) {
 #pragma unroll
-        for (int i = 0; i < LB; ++i) ids[i] = p.b_row_ids(t, cb.k * kTK + 2 * (lw * LB + i) + half);
+        for (int i = 0; i < LB; ++i) ids[i] = p.b_row_ids(t, cu.k * kTK + 2 * (lw * LB + i) + half);
       }
-      uint16_t* my_b = smem + kBRing + cb.slot * kBSlotElems + lw * LB * 512;
+      uint16_t* my_b = smem + kBRing + slot * kBSlotElems + lw * LB * 512;
       if constexpr (kBuf) {
-        const int k_bytes = cb.k * kTK * 2;
+        const int k_bytes = cu.k * kTK * 2;
         if constexpr (P::kBNC) {
           const uint32_t row_bytes = (uint32_t)t.Ncols * 2u;
           bool linear = false;
           if constexpr (!P::kRowIdsInMemory) {
-            linear = p.b_rows_linear(t, cb.k * kTK);
+            linear = p.b_rows_linear(t, cu.k * kTK);
             if (linear) {
               // 64 consecutive rows: this lane's row is first + 2 * (lw * LB + i) + half
-              const uint32_t first = (uint32_t)p.b_row_ids(t, cb.k * kTK) * row_bytes, hoff = half * row_bytes;
+              const uint32_t first = (uint32_t)p.b_row_ids(t, cu.k * kTK) * row_bytes, hoff = half * row_bytes;
 #pragma unroll
               for (int i = 0; i < LB; ++i)
                 MEFT_LOAD_1K_BUF(rsrc_b, ob[i & 3] + hoff, (int)(first + 2u * (lw * LB + i) * row_bytes), my_b, i);
@@ -497,25 +521,27 @@ __global__ __launch_bounds__(gemm_threads<P>(), 1) void gemm_mfma_kernel(P p, in
             MEFT_LOAD_1K(reinterpret_cast<const char*>(pb[i & 3]) + (uint64_t)(uint32_t)ids[i] * row_bytes, my_b, i);
         } else {
 #pragma unroll
-          for (int i = 0; i < LB; ++i) MEFT_LOAD_1K(pb[i] + cb.k * kTK, my_b, i);
+          for (int i = 0; i < LB; ++i) MEFT_LOAD_1K(pb[i] + cu.k * kTK, my_b, i);
         }
       }
-      ++cb.n;
-      cb.slot = cb.slot + 1 == SB ? 0 : cb.slot + 1;
-      if (++cb.k == t.nk) {
-        cb.wg += step; cb.k = 0; cb.ok = next_tile(cb.wg, cb.t);
-        if (cb.ok) setup_b();
+    };
+    // one k tile of each operand; false: the stream has ended, nothing was requested
+    auto request_operands = [&]() -> bool {
+      if (!cu.ok) return false;
+      request_a();
+      request_b();
+      ++cu.n;
+      slot = slot + 1 == SA ? 0 : slot + 1;
+      if (++cu.k == cu.t.nk) {
+        cu.wg += step; cu.k = 0; cu.ok = next_tile(cu.wg, cu.t);
+        if (cu.ok) { setup_a(); setup_b(); }
       }
       return true;
     };
-    // the requests that follow a barrier: one k tile of each operand, the one with the shorter lead first, so that
-    // the loads which may still be in flight at the next barrier are the most recent ones.  true: both were made.
+    // the requests that follow a barrier
     auto request_batch = [&]() -> bool {
       request_ids();
-      bool a, b;
-      if constexpr (DA <= DB) { a = request_a(); b = request_b(); }
-      else { b = request_b(); a = request_a(); }
-      return a && b;
+      return request_operands();
     };
 
   if (kSelf || wave >= kCW) {
@@ -523,16 +549,12 @@ __global__ __launch_bounds__(gemm_threads<P>(), 1) void gemm_mfma_kernel(P p, in
     setup_b();
     if constexpr (P::kBNC && P::kRowIdsInMemory) {
 #pragma unroll
-      for (int s = 0; s < DB + 1; ++s) request_ids();
+      for (int s = 0; s < DA + 1; ++s) request_ids();
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
-    // before the first barrier: position 0 of both operands first, then the positions the leads reach
-    bool full = request_a();
-    full = request_b() && full;
+    bool full = true;   // before the first barrier: the positions the lead reaches
 #pragma unroll
-    for (int s = 1; s < DA; ++s) full = request_a() && full;
-#pragma unroll
-    for (int s = 1; s < DB; ++s) full = request_b() && full;
+    for (int s = 0; s < DA; ++s) full = request_operands() && full;
     // compute waves that load: position 0 has to have landed at the first barrier (later positions are awaited
     // before the barrier that hands them over)
     if constexpr (kSelf) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -597,8 +619,6 @@ __global__ __launch_bounds__(gemm_threads<P>(), 1) void gemm_mfma_kernel(P p, in
 
     f32x16 acc[MI][4];
     const int nk = tc.nk;
-    bool more = false;
-    TileCoord tn;
     // The fragments of one k16 step.  Two sets alternate: the LDS reads of step s + 1 are issued before the matrix
     // instructions of step s, so that their latency passes under those 8 (12) instructions instead of in front of
     // the next ones.  (Left to itself the compiler reads each step's fragments into the same registers right before
@@ -716,8 +736,6 @@ __global__ __launch_bounds__(gemm_threads<P>(), 1) void gemm_mfma_kernel(P p, in
       };
       MEFT_BARRIER_LDS();   // (the tile's first position was awaited before: see above)
       request_batch();
-      wg += step;
-      more = next_tile(wg, tn);
       k_tile_self(std::true_type{});
       for (int kt = 1; kt < nk; ++kt) {
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
@@ -727,8 +745,6 @@ __global__ __launch_bounds__(gemm_threads<P>(), 1) void gemm_mfma_kernel(P p, in
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     } else {
     MEFT_BARRIER_LDS();   // the loaders have seen the tile's first k tile land
-    wg += step;
-    more = next_tile(wg, tn);
     load_frags(std::integral_constant<int, 0>{}, f0);
     MEFT_FENCE();
     k_steps(std::true_type{});
@@ -842,8 +858,8 @@ __global__ __launch_bounds__(gemm_threads<P>(), 1) void gemm_mfma_kernel(P p, in
       if (nj >= 4) epilogue(std::true_type{});
       else epilogue(std::false_type{});
     }
-    if (!more) break;
-    tc = tn;
+    wg += step;
+    if (!next_tile(wg, tc)) break;
   }
 }
 
@@ -911,7 +927,7 @@ __device__ __forceinline__ void build_sched_body(int rows, int slot0, int n_grou
   }
   __syncthreads();
   // Fewer non-empty groups than XCDs: a deal of whole groups would leave XCDs idle.  Then every list holds every
-  // group, len[kXcd] says so, and XCD x takes the tiles x, x + 8, ... of each group (locate_token_tile).
+  // group, len[kXcd] says so, and XCD x takes the tiles x, x + 8, ... of each group (TileFinder, GroupFinder).
   const bool split = n_full < kXcd;
   if (tid == 0) len[kXcd] = split ? 1 : 0;
   if (tid >= 64) return;
@@ -1039,46 +1055,119 @@ __global__ __launch_bounds__(1024) void build_sched_kernel(const int32_t* __rest
   }
 }
 
-// big_only: walk only the groups of more than small_rows tokens (the prefix of every list that the second set of
-// lengths describes)
-__device__ __forceinline__ bool locate_token_tile(const TokenSched& s, int wg, int tn,
-                                                   bool big_only, int& g, int& mt, int& nt, int& slot0, int& rows) {
-  const int x = wg & (kXcd - 1), local = wg >> 3;
-  const int n = as_const(s.len)[big_only ? kXcd + 1 + x : x];
-  const auto* list = as_const(s.grp) + (size_t)x * s.cap;
-  if (as_const(s.len)[kXcd] != 0) {
-    // split lists (fewer than 8 entries): XCD x takes the tiles x, x + 8, ... of every group, m tiles fastest
-    int rest = local;
-    for (int i = 0; i < n; ++i) {
-      const int tm = list[i + 1].w - list[i].w, all = tm * tn;
-      const int mine = all > x ? (all - x + kXcd - 1) / kXcd : 0;
-      if (rest < mine) {
-        const int w = x + kXcd * rest;
-        g = list[i].x;
-        nt = w / tm;
-        mt = w - nt * tm;
-        slot0 = list[i].y;
-        rows = list[i].z;
-        return true;
-      }
-      rest -= mine;
+// Waits for the vector loads before it, in a form that the compiler takes into account: without it the registers that a
+// finder loads now and then would count as on their way at every look-up, each of which would wait for all of the operand
+// requests in flight.
+__device__ __forceinline__ void finder_loaded() { __builtin_amdgcn_s_waitcnt(0x0F70); }   // vmcnt(0)
+
+// Where the token-major tiles of one XCD lie, out of registers: lane i holds entry i of the XCD's group list, so that a tile
+// is found by a ballot.  In memory it is a chain of six dependent scalar loads, a microsecond per tile, which in a launch
+// with loader waves stops the operand stream: a contraction of two k tiles (1.7 us) per output tile spent as long on looking
+// tiles up as on them.  Lists of more than 63 groups are taken 63 at a time.
+struct TileFinder {
+  int c, g, slot0, rows;   // lane: tiles before the entry (in m tiles; split lists: of this XCD's, all of them), group, its
+                           // first slot, its rows
+  uint32_t inv;            // what tile_div divides by the entry's m tiles with
+  int b, n, x, tn;
+  bool split;
+  template <int TM>
+  __device__ __forceinline__ void init(const TokenSched& s, int xcd, int n_tiles_n, bool big_only) {
+    x = xcd; tn = n_tiles_n; b = 0;
+    n = as_const(s.len)[big_only ? kXcd + 1 + x : x];
+    split = as_const(s.len)[kXcd] != 0;
+    load<TM>(s);
+    if (split) {   // at most 7 groups
+      const int mine = (int)(threadIdx.x & 63) < n ? share((rows + TM - 1) / TM) : 0;
+      c = wave_incl_scan(mine) - mine;
     }
-    return false;
   }
-  if (n == 0 || local >= list[n].w * tn) return false;
-  int lo = 0, hi = n;  // list[lo].w * tn <= local < list[hi].w * tn
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (list[mid].w * tn <= local) lo = mid; else hi = mid;
+  // tiles of a group of m x tn that are this XCD's (split lists: x, x + 8, ...)
+  __device__ __forceinline__ int share(int m) const { return m * tn > x ? (m * tn - x + kXcd - 1) / kXcd : 0; }
+  template <int TM>
+  __device__ __forceinline__ void load(const TokenSched& s) {
+    // (No branch in here differs per lane: the compiler would fold it into the look-up's loop, take the tile for a value
+    // that differs per lane, and issue every operand request from a loop over the lanes.)
+    const int i = min(b + (int)(threadIdx.x & 63), s.cap - 1);
+    const int4 e = s.grp[(size_t)x * s.cap + i];
+    const int2 t = s.tiles[(size_t)x * s.cap + i];
+    g = e.x; slot0 = e.y; rows = e.z;
+    c = TM == 64 ? t.x : t.y;
+    finder_loaded();
+    inv = tile_div_inverse((uint32_t)max((rows + TM - 1) / TM, 1));
   }
-  g = list[lo].x;
-  const int tm = list[lo + 1].w - list[lo].w;
-  const int w = local - list[lo].w * tn;
-  nt = w / tm;
-  mt = w - nt * tm;
-  slot0 = list[lo].y;
-  rows = list[lo].z;
-  return true;
-}
+  // tile number `local` of the XCD (tile ids x, x + 8, ... are numbers 0, 1, ...); false: there is none
+  template <int TM>
+  __device__ __forceinline__ bool find(const TokenSched& s, int local, int& mt, int& nt, TileCoord& tc) {
+    const int lane = threadIdx.x & 63;
+    int i, w;
+    if (split) {
+      const unsigned long long m = __ballot(lane < n && c <= local);
+      if (m == 0) return false;
+      i = __popcll(m) - 1;
+    } else {
+      while (b > 0 && local < __builtin_amdgcn_readlane(c, 0) * tn) {   // (a cursor that is behind another one)
+        b -= 63;
+        load<TM>(s);
+      }
+      while (n - b > 63 && local >= __builtin_amdgcn_readlane(c, 63) * tn) {
+        b += 63;
+        load<TM>(s);
+      }
+      const int here = min(n - b, 63);
+      if (here <= 0 || local >= __builtin_amdgcn_readlane(c, here) * tn) return false;
+      i = __popcll(__ballot(lane < here && c * tn <= local)) - 1;
+    }
+    tc.g = __builtin_amdgcn_readlane(g, i);
+    tc.slot0 = __builtin_amdgcn_readlane(slot0, i);
+    tc.aux = __builtin_amdgcn_readlane(rows, i);
+    const int m = (tc.aux + TM - 1) / TM, before = __builtin_amdgcn_readlane(c, i);
+    if (split) {
+      if (local - before >= share(m)) return false;
+      w = x + kXcd * (local - before);
+    } else {
+      w = local - before * tn;
+    }
+    nt = tile_div(w, m, (uint32_t)__builtin_amdgcn_readlane((int)inv, i));
+    mt = w - nt * m;
+    return true;
+  }
+};
+
+// The same for the neuron-major tiles, of which every group has tm x tn: lane i holds entry b + i of the list.
+struct GroupFinder {
+  int g, slot0, rows;      // lane: group, its first slot, its rows
+  int b, n, x, tm, per;    // tiles of a group on this XCD
+  uint32_t inv_per, inv_tm;
+  bool split;
+  __device__ __forceinline__ void init(const TokenSched& s, int xcd, int tiles_m, int tiles_n, bool big_only) {
+    x = xcd; tm = tiles_m; b = 0;
+    n = as_const(s.len)[big_only ? kXcd + 1 + x : x];
+    split = as_const(s.len)[kXcd] != 0;   // this XCD takes the tiles x, x + 8, ... of every group
+    const int all = tiles_m * tiles_n;
+    per = !split ? all : all > x ? (all - x + kXcd - 1) / kXcd : 0;
+    inv_per = tile_div_inverse((uint32_t)max(per, 1));
+    inv_tm = tile_div_inverse((uint32_t)tm);
+    load(s);
+  }
+  __device__ __forceinline__ void load(const TokenSched& s) {
+    const int4 e = s.grp[(size_t)x * s.cap + min(b + (int)(threadIdx.x & 63), s.cap - 1)];
+    g = e.x; slot0 = e.y; rows = e.z;
+    finder_loaded();
+  }
+  __device__ __forceinline__ bool find(const TokenSched& s, int local, int& mt, int& nt, TileCoord& tc) {
+    if (per == 0) return false;
+    const int gi = tile_div(local, per, inv_per);
+    if (gi >= n) return false;
+    if (gi < b || gi >= b + 64) { b = gi & ~63; load(s); }
+    int w = local - gi * per;
+    if (split) w = x + kXcd * w;
+    nt = tile_div(w, tm, inv_tm);
+    mt = w - nt * tm;
+    tc.g = __builtin_amdgcn_readlane(g, gi - b);
+    tc.slot0 = __builtin_amdgcn_readlane(slot0, gi - b);
+    tc.aux = __builtin_amdgcn_readlane(rows, gi - b);
+    return true;
+  }
+};
 
 }  // namespace meft

@@ -24,7 +24,6 @@
 // beyond the stream) gets an offset outside the buffer, which loads zeros without touching memory.
 #pragma once
 #include "gemm_mfma.h"
-#include "tile_div.h"
 
 namespace meft {
 
@@ -77,72 +76,6 @@ __device__ __forceinline__ int nc_key(int k) {
   static_assert(COLS == 128, "");
   return 4 * (k & 3);
 }
-
-// Where the tile ids of one XCD lie, out of registers: lane i holds entry i of the XCD's group list, so that a tile is
-// found by a ballot (in memory it is a chain of six dependent scalar loads, a microsecond per tile).  Lists of more than
-// 63 groups are taken 63 at a time; tile ids only grow.
-struct TileFinder {
-  int c, g, slot0, rows;   // lane: tiles before the entry (in m tiles), group, its first slot, its rows
-  int mts;                 // its m tiles
-  uint32_t inv;            // and what tile_div divides by it with
-  int first, mine;         // split lists: this XCD's tiles before the entry, and of it
-  int b, n, x, tn;
-  bool split;
-  template <int TM>
-  __device__ __forceinline__ void init(const TokenSched& s, int xcd, int n_tiles_n, bool big_only) {
-    x = xcd; tn = n_tiles_n; b = 0;
-    n = as_const(s.len)[big_only ? kXcd + 1 + x : x];
-    split = as_const(s.len)[kXcd] != 0;
-    load<TM>(s);
-  }
-  template <int TM>
-  __device__ __forceinline__ void load(const TokenSched& s) {
-    const int lane = threadIdx.x & 63, i = min(b + lane, s.cap - 1);
-    const int4 e = s.grp[(size_t)x * s.cap + i];
-    const int2 t = s.tiles[(size_t)x * s.cap + i];
-    g = e.x; slot0 = e.y; rows = e.z;
-    c = TM == 64 ? t.x : t.y;
-    mts = max(__shfl_down(c, 1, 64) - c, 1);
-    inv = tile_div_inverse((uint32_t)mts);
-    if (split) {   // at most 7 groups
-      const int all = mts * tn;
-      mine = lane < n && all > x ? (all - x + kXcd - 1) / kXcd : 0;
-      first = wave_incl_scan(mine) - mine;
-    }
-  }
-  // tile number `local` of the XCD (tile ids x, x + 8, ... are numbers 0, 1, ...); false: there is none
-  template <int TM>
-  __device__ __forceinline__ bool find(const TokenSched& s, int local, int& mt, int& nt, TileCoord& tc) {
-    const int lane = threadIdx.x & 63;
-    int i, w;
-    if (split) {
-      const unsigned long long m = __ballot(lane < n && first <= local);
-      if (m == 0) return false;
-      i = __popcll(m) - 1;
-      const int r = local - __builtin_amdgcn_readlane(first, i);
-      if (r >= __builtin_amdgcn_readlane(mine, i)) return false;
-      w = x + kXcd * r;
-    } else {
-      for (;;) {
-        const int here = min(n - b, 63);
-        if (here <= 0) return false;
-        if (local < __builtin_amdgcn_readlane(c, here) * tn) break;
-        if (b + here >= n) return false;
-        b += 63;
-        load<TM>(s);
-      }
-      i = __popcll(__ballot(lane < min(n - b, 63) && c * tn <= local)) - 1;
-      w = local - __builtin_amdgcn_readlane(c, i) * tn;
-    }
-    const int m = __builtin_amdgcn_readlane(mts, i);
-    nt = tile_div(w, m, (uint32_t)__builtin_amdgcn_readlane((int)inv, i));
-    mt = w - nt * m;
-    tc.g = __builtin_amdgcn_readlane(g, i);
-    tc.slot0 = __builtin_amdgcn_readlane(slot0, i);
-    tc.aux = __builtin_amdgcn_readlane(rows, i);
-    return true;
-  }
-};
 
 template <class P>
 constexpr int gemm_tile_lds() { return 3 * (P::kTM + P::kTNt) * kTK * 2; }

@@ -676,7 +676,7 @@ void launch_dispatch(const meft_shape& s, const DispatchWs& w, const int32_t* bl
                   s.top_e, epc, s.n_blocks, nullptr, w.chunk_hist, clear, clear_words);
     const DispatchTables tab{w.cnt, w.group_off, w.tile_off, BM, sched_cap(s), want_sched ? w.sched_pairs : nullptr,
                              w.sched_tiles, w.sched_len, small, small ? w.small_ent : nullptr, w.small_grp, w.small_cnt};
-    int32_t* tok = dense ? w.tok_of_slot : nullptr;
+    int32_t* tok = dense || want_sched ? w.tok_of_slot : nullptr;
     int lg = 0;
     while ((1 << lg) < s.n_blocks) ++lg;
     if (s.n_blocks <= kDispScanBlocks && (int64_t)n_chunks * s.n_blocks <= kDispScanMax) {
@@ -698,7 +698,7 @@ void launch_dispatch(const meft_shape& s, const DispatchWs& w, const int32_t* bl
   MEFT_LAUNCH("count_blocks", count_blocks_kernel, dim3(s.n_blocks), dim3(1024), 0, st, w.sblk, n_ent, w.cnt);
   MEFT_LAUNCH("fill_groups", fill_groups_kernel, dim3(s.n_blocks), dim3(1024), 0, st, w.sblk, n_ent, w.cnt,
               s.n_blocks, BM, w.group_off, w.tile_off, w.perm);
-  if (dense) {
+  if (dense || want_sched) {
     MEFT_LAUNCH("slot_maps", slot_maps_kernel, dim3((n_ent + kSlotPad + 255) / 256), dim3(256), 0, st, w.perm, w.group_off,
                 s.n_blocks, s.top_e, w.sblk, small, w.tok_of_slot, w.slot_of_ent);
   }

@@ -11,8 +11,8 @@
 
 namespace meft {
 
-// ceil(2^32 / m) for m > 1 (0 for m == 1, where tile_div does not use it)
-MEFT_HOST_DEVICE uint32_t tile_div_inverse(uint32_t m) { return m > 1 ? 0xFFFFFFFFu / m + 1u : 0u; }
+// ceil(2^32 / m) for m > 1 (0 for m == 1, where tile_div does not use it).  No branch: it would differ per lane.
+MEFT_HOST_DEVICE uint32_t tile_div_inverse(uint32_t m) { return 0xFFFFFFFFu / m + 1u; }
 
 // w / m for 0 <= w < 2^31 and 1 <= m < 2^31.  inv = (2^32 + e) / m with 0 <= e < m, so w * inv / 2^32 is too large by
 // w * e / (m * 2^32) < 1/2: its floor is the quotient or, from w * m around 2^32 on, one more.
