@@ -54,9 +54,10 @@ def kernel_models(cfg, n_touched):
         "score_gemm": dict(bound="mfma", flop=dense, bytes=act + N * d * s),
         "topk_select": dict(bound="hbm", flop=0.0, bytes=T * C * 4.0 + P * 8.0),
         # per-pair kernels: each pair moves one row per gathered matrix (no reuse across pairs is assumed)
-        "gather_fwd": dict(bound="hbm", flop=pair, bytes=P * d * s + act + P * 8.0),
-        "gather_bwd": dict(bound="hbm", flop=2 * pair, bytes=2.0 * P * d * s + 2.0 * act + P * 12.0),
-        "seg_reduce": dict(bound="hbm", flop=2 * pair, bytes=2.0 * P * d * s + P * 12.0 + 2.0 * rows),
+        "pair_out": dict(bound="hbm", flop=pair, bytes=P * d * s + act + P * 8.0),
+        "pair_dh": dict(bound="hbm", flop=pair, bytes=P * d * s + act + P * 8.0),
+        "seg_dv": dict(bound="hbm", flop=2 * pair, bytes=P * d * s + P * 12.0 + 2.0 * rows),
+        "seg_dk": dict(bound="hbm", flop=pair, bytes=P * d * s + P * 12.0 + rows),
         # block-dense kernels: compulsory = operand rows once + result rows once
         "value_gemm": dict(bound="hbm", flop=pair, bytes=rows + P * 8.0 + act, dense_flop=dense),
         "dact_gemm": dict(bound="hbm", flop=pair, bytes=act + rows + P * 8.0, dense_flop=dense),
@@ -85,7 +86,7 @@ STAGE_SYMBOL = {
     "topk_select": ("topk_select_reg_kernel<16, true>", "topk_select_reg_kernel<32, true>", "topk_select_reg_kernel<4, true>"),
     "out_rows": "token_rows_kernel<2, false>", "dh_rows": "token_rows_kernel<2, false>",
 }
-GATHER_SCATTER = ("value_gemm", "dact_gemm", "dh_gemm", "dV_gemm", "dK_gemm", "gather_fwd", "gather_bwd", "seg_reduce")
+GATHER_SCATTER = ("value_gemm", "dact_gemm", "dh_gemm", "dV_gemm", "dK_gemm", "pair_out", "pair_dh", "seg_dv", "seg_dk")
 
 
 def profiled_traffic(workload, stage):

@@ -77,6 +77,37 @@ struct Vec8<bf16_t> {
   }
 };
 
+// One 16-byte word of a row as floats.
+template <typename T>
+struct Vec16;
+
+template <>
+struct Vec16<float> {
+  static constexpr int kElems = 4;
+  static __device__ __forceinline__ void unpack(u32x4 a, float (&v)[4]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = __uint_as_float(a[i]);
+  }
+  static __device__ __forceinline__ void store(float* p, const float (&v)[4]) {
+    *reinterpret_cast<f32x4*>(p) = f32x4{v[0], v[1], v[2], v[3]};
+  }
+  static __device__ __forceinline__ void store_f32(float* p, const float (&v)[4]) { store(p, v); }
+};
+
+template <>
+struct Vec16<bf16_t> {
+  static constexpr int kElems = 8;
+  static __device__ __forceinline__ void unpack(u32x4 a, float (&v)[8]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      v[2 * i] = __uint_as_float(a[i] << 16);
+      v[2 * i + 1] = __uint_as_float(a[i] & 0xFFFF0000u);
+    }
+  }
+  static __device__ __forceinline__ void store(bf16_t* p, const float (&v)[8]) { Vec8<bf16_t>::store(p, v); }
+  static __device__ __forceinline__ void store_f32(float* p, const float (&v)[8]) { Vec8<float>::store(p, v); }
+};
+
 // ---- wave-level reductions -----------------------------------------------------------------
 // sum over the wave, in every lane: DPP moves inside the rows of 16 lanes, then two lane permutes
 __device__ __forceinline__ float wave_sum(float v) {
@@ -88,6 +119,31 @@ __device__ __forceinline__ float wave_sum(float v) {
 #undef MEFT_DPP_ADDF
   v += __shfl_xor(v, 16, kWave);
   return v + __shfl_xor(v, 32, kWave);
+}
+
+// eight sums at once: lane l receives the sum over the wave of v[l % 8].  Lanes hand the values they do not keep to a
+// neighbour (23 vector instructions and two permutes instead of eight times four and two).
+__device__ __forceinline__ float wave_sum8(const float (&v)[8]) {
+  const int lane = threadIdx.x & 63;
+  const bool b0 = (lane & 1) != 0, b1 = (lane & 2) != 0, b2 = (lane & 4) != 0;
+  float a[4], c[2];
+#define MEFT_DPP_GET(x, ctrl) __builtin_amdgcn_update_dpp(0.f, (x), ctrl, 0xF, 0xF, false)
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const float give = b0 ? v[2 * i] : v[2 * i + 1];
+    a[i] = (b0 ? v[2 * i + 1] : v[2 * i]) + MEFT_DPP_GET(give, 0xB1);   // quad_perm [1,0,3,2]
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const float give = b1 ? a[2 * i] : a[2 * i + 1];
+    c[i] = (b1 ? a[2 * i + 1] : a[2 * i]) + MEFT_DPP_GET(give, 0x4E);   // quad_perm [2,3,0,1]
+  }
+  const float give = b2 ? c[0] : c[1];
+  float r = (b2 ? c[1] : c[0]) + MEFT_DPP_GET(give, 0x124);             // row_ror:4, the quad four lanes away
+  r += MEFT_DPP_GET(r, 0x128);                                           // row_ror:8
+#undef MEFT_DPP_GET
+  r += __shfl_xor(r, 16, kWave);
+  return r + __shfl_xor(r, 32, kWave);
 }
 
 // orders a wave's own LDS accesses (writes by some lanes, then reads by others) without a workgroup barrier

@@ -290,6 +290,8 @@ struct BwdWs : DenseWs {
   // gather path
   float* ds;
   int32_t *cnt_n, *seg_off, *pair_list, *pair_sorted, *totals;   // pair_sorted also holds the pairs' places (pair_count)
+  int2* seg;         // (token, activation) of the pairs, segment by segment
+  float* ds_part;    // partial activation gradients in the same order, one piece per group of column slices
   PairSums* sums;
   SegWork* work;     // at most one chunk per touched neuron plus one per kSegChunk pairs
   int4* multi;       // neurons of more than one chunk
@@ -299,7 +301,7 @@ struct BwdWs : DenseWs {
     Carver c(ws);
     const size_t P = (size_t)s.T * s.top_k;
     ds = nullptr; cnt_n = seg_off = pair_list = pair_sorted = totals = nullptr; seg_part = nullptr;
-    sums = nullptr; work = nullptr; multi = nullptr;
+    sums = nullptr; work = nullptr; multi = nullptr; seg = nullptr; ds_part = nullptr;
     if (use_dense(s)) {
       carve_dense(s, c);
     } else {
@@ -314,6 +316,9 @@ struct BwdWs : DenseWs {
       work = c.take<SegWork>(n_seg + P / kSegChunk + 1);
       multi = c.take<int4>(P / kSegChunk + 1);
       seg_part = c.take<float>(seg_multi_chunks(s) * 2 * (size_t)s.d);
+      seg = c.take<int2>(P);
+      const size_t slices = ((size_t)s.d * (s.dtype == MEFT_BF16 ? 2 : 4) + 1023) / 1024;
+      ds_part = c.take<float>(P * (slices < kDsParts ? slices : kDsParts));
     }
     bytes = c.off;
   }
@@ -510,61 +515,57 @@ void launch_gemm_nt(const meft_shape& s, const GemmNTArgs& a, int max_mtiles_bf1
   }
 }
 
-template <typename T>
-void launch_gather_fwd(const meft_shape& s, const void* V, const int32_t* idx, const float* act, void* out,
-                       hipStream_t st) {
-  int nthr, nv;
-  row_launch(s.d, nthr, nv);
-  const T* v = static_cast<const T*>(V);
-  T* o = static_cast<T*>(out);
-#define GF(NV) MEFT_LAUNCH("gather_fwd", (gather_fwd_kernel<T, NV>), dim3(s.T), dim3(nthr), 0, st, v, idx, act, s.d, s.top_k, s.N, o)
-  switch (nv) { case 1: GF(1); break; case 2: GF(2); break; case 4: GF(4); break; default: GF(8); }
-#undef GF
-}
-
-// (also clears clear[0 .. n_clear))
-template <typename T>
-void launch_gather_bwd(const meft_shape& s, const void* K, const void* V, const void* dOut, const int32_t* idx,
-                       const float* act, float* ds, void* dh, int32_t* clear, size_t n_clear, hipStream_t st) {
-  const T *k = static_cast<const T*>(K), *v = static_cast<const T*>(V), *g = static_cast<const T*>(dOut);
-  T* o = static_cast<T*>(dh);
-  // a wave per pair holds dOut's and dh's rows in fp32 and one row each of V and K: up to 4096 bf16 or 2048 fp32 columns
-  const int cols = (s.d + 511) / 512, tx = s.T < (1 << 23) ? s.T : 1 << 23;
-#define GW(NV) MEFT_LAUNCH("gather_bwd", (gather_bwd_wave_kernel<T, NV>), dim3(tx, (s.T + tx - 1) / tx), dim3(256), 0, st, k, v, g, idx, act, s.T, s.d, s.top_k, s.N, ds, o, clear, n_clear)
-  if (cols <= 1) { GW(1); return; }
-  if (cols <= 2) { GW(2); return; }
-  if (cols <= 4) { GW(4); return; }
-  if constexpr (sizeof(T) == 2) {
-    if (cols <= 8) { GW(8); return; }
-  }
-#undef GW
-  MEFT_LAUNCH("fill_i32", fill_i32_kernel, dim3((unsigned)((n_clear + 255) / 256)), dim3(256), 0, st, clear, n_clear, 0);
-  int nthr, nv;
-  row_launch(s.d, nthr, nv);
-#define GB(NV, PB) MEFT_LAUNCH("gather_bwd", (gather_bwd_kernel<T, NV, PB>), dim3(s.T), dim3(nthr), 0, st, k, v, g, idx, act, s.d, s.top_k, s.N, ds, o)
-  if constexpr (sizeof(T) == 4) {   // bf16 rows of up to 4096 columns are above
-    if (nv <= 2) { GB(2, 8); return; }
-  }
-  if (nv == 4) GB(4, 4); else GB(8, 2);
-#undef GB
+// A launch of n workgroups of 256 threads, n rounded up to a multiple of 8 (they go to the XCDs in turn), along x and then y
+// (a launch takes fewer than 2^32 threads along x).
+dim3 grid_xcd(int64_t n) {
+  const int64_t all = (n + 7) / 8 * 8, x = all < (1 << 23) ? all : 1 << 23;
+  return dim3((unsigned)x, (unsigned)((all + x - 1) / x));
 }
 
 template <typename T>
-void launch_seg_reduce(const meft_shape& s, const BwdWs& w, const float* act, const void* h, const void* dOut, void* dK,
-                       void* dV, hipStream_t st) {
-  const T *hh = static_cast<const T*>(h), *g = static_cast<const T*>(dOut);
-  T *pk = static_cast<T*>(dK), *pv = static_cast<T*>(dV);
-  const int64_t P = (int64_t)s.T * s.top_k, n_seg = s.N < P ? s.N : P;
+int row_slices(const meft_shape& s) { return (s.d + 64 * Vec16<T>::kElems - 1) / (64 * Vec16<T>::kElems); }   // of 1 KB
+
+template <typename T, int kAcc>
+void launch_pair_rows(const char* name, const meft_shape& s, const void* W, const int32_t* idx, const float* coef,
+                      const float* gate, void* row, const SegFinish<T>& f, hipStream_t st) {
+  const int64_t groups = row ? ((int64_t)s.T + 3) / 4 * row_slices<T>(s) : 0;
+  if (groups + f.n_wg == 0) return;
+  MEFT_LAUNCH(name, (pair_rows_kernel<T, kAcc>), grid_xcd(f.n_wg + (groups + 7) / 8 * 8), dim3(256), 0, st, static_cast<const T*>(W), idx, coef,
+              gate, row ? s.T : 0, s.d, s.top_k, s.N, static_cast<T*>(row), f);
+}
+
+// The backward of the per-pair path.
+template <typename T>
+void launch_pair_bwd(const meft_shape& s, const BwdWs& w, const void* h, const void* K, const void* V, const int32_t* idx,
+                     const float* act, const void* dOut, void* dh, void* dK, void* dV, int32_t* touched, int32_t* n_touched,
+                     hipStream_t st) {
+  const int P = s.T * s.top_k;
+  const size_t n_pairs = (size_t)P;
+  const dim3 pairs((unsigned)(((int64_t)P + 255) / 256));
+  MEFT_LAUNCH("fill_i32", fill_i32_kernel, dim3((unsigned)(((size_t)s.N + 255) / 256)), dim3(256), 0, st, w.cnt_n, (size_t)s.N, 0);
+  MEFT_LAUNCH("pair_count", pair_count_kernel, pairs, dim3(256), 0, st, idx, P, s.N, w.cnt_n, w.pair_sorted);
+  const int n_chunks = (s.N + kScanChunk - 1) / kScanChunk;
+  if (w.sums && s.N > kScanSelfMax)
+    MEFT_LAUNCH("pair_sums", pair_sums_kernel, dim3(n_chunks), dim3(kScanThreads), 0, st, w.cnt_n, s.N, w.sums);
+  MEFT_LAUNCH("pair_scan", pair_scan_kernel, dim3(n_chunks), dim3(kScanThreads), 0, st, w.cnt_n, s.N,
+              s.N > kScanSelfMax ? w.sums : nullptr, w.seg_off, touched, n_touched, w.work, w.multi, w.totals);
+  MEFT_LAUNCH("pair_fill", pair_fill_kernel, pairs, dim3(256), 0, st, idx, P, s.N, w.seg_off, w.pair_sorted, w.pair_list);
   // four chunks per workgroup: at most one chunk per touched neuron plus one per kSegChunk pairs
-  const int64_t groups = (n_seg + P / kSegChunk + 3) / 4;
-  MEFT_LAUNCH("seg_reduce", seg_reduce_kernel<T>, dim3((unsigned)groups, (s.d + 511) / 512), dim3(256), 0, st, w.work,
-              w.totals, w.pair_list, w.pair_sorted, act, w.ds, hh, g, s.d, s.top_k, pk, pv, w.seg_part);
-  if (P > kSegChunk) {
-    const int finish = (int)(P / kSegChunk < 4096 ? P / kSegChunk + 1 : 4096);
-    MEFT_LAUNCH("seg_finish", seg_finish_kernel<T>, dim3(finish), dim3(256), 0, st, w.multi, w.totals, w.seg_part, s.d, pk, pv);
-  }
+  const int64_t n_seg = s.N < P ? s.N : P, groups = (n_seg + P / kSegChunk + 3) / 4;
+  // (a token's ids may repeat where they were clamped: more than kSegChunk pairs may have one neuron whatever T is)
+  const int n_multi = P <= kSegChunk ? 0 : P / kSegChunk < 512 ? P / kSegChunk + 1 : 512;
+  MEFT_LAUNCH("seg_sort", seg_sort_kernel, dim3((unsigned)(n_multi + ((int64_t)P + 255) / 256)), dim3(256), 0, st, w.multi, w.totals,
+              w.seg_off, w.pair_list, idx, act, P, s.N, s.top_k, n_multi, w.pair_sorted, w.seg);
+  const int slices = row_slices<T>(s), parts = slices < kDsParts ? slices : kDsParts;
+  auto seg_grid = [&](int n) { return grid_xcd(groups * n < kSegWorkgroups ? groups * n : kSegWorkgroups); };
+  MEFT_LAUNCH("seg_dv", seg_dv_kernel<T>, seg_grid(parts), dim3(256), 0, st, w.work, w.totals, w.seg,
+              static_cast<const T*>(V), static_cast<const T*>(dOut), s.d, slices, n_pairs, static_cast<T*>(dV), w.seg_part, w.ds_part);
+  MEFT_LAUNCH("seg_dk", seg_dk_kernel<T>, seg_grid(slices), dim3(256), 0, st, w.work, w.totals, w.seg, w.pair_sorted,
+              w.ds_part, static_cast<const T*>(h), s.d, slices, n_pairs, static_cast<T*>(dK), w.seg_part, dh ? w.ds : nullptr);
+  const int n_fin = n_multi == 0 ? 0 : P / kSegChunk < 4096 ? (P / kSegChunk + 8) / 8 * 8 : 4096;
+  const SegFinish<T> f{n_fin, w.multi, w.totals, w.seg_part, static_cast<T*>(dK), static_cast<T*>(dV)};
+  launch_pair_rows<T, 4>("pair_dh", s, K, idx, w.ds, act, dh, f, st);
 }
-
 
 constexpr int kPersistentWgs = 256;   // compute units of an MI355X; a multiple of the 8 XCDs
 
@@ -971,9 +972,9 @@ static meft_status fwd_impl(const meft_shape& s, const void* h, const void* K, c
     }, st);
     launch_token_rows("out_rows", s, w.part, w, V, idx, act, out, SmallDvdk{}, st);
   } else if (s.dtype == MEFT_BF16) {
-    launch_gather_fwd<bf16_t>(s, V, idx, act, out, st);
+    launch_pair_rows<bf16_t, 1>("pair_out", s, V, idx, act, nullptr, out, SegFinish<bf16_t>{}, st);
   } else {
-    launch_gather_fwd<float>(s, V, idx, act, out, st);
+    launch_pair_rows<float, 1>("pair_out", s, V, idx, act, nullptr, out, SegFinish<float>{}, st);
   }
   return launch_status();
 }
@@ -1000,8 +1001,6 @@ static meft_status bwd_impl(const meft_shape& s, const void* h, const void* K, c
                             const float* act, const void* dOut, void* dh, void* dK, void* dV, int32_t* touched,
                             int32_t* n_touched, const BwdWs& w, hipStream_t st, hipEvent_t wait_k,
                             hipEvent_t wait_v, HostRows dV_rows) {
-  const int P = s.T * s.top_k;
-
   if (use_dense(s)) {
     const int bsp = round64(s.block_size);
     const uint16_t *hh = static_cast<const uint16_t*>(h), *kk = static_cast<const uint16_t*>(K),
@@ -1089,22 +1088,8 @@ static meft_status bwd_impl(const meft_shape& s, const void* h, const void* K, c
 
   if (wait_v && hipStreamWaitEvent(st, wait_v, 0) != hipSuccess) return MEFT_ERR_DEVICE;
   if (wait_k && hipStreamWaitEvent(st, wait_k, 0) != hipSuccess) return MEFT_ERR_DEVICE;
-  if (s.dtype == MEFT_BF16) launch_gather_bwd<bf16_t>(s, K, V, dOut, idx, act, w.ds, dh, w.cnt_n, s.N, st);
-  else launch_gather_bwd<float>(s, K, V, dOut, idx, act, w.ds, dh, w.cnt_n, s.N, st);
-
-  MEFT_LAUNCH("pair_count", pair_count_kernel, dim3((P + 255) / 256), dim3(256), 0, st, idx, P, s.N, w.cnt_n, w.pair_sorted);
-  const int n_chunks = (s.N + kScanChunk - 1) / kScanChunk;
-  if (w.sums && s.N > kScanSelfMax)
-    MEFT_LAUNCH("pair_sums", pair_sums_kernel, dim3(n_chunks), dim3(256), 0, st, w.cnt_n, s.N, w.sums);
-  MEFT_LAUNCH("pair_scan", pair_scan_kernel, dim3(n_chunks), dim3(256), 0, st, w.cnt_n, s.N,
-              s.N > kScanSelfMax ? w.sums : nullptr, w.seg_off, touched, n_touched, w.work, w.multi, w.totals);
-  MEFT_LAUNCH("pair_fill", pair_fill_kernel, dim3((P + 255) / 256), dim3(256), 0, st, idx, P, s.N, w.seg_off,
-              w.pair_sorted, w.pair_list);
-  if (P > kSegChunk)   // else no segment of more than one chunk (a token's ids may repeat where they were clamped)
-    MEFT_LAUNCH("seg_sort", seg_sort_kernel, dim3(P / kSegChunk < 512 ? P / kSegChunk + 1 : 512), dim3(256), 0, st, w.multi,
-                w.totals, w.seg_off, w.pair_list, w.pair_sorted);
-  if (s.dtype == MEFT_BF16) launch_seg_reduce<bf16_t>(s, w, act, h, dOut, dK, dV, st);
-  else launch_seg_reduce<float>(s, w, act, h, dOut, dK, dV, st);
+  if (s.dtype == MEFT_BF16) launch_pair_bwd<bf16_t>(s, w, h, K, V, idx, act, dOut, dh, dK, dV, touched, n_touched, st);
+  else launch_pair_bwd<float>(s, w, h, K, V, idx, act, dOut, dh, dK, dV, touched, n_touched, st);
   if (dV_rows.dst) launch_rows_to_host(s, touched, n_touched, dV, dV_rows.dst, st);   // complete with dK: nothing to gain
   return launch_status();
 }
