@@ -190,12 +190,13 @@ bool route_on_tiles(const meft_shape& s) {
     const double chain = 9.0 + 0.62 * kt / parts, stream = 6.0 + 2.0 * s.T * (double)s.d / 4.6e6;
     return untiled > 1.05 * (chain > stream ? chain : stream);
   }
-  // The untiled time goes by tokens x groups of 64 blocks, and by the steps.  64 blocks, 16384 and 65536 tokens: fp32 d 256
-  // 26.1 / 25.3 and 87.8 / 50.4, d 768 43 / 57 and 159 / 112, d 1024 45 / 72 and 176 / 156, d 4096 167 / 279 and 672 / 588
-  // (1024 blocks, 16384 tokens: 2530 / 1957); bf16 d 1000 19.5 / 25.5 and 65 / 42, d 4104 85 / 68 and 385 / 142 (1024
-  // blocks, 16384 tokens: 1404 / 274).
+  // The untiled time goes by tokens x groups of 64 blocks, and by the steps.  fp32: 64 blocks, d 768 18.4 / 19.5 at 4096 tokens,
+  // 23.4 / 20.4 at 8192, 81 / 46 at 32768, d 4096 81 / 75 at 8192; 256 blocks, d 1024 24.5 / 24.7 at 2048, 80 / 54 at 8192;
+  // 1024 blocks, d 512 51 / 42 at 2048; 8 blocks, d 1024 69 / 53 at 32768 (the tiled one is level from about 6000 tokens on;
+  // the line takes it where it is ahead by a third at every size measured).  bf16, 16384 and 65536 tokens: d 1000 19.5 / 25.5
+  // and 65 / 42, d 4104 85 / 68 and 385 / 142 (1024 blocks, 16384 tokens: 1404 / 274).
   const int64_t reads = (int64_t)s.T * ((s.n_blocks + 63) / 64);
-  return reads * padded > (es == 2 ? 28672 : 49152) * steps;
+  return reads * padded > (es == 2 ? 28672 : 16384) * steps;
 }
 
 struct RouteWs {
@@ -504,15 +505,23 @@ void row_launch(int d, int& nthr, int& nv) {
   nv = need <= 1 ? 1 : need <= 2 ? 2 : need <= 4 ? 4 : 8;
 }
 
-void launch_gemm_nt(const meft_shape& s, const GemmNTArgs& a, int max_mtiles_bf16, int max_mtiles_f32,
-                    const char* name, hipStream_t st) {
+// Rows of a tile of the fp32 score kernel: 64, which take fewer bytes per flop, once that gives every compute unit four tiles.
+// Forward, us, 64 / 32 rows: one block of 16384, 1000 tokens, d 1024 366 / 404; 16 blocks of 256, d 4096, 2000 tokens 330 / 269.
+int gemm_f32_rows(int64_t rows, int groups, int cols) {
+  return (rows / 64 + groups / 2) * ((cols + kGemmF32BN - 1) / kGemmF32BN) >= 1024 ? 64 : 32;
+}
+
+// `rows` rows in `groups` groups, each of which may end with a partial tile
+void launch_gemm_nt(const meft_shape& s, const GemmNTArgs& a, int64_t rows, int groups, const char* name, hipStream_t st) {
   if (s.dtype == MEFT_BF16) {
-    dim3 grid(max_mtiles_bf16, (a.Ng + kGemmBN - 1) / kGemmBN);
+    dim3 grid((unsigned)(rows / kGemmBM + groups), (a.Ng + kGemmBN - 1) / kGemmBN);
     MEFT_LAUNCH(name, gemm_nt_bf16_kernel, grid, dim3(256), 0, st, a);
-  } else {
-    dim3 grid(max_mtiles_f32, (a.Ng + kGemmF32BN - 1) / kGemmF32BN);
-    MEFT_LAUNCH(name, gemm_nt_f32_kernel, grid, dim3(256), 0, st, a);
+    return;
   }
+  const int bm = gemm_f32_rows(rows, groups, a.Ng);
+  const dim3 grid((unsigned)(((rows / bm + groups) * ((a.Ng + kGemmF32BN - 1) / kGemmF32BN) + 7) / 8 * 8));
+  if (bm == 64) MEFT_LAUNCH(name, gemm_nt_f32_kernel<64>, grid, dim3(256), 0, st, a);
+  else MEFT_LAUNCH(name, gemm_nt_f32_kernel<32>, grid, dim3(256), 0, st, a);
 }
 
 // A launch of n workgroups of 256 threads, n rounded up to a multiple of 8 (they go to the XCDs in turn), along x and then y
@@ -872,7 +881,7 @@ static meft_status route_impl(const meft_shape& s, const void* h, const void* Wg
     a.A = h; a.Bm = Wg; a.C = p; a.perm = nullptr; a.group_off = nullptr; a.tile_off = nullptr;
     a.n_groups = 1; a.M = s.T; a.Ng = s.n_blocks; a.Kdim = s.d; a.lda = s.d; a.ldb = s.d; a.ldc = s.n_blocks;
     a.e = 1;
-    launch_gemm_nt(s, a, (s.T + kGemmBM - 1) / kGemmBM, (s.T + kGemmF32BM - 1) / kGemmF32BM, "router_gemm", st);
+    launch_gemm_nt(s, a, s.T, 1, "router_gemm", st);
   }
   const size_t stride = (size_t)s.T * s.n_blocks;
 #define PK(Z) MEFT_LAUNCH("route_pick", (route_pick_kernel<Z>), dim3((s.T + 3) / 4), dim3(256), 0, st, p, n_part, stride, bias, s.T, s.n_blocks, s.top_e, block_idx, block_score)
@@ -898,7 +907,8 @@ static meft_status fwd_impl(const meft_shape& s, const void* h, const void* K, c
                             hipStream_t st, hipEvent_t wait_k, hipEvent_t wait_v) {
   const int n_ent = s.T * s.top_e;
   const int C = s.top_e * s.block_size;
-  const int BM = s.dtype == MEFT_BF16 ? kGemmBM : kGemmF32BM;
+  const int nb_used = s.n_blocks < n_ent ? s.n_blocks : n_ent;
+  const int BM = s.dtype == MEFT_BF16 ? kGemmBM : gemm_f32_rows(n_ent, nb_used, s.block_size);
 
   if (few_tokens(s)) {
     if (wait_k && hipStreamWaitEvent(st, wait_k, 0) != hipSuccess) return MEFT_ERR_DEVICE;
@@ -931,9 +941,7 @@ static meft_status fwd_impl(const meft_shape& s, const void* h, const void* K, c
     a.A = h; a.Bm = K; a.C = w.sc; a.perm = w.perm; a.group_off = w.group_off; a.tile_off = w.tile_off;
     a.n_groups = s.n_blocks; a.M = 0; a.Ng = s.block_size; a.Kdim = s.d; a.lda = s.d; a.ldb = s.d;
     a.ldc = s.block_size; a.e = s.top_e;
-    // upper bound on the number of m-tiles: every group may end with one partial tile
-    const int nb_used = s.n_blocks < n_ent ? s.n_blocks : n_ent;
-    launch_gemm_nt(s, a, n_ent / kGemmBM + nb_used, n_ent / kGemmF32BM + nb_used, "score_gemm", st);
+    launch_gemm_nt(s, a, n_ent, nb_used, "score_gemm", st);
   }
   if (!dense && s.top_k <= kBoundMaxK && C > kBoundMinC && C <= 1024 * 64) {
     MEFT_LAUNCH("topk_select_bound", topk_select_bound_kernel, dim3(s.T), dim3(1024), 0, st, w.sc, w.sblk, C, s.block_size,
