@@ -5,7 +5,13 @@
 //   ceil(cnt / BM), and on the matrix-core path tok_of_slot, slot_of_ent and the per-XCD tile schedule.
 // slot_of_ent carries kSmallSlot where the entry's group is one of at most small_rows tokens (small_groups.h).
 //
-// Up to 1024 blocks and 2^20 entries this takes two launches over chunks of whole tokens, at most 1024 entries each:
+// Small dispatches (dispatch_one_kernel: up to kDispOneTokens tokens, kDispOneEntries entries and kDispOneWork entries x blocks)
+// take one launch: a workgroup per block looks through all the entries (they come out of L2, and a launch costs more) and places
+// its own, and one more counts the entries of all blocks, writes the tables and deals the groups to the XCDs.  Two launches /
+// one: 2048 tokens x 4, 64 blocks 21.8 -> 11.2 us; 8192 x 4, 64 blocks 24 -> 14; 4096 x 8, 256 blocks 30 -> 18 (of either about
+// half by the faster tables).  At the limits, whole forward of a layer with d 64: 16384 x 4, 64 blocks 105.2 -> 99.8, 128
+// blocks 116.3 -> 105.4; beyond them 16384 x 8, 16 blocks 114.2 -> 126.1.
+// Beyond that, up to 1024 blocks and 2^20 entries, it takes two launches over chunks of whole tokens, at most 1024 entries each:
 //   dispatch_count   sorts every token's blocks, counts the entries of every block per chunk, and clears what the
 //                    forward or backward needs cleared;
 //   dispatch_place   every workgroup adds the chunk counts up for itself (a few thousand integers out of L2 cost less
@@ -29,6 +35,10 @@ constexpr int kDispMaxBlocks = 1024;    // LDS: 16 waves x n_blocks counters
 constexpr int kDispMaxEntries = 1 << 20;   // at most 2045 chunks (of 513 entries at top_e 513)
 constexpr int kDispScanBlocks = 512;    // dispatch_place adds up the chunk counts itself up to this many blocks
 constexpr int kDispScanMax = 32768;     // and this many counts
+
+constexpr int kDispOneTokens = 16 * 1024;   // one launch: tokens (sixteen per thread)
+constexpr int kDispOneEntries = 1 << 16;    // entries, which one workgroup counts
+constexpr int kDispOneWork = 1 << 23;       // and entries x blocks
 
 // Rank of this lane's entry among the entries of the same block in its wave, in lane (= entry) order; lane
 // `leader of the block` also writes the block's count in the wave to row[block] (row zeroed by the caller).
@@ -105,14 +115,22 @@ struct DispatchTables {
   int32_t *small_grp, *small_cnt;
 };
 
-// Entries of block tid (0 beyond n_blocks) -> all the tables.  Executed by one whole workgroup of 1024 threads.
-__device__ __forceinline__ void dispatch_tables(const DispatchTables& t, int rows, int n_blocks, int* s_w) {
+// Entries of block tid (0 beyond n_blocks) -> all the tables; with pad_tok also `pad` valid entries behind the last slot of
+// tok_of_slot.  Executed by one whole workgroup of 1024 threads, once per launch, so it is written for short code rather than
+// few instructions: what runs once waits for its instructions to come from memory.
+__device__ __forceinline__ void dispatch_tables(const DispatchTables& t, int rows, int n_blocks, int* s_w, int32_t* pad_tok,
+                                                int pad) {
   const int tid = threadIdx.x;
   int all_g, all_t;
   const int go = block_excl_scan_1024(rows, s_w, all_g);
-  const int to = block_excl_scan_1024((rows + t.BM - 1) / t.BM, s_w, all_t);
-  if (tid < n_blocks) { t.cnt[tid] = rows; t.group_off[tid] = go; t.tile_off[tid] = to; }
-  if (tid == 0) { t.group_off[n_blocks] = all_g; t.tile_off[n_blocks] = all_t; }
+  if (tid < n_blocks) { t.cnt[tid] = rows; t.group_off[tid] = go; }
+  if (tid == 0) t.group_off[n_blocks] = all_g;
+  if (t.grp == nullptr) {   // (the contractions on a tile schedule do not use it)
+    const int to = block_excl_scan_1024((rows + t.BM - 1) / t.BM, s_w, all_t);
+    if (tid < n_blocks) t.tile_off[tid] = to;
+    if (tid == 0) t.tile_off[n_blocks] = all_t;
+  }
+  if (pad_tok != nullptr && tid < pad) pad_tok[all_g + tid] = 0;   // (entries of block -1 have no slot)
   if (t.small_ent != nullptr) {
     small_lists_body(rows, go, n_blocks, t.small_rows, t.small_ent, t.small_grp, t.small_cnt, s_w);
   }
@@ -139,7 +157,7 @@ __global__ __launch_bounds__(1024) void dispatch_scan_kernel(int32_t* __restrict
       }
     }
   }
-  dispatch_tables(t, tot, n_blocks, s_w);
+  dispatch_tables(t, tot, n_blocks, s_w, nullptr, 0);
 }
 
 // pass 2: perm, and with tok_of_slot != nullptr the slot maps (tok_of_slot padded by `pad` valid entries).
@@ -177,12 +195,7 @@ __global__ __launch_bounds__(1024) void dispatch_place_kernel(const int32_t* __r
     __syncthreads();
     const int rows = tid < n_blocks ? s_tot[tid] : 0;
     if (c == n_chunks) {
-      if (tok_of_slot != nullptr && tid < pad) {
-        int all = 0;   // entries in all (those of block -1 have no slot)
-        for (int z = 0; z < n_blocks; ++z) all += s_tot[z];
-        tok_of_slot[all + tid] = 0;
-      }
-      dispatch_tables(tab, rows, n_blocks, s_w);
+      dispatch_tables(tab, rows, n_blocks, s_w, tok_of_slot, pad);
       return;
     }
     int all;
@@ -218,6 +231,85 @@ __global__ __launch_bounds__(1024) void dispatch_place_kernel(const int32_t* __r
     }
   }
   if (!kScan && tok_of_slot != nullptr && c == 0 && tid < pad) tok_of_slot[tab.group_off[n_blocks] + tid] = 0;
+}
+
+// The whole dispatch in one launch of n_blocks + 1 workgroups.  kSort: `in` holds the token's blocks in any order, ids are
+// clamped, and sblk is written; otherwise `in` is sblk (-1: no entry).  A block that a token names twice gets two entries.
+// Also zeroes clear[0 .. clear_words).
+template <bool kSort>
+__global__ __launch_bounds__(1024) void dispatch_one_kernel(const int32_t* __restrict__ in, int n_tok, int e, int n_blocks,
+                                                            DispatchTables tab, int32_t* __restrict__ sblk,
+                                                            int32_t* __restrict__ perm, int32_t* __restrict__ tok_of_slot,
+                                                            int32_t* __restrict__ slot_of_ent, int pad,
+                                                            int32_t* __restrict__ clear, size_t clear_words) {
+  extern __shared__ int s_one[];   // [iterations][1024]: per token, blocks below b << 16 | entries of b;  [iterations * 16]
+  __shared__ int s_w[16];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int n_ent = n_tok * e, n_iter = (n_tok + 1023) >> 10;
+  for (size_t i = (size_t)blockIdx.x * 1024 + tid; i < clear_words; i += (size_t)gridDim.x * 1024) clear[i] = 0;
+  if (blockIdx.x == 0) {   // (first, as it takes longest)
+    if (tid < n_blocks) s_one[tid] = 0;
+    __syncthreads();
+    for (int i0 = 0; i0 < n_ent; i0 += 8 * 1024) {   // (eight loads on their way together)
+      int b[8];
+#pragma unroll
+      for (int z = 0; z < 8; ++z) {
+        const int i = i0 + z * 1024 + tid;
+        b[z] = in[min(i, n_ent - 1)];
+        if constexpr (kSort) b[z] = clampi(b[z], 0, n_blocks - 1);
+        b[z] = i < n_ent ? b[z] : -1;
+      }
+#pragma unroll
+      for (int z = 0; z < 8; ++z)
+        if ((unsigned)b[z] < (unsigned)n_blocks) atomicAdd(&s_one[b[z]], 1);
+    }
+    __syncthreads();
+    dispatch_tables(tab, tid < n_blocks ? s_one[tid] : 0, n_blocks, s_w, tok_of_slot, pad);
+    return;
+  }
+  const int b = (int)blockIdx.x - 1;
+  int* s_cnt = s_one + n_iter * 1024;
+  int below = 0;   // entries of this thread's tokens that belong to blocks before b
+#pragma unroll 1
+  for (int it = 0; it < n_iter; ++it) {
+    const int t = it * 1024 + tid;
+    int lt = 0, eq = 0;
+    if (t < n_tok) {
+      const int32_t* row = in + (size_t)t * e;
+#pragma unroll 4
+      for (int q = 0; q < e; ++q) {
+        int x = row[q];
+        if constexpr (kSort) x = clampi(x, 0, n_blocks - 1);
+        lt += (unsigned)x < (unsigned)b ? 1 : 0;
+        eq += x == b ? 1 : 0;
+      }
+    }
+    below += lt;
+    s_one[it * 1024 + tid] = lt << 16 | eq;
+    const int incl = wave_incl_scan(eq);
+    if (lane == 63) s_cnt[it * 16 + w] = incl;
+  }
+  int base, rows;   // entries of the blocks before, entries of this one
+  block_excl_scan_1024(below, s_w, base);   // (its barriers order the counts above as well)
+  const int mine = tid < n_iter * 16 ? s_cnt[tid] : 0;
+  const int before = block_excl_scan_1024(mine, s_w, rows);
+  if (tid < n_iter * 16) s_cnt[tid] = before;
+  __syncthreads();
+  const int flag = tok_of_slot != nullptr && rows <= tab.small_rows ? kSmallSlot : 0;
+#pragma unroll 1
+  for (int it = 0; it < n_iter; ++it) {
+    const int t = it * 1024 + tid, lt = s_one[t] >> 16, eq = s_one[t] & 0xFFFF;
+    const int first = base + s_cnt[it * 16 + w] + wave_incl_scan(eq) - eq;
+    for (int z = 0; z < eq; ++z) {
+      const int ent = t * e + lt + z, slot = first + z;
+      perm[slot] = ent;
+      if constexpr (kSort) sblk[ent] = b;
+      if (tok_of_slot != nullptr) {
+        tok_of_slot[slot] = t;
+        slot_of_ent[ent] = slot | flag;
+      }
+    }
+  }
 }
 
 }  // namespace meft

@@ -889,14 +889,6 @@ constexpr int kSchedLenInts = 2 * kXcd + 1;
 
 constexpr int kSchedSortMax = 1024;   // up to this many groups are dealt out longest first; more: round-robin
 
-// v[i] of a small wave-uniform array, i different per lane
-__device__ __forceinline__ int key_of_lane(const int (&v)[kXcd], int i) {
-  int r = v[0];
-#pragma unroll
-  for (int z = 1; z < kXcd; ++z) r = i == z ? v[z] : r;
-  return r;
-}
-
 __device__ __forceinline__ void sched_entry(int4* __restrict__ grp, int2* __restrict__ tiles, size_t at, int g, int slot0,
                                             int rows, int t64, int t128) {
   grp[at] = make_int4(g, slot0, rows, t128);
@@ -905,129 +897,127 @@ __device__ __forceinline__ void sched_entry(int4* __restrict__ grp, int2* __rest
 
 // Executed by one whole workgroup of 1024 threads; rows, slot0 = number of tokens and first slot of group threadIdx.x
 // (0 rows beyond n_groups).  n_groups <= kSchedSortMax.
+// One workgroup, once: what it costs is chains of instructions.  The ranks are counted by all threads, the deal proper is the
+// only serial part (scalar registers; a wave-wide arg-min per group took 110 ns each), and the lists are written by a wave per
+// XCD.  The workgroup that does this and the tables before it:
+// 15.5 -> 10 us with 64 groups, 24 -> 17 with 168 of 256.
 __device__ __forceinline__ void build_sched_body(int rows, int slot0, int n_groups, int cap, int4* __restrict__ grp,
                                                  int2* __restrict__ tiles, int* __restrict__ len, int small_rows) {
   __shared__ int s_rows[kSchedSortMax];
   __shared__ int s_slot[kSchedSortMax];
+  __shared__ int s_rank[kSchedSortMax];
   __shared__ int s_order[kSchedSortMax];
   __shared__ int s_sorted[kSchedSortMax];
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63;
   __syncthreads();   // the arrays may still be read from an earlier use
-  if (tid < n_groups) { s_rows[tid] = rows; s_slot[tid] = slot0; }
+  if (tid < n_groups) { s_rows[tid] = rows; s_slot[tid] = slot0; s_rank[tid] = 0; }
   const int n_full = __syncthreads_count(rows > 0);   // non-empty groups; also orders the writes above
-  if (tid < n_groups) {
-    int rank = 0;   // position in the order (rows descending, group id ascending): a permutation
-#pragma unroll 8
-    for (int g = 0; g < n_groups; ++g) {
-      const int r = s_rows[g];
-      rank += (r > rows || (r == rows && g < tid)) ? 1 : 0;
+  {
+    // position in the order (rows descending, group id ascending): a permutation.  Thread (part, g) counts the groups part,
+    // part + parts, ... before group g.
+    const int lg = n_groups > 1 ? 32 - __clz(n_groups - 1) : 0, g = tid & ((1 << lg) - 1), parts = 1024 >> lg;
+    if (g < n_groups) {
+      const int mine = s_rows[g];
+      int before = 0;
+#pragma unroll 4
+      for (int o = tid >> lg; o < n_groups; o += parts) before += s_rows[o] > mine - (o < g ? 1 : 0) ? 1 : 0;
+      if (before) atomicAdd(&s_rank[g], before);
     }
-    s_order[rank] = tid;
-    s_sorted[rank] = rows;
+  }
+  __syncthreads();
+  if (tid < n_groups) {
+    s_order[s_rank[tid]] = tid;
+    s_sorted[s_rank[tid]] = rows;
   }
   __syncthreads();
   // Fewer non-empty groups than XCDs: a deal of whole groups would leave XCDs idle.  Then every list holds every
   // group, len[kXcd] says so, and XCD x takes the tiles x, x + 8, ... of each group (TileFinder, GroupFinder).
   const bool split = n_full < kXcd;
   if (tid == 0) len[kXcd] = split ? 1 : 0;
-  if (tid >= 64) return;
-  const int lane = tid;
   if (split) {
-    if (lane < kXcd) {
+    if (tid < kXcd) {
       int t64 = 0, t128 = 0, n_big = 0;
       for (int i = 0; i < n_full; ++i) {
         const int g = s_order[i], r = s_sorted[i];
-        sched_entry(grp, tiles, (size_t)lane * cap + i, g, s_slot[g], r, t64, t128);
+        sched_entry(grp, tiles, (size_t)tid * cap + i, g, s_slot[g], r, t64, t128);
         n_big += r > small_rows ? 1 : 0;
         t64 += (r + 63) >> 6;
         t128 += (r + 127) >> 7;
       }
-      sched_entry(grp, tiles, (size_t)lane * cap + n_full, -1, 0, 0, t64, t128);
-      len[lane] = n_full;
-      len[kXcd + 1 + lane] = n_big;
+      sched_entry(grp, tiles, (size_t)tid * cap + n_full, -1, 0, 0, t64, t128);
+      len[tid] = n_full;
+      len[kXcd + 1 + tid] = n_big;
     }
     return;
   }
-  // The deal of the groups of more than 64 rows is sequential; lanes 0..7 each keep one XCD's load (in units of 64 rows
-  // plus a constant per group) as load * 8 + lane, a three-step DPP butterfly finds the least loaded XCD (ties to the
-  // lower one), and the loop does nothing else: 64 groups at a time come out of a register by lane reads and their XCDs
-  // go into one by lane writes.  List positions and tile numbers follow in parallel.
-  int n_deal = 0;
-  for (int i0 = 0; i0 < n_full; i0 += 64) n_deal += __popcll(__ballot(i0 + lane < n_full && s_sorted[min(i0 + lane, n_full - 1)] > 64));
-  int key = lane < kXcd ? lane : 0x7FFFFFFF;
-  int nx[kXcd], sx[kXcd], tx[kXcd], bx[kXcd];   // per XCD: list length, tiles of 64 and of 128 rows, groups > small_rows
+  int* s_xcd = s_rank;   // XCD of the i-th group of the order
+  if (tid < 64) {
+    // The groups of more than 64 rows one after another: each to the XCD with the least load (in units of 64 rows plus a
+    // constant per group; ties to the lower XCD).  key[0] < key[1] < ... are the loads * 8 + XCD; the first one grows by the
+    // group's weight and is put back in its place.
+    int n_deal = 0;
+    for (int i0 = 0; i0 < n_full; i0 += 64) n_deal += __popcll(__ballot(i0 + lane < n_full && s_sorted[min(i0 + lane, n_full - 1)] > 64));
+    int key[kXcd];
 #pragma unroll
-  for (int x = 0; x < kXcd; ++x) nx[x] = sx[x] = tx[x] = bx[x] = 0;
-  for (int i0 = 0; i0 < n_deal; i0 += 64) {
-    const int m = min(64, n_deal - i0), at = min(i0 + lane, n_deal - 1);
-    const int r = s_sorted[at], g = s_order[at];
-    const int inc = (((r + 63) >> 6) + 2) << 3;
-    int xcd = -1;
-    for (int i = 0; i < m; ++i) {
-      int k = key;
-      k = min(k, __builtin_amdgcn_update_dpp(k, k, 0xB1, 0xF, 0xF, false));    // quad_perm [1,0,3,2]
-      k = min(k, __builtin_amdgcn_update_dpp(k, k, 0x4E, 0xF, 0xF, false));    // quad_perm [2,3,0,1]
-      k = min(k, __builtin_amdgcn_update_dpp(k, k, 0x141, 0xF, 0xF, false));   // row_half_mirror
-      const int x = __builtin_amdgcn_readfirstlane(k) & (kXcd - 1);
-      key += lane == x ? __builtin_amdgcn_readlane(inc, i) : 0;
-      xcd = lane == i ? x : xcd;
+    for (int x = 0; x < kXcd; ++x) key[x] = x;
+    for (int i0 = 0; i0 < n_deal; i0 += 64) {
+      const int m = min(64, n_deal - i0), r = s_sorted[min(i0 + lane, n_deal - 1)];
+      const int inc = (((r + 63) >> 6) + 2) << 3;
+      int xcd = 0;
+      for (int i = 0; i < m; ++i) {
+        int k = key[0];
+        xcd = lane == i ? k & (kXcd - 1) : xcd;
+        k += __builtin_amdgcn_readlane(inc, i);
+#pragma unroll
+        for (int x = 1; x < kXcd; ++x) {
+          key[x - 1] = min(k, key[x]);
+          k = max(k, key[x]);
+        }
+        key[kXcd - 1] = k;
+      }
+      if (lane < m) s_xcd[i0 + lane] = xcd;
     }
+    // The groups of at most 64 rows all weigh the same (3), so the same deal has a closed form: XCD x takes its j-th one
+    // (from 0) when the least load is load[x] + 3 j, and that is group number
+    // sum over y of #{j' : (load[y] + 3 j', y) < (load[x] + 3 j, x)} of the rest.
+    const int n_eq = n_full - n_deal, x8 = lane & (kXcd - 1);
+    int my_load = 0;
+#pragma unroll
+    for (int y = 0; y < kXcd; ++y) my_load = (key[y] & (kXcd - 1)) == x8 ? key[y] >> 3 : my_load;
+    for (int j0 = 0; j0 < n_eq; j0 += 8) {
+      const int k = my_load + 3 * (j0 + (lane >> 3));
+      int rank = 0;
+#pragma unroll
+      for (int y = 0; y < kXcd; ++y) {
+        const int v = k - (key[y] >> 3) + ((key[y] & (kXcd - 1)) < x8 ? 1 : 0);
+        rank += v > 0 ? (v + 2) / 3 : 0;
+      }
+      if (!__ballot(rank < n_eq)) break;
+      if (rank < n_eq) s_xcd[n_deal + rank] = x8;
+    }
+  }
+  __syncthreads();
+  const int x = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if (x >= kXcd) return;
+  int n = 0, t64 = 0, t128 = 0, n_big = 0;
+  for (int i0 = 0; i0 < n_full; i0 += 64) {
+    const int at = min(i0 + lane, n_full - 1), r = s_sorted[at], g = s_order[at];
+    const bool mine = i0 + lane < n_full && s_xcd[at] == x;
+    const unsigned long long mask = __ballot(mine);
     const int u = (r + 63) >> 6, t = (r + 127) >> 7;
-#pragma unroll
-    for (int x = 0; x < kXcd; ++x) {
-      const bool mine = xcd == x;
-      const unsigned long long mask = __ballot(mine);
-      const int iu = wave_incl_scan(mine ? u : 0), it = wave_incl_scan(mine ? t : 0);
-      if (mine)
-        sched_entry(grp, tiles, (size_t)x * cap + nx[x] + __popcll(mask & ((1ull << lane) - 1ull)), g, s_slot[g], r,
-                    sx[x] + iu - u, tx[x] + it - t);
-      nx[x] += __popcll(mask);
-      sx[x] += __builtin_amdgcn_readlane(iu, 63);
-      tx[x] += __builtin_amdgcn_readlane(it, 63);
-      bx[x] += __popcll(__ballot(mine && r > small_rows));
-    }
+    const int iu = wave_incl_scan(mine ? u : 0), it = wave_incl_scan(mine ? t : 0);
+    if (mine)
+      sched_entry(grp, tiles, (size_t)x * cap + n + __popcll(mask & ((1ull << lane) - 1ull)), g, s_slot[g], r, t64 + iu - u,
+                  t128 + it - t);
+    n += __popcll(mask);
+    t64 += __builtin_amdgcn_readlane(iu, 63);
+    t128 += __builtin_amdgcn_readlane(it, 63);
+    n_big += __popcll(__ballot(mine && r > small_rows));
   }
-  // The groups of at most 64 rows all weigh the same (3) and have one tile, so the same deal has a closed form: XCD x
-  // takes its j-th one (from 0) when the least load is load[x] + 3 j, and that is group number
-  // sum over y of #{j' : (load[y] + 3 j', y) < (load[x] + 3 j, x)} of the rest.
-  const int n_eq = n_full - n_deal;
-  int load[kXcd];
-#pragma unroll
-  for (int x = 0; x < kXcd; ++x) load[x] = __builtin_amdgcn_readlane(key, x) >> 3;
-  const int x = lane & (kXcd - 1), my_load = key_of_lane(load, x), my_n = key_of_lane(nx, x), my_u = key_of_lane(sx, x),
-            my_t = key_of_lane(tx, x);
-  for (int j0 = 0; j0 < n_eq; j0 += 8) {
-    const int j = j0 + (lane >> 3), k = my_load + 3 * j;
-    int rank = 0;
-#pragma unroll
-    for (int y = 0; y < kXcd; ++y) {
-      const int v = k - load[y] + (y < x ? 1 : 0);
-      rank += v > 0 ? (v + 2) / 3 : 0;
-    }
-    const bool valid = rank < n_eq;
-    bool big = false;
-    if (valid) {
-      const int g = s_order[n_deal + rank], r = s_sorted[n_deal + rank];
-      sched_entry(grp, tiles, (size_t)x * cap + my_n + j, g, s_slot[g], r, my_u + j, my_t + j);
-      big = r > small_rows;
-    }
-    const unsigned long long mv = __ballot(valid), mb = __ballot(big);
-    if (!mv) break;
-#pragma unroll
-    for (int y = 0; y < kXcd; ++y) {
-      const unsigned long long my = 0x0101010101010101ull << y;
-      const int c = __popcll(mv & my);
-      nx[y] += c;
-      sx[y] += c;
-      tx[y] += c;
-      bx[y] += __popcll(mb & my);
-    }
-  }
-  if (lane < kXcd) {
-    const int n = key_of_lane(nx, lane);
-    sched_entry(grp, tiles, (size_t)lane * cap + n, -1, 0, 0, key_of_lane(sx, lane), key_of_lane(tx, lane));
-    len[lane] = n;
-    len[kXcd + 1 + lane] = key_of_lane(bx, lane);
+  if (lane == 0) {
+    sched_entry(grp, tiles, (size_t)x * cap + n, -1, 0, 0, t64, t128);
+    len[x] = n;
+    len[kXcd + 1 + x] = n_big;
   }
 }
 

@@ -668,6 +668,26 @@ void launch_dispatch(const meft_shape& s, const DispatchWs& w, const int32_t* bl
                      int32_t* clear, size_t clear_words, hipStream_t st) {
   const int n_ent = s.T * s.top_e;
   const int small = dense ? small_rows_of(s) : 0;
+  const DispatchTables tab{w.cnt, w.group_off, w.tile_off, BM, sched_cap(s), want_sched ? w.sched_pairs : nullptr,
+                           w.sched_tiles, w.sched_len, small, small ? w.small_ent : nullptr, w.small_grp, w.small_cnt};
+  int32_t* tok = dense || want_sched ? w.tok_of_slot : nullptr;
+  if (s.n_blocks <= kDispMaxBlocks && s.T <= kDispOneTokens && n_ent <= kDispOneEntries &&
+      (int64_t)n_ent * s.n_blocks <= kDispOneWork) {
+    const size_t lds = (size_t)((s.T + 1023) / 1024) * (1024 + 16) * sizeof(int);   // up to 65 KB
+    static std::once_flag configured_one;
+    std::call_once(configured_one, [] {
+      const int most = kDispOneTokens / 1024 * (1024 + 16) * (int)sizeof(int);
+      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&dispatch_one_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize, most);
+      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&dispatch_one_kernel<false>), hipFuncAttributeMaxDynamicSharedMemorySize, most);
+    });
+    if (block_idx)
+      MEFT_LAUNCH("dispatch", dispatch_one_kernel<true>, dim3(s.n_blocks + 1), dim3(1024), lds, st, block_idx, s.T, s.top_e, s.n_blocks,
+                  tab, w.sblk, w.perm, tok, w.slot_of_ent, kSlotPad, clear, clear_words);
+    else
+      MEFT_LAUNCH("dispatch", dispatch_one_kernel<false>, dim3(s.n_blocks + 1), dim3(1024), lds, st, w.sblk, s.T, s.top_e, s.n_blocks,
+                  tab, nullptr, w.perm, tok, w.slot_of_ent, kSlotPad, clear, clear_words);
+    return;
+  }
   if (fast_dispatch(s)) {
     const int epc = disp_chunk_entries(s), n_chunks = disp_chunks(s);
     const size_t lds = (size_t)16 * s.n_blocks * sizeof(int);
@@ -684,9 +704,6 @@ void launch_dispatch(const meft_shape& s, const DispatchWs& w, const int32_t* bl
     else
       MEFT_LAUNCH("dispatch_count", dispatch_count_kernel<false>, dim3(n_chunks), dim3(1024), lds, st, w.sblk, n_ent,
                   s.top_e, epc, s.n_blocks, nullptr, w.chunk_hist, clear, clear_words);
-    const DispatchTables tab{w.cnt, w.group_off, w.tile_off, BM, sched_cap(s), want_sched ? w.sched_pairs : nullptr,
-                             w.sched_tiles, w.sched_len, small, small ? w.small_ent : nullptr, w.small_grp, w.small_cnt};
-    int32_t* tok = dense || want_sched ? w.tok_of_slot : nullptr;
     int lg = 0;
     while ((1 << lg) < s.n_blocks) ++lg;
     if (s.n_blocks <= kDispScanBlocks && (int64_t)n_chunks * s.n_blocks <= kDispScanMax) {

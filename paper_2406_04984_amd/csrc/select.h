@@ -82,10 +82,9 @@ __device__ __forceinline__ int block_excl_scan_1024(int v, int* s_wave /*[16]*/,
   const int incl = wave_incl_scan(v);
   if (lane == 63) s_wave[w] = incl;
   __syncthreads();
-  int base = 0, tot = 0;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) { const int x = s_wave[i]; base += (i < w) ? x : 0; tot += x; }
-  total = tot;
+  const int sums = wave_incl_scan(lane < 16 ? s_wave[lane & 15] : 0);
+  total = __builtin_amdgcn_readlane(sums, 15);
+  const int base = __builtin_amdgcn_readlane(sums, __builtin_amdgcn_readfirstlane(w)) - s_wave[w];
   __syncthreads();
   return base + incl - v;
 }
