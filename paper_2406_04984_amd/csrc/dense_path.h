@@ -37,6 +37,7 @@ struct ProbRouter {
   static constexpr int kLoaders = 2;
   static constexpr bool kAMC = false;
   static constexpr bool kBNC = false;
+  static constexpr bool kBTags = false;
   static constexpr bool kRowIdsInMemory = false;
   const uint16_t* h; const uint16_t* Wg; float* p;
   int T, d, B, ksplit;
@@ -87,6 +88,7 @@ struct ProbTokKC {
   static constexpr int kLoaders = 2;
   static constexpr bool kAMC = false;
   static constexpr bool kBNC = false;
+  static constexpr bool kBTags = false;
   static constexpr bool kRowIdsInMemory = false;
   const uint16_t* X;          // h (scores) or dOut (activation gradient), [T, d]
   const uint16_t* W;          // K or V, [N, d]
@@ -277,6 +279,27 @@ struct ProbNeuTNRows : ProbNeuTN<TM> {
   static constexpr bool kRowsLinear = false;
   __device__ size_t row_off(const TileCoord&, int tag, int) const { return (size_t)(tag - 1) * Base::d; }
 };
+
+// The token-major problems with the rows of a block gathered from W: `tag` holds a row number + 1 for every row of every block,
+// 0 for a row of zeros (batch-union evaluation: K and V through the list of the union's neurons instead of compacted copies).
+// Buffer loads only: a row of zeros is one outside the buffer.
+template <int MODE>
+struct ProbTokKCRows : ProbTokKC<MODE> {
+  using Base = ProbTokKC<MODE>;
+  static constexpr bool kBTags = true;
+  const int32_t* tag;
+  __device__ const int32_t* b_tags(const TileCoord& tc) const { return tag + (size_t)tc.g * Base::bs + tc.n0; }
+  __device__ const uint16_t* b_row(const TileCoord&, int row) const { return Base::W + (size_t)row * Base::d; }
+};
+
+struct ProbTokNCRows : ProbTokNC {
+  static constexpr bool kRowIdsInMemory = true;
+  const int32_t* tag;
+  __device__ const int32_t* b_row_id_src(const TileCoord& tc, int k0) const { return tag + (size_t)tc.g * bs + k0; }
+  // of tag `row`: tag 0 wraps around to the end of the 32-bit offsets, outside the buffer
+  __device__ const uint16_t* b_row_ptr(int row) const { return W + ((int64_t)row - 1) * d; }
+};
+constexpr int kTagPad = 256;   // tags behind the last block's
 
 // ---- the same problems for gemm_tile_kernel -----------------------------------------------------
 template <int MODE, int TM, int TN>

@@ -124,7 +124,10 @@ struct TileCoord {
 //              __device__ int a_krow(const TileCoord&, int k) const;     the number of the row that holds contraction
 //              index k (possibly negative; a row of zeros beyond the contraction length)
 //   static constexpr bool kBNC;                         B contiguous along n (rows indexed by k)?
-//       false: __device__ const uint16_t* b_row(const TileCoord&, int n) const;    start of B row n, n < Ncols
+//       false: __device__ const uint16_t* b_row(const TileCoord&, int n) const;    start of B row n, n < Ncols;
+//              static constexpr bool kBTags: true where B's rows are gathered (buffer loads only):
+//              __device__ const int32_t* b_tags(const TileCoord&) const;  for the rows n0 .. n0 + 255 (readable also beyond
+//              the block) the number + 1 that b_row takes in n's place, 0 for a row of zeros
 //       true:  __device__ const uint16_t* b_row_ptr(int row) const;   start of B row `row`; rows are
 //              TileCoord::Ncols elements apart;  and, with static constexpr bool kRowIdsInMemory (false where B
 //              is k-contiguous),
@@ -278,6 +281,16 @@ __global__ __launch_bounds__(gemm_threads<P>(), 1) void gemm_mfma_kernel(P p, in
     // Rows beyond the group are not loaded (buffer loads), or any valid row is.  Gathered row numbers come by scalar loads,
     // eight per wave-load, of which each lane picks its row's: a vector load here would wait for every operand request on
     // its way.
+    [[maybe_unused]] auto id_of_row = [&](const int32_t* ids8) -> int {   // of this lane's row among a wave-load's eight
+      const auto* ids = as_const(ids8);
+      int s[8];
+#pragma unroll
+      for (int z = 0; z < 8; ++z) s[z] = ids[z];
+      const int s01 = (lr8 & 1) ? s[1] : s[0], s23 = (lr8 & 1) ? s[3] : s[2], s45 = (lr8 & 1) ? s[5] : s[4],
+                s67 = (lr8 & 1) ? s[7] : s[6];
+      const int s03 = (lr8 & 2) ? s23 : s01, s47 = (lr8 & 2) ? s67 : s45;
+      return (lr8 & 4) ? s47 : s03;
+    };
     [[maybe_unused]] auto a_row_start = [&](const TileCoord& t, int i) -> const uint16_t* {
       if constexpr (P::kAMC) {
         return nullptr;
@@ -285,14 +298,7 @@ __global__ __launch_bounds__(gemm_threads<P>(), 1) void gemm_mfma_kernel(P p, in
       const int row = (lw * LA + i) * 8 + lr8;
       int id = 0, m = t.m0 + row;
       if constexpr (P::kAIds) {
-        const auto* ids = as_const(p.a_ids(t) + (lw * LA + i) * 8);
-        int s[8];
-#pragma unroll
-        for (int z = 0; z < 8; ++z) s[z] = ids[z];
-        const int s01 = (lr8 & 1) ? s[1] : s[0], s23 = (lr8 & 1) ? s[3] : s[2], s45 = (lr8 & 1) ? s[5] : s[4],
-                  s67 = (lr8 & 1) ? s[7] : s[6];
-        const int s03 = (lr8 & 2) ? s23 : s01, s47 = (lr8 & 2) ? s67 : s45;
-        id = (lr8 & 4) ? s47 : s03;
+        id = id_of_row(p.a_ids(t) + (lw * LA + i) * 8);
       } else {
         m = m < t.Mrows ? m : t.Mrows - 1;
       }
@@ -357,8 +363,16 @@ __global__ __launch_bounds__(gemm_threads<P>(), 1) void gemm_mfma_kernel(P p, in
 #pragma unroll
           for (int i = 0; i < LB; ++i) {
             const int row = (lw * LB + i) * 8 + lr8, n = min(t.n0 + row, t.Ncols - 1);
-            const uint32_t o = byte_off(p.b_row(t, n) + (((lane & 7) ^ ((row >> 1) & 7)) << 3), p.b_base());
-            ob[i] = t.n0 + row < t.Ncols ? o : kNowhere;
+            const int swz = ((lane & 7) ^ ((row >> 1) & 7)) << 3;
+            // (no branch that differs per lane: see TileFinder::load)
+            int from = n, there = t.n0 + row < t.Ncols ? 1 : 0;
+            if constexpr (P::kBTags) {
+              const int tag = id_of_row(p.b_tags(t) + (lw * LB + i) * 8);
+              there &= tag > 0 ? 1 : 0;
+              from = max(tag, 1) - 1;
+            }
+            const uint32_t o = byte_off(p.b_row(t, from) + swz, p.b_base());
+            ob[i] = there ? o : kNowhere;
           }
         }
       } else {

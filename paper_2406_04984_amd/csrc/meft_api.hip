@@ -469,7 +469,7 @@ struct UnionWs : DispatchWs {
     const size_t n_ent = (size_t)s.T * g.nvb, rows = (size_t)g.nvb * g.vbs;
     chunk_cnt = c.take<int32_t>((size_t)(s.N + kFlagChunk - 1) / kFlagChunk);
     flag = c.take<int32_t>(s.N);
-    rowtag = c.take<int32_t>(rows);
+    rowtag = c.take<int32_t>(rows + kTagPad);
     Kc = c.take<uint16_t>(rows * s.d);
     Vc = c.take<uint16_t>(rows * s.d);
     zrow = c.take<uint16_t>((size_t)g.vbs * (1 + 2 * n_ent));   // one piece: row of zeros, A', DS' (see BwdWs)
@@ -614,6 +614,18 @@ void launch_gemm_mfma(const char* name, const P& prob, int grid, hipStream_t st)
   } else {
     MEFT_LAUNCH(name, (gemm_mfma_kernel<P, false>), dim3(launch), dim3(gemm_threads<P>()), gemm_lds_bytes<P>(), st, prob, grid);
   }
+}
+
+// for policies that exist with buffer loads only
+template <class P>
+void launch_gemm_mfma_buf(const char* name, const P& prob, int grid, hipStream_t st) {
+  static std::once_flag configured;
+  std::call_once(configured, [] {
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_mfma_kernel<P, true>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, gemm_lds_bytes<P>());
+  });
+  const int launch = grid < kPersistentWgs ? grid : kPersistentWgs;
+  MEFT_LAUNCH(name, (gemm_mfma_kernel<P, true>), dim3(launch), dim3(gemm_threads<P>()), gemm_lds_bytes<P>(), st, prob, grid);
 }
 
 template <class P>
@@ -1119,21 +1131,53 @@ static meft_status bwd_impl(const meft_shape& s, const void* h, const void* K, c
   return launch_status();
 }
 
+// Whether the contractions of the batch union gather K's and V's rows themselves instead of reading compacted copies: the
+// large tiles by buffer loads do.  The copies cost 2 x 43 us of 747 at 1023 tokens, 16384 rows x 2048.
+static bool union_direct(const meft_shape& s, const UnionGeom& g) {
+  return g_force_global_loads.load(std::memory_order_relaxed) == 0 && (uint64_t)s.N * s.d * 2 < kBufLimit &&
+         (uint64_t)s.T * s.d * 2 < kBufLimit && (uint64_t)s.T * g.nvb * g.vbs * 2 < kBufLimit && !small_tiles(g.vs, g.vbs) &&
+         !small_tiles(g.vs, s.d);
+}
+
+template <class P>
+static void fill_union_kc(P& p, const meft_shape& s, const UnionGeom& g, const UnionWs& w, const TokenSched& sched, const void* X,
+                          const void* W, uint16_t* DS, const uint16_t* Ap) {
+  set_gemm_extents(p, (uint64_t)s.T * s.d * 2, (uint64_t)s.N * s.d * 2);
+  p.X = static_cast<const uint16_t*>(X); p.W = static_cast<const uint16_t*>(W); p.tag = w.rowtag;
+  p.perm = w.perm; p.tok_of_slot = w.tok_of_slot; p.sched = sched; p.e = g.nvb; p.bs = g.vbs; p.bsp = g.vbs; p.d = s.d;
+  p.DS = DS; p.Ap = Ap;
+}
+
+static void launch_union_nc(const char* name, const meft_shape& s, const UnionGeom& g, const UnionWs& w, const TokenSched& sched,
+                            const uint16_t* A, const void* W, hipStream_t st) {
+  ProbTokNCRows p{};
+  set_gemm_extents(p, (uint64_t)s.T * g.nvb * g.vbs * 2, (uint64_t)s.N * s.d * 2);
+  p.A = A; p.W = static_cast<const uint16_t*>(W); p.tag = w.rowtag; p.sched = sched; p.bs = g.vbs; p.bsp = g.vbs; p.d = s.d;
+  p.part = w.part;
+  launch_gemm_mfma_buf(name, p, tile_bound(g.vs, (s.d + kTN - 1) / kTN), st);
+}
+
 // Shared front part of the batch-union forward and backward: index structure from n_S, tile schedule, compacted
 // K and V, and A' = ReLU(h K[S]^T).
 static void union_front(const meft_shape& s, const UnionGeom& g, const UnionWs& w, const void* h, const void* K,
                         const void* V, const int32_t* S, const int32_t* n_S, hipStream_t st) {
   const size_t n_slots = (size_t)g.nvb * s.T, n_rows = (size_t)g.nvb * g.vbs;
-  const size_t n_thr = (n_slots + kSlotPad) > n_rows ? (n_slots + kSlotPad) : n_rows;
+  const size_t n_thr = (n_slots + kSlotPad) > n_rows + kTagPad ? (n_slots + kSlotPad) : n_rows + kTagPad;
   MEFT_LAUNCH("union_maps", union_maps_kernel, dim3((unsigned)((n_thr + 255) / 256)), dim3(256), 0, st, S, n_S, g.cap,
               s.N, s.T, g.vbs, g.nvb, w.sblk, w.perm, w.tok_of_slot, w.slot_of_ent, w.group_off, w.rowtag,
               reinterpret_cast<int32_t*>(w.zrow));   // (vbs % 64 == 0)
   MEFT_LAUNCH("build_sched", build_sched_kernel, dim3(1), dim3(1024), 0, st, w.group_off, g.nvb, sched_cap(g.vs),
               w.sched_pairs, w.sched_tiles, w.sched_len, 0);
+  const TokenSched sched{w.sched_pairs, w.sched_tiles, w.sched_len, sched_cap(g.vs), sched_max_tiles(g.vs)};
+  if (union_direct(s, g)) {
+    ProbTokKCRows<kTokRelu> pr{};
+    fill_union_kc(pr, s, g, w, sched, h, K, w.Ap, nullptr);
+    launch_gemm_mfma_buf("union_score_gemm", pr, tile_bound(g.vs, (g.vbs + kTN - 1) / kTN), st);
+    return;
+  }
   const int rows_grid = (int)(n_rows < 4096 ? n_rows : 4096);
   MEFT_LAUNCH("gather_rows", gather_rows_kernel, dim3(rows_grid, 2), dim3(256), 0, st, static_cast<const uint16_t*>(K),
               static_cast<const uint16_t*>(V), S, n_S, g.cap, s.N, s.d, g.vbs, w.Kc, w.Vc);
-  const TokenSched sched{w.sched_pairs, w.sched_tiles, w.sched_len, sched_cap(g.vs), sched_max_tiles(g.vs)};
   launch_tok<TokKCLarge<kTokRelu>, TokKCSmall<kTokRelu>>("union_score_gemm", g.vs, g.vbs, (uint64_t)s.T * s.d * 2, (uint64_t)n_rows * s.d * 2, (uint64_t)s.T * g.nvb * g.vbs * 2, [&](auto& pr) {
     pr.X = static_cast<const uint16_t*>(h); pr.W = w.Kc; pr.perm = w.perm; pr.tok_of_slot = w.tok_of_slot;
     pr.sched = sched; pr.e = g.nvb; pr.bs = g.vbs; pr.bsp = g.vbs; pr.d = s.d;
@@ -1175,7 +1219,8 @@ meft_status meft_union_fwd(const meft_shape* shape, const void* h, const void* K
   launch_bwd_head(s, w.flag, w.chunk_cnt, S, n_S, nullptr, nullptr, nullptr, nullptr, nullptr, st);
   union_front(s, g, w, h, K, V, S, n_S, st);
   const TokenSched sched{w.sched_pairs, w.sched_tiles, w.sched_len, sched_cap(g.vs), sched_max_tiles(g.vs)};
-  launch_tok<ProbTokNC, TokNCSmall>("union_value_gemm", g.vs, s.d, (uint64_t)s.T * g.nvb * g.vbs * 2, (uint64_t)g.nvb * g.vbs * s.d * 2, (uint64_t)s.T * g.nvb * s.d * 2, [&](auto& pv) {
+  if (union_direct(s, g)) launch_union_nc("union_value_gemm", s, g, w, sched, w.Ap, V, st);
+  else launch_tok<ProbTokNC, TokNCSmall>("union_value_gemm", g.vs, s.d, (uint64_t)s.T * g.nvb * g.vbs * 2, (uint64_t)g.nvb * g.vbs * s.d * 2, (uint64_t)s.T * g.nvb * s.d * 2, [&](auto& pv) {
     pv.A = w.Ap; pv.W = w.Vc; pv.sched = sched; pv.bs = g.vbs; pv.bsp = g.vbs;
     pv.d = s.d; pv.part = w.part;
   }, st);
@@ -1204,12 +1249,19 @@ meft_status meft_union_bwd(const meft_shape* shape, const void* h, const void* K
   union_front(s, g, w, h, K, V, S, n_S, st);
   const TokenSched sched{w.sched_pairs, w.sched_tiles, w.sched_len, sched_cap(g.vs), sched_max_tiles(g.vs)};
   const uint16_t *hh = static_cast<const uint16_t*>(h), *gg = static_cast<const uint16_t*>(dOut);
+  const bool direct = union_direct(s, g);
+  if (direct) {
+    ProbTokKCRows<kTokMasked> pg{};
+    fill_union_kc(pg, s, g, w, sched, gg, V, w.DS, w.Ap);
+    launch_gemm_mfma_buf("union_dact_gemm", pg, tile_bound(g.vs, (g.vbs + kTN - 1) / kTN), st);
+  } else
   launch_tok<TokKCLarge<kTokMasked>, TokKCSmall<kTokMasked>>("union_dact_gemm", g.vs, g.vbs, (uint64_t)s.T * s.d * 2, (uint64_t)g.nvb * g.vbs * s.d * 2, (uint64_t)s.T * g.nvb * g.vbs * 2, [&](auto& pg) {
     pg.X = gg; pg.W = w.Vc; pg.perm = w.perm; pg.tok_of_slot = w.tok_of_slot; pg.sched = sched;
     pg.e = g.nvb; pg.bs = g.vbs; pg.bsp = g.vbs; pg.d = s.d; pg.Ap = w.Ap; pg.DS = w.DS;
   }, st);
   if (dh) {
-    launch_tok<ProbTokNC, TokNCSmall>("union_dh_gemm", g.vs, s.d, (uint64_t)s.T * g.nvb * g.vbs * 2, (uint64_t)g.nvb * g.vbs * s.d * 2, (uint64_t)s.T * g.nvb * s.d * 2, [&](auto& ph) {
+    if (direct) launch_union_nc("union_dh_gemm", s, g, w, sched, w.DS, K, st);
+    else launch_tok<ProbTokNC, TokNCSmall>("union_dh_gemm", g.vs, s.d, (uint64_t)s.T * g.nvb * g.vbs * 2, (uint64_t)g.nvb * g.vbs * s.d * 2, (uint64_t)s.T * g.nvb * s.d * 2, [&](auto& ph) {
       ph.A = w.DS; ph.W = w.Kc; ph.sched = sched; ph.bs = g.vbs; ph.bsp = g.vbs;
       ph.d = s.d; ph.part = w.part;
     }, st);

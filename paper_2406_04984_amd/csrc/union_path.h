@@ -1,6 +1,8 @@
 // Batch-union evaluation of the adapter (Algorithm 1 as printed): S = the union of all tokens' selections,
 // K[S] and V[S] are compacted, and every token is evaluated densely over S:
 //     out = ReLU(h K[S]^T) V[S],   with the matching backward.
+// (Where the contractions run on large tiles and K, V are within reach of buffer loads, nothing is copied: the rows are gathered
+// by the contractions.)
 // The compacted rows are cut into virtual blocks of `vbs` rows, and every token is given an entry for every
 // virtual block; with that index structure the contractions are the same grouped matrix-core GEMMs as in the
 // per-token block-dense path (group = one virtual block with all T tokens), the ReLU being applied in the score
@@ -22,7 +24,8 @@ __global__ __launch_bounds__(256) void mark_idx_kernel(const int32_t* __restrict
 // Index structure of the virtual blocks, from the union size U = *n_S (device):
 //   n_real = ceil(U / vbs) blocks hold rows; block g < n_real has all T tokens as its group, slot g*T + t.
 //   entry of token t for block g: t*nvb + g.  Blocks g >= n_real are empty (sblk = -1).
-// rowtag[i] = S[i] + 1: the row that the gradients of compacted row i go to; 0 where there is none.  Also clears zrow.
+// rowtag[i] = S[i] + 1: the row of K and V that compacted row i is, and that its gradients go to; 0 where there is none (also in
+// the kTagPad entries behind the last).  Also clears zrow.
 // One thread per (block, token) slot of the full nvb x T grid; the small tables are written by workgroup 0.
 __global__ __launch_bounds__(256) void union_maps_kernel(const int32_t* __restrict__ S,
                                                          const int32_t* __restrict__ n_S, int cap, int N, int T,
@@ -50,7 +53,7 @@ __global__ __launch_bounds__(256) void union_maps_kernel(const int32_t* __restri
   }
   // kSlotPad valid entries behind the last real slot (the GEMMs look row numbers up a little beyond a group)
   if (i >= (long long)n_real * T && i < (long long)n_real * T + kSlotPad) tok_of_slot[i] = 0;
-  if (i < (long long)nvb * vbs) {
+  if (i < (long long)nvb * vbs + kTagPad) {
     const int j = i < U ? S[i] : -1;
     rowtag[i] = (unsigned)j < (unsigned)N ? j + 1 : 0;
   }
