@@ -551,20 +551,30 @@ void launch_pair_bwd(const meft_shape& s, const BwdWs& w, const void* h, const v
   const int P = s.T * s.top_k;
   const size_t n_pairs = (size_t)P;
   const dim3 pairs((unsigned)(((int64_t)P + 255) / 256));
-  MEFT_LAUNCH("fill_i32", fill_i32_kernel, dim3((unsigned)(((size_t)s.N + 255) / 256)), dim3(256), 0, st, w.cnt_n, (size_t)s.N, 0);
-  MEFT_LAUNCH("pair_count", pair_count_kernel, pairs, dim3(256), 0, st, idx, P, s.N, w.cnt_n, w.pair_sorted);
-  const int n_chunks = (s.N + kScanChunk - 1) / kScanChunk;
-  if (w.sums && s.N > kScanSelfMax)
-    MEFT_LAUNCH("pair_sums", pair_sums_kernel, dim3(n_chunks), dim3(kScanThreads), 0, st, w.cnt_n, s.N, w.sums);
-  MEFT_LAUNCH("pair_scan", pair_scan_kernel, dim3(n_chunks), dim3(kScanThreads), 0, st, w.cnt_n, s.N,
-              s.N > kScanSelfMax ? w.sums : nullptr, w.seg_off, touched, n_touched, w.work, w.multi, w.totals);
-  MEFT_LAUNCH("pair_fill", pair_fill_kernel, pairs, dim3(256), 0, st, idx, P, s.N, w.seg_off, w.pair_sorted, w.pair_list);
   // four chunks per workgroup: at most one chunk per touched neuron plus one per kSegChunk pairs
   const int64_t n_seg = s.N < P ? s.N : P, groups = (n_seg + P / kSegChunk + 3) / 4;
   // (a token's ids may repeat where they were clamped: more than kSegChunk pairs may have one neuron whatever T is)
   const int n_multi = P <= kSegChunk ? 0 : P / kSegChunk < 512 ? P / kSegChunk + 1 : 512;
-  MEFT_LAUNCH("seg_sort", seg_sort_kernel, dim3((unsigned)(n_multi + ((int64_t)P + 255) / 256)), dim3(256), 0, st, w.multi, w.totals,
-              w.seg_off, w.pair_list, idx, act, P, s.N, s.top_k, n_multi, w.pair_sorted, w.seg);
+  if (P <= kPairOneP && s.N <= kPairOneN) {
+    static std::once_flag configured;
+    std::call_once(configured, [] {
+      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&pair_one_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                kPairOneLds * (int)sizeof(int32_t));
+    });
+    MEFT_LAUNCH("pair_one", pair_one_kernel, dim3(kPairOneWgs), dim3(kScanThreads), kPairOneLds * sizeof(int32_t), st, idx, act, P,
+                s.N, s.top_k, touched, n_touched, w.work, w.multi, w.totals, w.pair_sorted, w.seg);
+  } else {
+    MEFT_LAUNCH("fill_i32", fill_i32_kernel, dim3((unsigned)(((size_t)s.N + 255) / 256)), dim3(256), 0, st, w.cnt_n, (size_t)s.N, 0);
+    MEFT_LAUNCH("pair_count", pair_count_kernel, pairs, dim3(256), 0, st, idx, P, s.N, w.cnt_n, w.pair_sorted);
+    const int n_chunks = (s.N + kScanChunk - 1) / kScanChunk;
+    if (w.sums && s.N > kScanSelfMax)
+      MEFT_LAUNCH("pair_sums", pair_sums_kernel, dim3(n_chunks), dim3(kScanThreads), 0, st, w.cnt_n, s.N, w.sums);
+    MEFT_LAUNCH("pair_scan", pair_scan_kernel, dim3(n_chunks), dim3(kScanThreads), 0, st, w.cnt_n, s.N,
+                s.N > kScanSelfMax ? w.sums : nullptr, w.seg_off, touched, n_touched, w.work, w.multi, w.totals);
+    MEFT_LAUNCH("pair_fill", pair_fill_kernel, pairs, dim3(256), 0, st, idx, P, s.N, w.seg_off, w.pair_sorted, w.pair_list);
+    MEFT_LAUNCH("seg_sort", seg_sort_kernel, dim3((unsigned)(n_multi + ((int64_t)P + 255) / 256)), dim3(256), 0, st, w.multi, w.totals,
+                w.seg_off, w.pair_list, idx, act, P, s.N, s.top_k, n_multi, w.pair_sorted, w.seg);
+  }
   const int slices = row_slices<T>(s), parts = slices < kDsParts ? slices : kDsParts;
   auto seg_grid = [&](int n) { return grid_xcd(groups * n < kSegWorkgroups ? groups * n : kSegWorkgroups); };
   MEFT_LAUNCH("seg_dv", seg_dv_kernel<T>, seg_grid(parts), dim3(256), 0, st, w.work, w.totals, w.seg,

@@ -216,12 +216,59 @@ __global__ void pair_fill_kernel(const int32_t* __restrict__ idx, int P, int N,
   pair_list[seg_off[j] + pos[p]] = p;
 }
 
+// Puts one segment of L > kSegChunk pairs in ascending order, by a workgroup of NT threads: up to kBitonicMax by a bitonic sort
+// in LDS (a neuron that thousands of tokens selected would cost L^2 comparisons otherwise), beyond that (more tokens than
+// kBitonicMax selected one neuron) by ranks counted against the segment, which comes through LDS kBitonicMax pairs at a time: slow
+// but never wrong (65536 tokens x 16 pairs of 64 neurons: the whole backward 38.6 ms with the ranks counted against memory,
+// 8.2 ms so).  put(i, p): pair p is the i-th.
+constexpr int kBitonicMax = 8192;
+template <int NT, class Put>
+__device__ __forceinline__ void sort_long_segment(const int32_t* src, int L, int32_t* s_p, Put&& put) {
+  if (L <= kBitonicMax) {
+    int n = 512;
+    while (n < L) n <<= 1;
+    for (int i = threadIdx.x; i < n; i += NT) s_p[i] = i < L ? src[i] : 0x7FFFFFFF;   // padding sorts to the end
+    __syncthreads();
+    for (int size = 2; size <= n; size <<= 1)
+      for (int stride = size >> 1; stride > 0; stride >>= 1) {
+        for (int i = threadIdx.x; i < n / 2; i += NT) {
+          const int lo = ((i / stride) * stride * 2) + (i % stride), hi = lo + stride;
+          const bool up = (lo & size) == 0;   // ascending half of this merge
+          const int a = s_p[lo], b = s_p[hi];
+          if ((a > b) == up) { s_p[lo] = b; s_p[hi] = a; }
+        }
+        __syncthreads();
+      }
+    for (int i = threadIdx.x; i < L; i += NT) put(i, s_p[i]);
+    __syncthreads();
+    return;
+  }
+  constexpr int kOwn = 8;   // pairs a thread ranks at a time
+  for (int i0 = threadIdx.x; i0 - (int)threadIdx.x < L; i0 += NT * kOwn) {
+    int v[kOwn], r[kOwn];
+#pragma unroll
+    for (int z = 0; z < kOwn; ++z) { v[z] = i0 + NT * z < L ? src[i0 + NT * z] : 0; r[z] = 0; }
+    for (int b = 0; b < L; b += kBitonicMax) {
+      const int n = min(kBitonicMax, L - b);
+      __syncthreads();
+      for (int i = threadIdx.x; i < (n + 3) / 4 * 4; i += NT) s_p[i] = i < n ? src[b + i] : 0x7FFFFFFF;
+      __syncthreads();
+      for (int i = 0; i < n; i += 4) {
+        const i32x4 y = *reinterpret_cast<const i32x4*>(&s_p[i]);
+#pragma unroll
+        for (int z = 0; z < kOwn; ++z) r[z] += (y.x < v[z]) + (y.y < v[z]) + (y.z < v[z]) + (y.w < v[z]);
+      }
+    }
+#pragma unroll
+    for (int z = 0; z < kOwn; ++z)
+      if (i0 + NT * z < L) put(r[z], v[z]);
+  }
+  __syncthreads();
+}
+
 // Puts every segment in ascending pair order (pair ids are distinct) and notes (token, activation) of its pairs beside it, so
 // that the kernels that sum a segment, once per 1 KB of columns, find both with one coalesced read.  Workgroups 0 .. n_multi - 1
-// take the segments of more than kSegChunk pairs: up to kBitonicMax by a bitonic sort in LDS (a neuron that thousands of
-// tokens selected would cost L^2 comparisons otherwise), beyond that (more tokens than kBitonicMax selected one neuron) by
-// ranks counted against the segment, which comes through LDS kBitonicMax pairs at a time: slow but never wrong (65536 tokens
-// x 16 pairs of 64 neurons: the whole backward 38.6 ms with the ranks counted against memory, 8.2 ms so).  The others take the pairs of the remaining segments, a thread
+// take the segments of more than kSegChunk pairs; the others the pairs of the remaining segments, a thread
 // each, which counts the pair's rank among the at most kSegChunk of its neuron (a wave per segment: 18 instead of 6.5 us
 // at 64000 pairs of 41000 neurons).
 __global__ __launch_bounds__(256) void seg_sort_kernel(const int4* __restrict__ multi,
@@ -231,7 +278,6 @@ __global__ __launch_bounds__(256) void seg_sort_kernel(const int4* __restrict__ 
                                                        const int32_t* __restrict__ idx, const float* __restrict__ act,
                                                        int P, int N, int k, int n_multi, int32_t* __restrict__ pair_sorted,
                                                        int2* __restrict__ seg) {
-  constexpr int kBitonicMax = 8192;
   __shared__ __attribute__((aligned(16))) int32_t s_p[kBitonicMax];
   auto put = [&](int at, int p) {
     pair_sorted[at] = p;
@@ -240,48 +286,8 @@ __global__ __launch_bounds__(256) void seg_sort_kernel(const int4* __restrict__ 
   if ((int)blockIdx.x < n_multi) {
     for (int u = blockIdx.x; u < totals[2]; u += n_multi) {
       const int j = multi[u].x;
-      const int o = seg_off[j], L = seg_off[j + 1] - o;
-      const int32_t* src = pair_list + o;
-      if (L <= kBitonicMax) {
-        int n = 512;
-        while (n < L) n <<= 1;
-        for (int i = threadIdx.x; i < n; i += 256) s_p[i] = i < L ? src[i] : 0x7FFFFFFF;   // padding sorts to the end
-        __syncthreads();
-        for (int size = 2; size <= n; size <<= 1)
-          for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            for (int i = threadIdx.x; i < n / 2; i += 256) {
-              const int lo = ((i / stride) * stride * 2) + (i % stride), hi = lo + stride;
-              const bool up = (lo & size) == 0;   // ascending half of this merge
-              const int a = s_p[lo], b = s_p[hi];
-              if ((a > b) == up) { s_p[lo] = b; s_p[hi] = a; }
-            }
-            __syncthreads();
-          }
-        for (int i = threadIdx.x; i < L; i += 256) put(o + i, s_p[i]);
-        __syncthreads();
-      } else {
-        constexpr int kOwn = 8;   // pairs a thread ranks at a time
-        for (int i0 = threadIdx.x; i0 - (int)threadIdx.x < L; i0 += 256 * kOwn) {
-          int v[kOwn], r[kOwn];
-#pragma unroll
-          for (int z = 0; z < kOwn; ++z) { v[z] = i0 + 256 * z < L ? src[i0 + 256 * z] : 0; r[z] = 0; }
-          for (int b = 0; b < L; b += kBitonicMax) {
-            const int n = min(kBitonicMax, L - b);
-            __syncthreads();
-            for (int i = threadIdx.x; i < (n + 3) / 4 * 4; i += 256) s_p[i] = i < n ? src[b + i] : 0x7FFFFFFF;
-            __syncthreads();
-            for (int i = 0; i < n; i += 4) {
-              const i32x4 y = *reinterpret_cast<const i32x4*>(&s_p[i]);
-#pragma unroll
-              for (int z = 0; z < kOwn; ++z) r[z] += (y.x < v[z]) + (y.y < v[z]) + (y.z < v[z]) + (y.w < v[z]);
-            }
-          }
-#pragma unroll
-          for (int z = 0; z < kOwn; ++z)
-            if (i0 + 256 * z < L) put(o + r[z], v[z]);
-        }
-        __syncthreads();
-      }
+      const int o = seg_off[j];
+      sort_long_segment<256>(pair_list + o, seg_off[j + 1] - o, s_p, [&](int i, int p) { put(o + i, p); });
     }
     return;
   }
@@ -294,6 +300,103 @@ __global__ __launch_bounds__(256) void seg_sort_kernel(const int4* __restrict__ 
 #pragma unroll 4
   for (int z = 0; z < L; ++z) r += pair_list[o + z] < p ? 1 : 0;
   put(o + r, p);
+}
+
+// All of the above in one launch: up to kPairOneP pairs of kPairOneN neurons.  Every workgroup counts all pairs in LDS, eight a
+// thread, and scans all counters; neuron j belongs to workgroup j % kPairOneWgs, which writes its work entries and puts its pairs
+// in order.  The five launches that this replaces depend on each other and take 4-7 us each, however few the pairs.
+// fp32 steps, five launches / one: 78 tokens x 4 pairs, 2496 neurons 53.5 -> 41 us; 124 x 37, 7872 neurons 56.5 -> 52.  More pairs
+// than a thread's eight would have to be read again for every step: in that form 9937 pairs gained 2 us and 64000 lost 11 of 140.
+constexpr int kPairOnePairs = 8, kPairOneP = kPairOnePairs * kScanThreads, kPairOneN = 1 << 14, kPairOneWgs = 128;
+constexpr int kPairOnePer = kPairOneN / kScanThreads;   // consecutive counters of a thread
+constexpr int kPairOneLds = kPairOneN + kPairOneN / kPairOnePer + 1;
+__global__ __launch_bounds__(kScanThreads) void pair_one_kernel(const int32_t* __restrict__ idx, const float* __restrict__ act, int P,
+                                                       int N, int k, int32_t* __restrict__ touched,
+                                                       int32_t* __restrict__ n_touched, SegWork* __restrict__ work,
+                                                       int4* __restrict__ multi, int32_t* __restrict__ totals,
+                                                       int32_t* __restrict__ pair_sorted, int2* __restrict__ seg) {
+  constexpr int kPer = kPairOnePer, kThreads = kScanThreads;
+  static_assert(kPer <= kPairOneWgs && kPairOneP <= kBitonicMax, "");   // at most one of a thread's counters is the workgroup's
+  extern __shared__ int32_t s_cnt[];   // counts, then first places; neuron j at j + j / kPer, so that the scan's reads spread over the banks
+  __shared__ __attribute__((aligned(16))) int32_t s_p[kBitonicMax];
+  __shared__ int32_t s_list[kPairOneP];   // this workgroup's segments, where they are in the grouped list
+  __shared__ int32_t s_long[kPairOneN / kPairOneWgs], s_sum[5][kThreads / 64], s_nlong;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, wg = blockIdx.x;
+  auto slot = [](int j) { return j + j / kPer; };
+  auto mine = [&](int j) { return j % kPairOneWgs == wg; };
+  int jp[kPairOnePairs], at[kPairOnePairs];   // of the pairs tid + kThreads * z: neuron, place among the neuron's as they come
+#pragma unroll
+  for (int z = 0; z < kPairOnePairs; ++z) jp[z] = idx[min(tid + kThreads * z, P - 1)];
+  for (int i = tid; i <= slot(N); i += kThreads) s_cnt[i] = 0;
+  if (tid == 0) s_nlong = 0;
+  __syncthreads();
+#pragma unroll
+  for (int z = 0; z < kPairOnePairs; ++z) {
+    jp[z] = tid + kThreads * z < P ? clampi(jp[z], 0, N - 1) : -1;
+    at[z] = jp[z] >= 0 ? atomicAdd(&s_cnt[slot(jp[z])], 1) : 0;
+  }
+  __syncthreads();
+  const int j0 = tid * kPer;
+  int v[kPer];
+  PairSums sum{0, 0, 0, 0, 0};
+#pragma unroll
+  for (int z = 0; z < kPer; ++z) {
+    v[z] = j0 + z < N ? s_cnt[slot(j0 + z)] : 0;
+    sum.add(v[z]);
+  }
+  const int m[5] = {sum.c, sum.f, sum.wk, sum.mu, sum.mn};
+  int ex[5];
+#pragma unroll
+  for (int z = 0; z < 5; ++z) {
+    const int incl = wave_incl_scan(m[z]);
+    if (lane == 63) s_sum[z][w] = incl;
+    ex[z] = incl - m[z];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int z = 0; z < 5; ++z)
+    for (int i = 0; i < w; ++i) ex[z] += s_sum[z][i];
+  int off = ex[0], nt = ex[1], wo = ex[2], mo = ex[3], mn = ex[4];
+#pragma unroll
+  for (int z = 0; z < kPer; ++z) {
+    const int j = j0 + z, ch = (v[z] + kSegChunk - 1) / kSegChunk;
+    if (j < N) s_cnt[slot(j)] = off;
+    if (v[z] > 0 && mine(j)) {
+      touched[nt] = j;
+      if (ch > 1) multi[mn] = make_int4(j, mo, ch, 0);
+      for (int c = 0; c < ch; ++c)
+        work[wo + c] = SegWork{j, off + c * kSegChunk, min(v[z] - c * kSegChunk, kSegChunk), ch > 1 ? mo + c : -1};
+      if (ch > 1) s_long[atomicAdd(&s_nlong, 1)] = j;
+    }
+    off += v[z]; nt += v[z] > 0 ? 1 : 0; wo += ch; mo += ch > 1 ? ch : 0; mn += ch > 1 ? 1 : 0;
+  }
+  if (tid == kThreads - 1) {
+    s_cnt[slot(N)] = off;   // (behind every counter)
+    if (wg == 0) { *n_touched = nt; totals[0] = nt; totals[1] = wo; totals[2] = mn; }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int z = 0; z < kPairOnePairs; ++z)
+    if (jp[z] >= 0 && mine(jp[z])) s_list[s_cnt[slot(jp[z])] + at[z]] = tid + kThreads * z;
+  __syncthreads();
+  auto put = [&](int i, int p) {
+    pair_sorted[i] = p;
+    seg[i] = make_int2(p / k, __float_as_int(act[p]));
+  };
+#pragma unroll
+  for (int z = 0; z < kPairOnePairs; ++z) {
+    if (jp[z] < 0 || !mine(jp[z])) continue;
+    const int p = tid + kThreads * z, o = s_cnt[slot(jp[z])], L = s_cnt[slot(jp[z] + 1)] - o;
+    if (L > kSegChunk) continue;
+    int r = 0;
+#pragma unroll 4
+    for (int i = 0; i < L; ++i) r += s_list[o + i] < p ? 1 : 0;
+    put(o + r, p);
+  }
+  for (int u = 0; u < s_nlong; ++u) {
+    const int j = s_long[u], o = s_cnt[slot(j)];
+    sort_long_segment<kThreads>(s_list + o, s_cnt[slot(j + 1)] - o, s_p, [&](int i, int p) { put(o + i, p); });
+  }
 }
 
 // Work of the two kernels below: units of (run of consecutive chunks, 1 KB of columns).  The pairs of a run are consecutive in
