@@ -305,7 +305,7 @@ __global__ __launch_bounds__(256) void seg_sort_kernel(const int4* __restrict__ 
 // All of the above in one launch: up to kPairOneP pairs of kPairOneN neurons.  Every workgroup counts all pairs in LDS, eight a
 // thread, and scans all counters; neuron j belongs to workgroup j % kPairOneWgs, which writes its work entries and puts its pairs
 // in order.  The five launches that this replaces depend on each other and take 4-7 us each, however few the pairs.
-// fp32 steps, five launches / one: 78 tokens x 4 pairs, 2496 neurons 53.5 -> 41 us; 124 x 37, 7872 neurons 56.5 -> 52.  More pairs
+// fp32 steps, five launches / one: 78 tokens x 4 pairs, 2496 neurons 53.5 -> 41 us; 124 x 37, 7872 neurons 56.5 -> 51.  More pairs
 // than a thread's eight would have to be read again for every step: in that form 9937 pairs gained 2 us and 64000 lost 11 of 140.
 constexpr int kPairOnePairs = 8, kPairOneP = kPairOnePairs * kScanThreads, kPairOneN = 1 << 14, kPairOneWgs = 128;
 constexpr int kPairOnePer = kPairOneN / kScanThreads;   // consecutive counters of a thread
@@ -316,11 +316,11 @@ __global__ __launch_bounds__(kScanThreads) void pair_one_kernel(const int32_t* _
                                                        int4* __restrict__ multi, int32_t* __restrict__ totals,
                                                        int32_t* __restrict__ pair_sorted, int2* __restrict__ seg) {
   constexpr int kPer = kPairOnePer, kThreads = kScanThreads;
-  static_assert(kPer <= kPairOneWgs && kPairOneP <= kBitonicMax, "");   // at most one of a thread's counters is the workgroup's
+  static_assert(kPer <= kPairOneWgs && kPairOneP <= kBitonicMax && (long long)kPairOneP * kPairOneN <= 1ll << 31, "");   // at most one of a thread's counters is the workgroup's
   extern __shared__ int32_t s_cnt[];   // counts, then first places; neuron j at j + j / kPer, so that the scan's reads spread over the banks
   __shared__ __attribute__((aligned(16))) int32_t s_p[kBitonicMax];
   __shared__ int32_t s_list[kPairOneP];   // this workgroup's segments, where they are in the grouped list
-  __shared__ int32_t s_long[kPairOneN / kPairOneWgs], s_sum[5][kThreads / 64], s_nlong;
+  __shared__ int32_t s_long[kPairOneN / kPairOneWgs], s_sum[5][kThreads / 64], s_n, s_nlong;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, wg = blockIdx.x;
   auto slot = [](int j) { return j + j / kPer; };
   auto mine = [&](int j) { return j % kPairOneWgs == wg; };
@@ -328,7 +328,7 @@ __global__ __launch_bounds__(kScanThreads) void pair_one_kernel(const int32_t* _
 #pragma unroll
   for (int z = 0; z < kPairOnePairs; ++z) jp[z] = idx[min(tid + kThreads * z, P - 1)];
   for (int i = tid; i <= slot(N); i += kThreads) s_cnt[i] = 0;
-  if (tid == 0) s_nlong = 0;
+  if (tid == 0) s_n = s_nlong = 0;
   __syncthreads();
 #pragma unroll
   for (int z = 0; z < kPairOnePairs; ++z) {
@@ -377,22 +377,25 @@ __global__ __launch_bounds__(kScanThreads) void pair_one_kernel(const int32_t* _
   __syncthreads();
 #pragma unroll
   for (int z = 0; z < kPairOnePairs; ++z)
-    if (jp[z] >= 0 && mine(jp[z])) s_list[s_cnt[slot(jp[z])] + at[z]] = tid + kThreads * z;
+    if (jp[z] >= 0 && mine(jp[z])) {
+      s_list[s_cnt[slot(jp[z])] + at[z]] = tid + kThreads * z;
+      s_p[atomicAdd(&s_n, 1)] = (tid + kThreads * z) * kPairOneN + jp[z];
+    }
   __syncthreads();
   auto put = [&](int i, int p) {
     pair_sorted[i] = p;
     seg[i] = make_int2(p / k, __float_as_int(act[p]));
   };
-#pragma unroll
-  for (int z = 0; z < kPairOnePairs; ++z) {
-    if (jp[z] < 0 || !mine(jp[z])) continue;
-    const int p = tid + kThreads * z, o = s_cnt[slot(jp[z])], L = s_cnt[slot(jp[z] + 1)] - o;
+  // (a thread per pair of the workgroup: left where they are, a wave would rank its few one after the other)
+  for (int i = tid; i < s_n; i += kThreads) {
+    const int p = s_p[i] / kPairOneN, j = s_p[i] % kPairOneN, o = s_cnt[slot(j)], L = s_cnt[slot(j + 1)] - o;
     if (L > kSegChunk) continue;
     int r = 0;
 #pragma unroll 4
-    for (int i = 0; i < L; ++i) r += s_list[o + i] < p ? 1 : 0;
+    for (int y = 0; y < L; ++y) r += s_list[o + y] < p ? 1 : 0;
     put(o + r, p);
   }
+  __syncthreads();
   for (int u = 0; u < s_nlong; ++u) {
     const int j = s_long[u], o = s_cnt[slot(j)];
     sort_long_segment<kThreads>(s_list + o, s_cnt[slot(j + 1)] - o, s_p, [&](int i, int p) { put(o + i, p); });
