@@ -84,7 +84,7 @@ STAGE_SYMBOL = {
     "dV_gemm": ("gemm_mfma_kernel<ProbNeuTN<256>, true>", "gemm_mfma_kernel<ProbNeuTN<128>, true>"),
     "dK_gemm": ("gemm_mfma_kernel<ProbNeuTN<256>, true>", "gemm_mfma_kernel<ProbNeuTN<128>, true>"),
     "topk_select": ("topk_select_reg_kernel<16, true>", "topk_select_reg_kernel<32, true>", "topk_select_reg_kernel<4, true>"),
-    "out_rows": "token_rows_kernel<2, false>", "dh_rows": "token_rows_kernel<2, false>",
+    "out_rows": "token_rows_kernel<2, false, true>", "dh_rows": "token_rows_kernel<2, false, true>",
 }
 GATHER_SCATTER = ("value_gemm", "dact_gemm", "dh_gemm", "dV_gemm", "dK_gemm", "pair_out", "pair_dh", "seg_dv", "seg_dk")
 
