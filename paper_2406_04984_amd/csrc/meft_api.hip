@@ -3,7 +3,6 @@
 // the kernels of the headers included below.
 #include <hip/hip_runtime.h>
 
-#include <atomic>
 #include <cmath>
 #include <cstdint>
 #include <cstdlib>
@@ -591,18 +590,18 @@ constexpr int kPersistentWgs = 256;   // compute units of an MI355X; a multiple 
 // Bytes readable from an operand's lowest address; buffer loads (32-bit offsets) where both fit.  Setting
 // MEFT_GLOBAL_LOADS=1 in the environment selects the global-load kernels (those for operands of 4 GB and more)
 // at any size, so that tests reach them with small inputs.
-// (the environment is read once, when the library is loaded; meft_debug_global_loads overrides it)
-std::atomic<int> g_force_global_loads{[] {
+// (the environment is read once, when the library is loaded; meft_debug_global_loads overrides it.  Read and written under
+// g_api_mutex only: the launches of one call depend on each other's choice, so it may not change between them.)
+bool g_force_global_loads = [] {
   const char* env = getenv("MEFT_GLOBAL_LOADS");
-  return (env && env[0] == '1') ? 1 : 0;
-}()};
+  return env && env[0] == '1';
+}();
 
 constexpr uint64_t kBufLimit = 0xFFFF0000ull;   // bytes that a buffer resource's 32-bit offsets reach
 
 template <class P>
 void set_gemm_extents(P& p, uint64_t a_bytes, uint64_t b_bytes) {
-  const bool forced_global = g_force_global_loads.load(std::memory_order_relaxed) != 0;
-  p.buf = !forced_global && a_bytes < kBufLimit && b_bytes < kBufLimit;
+  p.buf = !g_force_global_loads && a_bytes < kBufLimit && b_bytes < kBufLimit;
   p.a_bytes = p.buf ? (uint32_t)a_bytes : 0u;
   p.b_bytes = p.buf ? (uint32_t)b_bytes : 0u;
 }
@@ -1144,7 +1143,7 @@ static meft_status bwd_impl(const meft_shape& s, const void* h, const void* K, c
 // Whether the contractions of the batch union gather K's and V's rows themselves instead of reading compacted copies: the
 // large tiles by buffer loads do.  The copies cost 2 x 43 us of 747 at 1023 tokens, 16384 rows x 2048.
 static bool union_direct(const meft_shape& s, const UnionGeom& g) {
-  return g_force_global_loads.load(std::memory_order_relaxed) == 0 && (uint64_t)s.N * s.d * 2 < kBufLimit &&
+  return !g_force_global_loads && (uint64_t)s.N * s.d * 2 < kBufLimit &&
          (uint64_t)s.T * s.d * 2 < kBufLimit && (uint64_t)s.T * g.nvb * g.vbs * 2 < kBufLimit && !small_tiles(g.vs, g.vbs) &&
          !small_tiles(g.vs, s.d);
 }
@@ -1169,7 +1168,7 @@ static void launch_union_nc(const char* name, const meft_shape& s, const UnionGe
 
 // Shared front part of the batch-union forward and backward: index structure from n_S, tile schedule, compacted
 // K and V, and A' = ReLU(h K[S]^T).
-static void union_front(const meft_shape& s, const UnionGeom& g, const UnionWs& w, const void* h, const void* K,
+static void union_front(const meft_shape& s, const UnionGeom& g, const UnionWs& w, bool direct, const void* h, const void* K,
                         const void* V, const int32_t* S, const int32_t* n_S, hipStream_t st) {
   const size_t n_slots = (size_t)g.nvb * s.T, n_rows = (size_t)g.nvb * g.vbs;
   const size_t n_thr = (n_slots + kSlotPad) > n_rows + kTagPad ? (n_slots + kSlotPad) : n_rows + kTagPad;
@@ -1179,7 +1178,7 @@ static void union_front(const meft_shape& s, const UnionGeom& g, const UnionWs& 
   MEFT_LAUNCH("build_sched", build_sched_kernel, dim3(1), dim3(1024), 0, st, w.group_off, g.nvb, sched_cap(g.vs),
               w.sched_pairs, w.sched_tiles, w.sched_len, 0);
   const TokenSched sched{w.sched_pairs, w.sched_tiles, w.sched_len, sched_cap(g.vs), sched_max_tiles(g.vs)};
-  if (union_direct(s, g)) {
+  if (direct) {
     ProbTokKCRows<kTokRelu> pr{};
     fill_union_kc(pr, s, g, w, sched, h, K, w.Ap, nullptr);
     launch_gemm_mfma_buf("union_score_gemm", pr, tile_bound(g.vs, (g.vbs + kTN - 1) / kTN), st);
@@ -1227,9 +1226,10 @@ meft_status meft_union_fwd(const meft_shape* shape, const void* h, const void* K
               (size_t)s.N, 0);
   MEFT_LAUNCH("mark_idx", mark_idx_kernel, dim3((P + 255) / 256), dim3(256), 0, st, idx, P, s.N, w.flag);
   launch_bwd_head(s, w.flag, w.chunk_cnt, S, n_S, nullptr, nullptr, nullptr, nullptr, nullptr, st);
-  union_front(s, g, w, h, K, V, S, n_S, st);
+  const bool direct = union_direct(s, g);
+  union_front(s, g, w, direct, h, K, V, S, n_S, st);
   const TokenSched sched{w.sched_pairs, w.sched_tiles, w.sched_len, sched_cap(g.vs), sched_max_tiles(g.vs)};
-  if (union_direct(s, g)) launch_union_nc("union_value_gemm", s, g, w, sched, w.Ap, V, st);
+  if (direct) launch_union_nc("union_value_gemm", s, g, w, sched, w.Ap, V, st);
   else launch_tok<ProbTokNC, TokNCSmall>("union_value_gemm", g.vs, s.d, (uint64_t)s.T * g.nvb * g.vbs * 2, (uint64_t)g.nvb * g.vbs * s.d * 2, (uint64_t)s.T * g.nvb * s.d * 2, [&](auto& pv) {
     pv.A = w.Ap; pv.W = w.Vc; pv.sched = sched; pv.bs = g.vbs; pv.bsp = g.vbs;
     pv.d = s.d; pv.part = w.part;
@@ -1256,10 +1256,10 @@ meft_status meft_union_bwd(const meft_shape* shape, const void* h, const void* K
   hipStream_t st = static_cast<hipStream_t>(stream);
   MEFT_API_LOCK();
   clear_stale_error();
-  union_front(s, g, w, h, K, V, S, n_S, st);
+  const bool direct = union_direct(s, g);
+  union_front(s, g, w, direct, h, K, V, S, n_S, st);
   const TokenSched sched{w.sched_pairs, w.sched_tiles, w.sched_len, sched_cap(g.vs), sched_max_tiles(g.vs)};
   const uint16_t *hh = static_cast<const uint16_t*>(h), *gg = static_cast<const uint16_t*>(dOut);
-  const bool direct = union_direct(s, g);
   if (direct) {
     ProbTokKCRows<kTokMasked> pg{};
     fill_union_kc(pg, s, g, w, sched, gg, V, w.DS, w.Ap);
@@ -1527,7 +1527,10 @@ meft_status meft_probe_mfma(float* out, int workgroups, int iters, void* stream)
 
 const char* meft_last_device_error(void) { return hipGetErrorString(g_last_device_error); }
 
-void meft_debug_global_loads(int on) { g_force_global_loads.store(on ? 1 : 0, std::memory_order_relaxed); }
+void meft_debug_global_loads(int on) {
+  MEFT_API_LOCK();
+  g_force_global_loads = on != 0;
+}
 
 void meft_profile_enable(int on) {
   MEFT_API_LOCK();

@@ -4,10 +4,12 @@
  */
 #define _GNU_SOURCE
 #include <dlfcn.h>
+#include <pthread.h>
 #include <stddef.h>
 #include <stdint.h>
 #include <stdlib.h>
 #include <string.h>
+#include <unistd.h>
 
 typedef struct { uint32_t x, y, z; } dim3_t;
 
@@ -26,6 +28,18 @@ static uint64_t next_handle = 0x1000;
 static int32_t counts_value = 1;   /* what a copy to the host delivers in every word */
 
 static int capturing;
+
+/* rec_flip(n, f): another thread calls f(1) while the n-th launch from now on is under way; rec_flipped() waits for it */
+static void (*flip_call)(int);
+static int flip_in;
+static pthread_t flip_thread;
+static void* flip_main(void* arg) { (void)arg; flip_call(1); return NULL; }
+void rec_flip(int n, void (*f)(int)) { flip_in = n; flip_call = f; }
+int rec_flipped(void) {
+  if (!flip_call || flip_in > 0) return 0;
+  flip_call = NULL;
+  return pthread_join(flip_thread, NULL) == 0;
+}
 
 void rec_capture(int on) { capturing = on; }
 int rec_count(void) { return n_recs; }
@@ -60,6 +74,10 @@ int hipLaunchKernel(const void* f, dim3_t grid, dim3_t block, void** args, size_
   r->block[0] = block.x; r->block[1] = block.y; r->block[2] = block.z;
   r->lds = lds;
   r->stream = (uint64_t)(uintptr_t)stream;
+  if (flip_in > 0 && --flip_in == 0) {
+    if (pthread_create(&flip_thread, NULL, flip_main, NULL)) abort();
+    usleep(100000);   /* a thread that does not have to wait for this call has come through by then */
+  }
   return 0;
 }
 

@@ -1,6 +1,7 @@
 """What libmeft asks of the HIP runtime, without a GPU: record([(shape, calls), ...]) makes the calls of the C ABI in a
 process where tests/hip_recorder.c stands in for the runtime, and returns the launches, copies, event records and stream
-waits of each entry, in order.  The call names "capture" and "no_capture" set what the runtime says of the stream from then on.
+waits of each entry, in order.  The call names "capture" and "no_capture" set what the runtime says of the stream from then on;
+"flip N" has another thread call meft_debug_global_loads(1) while the N-th launch from then on is under way.
 Addresses are made up; the library does not follow them on the host."""
 import ctypes
 import json
@@ -22,7 +23,7 @@ def record(jobs):
     with tempfile.TemporaryDirectory() as tmp:
         rec = os.path.join(tmp, "hip_recorder.so")
         subprocess.check_call(["gcc", "-shared", "-fPIC", "-O1", "-Wall", "-Wextra", "-o", rec,
-                               os.path.join(ROOT, "tests", "hip_recorder.c"), "-ldl"])
+                               os.path.join(ROOT, "tests", "hip_recorder.c"), "-ldl", "-pthread"])
         p = subprocess.run([sys.executable, os.path.abspath(__file__), rec], input=json.dumps(jobs), text=True,
                            stdout=subprocess.PIPE, stderr=subprocess.PIPE, timeout=300)
     assert p.returncode == 0, p.stderr[-4000:]
@@ -87,8 +88,14 @@ def _main(rec_path):
             if c.endswith("capture"):
                 rec.rec_capture(int(c == "capture"))
                 continue
+            if c.startswith("flip "):
+                rec.rec_flip(int(c[5:]), lib.meft_debug_global_loads)
+                continue
             rc = call(s, c)
             assert rc == 0, (fields, c, rc)
+        if any(c.startswith("flip ") for c in calls):
+            assert rec.rec_flipped(), calls
+            lib.meft_debug_global_loads(0)
         rows = []
         for i in range(rec.rec_count()):
             r = rec.rec_at(i).contents
