@@ -5,9 +5,8 @@
 //   ceil(cnt / BM), and on the matrix-core path tok_of_slot, slot_of_ent and the per-XCD tile schedule.
 // slot_of_ent carries kSmallSlot where the entry's group is one of at most small_rows tokens (small_groups.h).
 //
-// Small dispatches (dispatch_one_kernel: up to kDispOneTokens tokens, kDispOneEntries entries and kDispOneWork entries x blocks)
-// take one launch: a workgroup per block looks through all the entries (they come out of L2, and a launch costs more) and places
-// its own, and one more counts the entries of all blocks, writes the tables and deals the groups to the XCDs.  Two launches /
+// Small dispatches (dispatch_one_form) take one launch: a workgroup per block looks through all the entries (they come out of L2,
+// and a launch costs more) and places its own, and one more counts the entries of all blocks, writes the tables and deals the groups to the XCDs.  Two launches /
 // one: 2048 tokens x 4, 64 blocks 21.8 -> 11.2 us; 8192 x 4, 64 blocks 24 -> 14; 4096 x 8, 256 blocks 30 -> 18 (of either about
 // half by the faster tables).  At the limits, whole forward of a layer with d 64: 16384 x 4, 64 blocks 105.2 -> 99.8, 128
 // blocks 116.3 -> 105.4; beyond them 16384 x 8, 16 blocks 114.2 -> 126.1.
@@ -38,7 +37,22 @@ constexpr int kDispScanMax = 32768;     // and this many counts
 
 constexpr int kDispOneTokens = 16 * 1024;   // one launch: tokens (sixteen per thread)
 constexpr int kDispOneEntries = 1 << 16;    // entries, which one workgroup counts
-constexpr int kDispOneWork = 1 << 23;       // and entries x blocks
+constexpr int kDispOneWork = 1 << 23;       // entries x blocks
+constexpr int kDispOneShare = 3584;         // and, beyond kDispFewTokens tokens, entries per block
+constexpr int kDispFewTokens = 4096;        // more tokens, and at least 256 for each block (at most 64 blocks, then): kFew
+// Which form of dispatch_one_kernel: 0 none (two launches), 1 kFew, 2 the other.
+// Forwards without the value sum of layers with d 64 (us; two launches / one, without and with kFew): 16384 tokens x 1, one block
+// 60.2 / 69.6 / 59.3; x 4, 4 blocks 71.0 / 82.6 / 74.7; x 4, 16 blocks 75.6 / 79.9 / 76.6; 8192 x 8, 16 blocks 53.9 / 55.8 / 55.0;
+// 8192 x 4, 8 blocks 46.6 / 46.8 / 45.4; 6000 x 8, 16 blocks 44.8 / 43.8 / 44.1; 16384 x 4, 32 blocks 79.3 / 79.7 / 78.4; and with
+// Zipf-popular blocks 16384 x 4, 32 blocks 79.3 / 84.3 / 79.2; 8192 x 8, 24 blocks 55.4 / 58.6 / 55.6; 6000 x 4, 8 blocks 40.2 /
+// 39.8 / 38.0; 16384 x 4, 64 blocks 84.3 / 85.5 / 81.6 (with blocks alike 85.0 / 80.3 / 80.9).
+inline int dispatch_one_form(int n_tok, int e, int n_blocks) {
+  const long long n_ent = (long long)n_tok * e;
+  if (n_blocks > kDispMaxBlocks || n_tok > kDispOneTokens || n_ent > kDispOneEntries || n_ent * n_blocks > kDispOneWork) return 0;
+  if (n_tok <= kDispFewTokens) return 2;
+  if (n_ent > (long long)kDispOneShare * n_blocks) return 0;
+  return n_blocks * 256 <= n_tok ? 1 : 2;
+}
 
 // Rank of this lane's entry among the entries of the same block in its wave, in lane (= entry) order; lane
 // `leader of the block` also writes the block's count in the wave to row[block] (row zeroed by the caller).
@@ -236,7 +250,11 @@ __global__ __launch_bounds__(1024) void dispatch_place_kernel(const int32_t* __r
 // The whole dispatch in one launch of n_blocks + 1 workgroups.  kSort: `in` holds the token's blocks in any order, ids are
 // clamped, and sblk is written; otherwise `in` is sblk (-1: no entry).  A block that a token names twice gets two entries.
 // Also zeroes clear[0 .. clear_words).
-template <bool kSort>
+// kFew, for few blocks and many tokens, where what a workgroup does one step after the other is all there is: n_blocks * parts + 1
+// workgroups, part p of a block's placing the tokens p * 1024 .. of every parts * 1024 (all of them count the block's); several
+// steps' loads on their way together; several counters per block.  (The other form is as short as it was: code that runs once
+// waits for its instructions to come from memory; with all of this it took 0.7 us more at 2048 tokens x 4, 64 blocks.)
+template <bool kSort, bool kFew>
 __global__ __launch_bounds__(1024) void dispatch_one_kernel(const int32_t* __restrict__ in, int n_tok, int e, int n_blocks,
                                                             DispatchTables tab, int32_t* __restrict__ sblk,
                                                             int32_t* __restrict__ perm, int32_t* __restrict__ tok_of_slot,
@@ -248,7 +266,9 @@ __global__ __launch_bounds__(1024) void dispatch_one_kernel(const int32_t* __res
   const int n_ent = n_tok * e, n_iter = (n_tok + 1023) >> 10;
   for (size_t i = (size_t)blockIdx.x * 1024 + tid; i < clear_words; i += (size_t)gridDim.x * 1024) clear[i] = 0;
   if (blockIdx.x == 0) {   // (first, as it takes longest)
-    if (tid < n_blocks) s_one[tid] = 0;
+    // kFew: kCopies counters per block, which the lanes of a wave share out among them (adding to one word is done lane by lane)
+    constexpr int kCopies = kFew ? 16 : 1;
+    if (tid < n_blocks * kCopies) s_one[tid] = 0;
     __syncthreads();
     for (int i0 = 0; i0 < n_ent; i0 += 8 * 1024) {   // (eight loads on their way together)
       int b[8];
@@ -261,34 +281,60 @@ __global__ __launch_bounds__(1024) void dispatch_one_kernel(const int32_t* __res
       }
 #pragma unroll
       for (int z = 0; z < 8; ++z)
-        if ((unsigned)b[z] < (unsigned)n_blocks) atomicAdd(&s_one[b[z]], 1);
+        if ((unsigned)b[z] < (unsigned)n_blocks) atomicAdd(&s_one[b[z] * kCopies + lane % kCopies], 1);
     }
     __syncthreads();
+    if constexpr (kFew) {
+      int all = tid < n_blocks * kCopies ? s_one[tid] : 0;
+#pragma unroll
+      for (int z = 1; z < kCopies; z <<= 1) all += __shfl_xor(all, z, kWave);
+      __syncthreads();
+      if (tid % kCopies == 0 && tid < n_blocks * kCopies) s_one[tid / kCopies] = all;
+      __syncthreads();
+    }
     dispatch_tables(tab, tid < n_blocks ? s_one[tid] : 0, n_blocks, s_w, tok_of_slot, pad);
     return;
   }
-  const int b = (int)blockIdx.x - 1;
+  int b = (int)blockIdx.x - 1, part = 0, parts = 1;
+  if constexpr (kFew) { parts = ((int)gridDim.x - 1) / n_blocks; part = b / n_blocks; b -= part * n_blocks; }
   int* s_cnt = s_one + n_iter * 1024;
   int below = 0;   // entries of this thread's tokens that belong to blocks before b
-#pragma unroll 1
-  for (int it = 0; it < n_iter; ++it) {
-    const int t = it * 1024 + tid;
-    int lt = 0, eq = 0;
-    if (t < n_tok) {
-      const int32_t* row = in + (size_t)t * e;
+  // (kIt iterations' loads on their way together)
+  auto look = [&](auto its, int it0) {
+    constexpr int kIt = decltype(its)::value;
+    int lt[kIt], eq[kIt];
+    const int32_t* row[kIt];
+#pragma unroll
+    for (int u = 0; u < kIt; ++u) {
+      lt[u] = eq[u] = 0;
+      row[u] = in + (size_t)min((it0 + u) * 1024 + tid, n_tok - 1) * e;
+    }
 #pragma unroll 4
-      for (int q = 0; q < e; ++q) {
-        int x = row[q];
+    for (int q = 0; q < e; ++q) {
+#pragma unroll
+      for (int u = 0; u < kIt; ++u) {
+        int x = row[u][q];
         if constexpr (kSort) x = clampi(x, 0, n_blocks - 1);
-        lt += (unsigned)x < (unsigned)b ? 1 : 0;
-        eq += x == b ? 1 : 0;
+        lt[u] += (unsigned)x < (unsigned)b ? 1 : 0;
+        eq[u] += x == b ? 1 : 0;
       }
     }
-    below += lt;
-    s_one[it * 1024 + tid] = lt << 16 | eq;
-    const int incl = wave_incl_scan(eq);
-    if (lane == 63) s_cnt[it * 16 + w] = incl;
+#pragma unroll
+    for (int u = 0; u < kIt; ++u) {
+      if ((it0 + u) * 1024 + tid >= n_tok) lt[u] = eq[u] = 0;
+      below += lt[u];
+      s_one[(it0 + u) * 1024 + tid] = lt[u] << 16 | eq[u];
+      const int incl = wave_incl_scan(eq[u]);
+      if (lane == 63) s_cnt[(it0 + u) * 16 + w] = incl;
+    }
+  };
+  int it0 = 0;
+  if constexpr (kFew) {
+#pragma unroll 1
+    for (; it0 + 4 <= n_iter; it0 += 4) look(std::integral_constant<int, 4>{}, it0);
   }
+#pragma unroll 1
+  for (; it0 < n_iter; ++it0) look(std::integral_constant<int, 1>{}, it0);
   int base, rows;   // entries of the blocks before, entries of this one
   block_excl_scan_1024(below, s_w, base);   // (its barriers order the counts above as well)
   const int mine = tid < n_iter * 16 ? s_cnt[tid] : 0;
@@ -297,7 +343,7 @@ __global__ __launch_bounds__(1024) void dispatch_one_kernel(const int32_t* __res
   __syncthreads();
   const int flag = tok_of_slot != nullptr && rows <= tab.small_rows ? kSmallSlot : 0;
 #pragma unroll 1
-  for (int it = 0; it < n_iter; ++it) {
+  for (int it = part; it < n_iter; it += parts) {
     const int t = it * 1024 + tid, lt = s_one[t] >> 16, eq = s_one[t] & 0xFFFF;
     const int first = base + s_cnt[it * 16 + w] + wave_incl_scan(eq) - eq;
     for (int z = 0; z < eq; ++z) {

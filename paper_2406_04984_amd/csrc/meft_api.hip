@@ -692,21 +692,26 @@ void launch_dispatch(const meft_shape& s, const DispatchWs& w, const int32_t* bl
   const DispatchTables tab{w.cnt, w.group_off, w.tile_off, BM, sched_cap(s), want_sched ? w.sched_pairs : nullptr,
                            w.sched_tiles, w.sched_len, small, small ? w.small_ent : nullptr, w.small_grp, w.small_cnt};
   int32_t* tok = dense || want_sched ? w.tok_of_slot : nullptr;
-  if (s.n_blocks <= kDispMaxBlocks && s.T <= kDispOneTokens && n_ent <= kDispOneEntries &&
-      (int64_t)n_ent * s.n_blocks <= kDispOneWork) {
-    const size_t lds = (size_t)((s.T + 1023) / 1024) * (1024 + 16) * sizeof(int);   // up to 65 KB
+  if (const int form = dispatch_one_form(s.T, s.top_e, s.n_blocks)) {
+    const int n_iter = (s.T + 1023) / 1024;
+    const size_t lds = (size_t)n_iter * (1024 + 16) * sizeof(int);   // up to 65 KB
     static std::once_flag configured_one;
     std::call_once(configured_one, [] {
       const int most = kDispOneTokens / 1024 * (1024 + 16) * (int)sizeof(int);
-      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&dispatch_one_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize, most);
-      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&dispatch_one_kernel<false>), hipFuncAttributeMaxDynamicSharedMemorySize, most);
+      const void* forms[] = {reinterpret_cast<const void*>(&dispatch_one_kernel<true, true>), reinterpret_cast<const void*>(&dispatch_one_kernel<false, true>),
+                             reinterpret_cast<const void*>(&dispatch_one_kernel<true, false>), reinterpret_cast<const void*>(&dispatch_one_kernel<false, false>)};
+      for (const void* f : forms) (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, most);
     });
-    if (block_idx)
-      MEFT_LAUNCH("dispatch", dispatch_one_kernel<true>, dim3(s.n_blocks + 1), dim3(1024), lds, st, block_idx, s.T, s.top_e, s.n_blocks,
-                  tab, w.sblk, w.perm, tok, w.slot_of_ent, kSlotPad, clear, clear_words);
-    else
-      MEFT_LAUNCH("dispatch", dispatch_one_kernel<false>, dim3(s.n_blocks + 1), dim3(1024), lds, st, w.sblk, s.T, s.top_e, s.n_blocks,
-                  tab, nullptr, w.perm, tok, w.slot_of_ent, kSlotPad, clear, clear_words);
+    const int room = form == 1 ? 64 / s.n_blocks : 1, parts = room < n_iter ? room : n_iter;   // >= 1
+    const dim3 grid(s.n_blocks * parts + 1);
+    auto go = [&](auto kernel, const int32_t* in, int32_t* sorted) {
+      MEFT_LAUNCH("dispatch", kernel, grid, dim3(1024), lds, st, in, s.T, s.top_e, s.n_blocks, tab, sorted, w.perm, tok, w.slot_of_ent,
+                  kSlotPad, clear, clear_words);
+    };
+    if (block_idx && form == 1) go(dispatch_one_kernel<true, true>, block_idx, w.sblk);
+    else if (block_idx) go(dispatch_one_kernel<true, false>, block_idx, w.sblk);
+    else if (form == 1) go(dispatch_one_kernel<false, true>, w.sblk, nullptr);
+    else go(dispatch_one_kernel<false, false>, w.sblk, nullptr);
     return;
   }
   if (fast_dispatch(s)) {

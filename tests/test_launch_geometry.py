@@ -94,3 +94,18 @@ def test_gradient_rows_of_small_groups_share_a_launch(T, d, own):
     rows = [r for r in rows if "token_rows" in r["name"] or "small_dvdk" in r["name"]]
     assert any("small_dvdk_kernel" in r["name"] for r in rows) == own, rows
     assert not own or rows[-1]["grid"][0] == T, rows
+
+
+# The one-launch dispatch does one workgroup's work step after step where blocks are few and tokens many: 82.6 us for a forward
+# that took 71.0 with two launches (16384 tokens x 4 of 4 blocks), 69.6 / 60.2 (x 1 of 1); 58.7 / 55.3 with popular blocks
+# where a block's workgroup placed all of its tokens (8192 x 8 of 24).
+@pytest.mark.parametrize("T, top_e, n_blocks, form", [
+    (16384, 1, 1, "place"), (16384, 4, 4, "place"), (8192, 8, 16, "place"), (8192, 2, 2, "place"), (4096, 1, 1, "one"),
+    (4096, 16, 16, "one"), (4097, 1, 1, "place"), (4097, 1, 2, "few"), (8192, 8, 24, "few"), (8192, 2, 32, "few"), (8192, 2, 33, "one"),
+    (16384, 4, 64, "few"), (16384, 4, 65, "one"), (16384, 1, 4, "place"), (16384, 1, 5, "few")])
+def test_dispatch_of_few_blocks(T, top_e, n_blocks, form):
+    for call in ("fwd", "bwd"):
+        rows, = record([(shape(T, 64, n_blocks, 16, top_e, top_e, "bf16"), [call])])
+        got = {"place": "dispatch_place", "few": "dispatch_one_kernelILb%dELb1E" % (call == "fwd"),
+               "one": "dispatch_one_kernelILb%dELb0E" % (call == "fwd")}
+        assert [f for f, name in got.items() if any(name in r["name"] for r in rows)] == [form], rows
