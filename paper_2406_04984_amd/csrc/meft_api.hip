@@ -286,21 +286,29 @@ struct FwdWs : DenseWs {
 // ceil(L / kSegChunk) chunks are fewer than 2 L / kSegChunk
 size_t seg_multi_chunks(const meft_shape& s) { return 2 * (((size_t)s.T * s.top_k) / kSegChunk) + 1; }
 
+// Per-pair backward: whether the pairs are grouped by one launch (pair_one_kernel), and its buckets' neurons as a power of two
+int pair_one_shift(const meft_shape& s) {
+  int shift = 0;
+  while ((s.N - 1) >> shift >= kPairOneBuckets) ++shift;
+  return shift;
+}
+bool pair_one(const meft_shape& s) { return (int64_t)s.T * s.top_k <= kPairOneP && pair_one_shift(s) + kPairBits <= 32; }
+
 struct BwdWs : DenseWs {
   // gather path
   float* ds;
-  int32_t *cnt_n, *seg_off, *pair_list, *pair_sorted, *totals;   // pair_sorted also holds the pairs' places (pair_count)
+  int32_t *cnt_n, *seg_off, *pair_list, *pair_sorted, *totals, *first;   // pair_sorted also holds the pairs' places (pair_count)
   int2* seg;         // (token, activation) of the pairs, segment by segment
   float* ds_part;    // partial activation gradients in the same order, one piece per group of column slices
   PairSums* sums;
-  SegWork* work;     // at most one chunk per touched neuron plus one per kSegChunk pairs
+  SegWork* work;     // at most one chunk per touched neuron plus one per kSegChunk pairs; pair_one: an entry per pair
   int4* multi;       // neurons of more than one chunk
   float* seg_part;   // fp32 chunk sums of the neurons with more than kSegChunk pairs: [chunk][dV | dK][d]
   size_t bytes;
   BwdWs(const meft_shape& s, void* ws) {
     Carver c(ws);
     const size_t P = (size_t)s.T * s.top_k;
-    ds = nullptr; cnt_n = seg_off = pair_list = pair_sorted = totals = nullptr; seg_part = nullptr;
+    ds = nullptr; cnt_n = seg_off = pair_list = pair_sorted = totals = first = nullptr; seg_part = nullptr;
     sums = nullptr; work = nullptr; multi = nullptr; seg = nullptr; ds_part = nullptr;
     if (use_dense(s)) {
       carve_dense(s, c);
@@ -313,7 +321,8 @@ struct BwdWs : DenseWs {
       totals = c.take<int32_t>(3);
       sums = c.take<PairSums>(s.N > kScanSelfMax ? (size_t)(s.N + kScanChunk - 1) / kScanChunk : 0);
       const size_t n_seg = (size_t)s.N < P ? (size_t)s.N : P;
-      work = c.take<SegWork>(n_seg + P / kSegChunk + 1);
+      work = c.take<SegWork>(pair_one(s) ? P : n_seg + P / kSegChunk + 1);
+      first = c.take<int32_t>(pair_one(s) ? P : 0);
       multi = c.take<int4>(P / kSegChunk + 1);
       seg_part = c.take<float>(seg_multi_chunks(s) * 2 * (size_t)s.d);
       seg = c.take<int2>(P);
@@ -542,6 +551,18 @@ void launch_pair_rows(const char* name, const meft_shape& s, const void* W, cons
               gate, row ? s.T : 0, s.d, s.top_k, s.N, static_cast<T*>(row), f);
 }
 
+// Whether dV, ds and dK of a chunk come out of one kernel (seg_rows_kernel) or of two, by the bytes of the rows of one operand that
+// are touched at most.  Backward, us, two kernels / one.  Pairs grouped by one launch: 512 tokens x 16 of 16384 neurons (8192 rows) x
+// 1 KB 26.7 / 22.1, x 2 KB 31.3 / 30.4, x 3 KB 36.4 / 38.9; 250 x 64 of 65536 x 1.4 KB 44.8 / 44.7, x 2 KB 49.1 / 51.0; 1000 x 16 of
+// 4096 x 3 KB 39.8 / 42.4; 300 x 50 of 2000 x 3 KB 36.8 / 33.1, x 16 KB 66.4 / 86.4.  By five: 1500 x 16 of 3000 x 1 KB 36.0 /
+// 32.3, of 20000 40.0 / 41.7; 2500 x 25 of 1664 x 2 KB 63.9 / 62.2, x 3 KB 78.3 / 85.3; 8192 x 8 of 4000 x 2 KB 71.5 / 74.4;
+// 65536 x 16 of 1000 x 1 KB 691 / 703.
+bool seg_rows_fused(const meft_shape& s, int slices) {
+  const int64_t P = (int64_t)s.T * s.top_k, bytes = (s.N < P ? s.N : P) * s.d * (s.dtype == MEFT_BF16 ? 2 : 4), MB = 1 << 20;
+  if (pair_one(s)) return slices <= 2 ? bytes <= 24 * MB : bytes <= 12 * MB && P * slices <= 65536;
+  return slices <= 2 && bytes <= (slices == 1 ? 8 : 6) * MB && P <= 131072;
+}
+
 // The backward of the per-pair path.
 template <typename T>
 void launch_pair_bwd(const meft_shape& s, const BwdWs& w, const void* h, const void* K, const void* V, const int32_t* idx,
@@ -550,18 +571,20 @@ void launch_pair_bwd(const meft_shape& s, const BwdWs& w, const void* h, const v
   const int P = s.T * s.top_k;
   const size_t n_pairs = (size_t)P;
   const dim3 pairs((unsigned)(((int64_t)P + 255) / 256));
-  // four chunks per workgroup: at most one chunk per touched neuron plus one per kSegChunk pairs
-  const int64_t n_seg = s.N < P ? s.N : P, groups = (n_seg + P / kSegChunk + 3) / 4;
+  const int64_t n_seg = s.N < P ? s.N : P;
   // (a token's ids may repeat where they were clamped: more than kSegChunk pairs may have one neuron whatever T is)
   const int n_multi = P <= kSegChunk ? 0 : P / kSegChunk < 512 ? P / kSegChunk + 1 : 512;
-  if (P <= kPairOneP && s.N <= kPairOneN) {
-    static std::once_flag configured;
+  PairLists lists{};
+  if (pair_one(s)) {
+    lists = PairLists{w.first, P, touched, n_touched, w.multi, w.totals};
+    static std::once_flag configured;   // 80 KB of pairs
     std::call_once(configured, [] {
-      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&pair_one_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                kPairOneLds * (int)sizeof(int32_t));
+      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&pair_one_kernel<kPairOneBatch>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                kPairOneP * (int)sizeof(uint32_t));
     });
-    MEFT_LAUNCH("pair_one", pair_one_kernel, dim3(kPairOneWgs), dim3(kScanThreads), kPairOneLds * sizeof(int32_t), st, idx, act, P,
-                s.N, s.top_k, touched, n_touched, w.work, w.multi, w.totals, w.pair_sorted, w.seg);
+    auto one = P <= 8 * kScanThreads ? pair_one_kernel<8> : pair_one_kernel<kPairOneBatch>;
+    MEFT_LAUNCH("pair_one", one, dim3(kPairOneWgs), dim3(kScanThreads), (size_t)P * sizeof(uint32_t), st, idx, act, P, s.N, s.top_k,
+                pair_one_shift(s), w.work, w.multi, w.first, w.pair_sorted, w.seg);
   } else {
     MEFT_LAUNCH("fill_i32", fill_i32_kernel, dim3((unsigned)(((size_t)s.N + 255) / 256)), dim3(256), 0, st, w.cnt_n, (size_t)s.N, 0);
     MEFT_LAUNCH("pair_count", pair_count_kernel, pairs, dim3(256), 0, st, idx, P, s.N, w.cnt_n, w.pair_sorted);
@@ -575,11 +598,29 @@ void launch_pair_bwd(const meft_shape& s, const BwdWs& w, const void* h, const v
                 w.seg_off, w.pair_list, idx, act, P, s.N, s.top_k, n_multi, w.pair_sorted, w.seg);
   }
   const int slices = row_slices<T>(s), parts = slices < kDsParts ? slices : kDsParts;
-  auto seg_grid = [&](int n) { return grid_xcd(groups * n < kSegWorkgroups ? groups * n : kSegWorkgroups); };
-  MEFT_LAUNCH("seg_dv", seg_dv_kernel<T>, seg_grid(parts), dim3(256), 0, st, w.work, w.totals, w.seg,
-              static_cast<const T*>(V), static_cast<const T*>(dOut), s.d, slices, n_pairs, static_cast<T*>(dV), w.seg_part, w.ds_part);
-  MEFT_LAUNCH("seg_dk", seg_dk_kernel<T>, seg_grid(slices), dim3(256), 0, st, w.work, w.totals, w.seg, w.pair_sorted,
-              w.ds_part, static_cast<const T*>(h), s.d, slices, n_pairs, static_cast<T*>(dK), w.seg_part, dh ? w.ds : nullptr);
+  const int64_t n_work = lists.first ? P : n_seg + P / kSegChunk;   // work entries at most
+  if (seg_rows_fused(s, slices)) {
+    const int lg = slices >= 3 ? 2 : slices - 1;
+    const int64_t wgs = ((n_work << lg) + 3) / 4;
+    const int grid = (int)(wgs < kSegRowsWgs ? wgs : kSegRowsWgs) + (lists.first ? 1 : 0);
+    MEFT_LAUNCH("seg_rows", seg_rows_kernel<T>, dim3(grid), dim3(256), 0, st, w.work, w.totals, P, w.seg, w.pair_sorted,
+                static_cast<const T*>(V), static_cast<const T*>(dOut), static_cast<const T*>(h), s.d, slices, lg, static_cast<T*>(dV),
+                static_cast<T*>(dK), w.seg_part, dh ? w.ds : nullptr, lists);
+  } else {
+    // work entries per chunk, if the pairs fall on the neurons alike
+    const double chunks = s.N * -std::expm1(-(double)P / s.N);
+    const int entries = lists.first ? (int)(P / chunks + 0.5) : 1;
+    auto launch = [&](auto dv, auto dk) {
+      const int64_t groups = (n_work + 3) / 4;   // four entries per workgroup
+      auto grid = [&](int n, int more) { return grid_xcd((groups * n < kSegWorkgroups ? groups * n : kSegWorkgroups) + more); };
+      MEFT_LAUNCH("seg_dv", dv, grid(parts, lists.first ? 8 : 0), dim3(256), 0, st, w.work, w.totals, w.seg, static_cast<const T*>(V),
+                  static_cast<const T*>(dOut), s.d, slices, n_pairs, static_cast<T*>(dV), w.seg_part, w.ds_part, entries, lists);
+      MEFT_LAUNCH("seg_dk", dk, grid(slices, 0), dim3(256), 0, st, w.work, w.totals, w.seg, w.pair_sorted, w.ds_part,
+                  static_cast<const T*>(h), s.d, slices, n_pairs, static_cast<T*>(dK), w.seg_part, dh ? w.ds : nullptr, entries);
+    };
+    if (lists.first) launch(seg_dv_kernel<T, true>, seg_dk_kernel<T, true>);
+    else launch(seg_dv_kernel<T, false>, seg_dk_kernel<T, false>);
+  }
   const int n_fin = n_multi == 0 ? 0 : P / kSegChunk < 4096 ? (P / kSegChunk + 8) / 8 * 8 : 4096;
   const SegFinish<T> f{n_fin, w.multi, w.totals, w.seg_part, static_cast<T*>(dK), static_cast<T*>(dV)};
   launch_pair_rows<T, 4>("pair_dh", s, K, idx, w.ds, act, dh, f, st);

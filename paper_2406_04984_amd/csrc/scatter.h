@@ -5,7 +5,10 @@
 //   dV[j,:] = sum act * dOut[t,:],  ds = act > 0 ? dOut[t,:] . V[j,:] : 0,  dK[j,:] = sum ds * h[t,:].
 // Only touched rows are written.  A token's dh, the sum of ds * K[j,:] over its pairs, follows in gather.h.
 #pragma once
+#include <type_traits>
+
 #include "common.h"
+#include "select.h"
 
 namespace meft {
 
@@ -302,104 +305,182 @@ __global__ __launch_bounds__(256) void seg_sort_kernel(const int4* __restrict__ 
   put(o + r, p);
 }
 
-// All of the above in one launch: up to kPairOneP pairs of kPairOneN neurons.  Every workgroup counts all pairs in LDS, eight a
-// thread, and scans all counters; neuron j belongs to workgroup j % kPairOneWgs, which writes its work entries and puts its pairs
-// in order.  The five launches that this replaces depend on each other and take 4-7 us each, however few the pairs.
-// fp32 steps, five launches / one: 78 tokens x 4 pairs, 2496 neurons 53.5 -> 41 us; 124 x 37, 7872 neurons 56.5 -> 51.  More pairs
-// than a thread's eight would have to be read again for every step: in that form 9937 pairs gained 2 us and 64000 lost 11 of 140.
-constexpr int kPairOnePairs = 8, kPairOneP = kPairOnePairs * kScanThreads, kPairOneN = 1 << 14, kPairOneWgs = 128;
-constexpr int kPairOnePer = kPairOneN / kScanThreads;   // consecutive counters of a thread
-constexpr int kPairOneLds = kPairOneN + kPairOneN / kPairOnePer + 1;
+// All of the above in one launch, for up to kPairOneP pairs.  Every workgroup counts all pairs by bucket (2^shift consecutive
+// neurons, so that kPairOneBuckets cover them all) in LDS; bucket b belongs to workgroup b % kPairOneWgs, which lists its pairs
+// and puts them in order of (neuron, pair).  Nobody counts the touched neurons before a bucket, so the work entries are not
+// compacted: entry i is about the i-th pair in order, and holds a chunk where that is the chunk's first pair (len 0: none).
+// first[i] = neuron where the pair is its neuron's first (~neuron where the neuron has more than one chunk, which are then
+// described in multi[i / kSegChunk]), kNotFirst elsewhere: pair_lists_body makes the lists out of that.
+// The five launches that this replaces depend on each other and take 2 to 12 us each, however few the pairs; this one takes 5 at 8192
+// pairs.  Backward, five launches / one, us: 512 tokens x 16 pairs, d 256 bf16, 20480 neurons 33.5 / 22.5, 262144 neurons 36.8 /
+// 23.8; 250 x 64, d 784 fp32, 65536 neurons 70.9 / 61.2.  With more pairs the looking through all of them by every workgroup
+// costs what the launches do: 24000 pairs of 20000 neurons, d 256 fp32 40.0 / 39.7, d 512 bf16 41.4 / 41.7.
+constexpr int kPairBits = 15, kPairOneBatch = 20, kPairOneP = kPairOneBatch * kScanThreads, kPairOneBuckets = 4096, kPairOneWgs = 128;
+constexpr int kPairOneOwn = kPairOneBuckets / kPairOneWgs, kNotFirst = INT32_MIN;
+
+// A thread keeps kBatch pairs: 8 where they are enough, kPairOneBatch otherwise.
+template <int kBatch>
 __global__ __launch_bounds__(kScanThreads) void pair_one_kernel(const int32_t* __restrict__ idx, const float* __restrict__ act, int P,
-                                                       int N, int k, int32_t* __restrict__ touched,
-                                                       int32_t* __restrict__ n_touched, SegWork* __restrict__ work,
-                                                       int4* __restrict__ multi, int32_t* __restrict__ totals,
+                                                       int N, int k, int shift, SegWork* __restrict__ work,
+                                                       int4* __restrict__ multi, int32_t* __restrict__ first,
                                                        int32_t* __restrict__ pair_sorted, int2* __restrict__ seg) {
-  constexpr int kPer = kPairOnePer, kThreads = kScanThreads;
-  static_assert(kPer <= kPairOneWgs && kPairOneP <= kBitonicMax && (long long)kPairOneP * kPairOneN <= 1ll << 31, "");   // at most one of a thread's counters is the workgroup's
-  extern __shared__ int32_t s_cnt[];   // counts, then first places; neuron j at j + j / kPer, so that the scan's reads spread over the banks
-  __shared__ __attribute__((aligned(16))) int32_t s_p[kBitonicMax];
-  __shared__ int32_t s_list[kPairOneP];   // this workgroup's segments, where they are in the grouped list
-  __shared__ int32_t s_long[kPairOneN / kPairOneWgs], s_sum[5][kThreads / 64], s_n, s_nlong;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, wg = blockIdx.x;
-  auto slot = [](int j) { return j + j / kPer; };
-  auto mine = [&](int j) { return j % kPairOneWgs == wg; };
-  int jp[kPairOnePairs], at[kPairOnePairs];   // of the pairs tid + kThreads * z: neuron, place among the neuron's as they come
+  constexpr int kPer = kPairOneBuckets / kScanThreads;   // consecutive counters of a thread
+  constexpr uint32_t kPairMask = (1u << kPairBits) - 1;
+  static_assert(kPer == 4 && kPairOneOwn <= 32, "");
+  extern __shared__ uint32_t s_keys[];   // [P]: the workgroup's pairs, bucket by bucket: (neuron - bucket's first) << kPairBits | pair
+  __shared__ __attribute__((aligned(16))) int32_t s_cnt[kPairOneBuckets + 4];   // pairs of the bucket, then its first place
+  __shared__ int32_t s_off[kPairOneOwn + 1], s_at[kPairOneOwn], s_w[kScanThreads / 64];   // own buckets: where in s_keys
+  const int tid = threadIdx.x, wg = blockIdx.x;
+  int jp[kBatch];   // neurons of the pairs tid + kScanThreads * z
 #pragma unroll
-  for (int z = 0; z < kPairOnePairs; ++z) jp[z] = idx[min(tid + kThreads * z, P - 1)];
-  for (int i = tid; i <= slot(N); i += kThreads) s_cnt[i] = 0;
-  if (tid == 0) s_n = s_nlong = 0;
+  for (int z = 0; z < kBatch; ++z) jp[z] = idx[min(tid + kScanThreads * z, P - 1)];
+  auto pairs = [&](auto&& f) {   // f(pair, neuron) for every pair
+#pragma unroll
+    for (int z = 0; z < kBatch; ++z)
+      if (tid + kScanThreads * z < P) f(tid + kScanThreads * z, clampi(jp[z], 0, N - 1));
+  };
+  i32x4* cnt4 = reinterpret_cast<i32x4*>(s_cnt) + tid;
+  *cnt4 = i32x4{0, 0, 0, 0};
   __syncthreads();
-#pragma unroll
-  for (int z = 0; z < kPairOnePairs; ++z) {
-    jp[z] = tid + kThreads * z < P ? clampi(jp[z], 0, N - 1) : -1;
-    at[z] = jp[z] >= 0 ? atomicAdd(&s_cnt[slot(jp[z])], 1) : 0;
+  pairs([&](int, int j) { atomicAdd(&s_cnt[j >> shift], 1); });
+  __syncthreads();
+  const i32x4 v = *cnt4;
+  int all;
+  const int off = block_excl_scan_1024(v.x + v.y + v.z + v.w, s_w, all);   // (its barriers part the reads from the writes)
+  *cnt4 = i32x4{off, off + v.x, off + v.x + v.y, off + v.x + v.y + v.z};
+  if (tid == 0) s_cnt[kPairOneBuckets] = all;
+  __syncthreads();
+  if (tid < 64) {
+    const int b = min(tid, kPairOneOwn - 1) * kPairOneWgs + wg, len = tid < kPairOneOwn ? s_cnt[b + 1] - s_cnt[b] : 0;
+    const int incl = wave_incl_scan(len);
+    if (tid < kPairOneOwn) { s_off[tid] = s_at[tid] = incl - len; s_off[tid + 1] = incl; }   // (the same value from either writer)
   }
   __syncthreads();
-  const int j0 = tid * kPer;
-  int v[kPer];
-  PairSums sum{0, 0, 0, 0, 0};
-#pragma unroll
-  for (int z = 0; z < kPer; ++z) {
-    v[z] = j0 + z < N ? s_cnt[slot(j0 + z)] : 0;
-    sum.add(v[z]);
-  }
-  const int m[5] = {sum.c, sum.f, sum.wk, sum.mu, sum.mn};
-  int ex[5];
-#pragma unroll
-  for (int z = 0; z < 5; ++z) {
-    const int incl = wave_incl_scan(m[z]);
-    if (lane == 63) s_sum[z][w] = incl;
-    ex[z] = incl - m[z];
-  }
+  pairs([&](int p, int j) {
+    const int b = j >> shift;
+    if (b % kPairOneWgs == wg) s_keys[atomicAdd(&s_at[b / kPairOneWgs], 1)] = (uint32_t)(j - (b << shift)) << kPairBits | (uint32_t)p;
+  });
   __syncthreads();
-#pragma unroll
-  for (int z = 0; z < 5; ++z)
-    for (int i = 0; i < w; ++i) ex[z] += s_sum[z][i];
-  int off = ex[0], nt = ex[1], wo = ex[2], mo = ex[3], mn = ex[4];
-#pragma unroll
-  for (int z = 0; z < kPer; ++z) {
-    const int j = j0 + z, ch = (v[z] + kSegChunk - 1) / kSegChunk;
-    if (j < N) s_cnt[slot(j)] = off;
-    if (v[z] > 0 && mine(j)) {
-      touched[nt] = j;
-      if (ch > 1) multi[mn] = make_int4(j, mo, ch, 0);
-      for (int c = 0; c < ch; ++c)
-        work[wo + c] = SegWork{j, off + c * kSegChunk, min(v[z] - c * kSegChunk, kSegChunk), ch > 1 ? mo + c : -1};
-      if (ch > 1) s_long[atomicAdd(&s_nlong, 1)] = j;
-    }
-    off += v[z]; nt += v[z] > 0 ? 1 : 0; wo += ch; mo += ch > 1 ? ch : 0; mn += ch > 1 ? 1 : 0;
-  }
-  if (tid == kThreads - 1) {
-    s_cnt[slot(N)] = off;   // (behind every counter)
-    if (wg == 0) { *n_touched = nt; totals[0] = nt; totals[1] = wo; totals[2] = mn; }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int z = 0; z < kPairOnePairs; ++z)
-    if (jp[z] >= 0 && mine(jp[z])) {
-      s_list[s_cnt[slot(jp[z])] + at[z]] = tid + kThreads * z;
-      s_p[atomicAdd(&s_n, 1)] = (tid + kThreads * z) * kPairOneN + jp[z];
-    }
-  __syncthreads();
-  auto put = [&](int i, int p) {
+  // pair `key` of own bucket m is the r-th of the bucket, which has `before` pairs of lesser neurons, `upto` up to its neuron
+  auto put = [&](int m, uint32_t key, int r, int before, int upto) {
+    const int b = m * kPairOneWgs + wg, p = (int)(key & kPairMask), j = (b << shift) + (int)(key >> kPairBits);
+    const int i = s_cnt[b] + r, e = r - before, L = upto - before;
+    // (rows of partial sums: a neuron of L > 256 pairs has at most L / 128 chunks)
+    const int row = L > kSegChunk ? (i - e) / (kSegChunk / 2) : -1;
     pair_sorted[i] = p;
     seg[i] = make_int2(p / k, __float_as_int(act[p]));
+    first[i] = e > 0 ? kNotFirst : row < 0 ? j : ~j;
+    work[i] = SegWork{j, i, e % kSegChunk == 0 ? min(L - e, kSegChunk) : 0, row < 0 ? -1 : row + e / kSegChunk};
+    if (e == 0 && row >= 0) multi[i / kSegChunk] = make_int4(j, row, (L + kSegChunk - 1) / kSegChunk, 0);
   };
-  // (a thread per pair of the workgroup: left where they are, a wave would rank its few one after the other)
-  for (int i = tid; i < s_n; i += kThreads) {
-    const int p = s_p[i] / kPairOneN, j = s_p[i] % kPairOneN, o = s_cnt[slot(j)], L = s_cnt[slot(j + 1)] - o;
+  // a thread per pair of the workgroup counts its rank in buckets of a chunk or less
+  for (int x = tid; x < s_off[kPairOneOwn]; x += kScanThreads) {
+    int m = 0;
+#pragma unroll
+    for (int z = kPairOneOwn / 2; z > 0; z >>= 1) m += s_off[m + z] <= x ? z : 0;
+    const int o = s_off[m], L = s_off[m + 1] - o;
     if (L > kSegChunk) continue;
-    int r = 0;
+    const uint32_t key = s_keys[x], from = key & ~kPairMask, to = key | kPairMask;
+    int r = 0, before = 0, upto = 0;
 #pragma unroll 4
-    for (int y = 0; y < L; ++y) r += s_list[o + y] < p ? 1 : 0;
-    put(o + r, p);
+    for (int y = 0; y < L; ++y) {
+      const uint32_t other = s_keys[o + y];
+      r += other < key ? 1 : 0;
+      before += other < from ? 1 : 0;
+      upto += other <= to ? 1 : 0;
+    }
+    put(m, key, r, before, upto);
   }
   __syncthreads();
-  for (int u = 0; u < s_nlong; ++u) {
-    const int j = s_long[u], o = s_cnt[slot(j)];
-    sort_long_segment<kThreads>(s_list + o, s_cnt[slot(j + 1)] - o, s_p, [&](int i, int p) { put(o + i, p); });
+  // larger ones are sorted where they are: a bitonic network whose exchanges all put the lesser key first, so that places
+  // beyond the end can be left out
+  for (int m = 0; m < kPairOneOwn; ++m) {
+    const int o = s_off[m], L = s_off[m + 1] - o;
+    if (L <= kSegChunk) continue;
+    uint32_t* a = s_keys + o;
+    auto order = [&](int lo, int hi) {
+      if (hi < L) {
+        const uint32_t x = a[lo], y = a[hi];
+        if (x > y) { a[lo] = y; a[hi] = x; }
+      }
+    };
+    int lgn = 1;
+    while ((1 << lgn) < L) ++lgn;
+    for (int lg = 1; lg <= lgn; ++lg) {
+      for (int i = tid; i < 1 << (lgn - 1); i += kScanThreads) {   // i-th pair of places: mirrored in pieces of 2^lg
+        const int base = (i >> (lg - 1)) << lg, x = i & ((1 << (lg - 1)) - 1);
+        order(base + x, base + (1 << lg) - 1 - x);
+      }
+      __syncthreads();
+      for (int st = lg - 2; st >= 0; --st) {
+        for (int i = tid; i < 1 << (lgn - 1); i += kScanThreads) {
+          const int lo = (i >> st) << (st + 1) | (i & ((1 << st) - 1));
+          order(lo, lo + (1 << st));
+        }
+        __syncthreads();
+      }
+    }
+    auto below = [&](uint32_t x) {   // keys less than x
+      int lo = 0, hi = L;
+      while (lo < hi) {
+        const int h = (lo + hi) >> 1;
+        if (a[h] < x) lo = h + 1; else hi = h;
+      }
+      return lo;
+    };
+    for (int r = tid; r < L; r += kScanThreads) {
+      const uint32_t key = a[r], to = key | kPairMask;
+      put(m, key, r, below(key & ~kPairMask), to == 0xFFFFFFFFu ? L : below(to + 1));
+    }
   }
+}
+
+// The lists that pair_one_kernel's entries stand for: touched neurons, ascending, and the neurons of more than one chunk.  Executed by
+// one workgroup of 256 threads, a thread for kPairListPer consecutive entries at a time.
+constexpr int kPairListPer = 32;
+struct PairLists {
+  const int32_t* first;   // nullptr: the lists are there
+  int n_pairs;
+  int32_t *touched, *n_touched;
+  int4* multi;
+  int32_t* totals;
+};
+__device__ __forceinline__ void pair_lists_body(const PairLists& l) {
+  constexpr int kWindows = kPairOneP / kSegChunk;   // each holds the first pair of at most one neuron of more than one chunk
+  __shared__ int s_w[4], s_long[kWindows];
+  static_assert(kWindows <= 256, "");
+  const int tid = threadIdx.x, P = l.n_pairs;
+  if (tid < kWindows) s_long[tid] = 0;
+  __syncthreads();
+  int total = 0;
+#pragma unroll 1
+  for (int t0 = 0; t0 < P; t0 += 256 * kPairListPer) {
+    const int i0 = t0 + tid * kPairListPer;
+    int32_t v[kPairListPer];
+    int n = 0;
+#pragma unroll
+    for (int z = 0; z < kPairListPer; z += 4) {   // (arrays of the workspace are whole 256-byte pieces)
+      const i32x4 x = *reinterpret_cast<const i32x4*>(l.first + min(i0 + z, (P - 1) & ~3));
+#pragma unroll
+      for (int y = 0; y < 4; ++y) {
+        v[z + y] = i0 + z + y < P ? x[y] : kNotFirst;
+        n += v[z + y] != kNotFirst ? 1 : 0;
+        if (v[z + y] < 0 && v[z + y] != kNotFirst) s_long[(i0 + z + y) / kSegChunk] = 1;
+      }
+    }
+    int all, at = total + block_excl_scan_256(n, s_w, all);
+#pragma unroll
+    for (int z = 0; z < kPairListPer; ++z)
+      if (v[z] != kNotFirst) l.touched[at++] = v[z] < 0 ? ~v[z] : v[z];
+    total += all;
+  }
+  const int is = tid < kWindows ? s_long[min(tid, kWindows - 1)] : 0;
+  int4 m{};
+  if (is) m = l.multi[tid];
+  int n_multi;
+  const int at = block_excl_scan_256(is, s_w, n_multi);   // (every entry has been read before one is written)
+  if (is) l.multi[at] = m;
+  if (tid == 0) { *l.n_touched = total; l.totals[0] = total; l.totals[2] = n_multi; }
 }
 
 // Work of the two kernels below: units of (run of consecutive chunks, 1 KB of columns).  The pairs of a run are consecutive in
@@ -411,20 +492,22 @@ __global__ __launch_bounds__(kScanThreads) void pair_one_kernel(const int32_t* _
 // tokens have 4096 columns, that is one slice of 2 MB of h or dOut per XCD, which stays in its L2, so that the row reads, one per
 // (token, neuron) pair, do not go to memory.  The waves of an XCD take its units in turn (workgroup ids go to the XCDs in turn;
 // gridDim.x is a multiple of 8).
+// Where pair_one_kernel left the entries (kGaps), a run is that of consecutive entries, of which some hold no chunk.
 constexpr int kSegWorkgroups = 5 * 256;   // what the registers of either kernel let the compute units hold
-constexpr int kSegRun = 16;               // chunks per run at most; fewer where that leaves waves without one
+constexpr int kSegRun = 16;               // entries per run at most; fewer where that leaves waves without one
 
 struct SegRuns {
   long long unit, end;
   int slice, run, n_runs, len, step;
-  __device__ __forceinline__ bool init(int n_chunks, int n_slices) {
-    const long long share = (long long)n_chunks * n_slices / (kSegWorkgroups * 4);
-    len = share < 1 ? 1 : share > kSegRun ? kSegRun : (int)share;
-    n_runs = (n_chunks + len - 1) / len;
+  // Workgroup wg of n_wg; n_wg and the number of the launch's first a multiple of 8.  `entries` work entries per chunk.
+  __device__ __forceinline__ bool init(int n_entries, int entries, int n_slices, int wg, int n_wg) {
+    const long long share = (long long)(n_entries / entries) * n_slices / (kSegWorkgroups * 4);
+    len = min((share < 1 ? 1 : share > kSegRun ? kSegRun : (int)share) * entries, 64);
+    n_runs = (n_entries + len - 1) / len;
     const long long units = (long long)n_runs * n_slices, per = (units + 7) / 8;
-    const int x = blockIdx.x & 7;
-    step = (int)(gridDim.x >> 3) * 4;
-    unit = x * per + (int)(blockIdx.x >> 3) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int x = wg & 7;
+    step = (n_wg >> 3) * 4;
+    unit = x * per + (wg >> 3) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     end = min((x + 1) * per, units);
     if (unit >= end) return false;
     slice = (int)(unit / n_runs);
@@ -439,6 +522,22 @@ struct SegRuns {
   }
 };
 
+// The chunks of entries c0 .. c0 + m - 1 (m <= 64): lane i receives the i-th; returns their number, which may be 0 where there are gaps.
+template <bool kGaps>
+__device__ __forceinline__ int seg_run_chunks(const SegWork* __restrict__ work, int c0, int m, SegWork& w) {
+  const int lane = threadIdx.x & 63;
+  w = work[c0 + min(lane, m - 1)];
+  if constexpr (!kGaps) return m;
+  const bool is = lane < m && w.len > 0;
+  const unsigned long long mask = __ballot(is), before = (1ull << lane) - 1ull;
+  const int n = __popcll(mask), to = 4 * (is ? __popcll(mask & before) : n + __popcll(~mask & before));
+  w.j = __builtin_amdgcn_ds_permute(to, w.j);
+  w.off = __builtin_amdgcn_ds_permute(to, w.off);
+  w.len = __builtin_amdgcn_ds_permute(to, w.len);
+  w.part = __builtin_amdgcn_ds_permute(to, w.part);
+  return n;
+}
+
 // Up to this many partial dot products per pair (one per group of column slices)
 constexpr int kDsParts = 8;
 
@@ -449,19 +548,27 @@ constexpr int kDsParts = 8;
 // L2 about alike.  The activation gradients used to be formed token by token, which reads a row of V per pair from beyond L2; with
 // that gone: 2048 tokens x 256 pairs, d 4096, bf16, 65536 neurons: backward 1780 -> 1340 us (this kernel 460, dK 310, dh 550); 2048 x
 // 64 pairs, d 768, fp32, 8192 neurons: 180 -> 113.
-template <typename T>
+template <typename T, bool kGaps>
 __global__ __launch_bounds__(256, 5) void seg_dv_kernel(const SegWork* __restrict__ work, const int32_t* __restrict__ totals,
                                                         const int2* __restrict__ seg, const T* __restrict__ V,
                                                         const T* __restrict__ dOut, int d, int n_slices, size_t n_pairs,
                                                         T* __restrict__ dV, float* __restrict__ part,
-                                                        float* __restrict__ ds_part) {
+                                                        float* __restrict__ ds_part, int entries, PairLists lists) {
   constexpr int VE = Vec16<T>::kElems;
+  int wg = blockIdx.x, n_wg = gridDim.x;
+  if constexpr (kGaps) {   // the first eight workgroups: the lists
+    if (wg == 0) pair_lists_body(lists);
+    if (wg < 8) return;
+    wg -= 8; n_wg -= 8;
+  }
   const int lane = threadIdx.x & 63, n_groups = n_slices < kDsParts ? n_slices : kDsParts;
-  const int n_chunks = totals[1];
+  const int n_chunks = kGaps ? (int)n_pairs : totals[1];
   SegRuns cur;   // (its slices are the groups of slices)
-  for (bool more = cur.init(n_chunks, n_groups); more; more = cur.next()) {
-    const int c0 = cur.run * cur.len, nc = min(cur.len, n_chunks - c0);
-    const SegWork w = work[c0 + min(lane, nc - 1)];   // lane: its chunk of the run
+  for (bool more = cur.init(n_chunks, entries, n_groups, wg, n_wg); more; more = cur.next()) {
+    const int c0 = cur.run * cur.len;
+    SegWork w;   // lane: its chunk of the run
+    const int nc = seg_run_chunks<kGaps>(work, c0, min(cur.len, n_chunks - c0), w);
+    if (kGaps && nc == 0) continue;
     const int beg = __builtin_amdgcn_readlane(w.off, 0);
     const int end = __builtin_amdgcn_readlane(w.off, nc - 1) + __builtin_amdgcn_readlane(w.len, nc - 1);
     float* dsp = ds_part + cur.slice * n_pairs;
@@ -530,19 +637,21 @@ __global__ __launch_bounds__(256, 5) void seg_dv_kernel(const SegWork* __restric
 
 // ds of the pairs from their parts, in slice order, and dK of a run of chunks over one slice of columns.  ds == nullptr: not
 // wanted in token order.
-template <typename T>
+template <typename T, bool kGaps>
 __global__ __launch_bounds__(256, 6) void seg_dk_kernel(const SegWork* __restrict__ work, const int32_t* __restrict__ totals,
                                                         const int2* __restrict__ seg, const int32_t* __restrict__ pair_sorted,
                                                         const float* __restrict__ ds_part, const T* __restrict__ h, int d,
                                                         int n_slices, size_t n_pairs, T* __restrict__ dK,
-                                                        float* __restrict__ part, float* __restrict__ ds) {
+                                                        float* __restrict__ part, float* __restrict__ ds, int entries) {
   constexpr int VE = Vec16<T>::kElems;
   const int lane = threadIdx.x & 63, n_parts = n_slices < kDsParts ? n_slices : kDsParts;
-  const int n_chunks = totals[1];
+  const int n_chunks = kGaps ? (int)n_pairs : totals[1];
   SegRuns cur;
-  for (bool more = cur.init(n_chunks, n_slices); more; more = cur.next()) {
-    const int c0 = cur.run * cur.len, nc = min(cur.len, n_chunks - c0);
-    const SegWork w = work[c0 + min(lane, nc - 1)];
+  for (bool more = cur.init(n_chunks, entries, n_slices, blockIdx.x, gridDim.x); more; more = cur.next()) {
+    const int c0 = cur.run * cur.len;
+    SegWork w;
+    const int nc = seg_run_chunks<kGaps>(work, c0, min(cur.len, n_chunks - c0), w);
+    if (kGaps && nc == 0) continue;
     const int beg = __builtin_amdgcn_readlane(w.off, 0);
     const int end = __builtin_amdgcn_readlane(w.off, nc - 1) + __builtin_amdgcn_readlane(w.len, nc - 1);
     const int col = (cur.slice * 64 + lane) * VE, at = min(col, d - VE);
@@ -593,6 +702,161 @@ __global__ __launch_bounds__(256, 6) void seg_dk_kernel(const SegWork* __restric
       }
     }
     flush();
+  }
+}
+
+// dV, ds and dK of a chunk at once, where there is little to do: 2^lg waves of a workgroup take the chunk, each every 2^lg-th KB of
+// its columns; a part of ds per wave goes through LDS, the parts are added in wave order.  Up to kSegAhead rows of h are asked for with
+// those of dOut.  Work entries may be empty (pair_one_kernel); a wave looks at 64 of the workgroup's at a time.
+// Bound by the chain of loads per chunk (entry, pairs, rows), which a launch less outweighs only while waves have few chunks each:
+// see seg_rows_fused.
+constexpr int kSegAhead = 4;
+constexpr int kSegRowsWgs = 4 * 256;   // what the registers let the compute units hold
+template <typename T>
+__global__ __launch_bounds__(256, 4) void seg_rows_kernel(const SegWork* __restrict__ work, const int32_t* __restrict__ totals,
+                                                          int n_pairs, const int2* __restrict__ seg,
+                                                          const int32_t* __restrict__ pair_sorted, const T* __restrict__ V,
+                                                          const T* __restrict__ dOut, const T* __restrict__ h, int d, int n_slices,
+                                                          int lg, T* __restrict__ dV, T* __restrict__ dK,
+                                                          float* __restrict__ part, float* __restrict__ ds, PairLists lists) {
+  constexpr int VE = Vec16<T>::kElems;
+  __shared__ float s_ds[2][4][kSegChunk];
+  int wg = blockIdx.x, n_wg = gridDim.x;
+  if (lists.first != nullptr) {
+    if (wg == 0) {
+      pair_lists_body(lists);
+      return;
+    }
+    --wg; --n_wg;
+  }
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int G = 1 << lg, g = wave & (G - 1), group = wave >> lg, w0 = wave - g;
+  const int n = lists.first != nullptr ? n_pairs : totals[1], per = (n + n_wg - 1) / n_wg;
+  const int end = min(n, (wg + 1) * per);
+  int buf = 0;
+  for (int c0 = wg * per; c0 < end; c0 += 64) {
+    const int m = min(64, end - c0);
+    const SegWork e = work[c0 + min(lane, m - 1)];
+    unsigned long long live = __ballot(lane < m && e.len > 0);   // the same in every wave
+    while (live) {
+      int c = -1;   // this wave's entry: the group-th of the next ones
+      for (int z = 0; z < 4 >> lg; ++z) {
+        if (z == group && live) c = __ffsll(live) - 1;
+        live &= live - 1;
+      }
+      const bool has = c >= 0;
+      const int cc = max(c, 0);
+      const int j = __builtin_amdgcn_readlane(e.j, cc), off = __builtin_amdgcn_readlane(e.off, cc),
+                len = has ? __builtin_amdgcn_readlane(e.len, cc) : 0, to = __builtin_amdgcn_readlane(e.part, cc);
+      u32x4 hx[kSegAhead];
+      auto sum_v = [&](auto batch) {
+        constexpr int U = decltype(batch)::value;
+        for (int slice = g; slice < n_slices; slice += G) {
+          const int col = (slice * 64 + lane) * VE, at = min(col, d - VE);
+          float v[VE], aV[VE];
+          const u32x4 v_row = *reinterpret_cast<const u32x4*>(V + (size_t)j * d + at);
+#pragma unroll
+          for (int x = 0; x < VE; ++x) aV[x] = 0.f;
+          for (int i0 = 0; i0 < len; i0 += 64) {
+            const int np = min(64, len - i0);
+            const int2 p = seg[off + i0 + min(lane, np - 1)];
+            for (int q = 0; q < np; q += U) {
+              u32x4 rows[U];
+              float dot[8];
+#pragma unroll
+              for (int u = 0; u < U; ++u)
+                rows[u] = *reinterpret_cast<const u32x4*>(dOut + (size_t)__builtin_amdgcn_readlane(p.x, min(q + u, np - 1)) * d + at);
+              if constexpr (U <= kSegAhead) {
+                if (slice == g) {
+#pragma unroll
+                  for (int u = 0; u < U; ++u)
+                    hx[u] = *reinterpret_cast<const u32x4*>(h + (size_t)__builtin_amdgcn_readlane(p.x, min(u, np - 1)) * d + at);
+                }
+              }
+              Vec16<T>::unpack(v_row, v);
+#pragma unroll
+              for (int u = 0; u < 8; ++u) {
+                dot[u] = 0.f;
+                if (u < U && q + u < np) {
+                  const float a = __int_as_float(__builtin_amdgcn_readlane(p.y, q + u));
+                  float y[VE];
+                  Vec16<T>::unpack(rows[u % U], y);
+#pragma unroll
+                  for (int x = 0; x < VE; ++x) {
+                    aV[x] = fmaf(a, y[x], aV[x]);
+                    dot[u] = fmaf(y[x], v[x], dot[u]);
+                  }
+                  dot[u] = col < d ? dot[u] : 0.f;
+                }
+              }
+              const float r = wave_sum8(dot);
+              if (lane < U && q + lane < np) {
+                float* o = &s_ds[buf][wave][i0 + q + lane];
+                *o = slice == g ? r : *o + r;
+              }
+            }
+          }
+          if (col < d) {
+            if (to < 0) Vec16<T>::store(dV + (size_t)j * d + col, aV);
+            else Vec16<T>::store_f32(part + (size_t)to * 2 * d + col, aV);
+          }
+        }
+      };
+      auto sum_k = [&](auto batch) {
+        constexpr int U = decltype(batch)::value;
+        for (int slice = g; slice < n_slices; slice += G) {
+          const int col = (slice * 64 + lane) * VE, at = min(col, d - VE);
+          float aK[VE];
+#pragma unroll
+          for (int x = 0; x < VE; ++x) aK[x] = 0.f;
+          for (int i0 = 0; i0 < len; i0 += 64) {
+            const int np = min(64, len - i0), i = i0 + min(lane, np - 1);
+            const int2 p = seg[off + i];
+            float s = s_ds[buf][w0][i];
+            for (int z = 1; z < min(G, n_slices); ++z) s += s_ds[buf][w0 + z][i];
+            s = __int_as_float(p.y) > 0.f ? s : 0.f;
+            if (slice == 0 && ds != nullptr && lane < np) ds[pair_sorted[off + i]] = s;
+            for (int q = 0; q < np; q += U) {
+              u32x4 rows[U];
+              if (U > kSegAhead || slice != g) {
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                  rows[u] = *reinterpret_cast<const u32x4*>(h + (size_t)__builtin_amdgcn_readlane(p.x, min(q + u, np - 1)) * d + at);
+              } else if constexpr (U <= kSegAhead) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) rows[u] = hx[u];
+              }
+#pragma unroll
+              for (int u = 0; u < U; ++u) {
+                if (q + u < np) {
+                  const float cf = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(s), q + u));
+                  float y[VE];
+                  Vec16<T>::unpack(rows[u], y);
+#pragma unroll
+                  for (int x = 0; x < VE; ++x) aK[x] = fmaf(cf, y[x], aK[x]);
+                }
+              }
+            }
+          }
+          if (col < d) {
+            if (to < 0) Vec16<T>::store(dK + (size_t)j * d + col, aK);
+            else Vec16<T>::store_f32(part + (size_t)to * 2 * d + d + col, aK);
+          }
+        }
+      };
+      // (rows asked for twice cost as much as others: batches of what there is)
+      if (len == 1) sum_v(std::integral_constant<int, 1>{});
+      else if (len == 2) sum_v(std::integral_constant<int, 2>{});
+      else if (len > 0 && len <= kSegAhead) sum_v(std::integral_constant<int, kSegAhead>{});
+      else if (len > 0) sum_v(std::integral_constant<int, 8>{});
+      if (G > 1) __syncthreads();
+      else wave_lds_fence();
+      if (len == 1) sum_k(std::integral_constant<int, 1>{});
+      else if (len == 2) sum_k(std::integral_constant<int, 2>{});
+      else if (len > 0 && len <= kSegAhead) sum_k(std::integral_constant<int, kSegAhead>{});
+      else if (len > 0) sum_k(std::integral_constant<int, 8>{});
+      buf ^= 1;   // (one barrier per entry: the other half is written before this one has been read by all)
+    }
   }
 }
 
