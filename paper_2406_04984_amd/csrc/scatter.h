@@ -103,7 +103,8 @@ struct SegWork {
 // Per touched neuron u (ascending id): touched[u], and its chunks in work[]; per neuron of more than one chunk an entry
 // (neuron, first row of partial sums, chunks) in multi[]; seg_off = exclusive scan of cnt.  totals = {touched, chunks,
 // neurons of more than one chunk}.  A workgroup of 1024 threads takes kScanChunk counters and adds up the ones before them
-// itself, out of L2 (65536 neurons: 119 us by one workgroup for all of them, 16 us with 256 threads, 15 us with 1024), or, beyond
+// itself, out of L2 (65536 neurons: 119 us by one workgroup for all of them, 15 us so, 9 us with eight loads of a thread together,
+// short sums where no counter is of more than a chunk, and one pass over the waves' sums), or, beyond
 // kScanSelfMax counters, takes the sums that pair_sums_kernel left.
 constexpr int kScanChunk = 2048, kScanSelfMax = 1 << 17, kScanThreads = 1024, kScanPer = kScanChunk / kScanThreads;
 struct PairSums {
@@ -112,38 +113,37 @@ struct PairSums {
     const int ch = (v + kSegChunk - 1) / kSegChunk;
     c += v; f += v > 0; wk += ch; mu += ch > 1 ? ch : 0; mn += ch > 1 ? 1 : 0;
   }
+  // four counters: mostly, none is of more than a chunk
+  __device__ __forceinline__ void add4(i32x4 v) {
+    if (max(max(v.x, v.y), max(v.z, v.w)) > kSegChunk) {
+      add(v.x); add(v.y); add(v.z); add(v.w);
+      return;
+    }
+    const int n = (v.x > 0) + (v.y > 0) + (v.z > 0) + (v.w > 0);
+    c += v.x + v.y + v.z + v.w; f += n; wk += n;
+  }
 };
 
-// sums over a workgroup of kScanThreads threads, in every thread
-__device__ __forceinline__ PairSums pair_sums_all(PairSums x, int (*s)[kScanThreads / 64]) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int v[5] = {x.c, x.f, x.wk, x.mu, x.mn};
-  int r[5];
-#pragma unroll
-  for (int z = 0; z < 5; ++z) {
-    const int incl = wave_incl_scan(v[z]);
-    if (lane == 63) s[z][w] = incl;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int z = 0; z < 5; ++z) {
-    r[z] = 0;
-#pragma unroll
-    for (int i = 0; i < kScanThreads / 64; ++i) r[z] += s[z][i];
-  }
-  __syncthreads();
-  return PairSums{r[0], r[1], r[2], r[3], r[4]};
-}
-
 __global__ __launch_bounds__(kScanThreads) void pair_sums_kernel(const int32_t* __restrict__ cnt, int N, PairSums* __restrict__ sums) {
-  __shared__ int s[5][kScanThreads / 64];
+  __shared__ int s[kScanThreads / 64][5];
   PairSums x{0, 0, 0, 0, 0};
-  const int j0 = blockIdx.x * kScanChunk + threadIdx.x * kScanPer;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, j0 = blockIdx.x * kScanChunk + threadIdx.x * kScanPer;
 #pragma unroll
   for (int z = 0; z < kScanPer; ++z)
     if (j0 + z < N) x.add(cnt[j0 + z]);
-  x = pair_sums_all(x, s);
-  if (threadIdx.x == 0) sums[blockIdx.x] = x;
+  const int v[5] = {x.c, x.f, x.wk, x.mu, x.mn};
+#pragma unroll
+  for (int z = 0; z < 5; ++z) {
+    const int incl = wave_incl_scan(v[z]);
+    if (lane == 63) s[w][z] = incl;
+  }
+  __syncthreads();
+  if (threadIdx.x < 5) {
+    int r = 0;
+#pragma unroll
+    for (int i = 0; i < kScanThreads / 64; ++i) r += s[i][threadIdx.x];
+    (&sums[blockIdx.x].c)[threadIdx.x] = r;
+  }
 }
 
 __global__ __launch_bounds__(kScanThreads) void pair_scan_kernel(const int32_t* __restrict__ cnt, int N,
@@ -151,8 +151,14 @@ __global__ __launch_bounds__(kScanThreads) void pair_scan_kernel(const int32_t* 
                                                         int32_t* __restrict__ seg_off, int32_t* __restrict__ touched,
                                                         int32_t* __restrict__ n_touched, SegWork* __restrict__ work,
                                                         int4* __restrict__ multi, int32_t* __restrict__ totals) {
-  __shared__ int s[5][kScanThreads / 64];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, chunk = blockIdx.x;
+  constexpr int kWaves = kScanThreads / 64;
+  __shared__ int s_before[5][kWaves], s_mine[5][kWaves];
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), chunk = blockIdx.x;
+  const int j0 = chunk * kScanChunk + tid * kScanPer;
+  int v[kScanPer];
+  PairSums mine{0, 0, 0, 0, 0};
+#pragma unroll
+  for (int z = 0; z < kScanPer; ++z) v[z] = j0 + z < N ? cnt[j0 + z] : 0;
   PairSums before{0, 0, 0, 0, 0};
   if (sums != nullptr) {
     for (int c = tid; c < chunk; c += kScanThreads) {
@@ -161,35 +167,35 @@ __global__ __launch_bounds__(kScanThreads) void pair_scan_kernel(const int32_t* 
     }
   } else {
     const i32x4* c4 = reinterpret_cast<const i32x4*>(cnt);
-#pragma unroll 4
-    for (int c = tid; c < chunk * (kScanChunk / 4); c += kScanThreads) {
-      const i32x4 v = c4[c];
-      before.add(v.x); before.add(v.y); before.add(v.z); before.add(v.w);
+    const int n = chunk * (kScanChunk / 4);
+    for (int c = tid; c < n; c += 8 * kScanThreads) {   // (eight loads on their way together)
+      i32x4 x[8];
+#pragma unroll
+      for (int z = 0; z < 8; ++z) x[z] = c4[min(c + kScanThreads * z, n - 1)];
+#pragma unroll
+      for (int z = 0; z < 8; ++z)
+        if (c + kScanThreads * z < n) before.add4(x[z]);
     }
   }
-  before = pair_sums_all(before, s);
-  const int j0 = chunk * kScanChunk + tid * kScanPer;
-  int v[kScanPer];
-  PairSums mine{0, 0, 0, 0, 0};
 #pragma unroll
-  for (int z = 0; z < kScanPer; ++z) {
-    v[z] = j0 + z < N ? cnt[j0 + z] : 0;
-    mine.add(v[z]);
-  }
-  // exclusive prefix of the thread's sums inside the workgroup
-  const int m[5] = {mine.c, mine.f, mine.wk, mine.mu, mine.mn};
+  for (int z = 0; z < kScanPer; ++z) mine.add(v[z]);
+  // per wave, then over the waves (a lane each): the sums before the workgroup and the prefix inside it.  Short chains of
+  // instructions: this is what a workgroup with few counters before it takes.
+  const int b[5] = {before.c, before.f, before.wk, before.mu, before.mn}, m[5] = {mine.c, mine.f, mine.wk, mine.mu, mine.mn};
   int ex[5];
 #pragma unroll
   for (int z = 0; z < 5; ++z) {
-    const int incl = wave_incl_scan(m[z]);
-    if (lane == 63) s[z][w] = incl;
+    const int all = wave_incl_scan(b[z]), incl = wave_incl_scan(m[z]);
+    if (lane == 63) { s_before[z][w] = all; s_mine[z][w] = incl; }
     ex[z] = incl - m[z];
   }
   __syncthreads();
 #pragma unroll
-  for (int z = 0; z < 5; ++z)
-    for (int i = 0; i < w; ++i) ex[z] += s[z][i];
-  int off = before.c + ex[0], nt = before.f + ex[1], wo = before.wk + ex[2], mo = before.mu + ex[3], mn = before.mn + ex[4];
+  for (int z = 0; z < 5; ++z) {
+    const int waves = wave_incl_scan(lane < kWaves ? s_before[z][lane % kWaves] : lane < 2 * kWaves && lane - kWaves < w ? s_mine[z][lane % kWaves] : 0);
+    ex[z] += __builtin_amdgcn_readlane(waves, 63);
+  }
+  int off = ex[0], nt = ex[1], wo = ex[2], mo = ex[3], mn = ex[4];
 #pragma unroll
   for (int z = 0; z < kScanPer; ++z) {
     if (j0 + z < N) seg_off[j0 + z] = off;
