@@ -547,7 +547,9 @@ void launch_pair_rows(const char* name, const meft_shape& s, const void* W, cons
                       const float* gate, void* row, const SegFinish<T>& f, hipStream_t st) {
   const int64_t groups = row ? ((int64_t)s.T + 3) / 4 * row_slices<T>(s) : 0;
   if (groups + f.n_wg == 0) return;
-  MEFT_LAUNCH(name, (pair_rows_kernel<T, kAcc>), grid_xcd(f.n_wg + (groups + 7) / 8 * 8), dim3(256), 0, st, static_cast<const T*>(W), idx, coef,
+  auto kernel = s.top_k == 1 ? pair_rows_kernel<T, kAcc, 1> : s.top_k == 2 ? pair_rows_kernel<T, kAcc, 2>
+                : s.top_k <= 4 ? pair_rows_kernel<T, kAcc, 4> : pair_rows_kernel<T, kAcc, 8>;
+  MEFT_LAUNCH(name, kernel, grid_xcd(f.n_wg + (groups + 7) / 8 * 8), dim3(256), 0, st, static_cast<const T*>(W), idx, coef,
               gate, row ? s.T : 0, s.d, s.top_k, s.N, static_cast<T*>(row), f);
 }
 
