@@ -10,7 +10,7 @@
 //   A m-contiguous (rows indexed by k): dK, dV, whose A operand is the slot-major activation matrix, read as it is.
 //
 // Tile TM (m) x 256 (n) x 64 (k), a policy's kTM.  Two shapes of workgroup:
-//   kTM = 128 (or 192): 4 compute waves as 2 x 2, each wave TM/2 x 128 = (TM/64) x 4 MFMA tiles, plus two or four
+//   kTM = 128: 4 compute waves as 2 x 2, each wave 64 x 128 = 2 x 4 MFMA tiles, plus two or four
 //     loader waves that own the whole global -> LDS traffic (16 B per lane).  Ring depths kSA, kSB up to three.
 //     Used by the router, the token-major problems and (as an option) the neuron-major ones.
 //   kTM = 256: 8 compute waves as 4 x 2, each wave 64 x 128, and no loader waves (kLoaders = 0): the accumulators of
@@ -20,7 +20,8 @@
 //     many store phases.  Measured at the LLaMA-7B-shaped configuration: dV 0.355 -> 0.340 ms, dK 0.345 -> 0.339 ms.
 // The operands have a ring each in LDS: kSA slots of TM x 64 for A, kSB slots of 256 x 64 for B.  (A 192-row tile
 // for the token-major problems moves 22 % fewer operand bytes per flop than the 128-row one and was measured 15 %
-// faster per flop, but their groups then fill a whole number of tiles worse and the step as a whole did not gain.)
+// faster per flop, but their groups then fill a whole number of tiles worse and the step as a whole did not gain.  It
+// is gone; the tile schedule has prefixes of 64 and 128 rows only.)
 // LDS layouts are XOR-swizzled so that both the linear DMA writes and the fragment reads are free of bank conflicts:
 //   k-contiguous operand: rows of 64 k = 8 chunks of 16 B; logical chunk c of row r sits at chunk
 //     c ^ ((r >> 1) & 7); fragments are read with ds_read_b128.
@@ -107,7 +108,7 @@ struct TileCoord {
 };
 
 // A problem policy P provides:
-//   static constexpr int kTM, kSA, kSB;                 tile rows (128 or 192) and the slots of the A and B rings (kSA == kSB)
+//   static constexpr int kTM, kSA, kSB;                 tile rows (128 or 256) and the slots of the A and B rings (kSA == kSB)
 //   static constexpr int kLoaders;                      loader waves, 2 or 4
 //   Finder, __device__ Finder finder(int xcd) const;    what a wave of that XCD looks its tiles up with, in registers
 //   __device__ bool locate(Finder&, int wg, TileCoord&) const;   false: no tile with id wg, nor with any larger id on
@@ -210,14 +211,13 @@ __global__ __launch_bounds__(gemm_threads<P>(), 1) void gemm_mfma_kernel(P p, in
   constexpr bool kSelf = P::kLoaders == 0;          // the compute waves request the operands themselves
   constexpr int kLoaders = loading_waves<P>();      // waves that request operands
   constexpr int TM = P::kTM, SA = P::kSA, SB = P::kSB;
-  constexpr int WM = TM / (kCW / 2);                // rows of a compute wave: 64 or 96
-  constexpr int MI = WM / 32;                       // 32-row MFMA tiles per compute wave: 2 or 3
+  constexpr int WM = TM / (kCW / 2);                // rows of a compute wave
+  constexpr int MI = WM / 32;                       // 32-row MFMA tiles per compute wave
   constexpr int kASlotElems = TM * kTK;
   constexpr int kBRing = SA * kASlotElems;          // element offset of the B ring
   static_assert(kLoaders == 2 || kLoaders == 4 || kLoaders == 8, "waves that load: 2, 4 or 8");
-  static_assert((kCW == 4 && (TM == 128 || TM == 192)) || (kCW == 8 && TM == 256), "tile rows: 128, 192 or 256");
+  static_assert((kCW == 4 && TM == 128) || (kCW == 8 && TM == 256), "tile rows: 128 or 256, 64 to a compute wave");
   static_assert(SA >= 2 && SA <= 3 && SB == SA, "ring depths: 2 or 3, A and B requested for the same positions");
-  static_assert(!P::kAMC || TM == 128 || TM == 256, "the m-contiguous A layouts are written for 128 and 256 rows");
   static_assert(!kSelf || (P::kAMC && P::kBNC && SA == 2 && SB == 2 && kCW == 8),
                 "compute waves that load: written for the neuron-major problems with two slots per ring");
   extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
@@ -625,16 +625,14 @@ __global__ __launch_bounds__(gemm_threads<P>(), 1) void gemm_mfma_kernel(P p, in
   int wg = blockIdx.x;
   int slot_a = 0, slot_b = 0;   // run on across tiles, like the loaders' slots
   for (;;) {
-    // lane l: the tag of row wm + l of this tile (and, with 96 rows per wave, lane l < 32: of row wm + 64 + l).
-    // Asked before the k loop, so that a policy's memory read has long returned when the answer is needed.
+    // lane l: the tag of row wm + l of this tile.  Asked before the k loop, so that a policy's memory read has long
+    // returned when the answer is needed.
     const int my_tag = p.row_tag(tc, tc.m0 + wm + lane);
-    [[maybe_unused]] int my_tag_hi = 0;
-    if constexpr (WM > 64) my_tag_hi = lane < WM - 64 ? p.row_tag(tc, tc.m0 + wm + 64 + lane) : 0;
 
     f32x16 acc[MI][4];
     const int nk = tc.nk;
     // The fragments of one k16 step.  Two sets alternate: the LDS reads of step s + 1 are issued before the matrix
-    // instructions of step s, so that their latency passes under those 8 (12) instructions instead of in front of
+    // instructions of step s, so that their latency passes under those 8 instructions instead of in front of
     // the next ones.  (Left to itself the compiler reads each step's fragments into the same registers right before
     // their use, and the matrix pipe idles for an LDS round trip four times per k tile.)
     struct Frags { bf16x8 a[MI], b[4]; };
@@ -797,7 +795,6 @@ __global__ __launch_bounds__(gemm_threads<P>(), 1) void gemm_mfma_kernel(P p, in
         lane_at = p.row_off(tc, 1, tc.m0 + wm + lane_row) + ncol;   // one multiplication per tile
       }
       [[maybe_unused]] const unsigned long long ok_mask = __ballot(my_tag != 0);
-      [[maybe_unused]] const unsigned long long ok_mask_hi = __ballot(my_tag_hi != 0);
       auto epilogue = [&](auto full_tag) {
         constexpr bool kFull = decltype(full_tag)::value;   // all four fragments of the wave lie inside the output
 #pragma unroll
@@ -813,10 +810,9 @@ __global__ __launch_bounds__(gemm_threads<P>(), 1) void gemm_mfma_kernel(P p, in
               // the row's tag: a bit of the wave's ballot where it only says "stored or not" (no trip through the LDS
               // pipeline, which the loaders keep busy), a lane permute where it carries a number
               if constexpr (P::kRowsLinear) {
-                tag[qq] = i < 2 ? (int)((ok_mask >> rl) & 1ull) : (int)((ok_mask_hi >> (rl - 64)) & 1ull);
+                tag[qq] = (int)((ok_mask >> rl) & 1ull);
               } else {
-                tag[qq] = i < 2 ? __builtin_amdgcn_ds_bpermute(rl << 2, my_tag)
-                                : __builtin_amdgcn_ds_bpermute((rl - 64) << 2, my_tag_hi);
+                tag[qq] = __builtin_amdgcn_ds_bpermute(rl << 2, my_tag);
               }
               if constexpr (P::kAux) {
 #pragma unroll
@@ -1089,6 +1085,7 @@ struct TileFinder {
   __device__ __forceinline__ int share(int m) const { return m * tn > x ? (m * tn - x + kXcd - 1) / kXcd : 0; }
   template <int TM>
   __device__ __forceinline__ void load(const TokenSched& s) {
+    static_assert(TM == 64 || TM == 128, "the lists hold prefixes of tiles of 64 and of 128 rows");
     // (No branch in here differs per lane: the compiler would fold it into the look-up's loop, take the tile for a value
     // that differs per lane, and issue every operand request from a loop over the lanes.)
     const int i = min(b + (int)(threadIdx.x & 63), s.cap - 1);
