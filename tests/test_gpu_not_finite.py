@@ -1,0 +1,78 @@
+"""Rows that hold no numbers where nothing may come of them: V rows of pairs whose activation is not positive, through every form of
+the per-pair backward (the product dOut . V[j] is formed for such pairs too and left out afterwards), and fp32 keys of neurons that
+are not selected (their scores come out of matrix instructions together with their neighbours')."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+PAIRS = {  # by the kernels that the fp32 cases launch
+    ("pair_one", "seg_rows"): [(50, 72, 700, 9), (90, 520, 30, 20), (60, 1496, 900, 12)],   # 1, 4 and 4 waves to a chunk
+    ("pair_one", "seg_dv"): [(1000, 784, 5000, 16), (700, 2056, 900, 12)],
+    ("pair_scan", "seg_rows"): [(2100, 72, 900, 11)],
+    ("pair_scan", "seg_dv"): [(2100, 784, 9000, 11)],
+}
+
+
+@pytest.mark.parametrize("T, d, N, k", [c for cases in PAIRS.values() for c in cases])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_values_of_pairs_that_are_not_active(T, d, N, k, dtype):
+    import torch
+    from paper_2406_04984_amd import binding as B
+    if dtype == "bf16":
+        N = max(N, 65 * k)   # sparse enough for the per-pair kernels whatever d
+    s = B.make_shape(T, d, 1, N, 1, k, dtype)
+    gen = torch.Generator(device="cuda").manual_seed(9400 + T + d)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    h, dOut, K, V = (torch.randn((n, d), generator=gen, device="cuda").to(dt) for n in (T, T, N, N))
+    idx = torch.rand((T, N), generator=gen, device="cuda").topk(k, dim=1)[1].sort(1)[0].to(torch.int32)
+    act = torch.randn((T, k), generator=gen, device="cuda").clamp(min=0)
+    bad = torch.zeros(N, dtype=torch.bool, device="cuda")
+    bad[::3] = True
+    V[::6], V[3::6] = float("nan"), float("inf")
+    # a third of the tokens have active pairs of such rows; the others' are not active (zero of either sign)
+    dead = bad[idx.long()] & (torch.arange(T, device="cuda") % 3 > 0)[:, None]
+    act[dead] = -0.0
+    act[dead & (torch.arange(k, device="cuda") % 2 == 0)] = 0.0
+    live = (act > 0) & bad[idx.long()]
+    dh, dK, dV = torch.full((T, d), 7.0, dtype=dt, device="cuda"), torch.zeros((N, d), dtype=dt, device="cuda"), torch.zeros((N, d), dtype=dt, device="cuda")
+    touched, n = torch.zeros((min(N, T * k),), dtype=torch.int32, device="cuda"), torch.zeros((1,), dtype=torch.int32, device="cuda")
+    ws = torch.empty((B.meft_workspace_bytes(s),), dtype=torch.uint8, device="cuda").fill_(0xFF)
+    B.meft_sparse_bwd(s, h, K, V, idx, act, dOut, dh, dK, dV, touched, n, ws)
+    torch.cuda.synchronize()
+    hit = torch.zeros(N, dtype=torch.bool, device="cuda")
+    hit[idx.long()[live]] = True
+    assert 0 < int(live.sum()) and 0 < int(dead.sum())
+    assert bool(torch.isfinite(dV.float()).all())
+    assert torch.equal(~torch.isfinite(dh.float()).all(1), live.any(1))
+    assert torch.equal(~torch.isfinite(dK.float()).all(1), hit)
+    # what is left: the same bits as with those rows zero
+    again = [torch.zeros_like(dh), torch.zeros_like(dK), torch.zeros_like(dV)]
+    V[bad] = 0
+    B.meft_sparse_bwd(s, h, K, V, idx, act, dOut, *again, touched, n, ws)
+    torch.cuda.synchronize()
+    keep = ~live.any(1)
+    assert torch.equal(dh[keep], again[0][keep]) and torch.equal(dK[~hit], again[1][~hit]) and torch.equal(dV, again[2])
+
+
+@pytest.mark.parametrize("T, d, nb, bs, e, k", [(300, 40, 5, 72, 2, 20), (1100, 264, 6, 40, 2, 9), (3000, 72, 2, 1200, 1, 30), (500, 1000, 40, 64, 3, 40)])
+def test_keys_that_are_not_selected(T, d, nb, bs, e, k):
+    import torch
+    from paper_2406_04984_amd import binding as B
+    s = B.make_shape(T, d, nb, bs, e, k, "f32")
+    gen = torch.Generator(device="cuda").manual_seed(9500 + T)
+    N = nb * bs
+    h = torch.rand((T, d), generator=gen, device="cuda") + 0.01
+    K, V = torch.randn((N, d), generator=gen, device="cuda"), torch.randn((N, d), generator=gen, device="cuda")
+    blocks = torch.rand((T, nb), generator=gen, device="cuda").topk(e, dim=1)[1].to(torch.int32)
+    ws = torch.empty((B.meft_workspace_bytes(s),), dtype=torch.uint8, device="cuda")
+    got = []
+    for low in (-float("inf"), -1e30):   # scores below all others
+        K[::5] = low
+        out, idx, act = torch.zeros((T, d), device="cuda"), torch.zeros((T, k), dtype=torch.int32, device="cuda"), torch.zeros((T, k), device="cuda")
+        B.meft_sparse_fwd(s, h, K, V, blocks, out, idx, act, ws)
+        torch.cuda.synchronize()
+        got.append((out, idx, act))
+    assert not bool((got[0][1] % 5 == 0).any())
+    for x, y in zip(*got):
+        assert torch.equal(x, y)

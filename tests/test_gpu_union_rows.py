@@ -1,16 +1,19 @@
 """Batch union with K's and V's rows gathered by the contractions, bit for bit against compacted copies (which
-meft_debug_global_loads forces): unions that end inside a k tile, inside a column tile and with a virtual block, one and several
-virtual blocks, and rows outside the union that hold no numbers, which nothing may touch."""
+meft_debug_global_loads forces): unions that end inside a k tile, inside a column tile, with a virtual block and one row behind it,
+virtual blocks that are no multiple of a column tile, hidden sizes that are none, one and several virtual blocks, and rows outside
+the union that hold no numbers, which nothing may touch.  SMALL: on small tiles, which read compacted copies either way."""
 import pytest
 
 pytestmark = pytest.mark.gpu
 
-CASES = [  # T, d, N, neurons in the union, top_k
-    (1700, 512, 5000, 3111, 8), (2100, 1024, 4096, 4096, 4), (1500, 4096, 2048, 1025, 16), (9000, 320, 1300, 1100, 3),
+GATHERED = [  # T, d, N, neurons in the union, top_k
+    (1700, 512, 5000, 3111, 8), (2100, 1024, 4096, 4096, 4),
+    (8100, 960, 900, 801, 4), (2100, 960, 1500, 1025, 4), (8100, 448, 2000, 1999, 2),
 ]
+SMALL = [(1500, 4096, 2048, 1025, 16), (9000, 320, 1300, 1100, 3)]
 
 
-@pytest.mark.parametrize("T, d, N, U, k", CASES, ids=lambda v: str(v))
+@pytest.mark.parametrize("T, d, N, U, k", GATHERED + SMALL, ids=lambda v: str(v))
 def test_same_bits_as_compacted_copies(T, d, N, U, k):
     import torch
     from paper_2406_04984_amd import binding as B

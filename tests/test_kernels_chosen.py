@@ -3,7 +3,10 @@ runtime (tests/hostcalls.py)."""
 import pytest
 
 from tests.hostcalls import record, shape
+from tests.test_gpu_not_finite import PAIRS
+from tests.test_gpu_pair_rows import ONE_KERNEL, TWO_KERNELS
 from tests.test_gpu_select_bound import CASES
+from tests.test_gpu_union_rows import GATHERED, SMALL
 
 
 def _names(calls, flags=0, **kw):
@@ -41,3 +44,22 @@ def test_few_tokens_and_block_dense(few, kw):
     assert _has(names, "few_out") == few and _has(names, "select_reg") != few
     reuse = _names(["bwd"], flags=8, dtype="bf16", **kw)
     assert _has(reuse, "act_rows") == few      # the few-token forward leaves nothing to reuse
+
+
+def test_pairs_of_the_per_pair_backward():
+    for kernels, cases in PAIRS.items():
+        for T, d, N, k in cases:
+            names = _names(["bwd"], T=T, d=d, n_blocks=1, block_size=N, top_e=1, top_k=k, dtype="f32")
+            assert all(_has(names, kernel) for kernel in kernels), (T, d, N, k, names)
+    for cases, kernel in ((ONE_KERNEL, "seg_rows"), (TWO_KERNELS, "seg_dv")):
+        for T, d, nb, bs, e, k, dtype in cases:
+            names = _names(["bwd"], T=T, d=d, n_blocks=nb, block_size=bs, top_e=e, top_k=k, dtype=dtype)
+            assert _has(names, kernel) and _has(names, "pair_one") == (T * k <= 20480), (T, d, nb, bs, k, names)
+
+
+@pytest.mark.parametrize("call", ["union_fwd", "union_bwd"])
+def test_rows_of_the_batch_union(call):
+    for cases, gathered in ((GATHERED, True), (SMALL, False)):
+        for T, d, N, _, k in cases:
+            names = _names([call], T=T, d=d, n_blocks=1, block_size=N, top_e=1, top_k=k, dtype="bf16")
+            assert _has(names, "gather_rows") != gathered and _has(names, "NCRows") == gathered, (T, d, N, k, names)
