@@ -58,6 +58,7 @@ def kernel_models(cfg, n_touched):
         "pair_dh": dict(bound="hbm", flop=pair, bytes=P * d * s + act + P * 8.0),
         "seg_dv": dict(bound="hbm", flop=2 * pair, bytes=P * d * s + P * 12.0 + 2.0 * rows),
         "seg_dk": dict(bound="hbm", flop=pair, bytes=P * d * s + P * 12.0 + rows),
+        "seg_rows": dict(bound="hbm", flop=3 * pair, bytes=2.0 * P * d * s + P * 12.0 + 3.0 * rows),   # few pairs: both at once
         # block-dense kernels: compulsory = operand rows once + result rows once
         "value_gemm": dict(bound="hbm", flop=pair, bytes=rows + P * 8.0 + act, dense_flop=dense),
         "dact_gemm": dict(bound="hbm", flop=pair, bytes=act + rows + P * 8.0, dense_flop=dense),
@@ -86,7 +87,7 @@ STAGE_SYMBOL = {
     "topk_select": ("topk_select_reg_kernel<16, true>", "topk_select_reg_kernel<32, true>", "topk_select_reg_kernel<4, true>"),
     "out_rows": "token_rows_kernel<2, false, true>", "dh_rows": "token_rows_kernel<2, false, true>",
 }
-GATHER_SCATTER = ("value_gemm", "dact_gemm", "dh_gemm", "dV_gemm", "dK_gemm", "pair_out", "pair_dh", "seg_dv", "seg_dk")
+GATHER_SCATTER = ("value_gemm", "dact_gemm", "dh_gemm", "dV_gemm", "dK_gemm", "pair_out", "pair_dh", "seg_dv", "seg_dk", "seg_rows")
 
 
 def profiled_traffic(workload, stage):

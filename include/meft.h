@@ -272,7 +272,8 @@ meft_status meft_union_bwd(const meft_shape* shape, const void* h, const void* K
  * Test aid (not part of the paper's method): the matrix-core kernels read operand matrices below 4 GB through
  * buffer resources and larger ones through 64-bit global pointers.  on != 0 selects the global-pointer kernels at
  * any size, so that a test reaches them with small inputs; on == 0 restores the choice by size.  The initial state
- * is that of the environment variable MEFT_GLOBAL_LOADS ("1" = on), read once when the library is loaded.
+ * is that of the environment variable MEFT_GLOBAL_LOADS ("1" = on), read once when the library is loaded.  Serialised
+ * with the entry points: a call that is under way on another host thread keeps its choice.
  */
 void meft_debug_global_loads(int on);
 

@@ -6,10 +6,10 @@
 // slot_of_ent carries kSmallSlot where the entry's group is one of at most small_rows tokens (small_groups.h).
 //
 // Small dispatches (dispatch_one_form) take one launch: a workgroup per block looks through all the entries (they come out of L2,
-// and a launch costs more) and places its own, and one more counts the entries of all blocks, writes the tables and deals the groups to the XCDs.  Two launches /
-// one: 2048 tokens x 4, 64 blocks 21.8 -> 11.2 us; 8192 x 4, 64 blocks 24 -> 14; 4096 x 8, 256 blocks 30 -> 18 (of either about
-// half by the faster tables).  At the limits, whole forward of a layer with d 64: 16384 x 4, 64 blocks 105.2 -> 99.8, 128
-// blocks 116.3 -> 105.4; beyond them 16384 x 8, 16 blocks 114.2 -> 126.1.
+// and a launch costs more) and places its own, and one more counts the entries of all blocks, writes the tables and deals the
+// groups to the XCDs.  Two launches / one: 2048 tokens x 4, 64 blocks 21.8 -> 11.2 us; 8192 x 4, 64 blocks 24 -> 14; 4096 x 8, 256
+// blocks 30 -> 18 (of either about half by the faster tables).  At the limits, whole forward of a layer with d 64: 16384 x 4, 64
+// blocks 105.2 -> 99.8, 128 blocks 116.3 -> 105.4; beyond them 16384 x 8, 16 blocks 114.2 -> 126.1.
 // Beyond that, up to 1024 blocks and 2^20 entries, it takes two launches over chunks of whole tokens, at most 1024 entries each:
 //   dispatch_count   sorts every token's blocks, counts the entries of every block per chunk, and clears what the
 //                    forward or backward needs cleared;
@@ -17,8 +17,8 @@
 //                    than a launch) and places its chunk's entries, while one more workgroup writes the tables and
 //                    deals the groups to the XCDs, which is a serial chain.
 // Against four launches (sort, count, one workgroup that scans and deals, place): 41 -> 24 us at 8192 x 4 entries and 64
-// blocks, 67 -> 30 us at 4096 x 8 and 256.  Where the chunk counts are too many for every workgroup to add up (more than kDispScanMax), one workgroup
-// does it in a launch of its own in between.
+// blocks, 67 -> 30 us at 4096 x 8 and 256.  Where the chunk counts are too many for every workgroup to add up (more than
+// kDispScanMax), one workgroup does it in a launch of its own in between.
 // The rank of an entry inside its wave comes from ballots over the distinct blocks of the wave, the rest from prefix
 // sums, so the order is the entry order and nothing depends on the timing of atomics.
 // (Shapes beyond these limits use count_blocks / fill_groups / slot_maps / build_sched, which scan the entries

@@ -17,14 +17,15 @@ struct SegFinish {
 };
 
 // row[t,:] = sum over the token's pairs of coef * W[idx,:], fp32: kAcc sums, of the pairs kAcc apart in list order, which are
-// added at the end.  U: rows a wave asks for together: 8, or as few as a token has pairs (a row asked for twice costs as much as
-// another: 10000 tokens x 1 pair, d 4096, fp32, backward 249 -> 216 us).  gate: pairs whose gate is not positive are left out (their W row is not read); nullptr: none.
+// added at the end.  gate: pairs whose gate is not positive are left out (their W row is not read); nullptr: none.
+// U: rows a wave asks for together: 8, or as few as a token has pairs (a row asked for twice costs as much as another: 10000
+// tokens x 1 pair, d 4096, fp32, backward 249 -> 216 us).
 // A wave takes (token, 1 KB of columns), a workgroup four tokens of the same columns, and the columns are dealt to the XCDs: XCD
 // x takes the x-th eighth of the units, ordered by columns first.  The tokens' lists ascend (the selection writes them so), and
-// the waves of an XCD go through them side by side, so a row's KB that several tokens selected is asked for by all of them at
-// about the same time and comes from memory once; a compute unit has about a hundred 128-byte lines in flight, so what counts
-// is how soon a line is there.  2048 tokens x 256 pairs,
-// d 4096, bf16, 65536 neurons (4.3 GB of rows): 575 -> 523 us; 1000 x 64, d 768, fp32, 8192 neurons: 23 -> 16.
+// the waves of an XCD go through them side by side, so a row's KB that several tokens selected is asked for by them within a short
+// time; they drift further apart than an L2 holds all the same: of 4.3 GB of rows an eighth is found there (3.7 GB come from beyond
+// it, at 7 TB/s).  A compute unit has about a hundred 128-byte lines in flight, so what counts is how soon a line is there.  2048
+// tokens x 256 pairs, d 4096, bf16, 65536 neurons: 575 -> 510 us; 1000 x 64, d 768, fp32, 8192 neurons: 22 -> 16.
 template <typename T, int kAcc, int U>
 __global__ __launch_bounds__(256) void pair_rows_kernel(const T* __restrict__ W, const int32_t* __restrict__ idx,
                                                         const float* __restrict__ coef, const float* __restrict__ gate,

@@ -167,7 +167,8 @@ __global__ __launch_bounds__(256) void gemm_nt_bf16_kernel(GemmNTArgs a) {
 // same permuted order in both.  LDS rows of 128 bytes, 16-byte chunk c of row r at chunk c ^ (r & 7).
 // The tiles are dealt to the XCDs in eighths, those of a group side by side, so that a group's rows are fetched into one L2.
 // Against a vector-unit kernel of 64 x 64 tiles: 1000 tokens x 4 of 32 blocks
-// of 256, d 768: 59 -> 22 us; 1000 x 4 of 16 of 256, d 4096: 338 -> 100.
+// of 256, d 768: 60 -> 32 us; 1000 x 4 of 16 of 256, d 4096: 288 -> 136 (a third of the rate: one barrier per 32 k, and every
+// tile's operands out of L2).
 // ---------------------------------------------------------------------------------------------
 constexpr int kGemmF32BN = 64, kGemmF32BK = 32;
 

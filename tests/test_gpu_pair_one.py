@@ -1,6 +1,6 @@
 """The pairs of the per-pair backward grouped in one launch, against the oracle: one pair, fewer neurons than workgroups (128),
-ragged ones, the most pairs and neurons of the launch and one step beyond either, segments that are sorted in LDS (more than 256
-pairs) beside short ones, and all pairs in one segment."""
+ragged ones, around the pairs (8192) and neurons (16384) up to which the kernel has its short form and buckets of more than four
+neurons begin, segments that are sorted in LDS (more than 256 pairs) beside short ones, and all pairs in one segment."""
 import numpy as np
 import pytest
 
