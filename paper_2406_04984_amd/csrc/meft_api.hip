@@ -554,15 +554,18 @@ void launch_pair_rows(const char* name, const meft_shape& s, const void* W, cons
 }
 
 // Whether dV, ds and dK of a chunk come out of one kernel (seg_rows_kernel) or of two, by the bytes of the rows of one operand that
-// are touched at most.  Backward, us, two kernels / one.  Pairs grouped by one launch: 512 tokens x 16 of 16384 neurons (8192 rows) x
-// 1 KB 26.7 / 22.1, x 2 KB 31.3 / 30.4, x 3 KB 36.4 / 38.9; 250 x 64 of 65536 x 1.4 KB 44.8 / 44.7, x 2 KB 49.1 / 51.0; 1000 x 16 of
-// 4096 x 3 KB 39.8 / 42.4; 300 x 50 of 2000 x 3 KB 36.8 / 33.1, x 16 KB 66.4 / 86.4.  By five: 1500 x 16 of 3000 x 1 KB 36.0 /
-// 32.3, of 20000 40.0 / 41.7; 2500 x 25 of 1664 x 2 KB 63.9 / 62.2, x 3 KB 78.3 / 85.3; 8192 x 8 of 4000 x 2 KB 71.5 / 74.4;
-// 65536 x 16 of 1000 x 1 KB 691 / 703.
+// are touched at most; with more slices than waves to a chunk, only where most neurons have one pair.  Backward, us, two kernels /
+// one.  Pairs grouped by one launch: 512 tokens x 16 of 16384 neurons (8192 rows) x 1 KB 26.7 / 22.1, x 2 KB 31.3 / 30.4, x 3 KB 36.4 /
+// 38.9; 250 x 64 of 65536 x 1.4 KB 44.8 / 44.7, x 2 KB 49.1 / 51.0; 1000 x 16 of 4096 x 3 KB 39.8 / 42.4; 300 x 50 of 2000 x 3 KB
+// 36.8 / 33.1; 1500 x 4 of 1500 x 4 KB 27.8 / 27.8, x 6 KB 35.1 / 38.2; 100 x 8 of 5000 x 6 KB 20.9 / 16.6, x 16 KB 28.2 / 24.9; 200 x
+// 20 of 4096 x 6 KB 31.3 / 32.8.  By five: 1500 x 16 of 3000 x 1 KB 36.0 / 32.3, of 20000 40.0 / 41.7; 2500 x 25 of 1664 x 2 KB 63.9 /
+// 62.2, x 3 KB 78.3 / 85.3; 8192 x 8 of 4000 x 2 KB 71.5 / 74.4; 65536 x 16 of 1000 x 1 KB 691 / 703.
 bool seg_rows_fused(const meft_shape& s, int slices) {
   const int64_t P = (int64_t)s.T * s.top_k, bytes = (s.N < P ? s.N : P) * s.d * (s.dtype == MEFT_BF16 ? 2 : 4), MB = 1 << 20;
-  if (pair_one(s)) return slices <= 2 ? bytes <= 24 * MB : bytes <= 12 * MB && P * slices <= 65536;
-  return slices <= 2 && bytes <= (slices == 1 ? 8 : 6) * MB && P <= 131072;
+  if (!pair_one(s)) return slices <= 2 && bytes <= (slices == 1 ? 8 : 6) * MB && P <= 131072;
+  if (slices <= 2) return bytes <= 24 * MB;
+  if (slices <= 4) return bytes <= 12 * MB && P * slices <= 65536;
+  return bytes <= 16 * MB && 4 * P <= s.N;
 }
 
 // The backward of the per-pair path.
@@ -614,7 +617,9 @@ void launch_pair_bwd(const meft_shape& s, const BwdWs& w, const void* h, const v
     const int entries = lists.first ? (int)(P / chunks + 0.5) : 1;
     auto launch = [&](auto dv, auto dk) {
       const int64_t groups = (n_work + 3) / 4;   // four entries per workgroup
-      auto grid = [&](int n, int more) { return grid_xcd((groups * n < kSegWorkgroups ? groups * n : kSegWorkgroups) + more); };
+      auto grid = [&](int n, int more) {   // (no workgroup beyond what runs at once: it would have to wait for another)
+        return grid_xcd((groups * n < kSegWorkgroups - more ? groups * n : kSegWorkgroups - more) + more);
+      };
       MEFT_LAUNCH("seg_dv", dv, grid(parts, lists.first ? 8 : 0), dim3(256), 0, st, w.work, w.totals, w.seg, static_cast<const T*>(V),
                   static_cast<const T*>(dOut), s.d, slices, n_pairs, static_cast<T*>(dV), w.seg_part, w.ds_part, entries, lists);
       MEFT_LAUNCH("seg_dk", dk, grid(slices, 0), dim3(256), 0, st, w.work, w.totals, w.seg, w.pair_sorted, w.ds_part,

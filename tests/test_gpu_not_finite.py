@@ -7,7 +7,7 @@ pytestmark = pytest.mark.gpu
 
 
 PAIRS = {  # by the kernels that the fp32 cases launch
-    ("pair_one", "seg_rows"): [(50, 72, 700, 9), (90, 520, 30, 20), (60, 1496, 900, 12)],   # 1, 4 and 4 waves to a chunk
+    ("pair_one", "seg_rows"): [(50, 72, 700, 9), (90, 520, 30, 20), (60, 1016, 900, 12), (15, 1496, 900, 12)],   # 1, 4, 4, 4 waves to a chunk
     ("pair_one", "seg_dv"): [(1000, 784, 5000, 16), (700, 2056, 900, 12)],
     ("pair_scan", "seg_rows"): [(2100, 72, 900, 11)],
     ("pair_scan", "seg_dv"): [(2100, 784, 9000, 11)],

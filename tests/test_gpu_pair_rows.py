@@ -11,12 +11,13 @@ pytestmark = pytest.mark.gpu
 
 ONE_KERNEL = [  # T, d, n_blocks, block_size, top_e, top_k, dtype
     (3, 8, 2, 9000, 1, 5, "f32"), (40, 256, 1, 20000, 1, 30, "f32"), (70, 264, 3, 15, 2, 20, "f32"), (33, 776, 1, 4097, 1, 9, "f32"),
-    (90, 1032, 6, 64, 3, 33, "f32"), (8192, 16, 5, 1000, 1, 1, "f32"), (2731, 16, 5, 1000, 1, 3, "f32"),   # 8192, 8193 pairs
+    (90, 1016, 6, 64, 3, 33, "f32"), (40, 2056, 1, 9000, 1, 30, "f32"), (8192, 16, 5, 1000, 1, 1, "f32"), (2731, 16, 5, 1000, 1, 3, "f32"),   # 8192, 8193 pairs
     (20480, 8, 2, 3000, 1, 1, "f32"), (20481, 8, 2, 3000, 1, 1, "f32"), (20481, 264, 1, 500, 1, 1, "f32"),
     (120, 512, 1, 4200, 1, 60, "bf16"), (120, 520, 1, 70000, 1, 60, "bf16"), (100, 1544, 1, 2600, 1, 4, "bf16"),
     (130, 40, 1, 7, 1, 2, "f32"), (260, 24, 1, 33, 1, 1, "f32"), (400, 72, 2, 11, 1, 4, "bf16"), (150, 24, 1, 33, 1, 9, "f32"),
 ]
 TWO_KERNELS = [
+    (90, 1032, 6, 64, 3, 33, "f32"),
     (700, 2056, 1, 900, 1, 12, "f32"), (300, 1000, 1, 30000, 1, 40, "f32"), (900, 4104, 1, 9000, 1, 11, "bf16"), (410, 784, 1, 5000, 1, 50, "f32"),
     (20480, 776, 1, 30000, 1, 1, "f32"), (20481, 776, 1, 30000, 1, 1, "f32"), (20481, 520, 1, 500, 1, 1, "f32"),
 ]
