@@ -13,6 +13,7 @@ typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(4))) int32_t i32x4;
+typedef u32x4 u32x4_dw __attribute__((aligned(4)));   // the same in memory where only four bytes are sure to be aligned
 
 // ---- storage types -------------------------------------------------------------------------
 struct bf16_t {

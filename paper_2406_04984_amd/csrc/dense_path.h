@@ -16,6 +16,7 @@
 #pragma once
 #include "gemm_mfma.h"
 #include "gemm_tile.h"
+#include "gemm_wide.h"
 #include "select.h"
 #include "small_groups.h"
 
@@ -148,6 +149,24 @@ struct ProbTokKC {
     if (n >= bsp) return;   // bsp is even: n + 1 < bsp
     *reinterpret_cast<uint32_t*>(DS + at) = keep(pk, n, mk);
   }
+  // the same for 16 bytes of a row: four columns of fp32, or eight of bf16 (bsp % 64 == 0: all of them inside)
+  __device__ u32x4 load_aux16(const TileCoord& tc, int m, int n) const {
+    const int mm = m < tc.Mrows ? m : tc.Mrows - 1, nn = n < bsp ? n : bsp - 8;
+    return *reinterpret_cast<const u32x4_dw*>(Ap + (size_t)(tc.slot0 + mm) * bsp + nn);
+  }
+  __device__ void store16(size_t at, int n, u32x4 v, u32x4 mk) const {
+    if constexpr (tok_fp32_out(MODE)) {
+      if (n + 4 <= bs) {
+        *reinterpret_cast<u32x4_dw*>(sc + at) = v;   // (rows of an odd length: aligned to four bytes)
+      } else {
+#pragma unroll
+        for (int z = 0; z < 4; ++z)
+          if (n + z < bs) sc[at + z] = __uint_as_float(v[z]);
+      }
+    } else {
+      *reinterpret_cast<u32x4_dw*>(DS + at) = u32x4{keep(v.x, n, mk.x), keep(v.y, n + 2, mk.y), keep(v.z, n + 4, mk.z), keep(v.w, n + 6, mk.w)};
+    }
+  }
   __device__ uint32_t keep(uint32_t pk, int n, uint32_t mk) const {
     // a half is kept where the deciding value is positive: sign bit clear and not zero
     uint32_t keep = 0u;
@@ -207,6 +226,7 @@ struct ProbTokNC {
   __device__ size_t row_off(const TileCoord& tc, int, int m) const { return (size_t)(tc.slot0 + m) * d; }
   static constexpr bool kOutBf16 = true;
   __device__ void store_pk(size_t at, int, uint32_t pk, uint32_t) const { *reinterpret_cast<uint32_t*>(part + at) = pk; }
+  __device__ void store16(size_t at, int, u32x4 v, u32x4) const { *reinterpret_cast<u32x4_dw*>(part + at) = v; }
 };
 
 // Neuron-major, both operands indexed by the contraction index (slot) in their rows:
@@ -215,13 +235,12 @@ struct ProbTokNC {
 // so no transposed copy of the activations exists.  The contraction length is padded to 64: the padding rows of A
 // come from a row of zeros that the workspace keeps in front of the activation matrices, those of X are any valid
 // rows.  Only rows whose neuron is touched are written.
-// TM = 256: 256 x 256 tiles, eight compute waves that request their operands themselves, two slots per ring; TM = 128:
-// 128 x 256 with four compute and four loader waves (measured: 0.425 -> 0.388 ms (dV) against two).  The host takes
-// the larger tile where it does not add rows beyond the block (neu_tile_rows).
+// TM = 256: for gemm_wide_kernel; TM = 128: 128 x 256 with four compute and four loader waves (measured: 0.425 -> 0.388 ms (dV)
+// against two).  The host takes the larger tile where it does not add rows beyond the block (neu_tile_rows).
 template <int TM>
 struct ProbNeuTN {
-  static constexpr int kTM = TM, kSA = TM == 256 ? 2 : 3, kSB = kSA, kCW = TM == 256 ? 8 : 4;
-  static constexpr int kLoaders = TM == 256 ? 0 : 4;
+  static constexpr int kTM = TM, kSA = 3, kSB = 3, kCW = 4;
+  static constexpr int kLoaders = 4;
   static constexpr bool kAMC = true;
   static constexpr bool kBNC = true;
   static constexpr bool kRowIdsInMemory = true;
@@ -266,6 +285,7 @@ struct ProbNeuTN {
   __device__ size_t row_off(const TileCoord& tc, int, int m) const { return ((size_t)tc.g * bs + m) * d; }
   static constexpr bool kOutBf16 = true;
   __device__ void store_pk(size_t at, int, uint32_t pk, uint32_t) const { *reinterpret_cast<uint32_t*>(G + at) = pk; }
+  __device__ void store16(size_t at, int, u32x4 v, u32x4) const { *reinterpret_cast<u32x4_dw*>(G + at) = v; }
 };
 
 // The same with an output row number + 1 in every entry of `flag` (0: not stored): batch-union evaluation, whose compacted
@@ -300,6 +320,29 @@ struct ProbTokNCRows : ProbTokNC {
   __device__ const uint16_t* b_row_ptr(int row) const { return W + ((int64_t)row - 1) * d; }
 };
 constexpr int kTagPad = 256;   // tags behind the last block's
+
+// ---- the token-major problems for gemm_wide_kernel (the neuron-major one of 256 rows is as it is) -----------------------------
+template <class Base>
+struct WideTok : Base {
+  static constexpr int kTM = kWideM;
+  using Finder = WideFinder;
+  __device__ int cols() const {
+    if constexpr (Base::kBNC) return Base::d;
+    else return Base::bs;
+  }
+  __device__ Finder finder(int xcd) const {
+    Finder f;
+    f.init(Base::sched, xcd, (cols() + kTN - 1) / kTN, Base::big_only != 0);
+    return f;
+  }
+  __device__ bool locate(Finder& f, int wg, TileCoord& tc) const {
+    int m0, nt;
+    if (!f.find(Base::sched, wg >> 3, m0, nt, tc)) return false;
+    tc.m0 = m0; tc.n0 = nt * kTN; tc.Ncols = cols();
+    tc.nk = (Base::kBNC ? Base::bsp : Base::d) / kTK;
+    return true;
+  }
+};
 
 // ---- the same problems for gemm_tile_kernel -----------------------------------------------------
 template <int MODE, int TM, int TN>

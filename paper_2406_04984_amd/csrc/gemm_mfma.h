@@ -9,24 +9,17 @@
 //     dOut, h are contiguous in d: the value sum of Eq. 4, dh, dK, dV;
 //   A m-contiguous (rows indexed by k): dK, dV, whose A operand is the slot-major activation matrix, read as it is.
 //
-// Tile TM (m) x 256 (n) x 64 (k), a policy's kTM.  Two shapes of workgroup:
-//   kTM = 128: 4 compute waves as 2 x 2, each wave 64 x 128 = 2 x 4 MFMA tiles, plus two or four
-//     loader waves that own the whole global -> LDS traffic (16 B per lane).  Ring depths kSA, kSB up to three.
-//     Used by the router, the token-major problems and (as an option) the neuron-major ones.
-//   kTM = 256: 8 compute waves as 4 x 2, each wave 64 x 128, and no loader waves (kLoaders = 0): the accumulators of
-//     8 waves leave no registers for further waves on their SIMDs, so every compute wave requests an eighth of the
-//     operands itself, right after each barrier.  Two slots per ring (128 KB).  Used by the neuron-major problems
-//     (dV, dK), whose output has no ragged edge: a third fewer operand bytes per flop through L2 -> LDS, and half as
-//     many store phases.  Measured at the LLaMA-7B-shaped configuration: dV 0.355 -> 0.340 ms, dK 0.345 -> 0.339 ms.
-// The operands have a ring each in LDS: kSA slots of TM x 64 for A, kSB slots of 256 x 64 for B.  (A 192-row tile
+// Tile 128 (m) x 256 (n) x 64 (k): 4 compute waves as 2 x 2, each wave 64 x 128 = 2 x 4 MFMA tiles, plus two or four
+// loader waves that own the whole global -> LDS traffic (16 B per lane).  Ring depths kSA, kSB up to three.  Problems that fill
+// 256 x 256 tiles go to gemm_wide_kernel (gemm_wide.h); here are the router, small groups, operands beyond buffer loads.
+// The operands have a ring each in LDS: kSA slots of 128 x 64 for A, kSB slots of 256 x 64 for B.  (A 192-row tile
 // for the token-major problems moves 22 % fewer operand bytes per flop than the 128-row one and was measured 15 %
 // faster per flop, but their groups then fill a whole number of tiles worse and the step as a whole did not gain.  It
 // is gone; the tile schedule has prefixes of 64 and 128 rows only.)
 // LDS layouts are XOR-swizzled so that both the linear DMA writes and the fragment reads are free of bank conflicts:
 //   k-contiguous operand: rows of 64 k = 8 chunks of 16 B; logical chunk c of row r sits at chunk
 //     c ^ ((r >> 1) & 7); fragments are read with ds_read_b128.
-//   n-contiguous B, and m-contiguous A of 256 rows: rows of 256 = 32 chunks; logical chunk c of row k sits at chunk
-//     c ^ (2 * (k & 7));
+//   n-contiguous B: rows of 256 = 32 chunks; logical chunk c of row k sits at chunk c ^ (2 * (k & 7));
 //   m-contiguous A of 128 rows: 16 chunks per row; logical chunk c of row k sits at chunk c ^ (4 * (k & 3));
 //     these are read with the transposing ds_read_b64_tr_b16, which hands lane i of a 16-lane group the four
 //     k-consecutive values of column i of a 4 x 16 block.
@@ -62,25 +55,18 @@
 namespace meft {
 
 constexpr int kTN = 256, kTK = 64;
-#ifndef MEFT_NEU_TM
-#define MEFT_NEU_TM 256
-#endif
 constexpr int kTMTok = 128;            // tile rows of the token-major problems (groups of tokens against a block's rows)
 constexpr int kTMNeu = 128;            // tile rows of the router
-constexpr int kTMNeuW = MEFT_NEU_TM;   // largest tile rows of the neuron-major problems (dV, dK): 256; 128 rules the larger tile out
 constexpr int kBSlotElems = kTN * kTK;                         // one B slot: 32 KB
 constexpr int kIdRingSlots = 4;                                // k tiles of gathered-row numbers kept per loader
 constexpr int kXcd = 8;
-// waves that request operands: the policy's loader waves, or (kLoaders == 0) its compute waves themselves
-template <class P>
-constexpr int loading_waves() { return P::kLoaders ? P::kLoaders : P::kCW; }
 // LDS of a launch: the two operand rings and, where the numbers of gathered B rows travel through LDS, 1 KB per
 // loading wave
 template <class P>
 constexpr int operand_lds_bytes() { return (P::kSA * P::kTM + P::kSB * kTN) * kTK * 2; }
 template <class P>
 constexpr int gemm_lds_bytes() {
-  return operand_lds_bytes<P>() + (P::kRowIdsInMemory ? loading_waves<P>() * kIdRingSlots * 64 * 4 : 0);
+  return operand_lds_bytes<P>() + (P::kRowIdsInMemory ? P::kLoaders * kIdRingSlots * 64 * 4 : 0);
 }
 // threads of a launch: the policy's compute waves plus its loader waves
 template <class P>
@@ -108,7 +94,7 @@ struct TileCoord {
 };
 
 // A problem policy P provides:
-//   static constexpr int kTM, kSA, kSB;                 tile rows (128 or 256) and the slots of the A and B rings (kSA == kSB)
+//   static constexpr int kTM, kSA, kSB;                 tile rows (128) and the slots of the A and B rings (kSA == kSB)
 //   static constexpr int kLoaders;                      loader waves, 2 or 4
 //   Finder, __device__ Finder finder(int xcd) const;    what a wave of that XCD looks its tiles up with, in registers
 //   __device__ bool locate(Finder&, int wg, TileCoord&) const;   false: no tile with id wg, nor with any larger id on
@@ -160,36 +146,6 @@ struct TileCoord {
 //                the policy wants next to the two values of (m, n), e.g. a mask; called for every position of the
 //                tile, stored or not, so the policy clamps m and n to valid ones
 
-// Twelve transposing LDS reads of one k16 step (the two m-contiguous A fragments and the four n-contiguous B
-// fragments, low and high k half each) followed by the wait for them.  xa = {A0 low, A0 high, A1 low, A1 high}.
-// Written as one asm block for the compute waves that also request operands: issued through the builtin, the
-// compiler would order these reads after every outstanding global->LDS load (it cannot tell the slots apart),
-// which would drain the operand pipeline at every k tile.  The barrier that hands a position over already
-// guarantees that the slots read here have landed.
-template <int OFFA, int OFFB>
-__device__ __forceinline__ void tr_read12(u32x2 (&oa)[4], u32x2 (&ob)[8], const uint32_t (&xa)[4],
-                                          const uint32_t (&blo)[4], const uint32_t (&bhi)[4]) {
-  asm volatile(
-      "ds_read_b64_tr_b16 %0, %12 offset:%24\n\t"
-      "ds_read_b64_tr_b16 %1, %13 offset:%24\n\t"
-      "ds_read_b64_tr_b16 %2, %14 offset:%24\n\t"
-      "ds_read_b64_tr_b16 %3, %15 offset:%24\n\t"
-      "ds_read_b64_tr_b16 %4, %16 offset:%25\n\t"
-      "ds_read_b64_tr_b16 %5, %17 offset:%25\n\t"
-      "ds_read_b64_tr_b16 %6, %18 offset:%25\n\t"
-      "ds_read_b64_tr_b16 %7, %19 offset:%25\n\t"
-      "ds_read_b64_tr_b16 %8, %20 offset:%25\n\t"
-      "ds_read_b64_tr_b16 %9, %21 offset:%25\n\t"
-      "ds_read_b64_tr_b16 %10, %22 offset:%25\n\t"
-      "ds_read_b64_tr_b16 %11, %23 offset:%25\n\t"
-      "s_waitcnt lgkmcnt(0)"
-      : "=&v"(oa[0]), "=&v"(oa[1]), "=&v"(oa[2]), "=&v"(oa[3]), "=&v"(ob[0]), "=&v"(ob[1]), "=&v"(ob[2]),
-        "=&v"(ob[3]), "=&v"(ob[4]), "=&v"(ob[5]), "=&v"(ob[6]), "=&v"(ob[7])
-      : "v"(xa[0]), "v"(xa[1]), "v"(xa[2]), "v"(xa[3]), "v"(blo[0]), "v"(bhi[0]), "v"(blo[1]), "v"(bhi[1]),
-        "v"(blo[2]), "v"(bhi[2]), "v"(blo[3]), "v"(bhi[3]), "n"(OFFA), "n"(OFFB)
-      : "memory");
-}
-
 // Workgroup barrier of a compute wave: it first waits for its own LDS traffic.  (A loader wave waits for the
 // operand loads that have to have landed instead.)
 #define MEFT_BARRIER_LDS() asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory")
@@ -207,19 +163,16 @@ __device__ __forceinline__ uint32_t byte_off(const uint16_t* ptr, const uint16_t
 
 template <class P, bool kBuf>
 __global__ __launch_bounds__(gemm_threads<P>(), 1) void gemm_mfma_kernel(P p, int n_tiles_bound) {
-  constexpr int kCW = P::kCW;                       // compute waves: 4 (2 x 2) or 8 (4 x 2)
-  constexpr bool kSelf = P::kLoaders == 0;          // the compute waves request the operands themselves
-  constexpr int kLoaders = loading_waves<P>();      // waves that request operands
+  constexpr int kCW = P::kCW;                       // compute waves: 4 (2 x 2)
+  constexpr int kLoaders = P::kLoaders;             // waves that request operands
   constexpr int TM = P::kTM, SA = P::kSA, SB = P::kSB;
   constexpr int WM = TM / (kCW / 2);                // rows of a compute wave
   constexpr int MI = WM / 32;                       // 32-row MFMA tiles per compute wave
   constexpr int kASlotElems = TM * kTK;
   constexpr int kBRing = SA * kASlotElems;          // element offset of the B ring
-  static_assert(kLoaders == 2 || kLoaders == 4 || kLoaders == 8, "waves that load: 2, 4 or 8");
-  static_assert((kCW == 4 && TM == 128) || (kCW == 8 && TM == 256), "tile rows: 128 or 256, 64 to a compute wave");
+  static_assert(kLoaders == 2 || kLoaders == 4, "waves that load: 2 or 4");
+  static_assert(kCW == 4 && TM == 128, "128 tile rows, 64 to a compute wave");
   static_assert(SA >= 2 && SA <= 3 && SB == SA, "ring depths: 2 or 3, A and B requested for the same positions");
-  static_assert(!kSelf || (P::kAMC && P::kBNC && SA == 2 && SB == 2 && kCW == 8),
-                "compute waves that load: written for the neuron-major problems with two slots per ring");
   extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -233,9 +186,8 @@ __global__ __launch_bounds__(gemm_threads<P>(), 1) void gemm_mfma_kernel(P p, in
   if (!next_tile(blockIdx.x, tc)) return;   // the same answer in every wave
 
   // ---------------------------------------------------------------------- operand requests
-  // (state and steps of a wave that loads: a loader wave, or with kSelf every compute wave; dead code in the compute
-  // waves of a launch with loader waves)
-    const int lw = kSelf ? wave : wave - kCW;
+  // (state and steps of a loader wave; dead code in the compute waves)
+    const int lw = wave - kCW;
     constexpr int LA = TM / 8 / kLoaders;    // A wave-loads (1 KB each) per loader and slot: 12, 8, 6 or 4
     constexpr int LB = kTN / 8 / kLoaders;   // B wave-loads (1 KB each) per loader and slot: 16 or 8
     constexpr int DA = SA - 1;               // positions ahead of the barrier at which they are requested
@@ -308,14 +260,7 @@ __global__ __launch_bounds__(gemm_threads<P>(), 1) void gemm_mfma_kernel(P p, in
     auto setup_a = [&]() {
       const TileCoord& t = cu.t;
       if constexpr (kBuf) {
-        if constexpr (P::kAMC && TM == 256) {
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int chunk = (lane & 31) ^ (2 * ((2 * q + half) & 7));
-            const int col = t.m0 + chunk * 8, last = p.a_cols(t) - 8;
-            oa[q] = byte_off(p.a_mat() + (col > last ? last : col), p.a_base());
-          }
-        } else if constexpr (P::kAMC) {
+        if constexpr (P::kAMC) {
           const int chunk = (lane & 15) ^ (4 * ((lane >> 4) & 3));
           const int col = t.m0 + chunk * 8, last = p.a_cols(t) - 8;
           const uint32_t o = byte_off(p.a_mat() + (col > last ? last : col), p.a_base());
@@ -329,14 +274,7 @@ __global__ __launch_bounds__(gemm_threads<P>(), 1) void gemm_mfma_kernel(P p, in
           }
         }
       } else {
-        if constexpr (P::kAMC && TM == 256) {
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int chunk = (lane & 31) ^ (2 * ((2 * q + half) & 7));
-            const int col = t.m0 + chunk * 8, last = p.a_cols(t) - 8;
-            pa[q] = p.a_mat() + ((col > last ? last : col) - q * 512);   // clamp (rows beyond Mrows are never stored)
-          }
-        } else if constexpr (P::kAMC) {
+        if constexpr (P::kAMC) {
           const int chunk = (lane & 15) ^ (4 * ((lane >> 4) & 3));
           const int col = t.m0 + chunk * 8, last = p.a_cols(t) - 8;
           const int acol = col > last ? last : col;                       // clamp (rows beyond Mrows are never stored)
@@ -438,7 +376,7 @@ __global__ __launch_bounds__(gemm_threads<P>(), 1) void gemm_mfma_kernel(P p, in
 #pragma unroll
         for (int i = 0; i < LA; ++i) {
           if constexpr (P::kAMC) {
-            const int row = p.a_krow(t, cu.k * kTK + (TM == 256 ? 2 * (lw * LA + i) + half : 4 * (lw * LA + i) + (lane >> 4)));
+            const int row = p.a_krow(t, cu.k * kTK + 4 * (lw * LA + i) + (lane >> 4));
             MEFT_LOAD_1K_BUF(rsrc_a, oa[i & 3] + (uint32_t)row * (uint32_t)a_row_bytes, 0, my_a, i);
           } else {
             MEFT_LOAD_1K_BUF(rsrc_a, oa[i], k_bytes, my_a, i);
@@ -448,7 +386,7 @@ __global__ __launch_bounds__(gemm_threads<P>(), 1) void gemm_mfma_kernel(P p, in
 #pragma unroll
         for (int i = 0; i < LA; ++i) {
           if constexpr (P::kAMC) {
-            const int row = p.a_krow(t, cu.k * kTK + (TM == 256 ? 2 * (lw * LA + i) + half : 4 * (lw * LA + i) + (lane >> 4)));
+            const int row = p.a_krow(t, cu.k * kTK + 4 * (lw * LA + i) + (lane >> 4));
             MEFT_LOAD_1K(reinterpret_cast<const char*>(pa[i & 3]) + (int64_t)row * a_row_bytes, my_a, i);
           } else {
             MEFT_LOAD_1K(pa[i] + cu.k * kTK, my_a, i);
@@ -480,15 +418,8 @@ __global__ __launch_bounds__(gemm_threads<P>(), 1) void gemm_mfma_kernel(P p, in
               "=&v"(ids[13]), "=&v"(ids[14]), "=&v"(ids[15])
             : "v"(a)
             : "memory");
-        } else if constexpr (LB == 4) {
-        asm volatile(
-            "ds_read_b32 %0, %4\n\tds_read_b32 %1, %4 offset:8\n\tds_read_b32 %2, %4 offset:16\n\t"
-            "ds_read_b32 %3, %4 offset:24\n\ts_waitcnt lgkmcnt(0)"
-            : "=&v"(ids[0]), "=&v"(ids[1]), "=&v"(ids[2]), "=&v"(ids[3])
-            : "v"(a)
-            : "memory");
         } else {
-        static_assert(LB == 16 || LB == 8 || LB == 4, "row-number reads are written out for 16, 8 and 4 loads");
+        static_assert(LB == 16 || LB == 8, "row-number reads are written out for 16 and 8 loads");
         asm volatile(
             "ds_read_b32 %0, %8\n\tds_read_b32 %1, %8 offset:8\n\tds_read_b32 %2, %8 offset:16\n\t"
             "ds_read_b32 %3, %8 offset:24\n\tds_read_b32 %4, %8 offset:32\n\tds_read_b32 %5, %8 offset:40\n\t"
@@ -558,7 +489,7 @@ __global__ __launch_bounds__(gemm_threads<P>(), 1) void gemm_mfma_kernel(P p, in
       return request_operands();
     };
 
-  if (kSelf || wave >= kCW) {
+  if (wave >= kCW) {
     setup_a();
     setup_b();
     if constexpr (P::kBNC && P::kRowIdsInMemory) {
@@ -569,12 +500,9 @@ __global__ __launch_bounds__(gemm_threads<P>(), 1) void gemm_mfma_kernel(P p, in
     bool full = true;   // before the first barrier: the positions the lead reaches
 #pragma unroll
     for (int s = 0; s < DA; ++s) full = request_operands() && full;
-    // compute waves that load: position 0 has to have landed at the first barrier (later positions are awaited
-    // before the barrier that hands them over)
-    if constexpr (kSelf) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 
     // ------------------------------------------------------------------ loader waves
-    for (; !kSelf;) {
+    for (;;) {
       for (int kt = 0; kt < nk_c; ++kt) {
         // The position handed over now has landed once at most the kAhead most recent loads are outstanding (the
         // counter retires in issue order), provided the last batch of requests was complete; near the end of the
@@ -610,7 +538,7 @@ __global__ __launch_bounds__(gemm_threads<P>(), 1) void gemm_mfma_kernel(P p, in
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       const int m = wm + i * 32 + 16 * (gq & 1) + 4 * (s & 3);
-      const int x_lo = TM == 256 ? 2 * (k_lo & 7) : 4 * (k_lo & 3), x_hi = TM == 256 ? 2 * (k_hi & 7) : 4 * (k_hi & 3);
+      const int x_lo = 4 * (k_lo & 3), x_hi = 4 * (k_hi & 3);
       tra_lo[i] = (uint32_t)(k_lo * TM + (((m >> 3) ^ x_lo) << 3) + (m & 7)) * 2u;
       tra_hi[i] = (uint32_t)(k_hi * TM + (((m >> 3) ^ x_hi) << 3) + (m & 7)) * 2u;
     }
@@ -706,56 +634,6 @@ __global__ __launch_bounds__(gemm_threads<P>(), 1) void gemm_mfma_kernel(P p, in
       slot_a = slot_a + 1 == SA ? 0 : slot_a + 1;
       slot_b = slot_b + 1 == SB ? 0 : slot_b + 1;
     };
-    if constexpr (kSelf) {
-      // Compute waves that load.  The compiler orders every LDS read it knows of behind all outstanding global -> LDS
-      // loads (it cannot tell the slots apart), which would undo the prefetch, so here the fragments are read by asm
-      // blocks that wait for themselves; with two compute waves per SIMD the other wave's matrix instructions cover
-      // that wait.  A position's operands are requested right after the barrier that hands over the position before
-      // it, and awaited (vmcnt) right before the barrier that hands it over; the first position of a tile is awaited
-      // before the previous tile's stores, so that no barrier waits for stores.
-      auto k_tile_self = [&](auto first_tag) {
-        const uint16_t* sta = smem + slot_a * kASlotElems;
-        const uint16_t* stb = smem + kBRing + slot_b * kBSlotElems;
-        const uint32_t abase = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)(sta);
-        const uint32_t sbase = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)(stb);
-        const uint32_t xa[4] = {abase + tra_lo[0], abase + tra_hi[0], abase + tra_lo[1], abase + tra_hi[1]};
-        uint32_t alo[4], ahi[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) { alo[j] = sbase + tr_lo[j]; ahi[j] = sbase + tr_hi[j]; }
-        auto step16 = [&](auto ks_tag, auto zero_tag) {
-          constexpr int ks = decltype(ks_tag)::value;
-          u32x2 oa[4], o[8];
-          tr_read12<ks * (int)kStepA, ks * 8192>(oa, o, xa, alo, ahi);
-          Frags f;
-#pragma unroll
-          for (int i = 0; i < 2; ++i) {
-            const u32x4 w = {oa[2 * i].x, oa[2 * i].y, oa[2 * i + 1].x, oa[2 * i + 1].y};
-            f.a[i] = __builtin_bit_cast(bf16x8, w);
-          }
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const u32x4 w = {o[2 * j].x, o[2 * j].y, o[2 * j + 1].x, o[2 * j + 1].y};
-            f.b[j] = __builtin_bit_cast(bf16x8, w);
-          }
-          mma(zero_tag, f);
-        };
-        step16(std::integral_constant<int, 0>{}, first_tag);
-        step16(std::integral_constant<int, 1>{}, std::false_type{});
-        step16(std::integral_constant<int, 2>{}, std::false_type{});
-        step16(std::integral_constant<int, 3>{}, std::false_type{});
-        slot_a = slot_a + 1 == SA ? 0 : slot_a + 1;
-        slot_b = slot_b + 1 == SB ? 0 : slot_b + 1;
-      };
-      MEFT_BARRIER_LDS();   // (the tile's first position was awaited before: see above)
-      request_batch();
-      k_tile_self(std::true_type{});
-      for (int kt = 1; kt < nk; ++kt) {
-        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        request_batch();
-        k_tile_self(std::false_type{});
-      }
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    } else {
     MEFT_BARRIER_LDS();   // the loaders have seen the tile's first k tile land
     load_frags(std::integral_constant<int, 0>{}, f0);
     MEFT_FENCE();
@@ -772,7 +650,6 @@ __global__ __launch_bounds__(gemm_threads<P>(), 1) void gemm_mfma_kernel(P p, in
       k_steps(std::false_type{});
     }
     mma(std::false_type{}, f1);
-    }
 #undef MEFT_FENCE
 
     // ---- epilogue, out of the registers.  acc[i][j][r] is C[m][n] with m = wm + i*32 + (r/4)*8 + (lane/32)*4 + r%4

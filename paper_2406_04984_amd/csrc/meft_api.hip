@@ -673,6 +673,17 @@ void launch_gemm_mfma(const char* name, const P& prob, int grid, hipStream_t st)
   }
 }
 
+template <class P>
+void launch_gemm_wide(const char* name, const P& prob, int grid, hipStream_t st) {
+  static std::once_flag configured;
+  std::call_once(configured, [] {
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_wide_kernel<P>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                              kWideLds);
+  });
+  const int launch = grid < kPersistentWgs ? grid : kPersistentWgs;
+  MEFT_LAUNCH(name, gemm_wide_kernel<P>, dim3(launch), dim3(256), kWideLds, st, prob, grid);
+}
+
 // for policies that exist with buffer loads only
 template <class P>
 void launch_gemm_mfma_buf(const char* name, const P& prob, int grid, hipStream_t st) {
@@ -709,9 +720,53 @@ bool small_tiles(const meft_shape& s, int cols) {
   return (small < kPersistentWgs ? kPersistentWgs : small) * 24 < cost_large;
 }
 
+// Whether a token-major contraction of nk k tiles over `cols` output columns runs on tiles of 256 rows (gemm_wide_kernel) rather
+// than of 128 (gemm_mfma_kernel), by what one compute unit takes for a k tile and for a tile, in hundredths of a whole tile's k
+// tile (1.7-2.4 us): 256 rows 100 and 150, the short tile at the end of a group 74 and 120 (its columns' lines are nobody else's by then),
+// 128 rows 56 and 50.  Whole tiles come first and short ones fill up their last round (WideFinder).  Groups are taken
+// to lie within 30 % of their average, as the router's do.  At d 4096 with 64 blocks of 1024, us for the activation gradient on 128 /
+// 256 rows: 512 rows a group 344 / 331, 256 rows 236 / 267 (half of the groups a few rows too long), 192 rows 213 / 195.
+// Groups of fewer than 224 rows are bound by the block's rows out of HBM, which fewer and deeper requests bring faster (4096
+// tokens x 8 of 256 blocks 606 / 488), down to 96 rows, where both read them at the same rate (64: 183 / 186) and most
+// tiles would be short; contractions of a few k tiles not (4 k tiles, 128 rows: 15.0 / 16.7).
+bool wide_tiles(const meft_shape& s, int cols, int nk) {
+  const int64_t n_ent = (int64_t)s.T * s.top_e, groups = s.n_blocks < n_ent ? s.n_blocks : n_ent, rows = n_ent / groups;
+  if (rows < 96) return false;
+  if (rows < 224) return nk >= 8;
+  int64_t whole = 0, shorts = 0, tiles128 = 0;
+  for (int z = 7; z <= 13; ++z) {
+    const int64_t r = s.top_e == s.n_blocks ? rows : rows * z / 10, f = (r + 127) / 256;
+    whole += f;
+    shorts += r > f * kWideM ? 1 : 0;
+    tiles128 += (r + 127) / 128;
+  }
+  // of one of the eight XCDs' 32 compute units each
+  const int64_t per = groups * ((cols + kTN - 1) / kTN), cu = kPersistentWgs / kXcd, by = 7 * kXcd;
+  whole = (whole * per + by - 1) / by;
+  shorts = (shorts * per + by - 1) / by;
+  tiles128 = (tiles128 * per + by - 1) / by;
+  const int64_t rounds = (whole + cu - 1) / cu, room = rounds * cu - whole, late = shorts > room ? shorts - room : 0;
+  const int64_t cost_wide = rounds * (nk * 100 + 150) + (late + cu - 1) / cu * (nk * 74 + 120);
+  return cost_wide <= (tiles128 + cu - 1) / cu * (nk * 56 + 50);
+}
+
+// Launches a token-major policy that exists with buffer loads only, with the tiles that suit the problem.
+template <class Large, class F>
+void launch_tok_buf(const char* name, const meft_shape& s, int cols, int nk, F&& fill, hipStream_t st) {
+  if (wide_tiles(s, cols, nk)) {
+    WideTok<Large> p{};
+    fill(p);
+    launch_gemm_wide(name, p, tile_bound(s, (cols + kTN - 1) / kTN), st);
+  } else {
+    Large p{};
+    fill(p);
+    launch_gemm_mfma_buf(name, p, tile_bound(s, (cols + kTN - 1) / kTN), st);
+  }
+}
+
 // Fills in a token-major policy's fields and launches it with the tiles that suit the problem.
 template <class Large, class Small, class F>
-void launch_tok(const char* name, const meft_shape& s, int cols, uint64_t a_bytes, uint64_t b_bytes, uint64_t o_bytes, F&& fill,
+void launch_tok(const char* name, const meft_shape& s, int cols, int nk, uint64_t a_bytes, uint64_t b_bytes, uint64_t o_bytes, F&& fill,
                 hipStream_t st) {
   Small q{};
   set_gemm_extents(q, a_bytes, b_bytes);
@@ -720,6 +775,13 @@ void launch_tok(const char* name, const meft_shape& s, int cols, uint64_t a_byte
     fill(q);
     const int64_t m_tiles = (int64_t)s.T * s.top_e / Small::kTM + s.n_blocks;
     launch_gemm_tile(name, q, kXcd * m_tiles * ((cols + Small::kTNt - 1) / Small::kTNt), st);
+    return;
+  }
+  if (q.buf && wide_tiles(s, cols, nk)) {
+    WideTok<Large> p{};
+    set_gemm_extents(p, a_bytes, b_bytes);
+    fill(p);
+    launch_gemm_wide(name, p, tile_bound(s, (cols + kTN - 1) / kTN), st);
     return;
   }
   Large p{};
@@ -867,9 +929,9 @@ void launch_bwd_head(const meft_shape& s, const int32_t* flag, int32_t* chunk_cn
               w ? w->tok_of_slot : nullptr, s.d, s.top_k, s.block_size, w ? w->ds32 : nullptr);
 }
 
-// Tile rows of the dV / dK contractions: 256 where that computes no more padded rows of the block than 128 would
+// Tile rows of the dV / dK contractions: 256 (gemm_wide_kernel) where that computes no more padded rows of the block than 128 would
 int neu_tile_rows(int block_rows) {
-  return kTMNeuW == 256 && (block_rows + 255) / 256 * 256 == (block_rows + 127) / 128 * 128 ? 256 : 128;
+  return (block_rows + 255) / 256 * 256 == (block_rows + 127) / 128 * 128 ? 256 : 128;
 }
 
 // One weight-gradient contraction (dV: A = A', X = dOut; dK: A = DS', X = h) over the groups of a tile schedule
@@ -881,23 +943,24 @@ struct NeuArgs {
   uint64_t a_bytes, x_bytes;   // bytes readable from the lowest address of either operand
 };
 
-template <class P>
-void launch_neu_tm(const char* name, const NeuArgs& a, hipStream_t st) {
-  constexpr int TM = P::kTM;
-  P pn{};
-  pn.A = a.A; pn.zrow = a.zrow; pn.X = a.X; pn.G = a.G;
-  pn.tok_of_slot = a.tok_of_slot; pn.flag = a.flag;
-  pn.sched = a.sched; pn.big_only = a.big_only; pn.bs = a.bs; pn.bsp = a.bsp; pn.d = a.d;
-  set_gemm_extents(pn, a.a_bytes, a.x_bytes);
-  // every listed group has the same tiles; in the worst case one XCD holds all groups
-  const int64_t tiles = (int64_t)kXcd * a.n_groups * ((a.bs + TM - 1) / TM) * ((a.d + kTN - 1) / kTN);
-  launch_gemm_mfma(name, pn, (int)(tiles < (int64_t)INT32_MAX ? tiles : (int64_t)INT32_MAX), st);
-}
-
 template <template <int> class P = ProbNeuTN>
 void launch_neu(const char* name, const NeuArgs& a, hipStream_t st) {
-  if (neu_tile_rows(a.bs) == 256) launch_neu_tm<P<256>>(name, a, st);
-  else launch_neu_tm<P<128>>(name, a, st);
+  auto launch = [&](auto pn) {
+    constexpr int TM = decltype(pn)::kTM;
+    pn.A = a.A; pn.zrow = a.zrow; pn.X = a.X; pn.G = a.G;
+    pn.tok_of_slot = a.tok_of_slot; pn.flag = a.flag;
+    pn.sched = a.sched; pn.big_only = a.big_only; pn.bs = a.bs; pn.bsp = a.bsp; pn.d = a.d;
+    set_gemm_extents(pn, a.a_bytes, a.x_bytes);
+    if (TM == 256 && !pn.buf) return false;
+    // every listed group has the same tiles; in the worst case one XCD holds all groups
+    const int64_t tiles = (int64_t)kXcd * a.n_groups * ((a.bs + TM - 1) / TM) * ((a.d + kTN - 1) / kTN);
+    const int bound = (int)(tiles < (int64_t)INT32_MAX ? tiles : (int64_t)INT32_MAX);
+    if constexpr (TM == 256) launch_gemm_wide(name, pn, bound, st);
+    else launch_gemm_mfma(name, pn, bound, st);
+    return true;
+  };
+  if (neu_tile_rows(a.bs) == 256 && launch(P<256>{})) return;
+  launch(P<128>{});
 }
 
 }  // namespace
@@ -1020,12 +1083,17 @@ static meft_status fwd_impl(const meft_shape& s, const void* h, const void* K, c
       ps.e = s.top_e; ps.bs = s.block_size; ps.bsp = bsp; ps.d = s.d; ps.sc = w.sc;
     };
     if (dense) {
-      launch_tok<TokKCLarge<kTokSlotScores>, TokKCSmall<kTokSlotScores>>("score_gemm", s, s.block_size, (uint64_t)s.T * s.d * 2, (uint64_t)s.N * s.d * 2, (uint64_t)n_ent * s.block_size * 4, fill, st);
+      launch_tok<TokKCLarge<kTokSlotScores>, TokKCSmall<kTokSlotScores>>("score_gemm", s, s.block_size, s.d / kTK, (uint64_t)s.T * s.d * 2, (uint64_t)s.N * s.d * 2, (uint64_t)n_ent * s.block_size * 4, fill, st);
     } else {
       ProbTokKC<kTokScores> ps{};
       set_gemm_extents(ps, (uint64_t)s.T * s.d * 2, (uint64_t)s.N * s.d * 2);
       fill(ps);
-      launch_gemm_mfma("score_gemm", ps, tile_bound(s, (s.block_size + kTN - 1) / kTN), st);
+      if (ps.buf && wide_tiles(s, s.block_size, s.d / kTK)) {
+        WideTok<ProbTokKC<kTokScores>> pw{ps};
+        launch_gemm_wide("score_gemm", pw, tile_bound(s, (s.block_size + kTN - 1) / kTN), st);
+      } else {
+        launch_gemm_mfma("score_gemm", ps, tile_bound(s, (s.block_size + kTN - 1) / kTN), st);
+      }
     }
   } else {
     GemmNTArgs a{};
@@ -1065,7 +1133,7 @@ static meft_status fwd_impl(const meft_shape& s, const void* h, const void* K, c
   if (wait_v && hipStreamWaitEvent(st, wait_v, 0) != hipSuccess) return MEFT_ERR_DEVICE;
   if (!out) return launch_status();   // selection only
   if (dense) {
-    launch_tok<ProbTokNC, TokNCSmall>("value_gemm", s, s.d, (uint64_t)n_ent * bsp * 2, (uint64_t)s.N * s.d * 2, (uint64_t)n_ent * s.d * 2, [&](auto& pv) {
+    launch_tok<ProbTokNC, TokNCSmall>("value_gemm", s, s.d, bsp / kTK, (uint64_t)n_ent * bsp * 2, (uint64_t)s.N * s.d * 2, (uint64_t)n_ent * s.d * 2, [&](auto& pv) {
       pv.A = w.Ap; pv.W = vv; pv.sched = sched; pv.bs = s.block_size; pv.bsp = bsp;
       pv.d = s.d; pv.part = w.part; pv.big_only = small_rows_of(s) > 0;
     }, st);
@@ -1160,7 +1228,7 @@ static meft_status bwd_impl(const meft_shape& s, const void* h, const void* K, c
     };
     if (dV_rows.dst && !(small && wait_v) && !dv_to_host()) return MEFT_ERR_DEVICE;
     if (wait_v && hipStreamWaitEvent(st, wait_v, 0) != hipSuccess) return MEFT_ERR_DEVICE;
-    launch_tok<TokKCLarge<kTokMasked>, TokKCSmall<kTokMasked>>("dact_gemm", s, s.block_size, (uint64_t)s.T * s.d * 2, (uint64_t)s.N * s.d * 2, (uint64_t)n_ent * bsp * 2, [&](auto& pg) {
+    launch_tok<TokKCLarge<kTokMasked>, TokKCSmall<kTokMasked>>("dact_gemm", s, s.block_size, s.d / kTK, (uint64_t)s.T * s.d * 2, (uint64_t)s.N * s.d * 2, (uint64_t)n_ent * bsp * 2, [&](auto& pg) {
       pg.X = gg; pg.W = vv; pg.perm = w.perm; pg.tok_of_slot = w.tok_of_slot; pg.sched = sched;
       pg.e = s.top_e; pg.bs = s.block_size; pg.bsp = bsp; pg.d = s.d; pg.Ap = w.Ap; pg.DS = w.DS;
       pg.big_only = big_only;
@@ -1171,7 +1239,7 @@ static meft_status bwd_impl(const meft_shape& s, const void* h, const void* K, c
     }
     if (wait_k && hipStreamWaitEvent(st, wait_k, 0) != hipSuccess) return MEFT_ERR_DEVICE;
     if (dh) {
-      launch_tok<ProbTokNC, TokNCSmall>("dh_gemm", s, s.d, (uint64_t)n_ent * bsp * 2, (uint64_t)s.N * s.d * 2, (uint64_t)n_ent * s.d * 2, [&](auto& ph) {
+      launch_tok<ProbTokNC, TokNCSmall>("dh_gemm", s, s.d, bsp / kTK, (uint64_t)n_ent * bsp * 2, (uint64_t)s.N * s.d * 2, (uint64_t)n_ent * s.d * 2, [&](auto& ph) {
         ph.A = w.DS; ph.W = kk; ph.sched = sched; ph.bs = s.block_size; ph.bsp = bsp;
         ph.d = s.d; ph.part = w.part; ph.big_only = big_only;
       }, st);
@@ -1212,11 +1280,11 @@ static void fill_union_kc(P& p, const meft_shape& s, const UnionGeom& g, const U
 
 static void launch_union_nc(const char* name, const meft_shape& s, const UnionGeom& g, const UnionWs& w, const TokenSched& sched,
                             const uint16_t* A, const void* W, hipStream_t st) {
-  ProbTokNCRows p{};
-  set_gemm_extents(p, (uint64_t)s.T * g.nvb * g.vbs * 2, (uint64_t)s.N * s.d * 2);
-  p.A = A; p.W = static_cast<const uint16_t*>(W); p.tag = w.rowtag; p.sched = sched; p.bs = g.vbs; p.bsp = g.vbs; p.d = s.d;
-  p.part = w.part;
-  launch_gemm_mfma_buf(name, p, tile_bound(g.vs, (s.d + kTN - 1) / kTN), st);
+  launch_tok_buf<ProbTokNCRows>(name, g.vs, s.d, g.vbs / kTK, [&](auto& p) {
+    set_gemm_extents(p, (uint64_t)s.T * g.nvb * g.vbs * 2, (uint64_t)s.N * s.d * 2);
+    p.A = A; p.W = static_cast<const uint16_t*>(W); p.tag = w.rowtag; p.sched = sched; p.bs = g.vbs; p.bsp = g.vbs; p.d = s.d;
+    p.part = w.part;
+  }, st);
 }
 
 // Shared front part of the batch-union forward and backward: index structure from n_S, tile schedule, compacted
@@ -1232,15 +1300,15 @@ static void union_front(const meft_shape& s, const UnionGeom& g, const UnionWs& 
               w.sched_pairs, w.sched_tiles, w.sched_len, 0);
   const TokenSched sched{w.sched_pairs, w.sched_tiles, w.sched_len, sched_cap(g.vs), sched_max_tiles(g.vs)};
   if (direct) {
-    ProbTokKCRows<kTokRelu> pr{};
-    fill_union_kc(pr, s, g, w, sched, h, K, w.Ap, nullptr);
-    launch_gemm_mfma_buf("union_score_gemm", pr, tile_bound(g.vs, (g.vbs + kTN - 1) / kTN), st);
+    launch_tok_buf<ProbTokKCRows<kTokRelu>>("union_score_gemm", g.vs, g.vbs, s.d / kTK, [&](auto& pr) {
+      fill_union_kc(pr, s, g, w, sched, h, K, w.Ap, nullptr);
+    }, st);
     return;
   }
   const int rows_grid = (int)(n_rows < 4096 ? n_rows : 4096);
   MEFT_LAUNCH("gather_rows", gather_rows_kernel, dim3(rows_grid, 2), dim3(256), 0, st, static_cast<const uint16_t*>(K),
               static_cast<const uint16_t*>(V), S, n_S, g.cap, s.N, s.d, g.vbs, w.Kc, w.Vc);
-  launch_tok<TokKCLarge<kTokRelu>, TokKCSmall<kTokRelu>>("union_score_gemm", g.vs, g.vbs, (uint64_t)s.T * s.d * 2, (uint64_t)n_rows * s.d * 2, (uint64_t)s.T * g.nvb * g.vbs * 2, [&](auto& pr) {
+  launch_tok<TokKCLarge<kTokRelu>, TokKCSmall<kTokRelu>>("union_score_gemm", g.vs, g.vbs, s.d / kTK, (uint64_t)s.T * s.d * 2, (uint64_t)n_rows * s.d * 2, (uint64_t)s.T * g.nvb * g.vbs * 2, [&](auto& pr) {
     pr.X = static_cast<const uint16_t*>(h); pr.W = w.Kc; pr.perm = w.perm; pr.tok_of_slot = w.tok_of_slot;
     pr.sched = sched; pr.e = g.nvb; pr.bs = g.vbs; pr.bsp = g.vbs; pr.d = s.d;
     pr.DS = w.Ap;
@@ -1283,7 +1351,7 @@ meft_status meft_union_fwd(const meft_shape* shape, const void* h, const void* K
   union_front(s, g, w, direct, h, K, V, S, n_S, st);
   const TokenSched sched{w.sched_pairs, w.sched_tiles, w.sched_len, sched_cap(g.vs), sched_max_tiles(g.vs)};
   if (direct) launch_union_nc("union_value_gemm", s, g, w, sched, w.Ap, V, st);
-  else launch_tok<ProbTokNC, TokNCSmall>("union_value_gemm", g.vs, s.d, (uint64_t)s.T * g.nvb * g.vbs * 2, (uint64_t)g.nvb * g.vbs * s.d * 2, (uint64_t)s.T * g.nvb * s.d * 2, [&](auto& pv) {
+  else launch_tok<ProbTokNC, TokNCSmall>("union_value_gemm", g.vs, s.d, g.vbs / kTK, (uint64_t)s.T * g.nvb * g.vbs * 2, (uint64_t)g.nvb * g.vbs * s.d * 2, (uint64_t)s.T * g.nvb * s.d * 2, [&](auto& pv) {
     pv.A = w.Ap; pv.W = w.Vc; pv.sched = sched; pv.bs = g.vbs; pv.bsp = g.vbs;
     pv.d = s.d; pv.part = w.part;
   }, st);
@@ -1314,17 +1382,17 @@ meft_status meft_union_bwd(const meft_shape* shape, const void* h, const void* K
   const TokenSched sched{w.sched_pairs, w.sched_tiles, w.sched_len, sched_cap(g.vs), sched_max_tiles(g.vs)};
   const uint16_t *hh = static_cast<const uint16_t*>(h), *gg = static_cast<const uint16_t*>(dOut);
   if (direct) {
-    ProbTokKCRows<kTokMasked> pg{};
-    fill_union_kc(pg, s, g, w, sched, gg, V, w.DS, w.Ap);
-    launch_gemm_mfma_buf("union_dact_gemm", pg, tile_bound(g.vs, (g.vbs + kTN - 1) / kTN), st);
+    launch_tok_buf<ProbTokKCRows<kTokMasked>>("union_dact_gemm", g.vs, g.vbs, s.d / kTK, [&](auto& pg) {
+      fill_union_kc(pg, s, g, w, sched, gg, V, w.DS, w.Ap);
+    }, st);
   } else
-  launch_tok<TokKCLarge<kTokMasked>, TokKCSmall<kTokMasked>>("union_dact_gemm", g.vs, g.vbs, (uint64_t)s.T * s.d * 2, (uint64_t)g.nvb * g.vbs * s.d * 2, (uint64_t)s.T * g.nvb * g.vbs * 2, [&](auto& pg) {
+  launch_tok<TokKCLarge<kTokMasked>, TokKCSmall<kTokMasked>>("union_dact_gemm", g.vs, g.vbs, s.d / kTK, (uint64_t)s.T * s.d * 2, (uint64_t)g.nvb * g.vbs * s.d * 2, (uint64_t)s.T * g.nvb * g.vbs * 2, [&](auto& pg) {
     pg.X = gg; pg.W = w.Vc; pg.perm = w.perm; pg.tok_of_slot = w.tok_of_slot; pg.sched = sched;
     pg.e = g.nvb; pg.bs = g.vbs; pg.bsp = g.vbs; pg.d = s.d; pg.Ap = w.Ap; pg.DS = w.DS;
   }, st);
   if (dh) {
     if (direct) launch_union_nc("union_dh_gemm", s, g, w, sched, w.DS, K, st);
-    else launch_tok<ProbTokNC, TokNCSmall>("union_dh_gemm", g.vs, s.d, (uint64_t)s.T * g.nvb * g.vbs * 2, (uint64_t)g.nvb * g.vbs * s.d * 2, (uint64_t)s.T * g.nvb * s.d * 2, [&](auto& ph) {
+    else launch_tok<ProbTokNC, TokNCSmall>("union_dh_gemm", g.vs, s.d, g.vbs / kTK, (uint64_t)s.T * g.nvb * g.vbs * 2, (uint64_t)g.nvb * g.vbs * s.d * 2, (uint64_t)s.T * g.nvb * s.d * 2, [&](auto& ph) {
       ph.A = w.DS; ph.W = w.Kc; ph.sched = sched; ph.bs = g.vbs; ph.bsp = g.vbs;
       ph.d = s.d; ph.part = w.part;
     }, st);
