@@ -149,6 +149,9 @@ struct ProbTokKC {
     if (n >= bsp) return;   // bsp is even: n + 1 < bsp
     *reinterpret_cast<uint32_t*>(DS + at) = keep(pk, n, mk);
   }
+  // Nontemporal, here and in the other problems' store16: the next kernel reads it, which is larger than L2 or finds it in the
+  // memory-side cache; the lines that L2 keeps are the operands'.  us per step, plain / nontemporal: 8192 tokens, 64 blocks of
+  // 1024 x 4096 2126 / 2078; 1500 tokens, 64 of 512, top 8 708 / 676; 6000, 64 of 512 x 1024 368 / 359.
   // the same for 16 bytes of a row: four columns of fp32, or eight of bf16 (bsp % 64 == 0: all of them inside)
   __device__ u32x4 load_aux16(const TileCoord& tc, int m, int n) const {
     const int mm = m < tc.Mrows ? m : tc.Mrows - 1, nn = n < bsp ? n : bsp - 8;
@@ -157,14 +160,15 @@ struct ProbTokKC {
   __device__ void store16(size_t at, int n, u32x4 v, u32x4 mk) const {
     if constexpr (tok_fp32_out(MODE)) {
       if (n + 4 <= bs) {
-        *reinterpret_cast<u32x4_dw*>(sc + at) = v;   // (rows of an odd length: aligned to four bytes)
+        __builtin_nontemporal_store(v, reinterpret_cast<u32x4_dw*>(sc + at));   // (rows of an odd length: aligned to four bytes)
       } else {
 #pragma unroll
         for (int z = 0; z < 4; ++z)
           if (n + z < bs) sc[at + z] = __uint_as_float(v[z]);
       }
     } else {
-      *reinterpret_cast<u32x4_dw*>(DS + at) = u32x4{keep(v.x, n, mk.x), keep(v.y, n + 2, mk.y), keep(v.z, n + 4, mk.z), keep(v.w, n + 6, mk.w)};
+      const u32x4 kept = {keep(v.x, n, mk.x), keep(v.y, n + 2, mk.y), keep(v.z, n + 4, mk.z), keep(v.w, n + 6, mk.w)};
+      __builtin_nontemporal_store(kept, reinterpret_cast<u32x4_dw*>(DS + at));
     }
   }
   __device__ uint32_t keep(uint32_t pk, int n, uint32_t mk) const {
@@ -225,8 +229,8 @@ struct ProbTokNC {
   __device__ int out_ld(const TileCoord&) const { return d; }
   __device__ size_t row_off(const TileCoord& tc, int, int m) const { return (size_t)(tc.slot0 + m) * d; }
   static constexpr bool kOutBf16 = true;
-  __device__ void store_pk(size_t at, int, uint32_t pk, uint32_t) const { *reinterpret_cast<uint32_t*>(part + at) = pk; }
-  __device__ void store16(size_t at, int, u32x4 v, u32x4) const { *reinterpret_cast<u32x4_dw*>(part + at) = v; }
+  __device__ void store_pk(size_t at, int, uint32_t pk, uint32_t) const { __builtin_nontemporal_store(pk, reinterpret_cast<uint32_t*>(part + at)); }
+  __device__ void store16(size_t at, int, u32x4 v, u32x4) const { __builtin_nontemporal_store(v, reinterpret_cast<u32x4_dw*>(part + at)); }
 };
 
 // Neuron-major, both operands indexed by the contraction index (slot) in their rows:
@@ -284,8 +288,8 @@ struct ProbNeuTN {
   __device__ int out_ld(const TileCoord&) const { return d; }
   __device__ size_t row_off(const TileCoord& tc, int, int m) const { return ((size_t)tc.g * bs + m) * d; }
   static constexpr bool kOutBf16 = true;
-  __device__ void store_pk(size_t at, int, uint32_t pk, uint32_t) const { *reinterpret_cast<uint32_t*>(G + at) = pk; }
-  __device__ void store16(size_t at, int, u32x4 v, u32x4) const { *reinterpret_cast<u32x4_dw*>(G + at) = v; }
+  __device__ void store_pk(size_t at, int, uint32_t pk, uint32_t) const { __builtin_nontemporal_store(pk, reinterpret_cast<uint32_t*>(G + at)); }
+  __device__ void store16(size_t at, int, u32x4 v, u32x4) const { __builtin_nontemporal_store(v, reinterpret_cast<u32x4_dw*>(G + at)); }
 };
 
 // The same with an output row number + 1 in every entry of `flag` (0: not stored): batch-union evaluation, whose compacted
