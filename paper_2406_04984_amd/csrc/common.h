@@ -61,8 +61,12 @@ struct Vec8<float> {
 template <>
 struct Vec8<bf16_t> {
   static constexpr int kBytes = 16;
-  static __device__ __forceinline__ void load(const bf16_t* p, float (&v)[8]) {
-    const u32x4 a = *reinterpret_cast<const u32x4*>(p);
+  static __device__ __forceinline__ void load(const bf16_t* p, float (&v)[8]) { widen(*reinterpret_cast<const u32x4*>(p), v); }
+  // what nobody reads again
+  static __device__ __forceinline__ void load_once(const bf16_t* p, float (&v)[8]) {
+    widen(__builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p)), v);
+  }
+  static __device__ __forceinline__ void widen(u32x4 a, float (&v)[8]) {
     v[0] = __uint_as_float(a.x << 16); v[1] = __uint_as_float(a.x & 0xFFFF0000u);
     v[2] = __uint_as_float(a.y << 16); v[3] = __uint_as_float(a.y & 0xFFFF0000u);
     v[4] = __uint_as_float(a.z << 16); v[5] = __uint_as_float(a.z & 0xFFFF0000u);
