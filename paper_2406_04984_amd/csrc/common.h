@@ -82,7 +82,9 @@ struct Vec8<bf16_t> {
   }
 };
 
-// One 16-byte word of a row as floats.
+// One 16-byte word of a row as floats.  `store` is for finished rows, past L2, which keeps the slices of h and dOut that the
+// per-pair kernels gather from (us per step, plain / nontemporal: 2048 tokens, one block of 65536 x 4096 2865 / 2823; 700 tokens,
+// one of 16384 x 2048 227 / 211); `store_f32` for sums that are read again.
 template <typename T>
 struct Vec16;
 
@@ -94,9 +96,11 @@ struct Vec16<float> {
     for (int i = 0; i < 4; ++i) v[i] = __uint_as_float(a[i]);
   }
   static __device__ __forceinline__ void store(float* p, const float (&v)[4]) {
+    __builtin_nontemporal_store((f32x4{v[0], v[1], v[2], v[3]}), reinterpret_cast<f32x4*>(p));
+  }
+  static __device__ __forceinline__ void store_f32(float* p, const float (&v)[4]) {
     *reinterpret_cast<f32x4*>(p) = f32x4{v[0], v[1], v[2], v[3]};
   }
-  static __device__ __forceinline__ void store_f32(float* p, const float (&v)[4]) { store(p, v); }
 };
 
 template <>
@@ -109,7 +113,10 @@ struct Vec16<bf16_t> {
       v[2 * i + 1] = __uint_as_float(a[i] & 0xFFFF0000u);
     }
   }
-  static __device__ __forceinline__ void store(bf16_t* p, const float (&v)[8]) { Vec8<bf16_t>::store(p, v); }
+  static __device__ __forceinline__ void store(bf16_t* p, const float (&v)[8]) {
+    const u32x4 a = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])};
+    __builtin_nontemporal_store(a, reinterpret_cast<u32x4*>(p));
+  }
   static __device__ __forceinline__ void store_f32(float* p, const float (&v)[8]) { Vec8<float>::store(p, v); }
 };
 
