@@ -229,7 +229,7 @@ struct ProbTokNC {
   __device__ int out_ld(const TileCoord&) const { return d; }
   __device__ size_t row_off(const TileCoord& tc, int, int m) const { return (size_t)(tc.slot0 + m) * d; }
   static constexpr bool kOutBf16 = true;
-  __device__ void store_pk(size_t at, int, uint32_t pk, uint32_t) const { __builtin_nontemporal_store(pk, reinterpret_cast<uint32_t*>(part + at)); }
+  __device__ void store_pk(size_t at, int, uint32_t pk, uint32_t) const { *reinterpret_cast<uint32_t*>(part + at) = pk; }
   __device__ void store16(size_t at, int, u32x4 v, u32x4) const { __builtin_nontemporal_store(v, reinterpret_cast<u32x4_dw*>(part + at)); }
 };
 
@@ -288,7 +288,7 @@ struct ProbNeuTN {
   __device__ int out_ld(const TileCoord&) const { return d; }
   __device__ size_t row_off(const TileCoord& tc, int, int m) const { return ((size_t)tc.g * bs + m) * d; }
   static constexpr bool kOutBf16 = true;
-  __device__ void store_pk(size_t at, int, uint32_t pk, uint32_t) const { __builtin_nontemporal_store(pk, reinterpret_cast<uint32_t*>(G + at)); }
+  __device__ void store_pk(size_t at, int, uint32_t pk, uint32_t) const { *reinterpret_cast<uint32_t*>(G + at) = pk; }
   __device__ void store16(size_t at, int, u32x4 v, u32x4) const { __builtin_nontemporal_store(v, reinterpret_cast<u32x4_dw*>(G + at)); }
 };
 

@@ -174,15 +174,16 @@ __device__ __forceinline__ void token_rows_body(const TokenRows& a, int t, int2*
     if (a.sblk[(size_t)t * a.e + q] < 0) continue;
     const int slot = a.slot_of_ent[(size_t)t * a.e + q];
     if (slot < 0) { small = true; continue; }
-    // (read once: the lines stay out of L2's way, which the next contraction's operands need.  us per pass, before / now: union
-    // of 1023 tokens, 16384 rows x 2048 571 / 549; 2003 tokens, 64 blocks of 96 x 4096, top 8 334 / 324)
+    // (read once.  Rows of up to 4 KB past L2, out of the way of the next contraction's operands: union of 1023 tokens, 16384 rows x
+    // 2048, 620 us per pass / 605; longer ones through it: 2003 tokens x 4096, 8 blocks each, 337 / 352 past it)
     const bf16_t* row = reinterpret_cast<const bf16_t*>(a.part) + (size_t)slot * d;
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
       const int col = (tid + v * nthr) * 8;
       if (col < d) {
         float x[8];
-        Vec8<bf16_t>::load_once(row + col, x);
+        if constexpr (NV == 1) Vec8<bf16_t>::load_once(row + col, x);
+        else Vec8<bf16_t>::load(row + col, x);
 #pragma unroll
         for (int c = 0; c < 8; ++c) acc[v][c] += x[c];
       }
@@ -240,7 +241,7 @@ __device__ __forceinline__ void token_rows_split_body(const TokenRows& a, int t,
     if (slot < 0) { small = true; continue; }
     if ((q & 3) == wave && live) {
       float x[8];
-      Vec8<bf16_t>::load_once(reinterpret_cast<const bf16_t*>(a.part) + (size_t)slot * d + col, x);
+      Vec8<bf16_t>::load(reinterpret_cast<const bf16_t*>(a.part) + (size_t)slot * d + col, x);
 #pragma unroll
       for (int c = 0; c < 8; ++c) acc[c] += x[c];
     }
