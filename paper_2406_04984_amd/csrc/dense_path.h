@@ -334,12 +334,13 @@ struct WideTok : Base {
     if constexpr (Base::kBNC) return Base::d;
     else return Base::bs;
   }
-  __device__ Finder finder(int xcd) const {
+  // (inlined whatever their size: a call would put the policy, the finder and the tile into scratch memory)
+  __device__ __forceinline__ Finder finder(int xcd) const {
     Finder f;
     f.init(Base::sched, xcd, (cols() + kTN - 1) / kTN, Base::big_only != 0);
     return f;
   }
-  __device__ bool locate(Finder& f, int wg, TileCoord& tc) const {
+  __device__ __forceinline__ bool locate(Finder& f, int wg, TileCoord& tc) const {
     int m0, nt;
     if (!f.find(Base::sched, wg >> 3, m0, nt, tc)) return false;
     tc.m0 = m0; tc.n0 = nt * kTN; tc.Ncols = cols();

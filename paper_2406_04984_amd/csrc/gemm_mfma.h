@@ -818,7 +818,8 @@ __device__ __forceinline__ void build_sched_body(int rows, int slot0, int n_grou
   }
   __syncthreads();
   // Fewer non-empty groups than XCDs: a deal of whole groups would leave XCDs idle.  Then every list holds every
-  // group, len[kXcd] says so, and XCD x takes the tiles x, x + 8, ... of each group (TileFinder, GroupFinder).
+  // group, len[kXcd] says so, and XCD x takes the tiles x, x + 8, ... of each group (TileFinder, GroupFinder) or a consecutive
+  // part of all of them (WideFinder).
   const bool split = n_full < kXcd;
   if (tid == 0) len[kXcd] = split ? 1 : 0;
   if (split) {

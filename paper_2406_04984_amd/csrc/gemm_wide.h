@@ -23,6 +23,7 @@
 // whole ones in each XCD's order, so that the last round is one of short tiles.
 #pragma once
 #include "gemm_mfma.h"
+#include "tile_share.h"
 
 namespace meft {
 
@@ -33,19 +34,19 @@ constexpr int kWideTurn = 4096;                         // a wave's piece of the
 constexpr int kWideLds = 2 * kWideStage + 4 * 2 * kWideTurn;
 
 // Where the tiles of one XCD lie: of up to 63 groups at a time the whole tiles (256 rows, more than 128 of them the group's) first,
-// then the short ones (a group's last rows, at most 128).  Inside a group the m tiles vary fastest.
+// then the short ones (a group's last rows, at most 128).  Inside a group the m tiles vary fastest.  Lists that every XCD holds
+// (fewer groups than XCDs) are numbered through and dealt in consecutive parts (tile_share.h), the short tiles from the other end:
+// an XCD with one whole tile more than others then has none of the short ones left over.
 struct WideFinder {
   int g, slot0, rows;            // lane: group, its first slot, its rows
-  int nf, cf, ch;                // lane: whole m tiles; whole and short tiles before the entry
+  int nf, cf, ch;                // lane: whole m tiles; whole and short tiles before the entry, from this XCD's first one on
   uint32_t inv;                  // what tile_div divides by nf with
-  int b, n, x, base, all_f, all_h;
-  int tn;                        // n tiles of a group that are this XCD's (split lists: x, x + 8, ...)
+  int b, n, x, base, tn, all_f, all_h;
   bool split;
   __device__ __forceinline__ void init(const TokenSched& s, int xcd, int n_tiles_n, bool big_only) {
-    x = xcd; b = 0; base = 0;
+    x = xcd; b = 0; base = 0; tn = n_tiles_n;
     n = as_const(s.len)[big_only ? kXcd + 1 + x : x];
     split = as_const(s.len)[kXcd] != 0;
-    tn = !split ? n_tiles_n : n_tiles_n > x ? (n_tiles_n - x + kXcd - 1) / kXcd : 0;
     load(s);
   }
   __device__ __forceinline__ int live() const {
@@ -64,6 +65,12 @@ struct WideFinder {
     all_f = __builtin_amdgcn_readlane(cf, 63);
     all_h = __builtin_amdgcn_readlane(ch, 63);
     cf -= f; ch -= h;
+    if (split) {
+      const int at_f = tile_share_first(all_f, x), at_h = tile_share_first(all_h, kXcd - 1 - x);
+      all_f = tile_share_first(all_f, x + 1) - at_f;
+      all_h = tile_share_first(all_h, kXcd - x) - at_h;
+      cf -= at_f; ch -= at_h;
+    }
   }
   // tile number `local` of the XCD: its first row, its n tile, and tc.g, tc.slot0, tc.aux = tc.Mrows = the group's rows;
   // false: there is none
@@ -87,7 +94,6 @@ struct WideFinder {
     nt = whole ? tile_div(w, max(f, 1), (uint32_t)__builtin_amdgcn_readlane((int)inv, i)) : w;
     m0 = (whole ? w - nt * f : f) * kWideM;
     tc.Mrows = tc.aux;
-    if (split) nt = x + kXcd * nt;
     return true;
   }
 };

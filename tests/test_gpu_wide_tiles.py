@@ -2,7 +2,7 @@
 meft_debug_global_loads forces: the same products in the same order): groups that end in a short tile of one row, of 128 rows,
 one row before and after it becomes a whole one, a few rows more than a whole one; blocks and hidden sizes that leave columns of a
 tile empty; one to a few k tiles (fewer than are requested ahead) in the weight gradients; fewer groups than XCDs, more than
-a tile search holds in registers."""
+a tile search holds in registers.  SPLIT: fewer columns of tiles than XCDs, whose tiles all XCDs have to share."""
 import numpy as np
 import pytest
 
@@ -10,6 +10,11 @@ from paper_2406_04984_amd import synth
 
 pytestmark = pytest.mark.gpu
 
+SPLIT = [   # every XCD's list holds every group
+    dict(T=4096, d=1024, n_blocks=6, block_size=1024, top_e=3, top_k=256),    # four columns of tiles both ways
+    dict(T=4100, d=1792, n_blocks=5, block_size=1792, top_e=2, top_k=100),    # seven
+    dict(T=8100, d=512, n_blocks=4, block_size=512, top_e=2, top_k=128),      # two
+]
 CASES = [
     dict(T=97, d=512, n_blocks=16, block_size=1000, top_e=16, top_k=260),     # short tiles only, columns beyond the block
     dict(T=128, d=576, n_blocks=16, block_size=1024, top_e=16, top_k=260),    # short tiles full to the last row
@@ -20,7 +25,7 @@ CASES = [
     dict(T=2600, d=512, n_blocks=64, block_size=512, top_e=3, top_k=60, zipf_s=0.4),   # groups of every size
     dict(T=30000, d=512, n_blocks=600, block_size=64, top_e=3, top_k=12),     # 75 groups per XCD
     dict(T=70, d=320, n_blocks=9, block_size=200, top_e=2, top_k=24),         # weight gradients of one k tile
-]
+] + SPLIT
 NAMES = ("idx", "act", "out", "dh", "dK_bits", "dV_bits", "touched")
 
 

@@ -7,6 +7,7 @@ from tests.test_gpu_not_finite import PAIRS
 from tests.test_gpu_pair_rows import ONE_KERNEL, TWO_KERNELS
 from tests.test_gpu_select_bound import CASES
 from tests.test_gpu_union_rows import GATHERED, SMALL
+from tests.test_gpu_wide_tiles import SPLIT
 
 
 def _names(calls, flags=0, **kw):
@@ -63,3 +64,9 @@ def test_rows_of_the_batch_union(call):
         for T, d, N, _, k in cases:
             names = _names([call], T=T, d=d, n_blocks=1, block_size=N, top_e=1, top_k=k, dtype="bf16")
             assert _has(names, "gather_rows") != gathered and _has(names, "NCRows") == gathered, (T, d, N, k, names)
+
+
+def test_lists_that_every_xcd_holds_on_tiles_of_256_rows():
+    for kw in SPLIT:
+        wide = [n for n in _names(["fwd", "bwd"], dtype="bf16", **kw) if _has([n], "gemm_wide_kernel")]
+        assert kw["n_blocks"] < 8 and all(_has(wide, p) for p in ("ProbTokKCILi3E", "ProbTokKCILi1E", "ProbTokNC")), (kw, wide)
