@@ -102,13 +102,17 @@ struct WideFinder {
 // as soon as one step of the loop looks so.
 __device__ __forceinline__ int same(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
-// One 16-byte-per-lane load into LDS at `lds` + `at` (a literal) (a wave's lanes fill 1 KB in order).  The wait states are those of M0 (one)
-// and of scalar registers that a vector instruction has written (five), which the compiler does not look for inside an asm block.
+// One 16-byte-per-lane load into LDS at `lds` + `at` (a literal) (a wave's lanes fill 1 KB in order).  The wait states before it are
+// those of M0 (one) and of scalar registers that a vector instruction has written (five: rsrc and soff may come by v_readlane),
+// which the compiler does not look for inside an asm block: s_add_i32 is one, s_nop 3 four.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"   // (M0 is reserved: nothing of the compiler's outlives a statement in it)
 __device__ __forceinline__ void wide_load(i32x4 rsrc, uint32_t voff, int soff, int lds, int at) {
-  asm volatile("s_add_i32 m0, %3, %4\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds" ::"v"(voff), "s"(rsrc), "s"(same(soff)),
+  asm volatile("s_add_i32 m0, %3, %4\n\ts_nop 3\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds" ::"v"(voff), "s"(rsrc), "s"(same(soff)),
                "s"(same(lds)), "i"(at)
                : "m0", "scc");
 }
+#pragma clang diagnostic pop
 
 // A policy is one of gemm_mfma_kernel's, or one with kTM == kWideM, whose locate() deals in tiles of 256 rows; the operands are
 // within reach of buffer loads.
