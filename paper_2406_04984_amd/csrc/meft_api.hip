@@ -724,30 +724,63 @@ bool small_tiles(const meft_shape& s, int cols) {
 // than of 128 (gemm_mfma_kernel), by what one compute unit takes for a k tile and for a tile, in hundredths of a whole tile's k
 // tile (1.7-2.4 us): 256 rows 100 and 150, the short tile at the end of a group 74 and 120 (its columns' lines are nobody else's by then),
 // 128 rows 56 and 50.  Whole tiles come first and short ones fill up their last round (WideFinder).  Groups are taken
-// to lie within 30 % of their average, as the router's do.  At d 4096 with 64 blocks of 1024, us for the activation gradient on 128 /
-// 256 rows: 512 rows a group 344 / 331, 256 rows 236 / 267 (half of the groups a few rows too long), 192 rows 213 / 195.
-// Groups of fewer than 224 rows are bound by the block's rows out of HBM, which fewer and deeper requests bring faster (4096
-// tokens x 8 of 256 blocks 606 / 488), down to 96 rows, where both read them at the same rate (64: 183 / 186) and most
-// tiles would be short; contractions of a few k tiles not (4 k tiles, 128 rows: 15.0 / 16.7).
+// to lie within 30 % of their average, as the router's do, or to be alike where every token is in every block.  us on 128 / 256
+// rows: 64 blocks of 1024 x 4096, activation gradient at 512 rows a group 316 / 294, at 256 rows 203 / 222 (half of the groups a few
+// rows too long); 64 blocks of 512 x 1024, scores at 96 to 192 rows 22 / 29 (two columns of tiles: 128 whole tiles leave half of the
+// compute units idle); one block of 9984 x 3264, 138 tokens 40 / 64, of 34560 x 2560 83 / 58.
+// Between one and four groups per XCD the XCD with one more counts: union of 879 tokens over 10 x 1024, 1344 columns 48 / 59; 18 blocks
+// of 816, 444 rows a group, 1472 columns 38 / 41.
+// Over 330 contractions of random layers and unions this takes 3 % longer than the better form of each would, 128 rows always 7 %.
+//
+// Groups of fewer than 224 rows, but enough tiles for every compute unit, are bound by the block's rows out of HBM, which fewer
+// and deeper requests bring faster: 256 columns' rows of 32 k tiles and more (64 blocks of 1024 x 4096, scores at 128 rows 154 / 136),
+// or four rounds of tiles, whose last one is a small part (256 unbalanced blocks of 1024 x 4096, values 550 / 440).  With fewer
+// tiles of fewer k tiles the rounds decide here too (28 blocks of 864 x 2688 at 104 rows, values 38 / 44).
 bool wide_tiles(const meft_shape& s, int cols, int nk) {
   const int64_t n_ent = (int64_t)s.T * s.top_e, groups = s.n_blocks < n_ent ? s.n_blocks : n_ent, rows = n_ent / groups;
   if (rows < 96) return false;
-  if (rows < 224) return nk >= 8;
-  int64_t whole = 0, shorts = 0, tiles128 = 0;
-  for (int z = 7; z <= 13; ++z) {
-    const int64_t r = s.top_e == s.n_blocks ? rows : rows * z / 10, f = (r + 127) / 256;
-    whole += f;
-    shorts += r > f * kWideM ? 1 : 0;
-    tiles128 += (r + 127) / 128;
+  const int64_t tn = (cols + kTN - 1) / kTN, per = groups * tn;
+  if (rows < 224 && (per >= 4 * kPersistentWgs || (per >= kPersistentWgs && nk >= 32))) return nk >= 8;
+  struct Tiles {
+    int64_t whole, shorts, of128;   // of one XCD
+    void add(int64_t r, int64_t n) {
+      const int64_t f = (r + 127) / 256;
+      whole += f * n;
+      shorts += r > f * kWideM ? n : 0;
+      of128 += (r + 127) / 128 * n;
+    }
+  };
+  int64_t cost_wide = 0, cost_128 = 0;
+  auto count = [&](const Tiles& t) {   // an XCD has 32 compute units
+    const int64_t cu = kPersistentWgs / kXcd, rounds = (t.whole + cu - 1) / cu, room = rounds * cu - t.whole;
+    const int64_t late = t.shorts > room ? t.shorts - room : 0;
+    const int64_t wide = rounds * (nk * 100 + 150) + (late + cu - 1) / cu * (nk * 74 + 120);
+    const int64_t small = (t.of128 + cu - 1) / cu * (nk * 56 + 50);
+    cost_wide = wide > cost_wide ? wide : cost_wide;
+    cost_128 = small > cost_128 ? small : cost_128;
+  };
+  Tiles t{};
+  if (s.top_e == s.n_blocks) {
+    const int64_t by = groups > kXcd ? 1 : kXcd;   // whole groups, or tiles of each
+    t.add(rows, groups > kXcd ? (groups + kXcd - 1) / kXcd * tn : per);
+    count({(t.whole + by - 1) / by, (t.shorts + by - 1) / by, (t.of128 + by - 1) / by});
+  } else if (groups > kXcd && groups < 4 * kXcd && groups % kXcd != 0) {   // dealt longest first (build_sched_body)
+    int64_t load[kXcd] = {};
+    Tiles x[kXcd] = {};
+    for (int64_t i = 0; i < groups; ++i) {
+      const int64_t r = rows * (130 - 60 * i / (groups - 1)) / 100;
+      int k = 0;
+      for (int j = 1; j < kXcd; ++j) k = load[j] < load[k] ? j : k;
+      load[k] += (r + 63) / 64 + 2;
+      x[k].add(r, tn);
+    }
+    for (const Tiles& one : x) count(one);
+  } else {
+    const int64_t by = 7 * kXcd;
+    for (int z = 7; z <= 13; ++z) t.add(rows * z / 10, per);
+    count({(t.whole + by - 1) / by, (t.shorts + by - 1) / by, (t.of128 + by - 1) / by});
   }
-  // of one of the eight XCDs' 32 compute units each
-  const int64_t per = groups * ((cols + kTN - 1) / kTN), cu = kPersistentWgs / kXcd, by = 7 * kXcd;
-  whole = (whole * per + by - 1) / by;
-  shorts = (shorts * per + by - 1) / by;
-  tiles128 = (tiles128 * per + by - 1) / by;
-  const int64_t rounds = (whole + cu - 1) / cu, room = rounds * cu - whole, late = shorts > room ? shorts - room : 0;
-  const int64_t cost_wide = rounds * (nk * 100 + 150) + (late + cu - 1) / cu * (nk * 74 + 120);
-  return cost_wide <= (tiles128 + cu - 1) / cu * (nk * 56 + 50);
+  return cost_wide <= cost_128;
 }
 
 // Launches a token-major policy that exists with buffer loads only, with the tiles that suit the problem.

@@ -70,3 +70,24 @@ def test_lists_that_every_xcd_holds_on_tiles_of_256_rows():
     for kw in SPLIT:
         wide = [n for n in _names(["fwd", "bwd"], dtype="bf16", **kw) if _has([n], "gemm_wide_kernel")]
         assert kw["n_blocks"] < 8 and all(_has(wide, p) for p in ("ProbTokKCILi3E", "ProbTokKCILi1E", "ProbTokNC")), (kw, wide)
+
+
+# Forms of a token-major contraction, where the rounds of tiles decide: (call, shape, policy, on tiles of 256 rows?)
+TOKEN_TILES = [
+    ("fwd", dict(T=2048, d=1024, n_blocks=64, block_size=512, top_e=4, top_k=128), "ProbTokKCILi3E", False),
+    ("fwd", dict(T=2048, d=4096, n_blocks=64, block_size=1024, top_e=4, top_k=256), "ProbTokKCILi3E", True),
+    ("fwd", dict(T=8192, d=4096, n_blocks=64, block_size=1024, top_e=4, top_k=256), "ProbTokNC", True),
+    ("fwd", dict(T=4096, d=4096, n_blocks=256, block_size=1024, top_e=8, top_k=512), "ProbTokNC", True),
+    ("fwd", dict(T=2928, d=2688, n_blocks=28, block_size=864, top_e=1, top_k=200), "ProbTokNC", False),
+    ("fwd", dict(T=8008, d=1472, n_blocks=18, block_size=816, top_e=1, top_k=100), "ProbTokNC", False),
+    ("fwd", dict(T=138, d=3264, n_blocks=1, block_size=9984, top_e=1, top_k=100), "ProbTokKCILi0E", False),
+    ("fwd", dict(T=137, d=2560, n_blocks=1, block_size=34560, top_e=1, top_k=100), "ProbTokKCILi0E", True),
+    ("union_fwd", dict(T=879, d=1344, n_blocks=1, block_size=10240, top_e=1, top_k=64), "ProbTokNCRows", False),
+    ("union_fwd", dict(T=1023, d=2048, n_blocks=32, block_size=512, top_e=4, top_k=128), "ProbTokNCRows", True),
+]
+
+
+@pytest.mark.parametrize("call, kw, policy, wide", TOKEN_TILES, ids=lambda v: f"T{v['T']}_d{v['d']}" if isinstance(v, dict) else str(v))
+def test_rows_of_a_token_major_tile(call, kw, policy, wide):
+    names = [n for n in _names([call], dtype="bf16", **kw) if _has([n], policy)]
+    assert len(names) == 1 and _has(names, "gemm_wide_kernel" if wide else "gemm_mfma_kernel"), names
