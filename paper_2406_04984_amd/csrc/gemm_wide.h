@@ -102,13 +102,15 @@ struct WideFinder {
 // as soon as one step of the loop looks so.
 __device__ __forceinline__ int same(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
-// One 16-byte-per-lane load into LDS at `lds` + `at` (a literal) (a wave's lanes fill 1 KB in order).  The wait states before it are
-// those of M0 (one) and of scalar registers that a vector instruction has written (five: rsrc and soff may come by v_readlane),
-// which the compiler does not look for inside an asm block: s_add_i32 is one, s_nop 3 four.
+// One 16-byte-per-lane load into LDS at `lds` + `at` (a literal) (a wave's lanes fill 1 KB in order).  M0 wants one wait state before
+// the load, and it has it.  A scalar register that a vector instruction has written (v_readlane of a spilled descriptor, say) wants
+// five, which the compiler does not look for in front of an asm block.  They are not in here: sixteen loads per k tile with
+// three states more each cost the weight gradients 3 to 5 % (17 blocks of 928 x 1088 85.6 / 90.0 us, step of 8192 tokens, 64 blocks of
+// 1024 x 4096 2041 / 2072).  tests/test_wait_states.py reads every such load of the built library instead.
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"   // (M0 is reserved: nothing of the compiler's outlives a statement in it)
 __device__ __forceinline__ void wide_load(i32x4 rsrc, uint32_t voff, int soff, int lds, int at) {
-  asm volatile("s_add_i32 m0, %3, %4\n\ts_nop 3\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds" ::"v"(voff), "s"(rsrc), "s"(same(soff)),
+  asm volatile("s_add_i32 m0, %3, %4\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds" ::"v"(voff), "s"(rsrc), "s"(same(soff)),
                "s"(same(lds)), "i"(at)
                : "m0", "scc");
 }
