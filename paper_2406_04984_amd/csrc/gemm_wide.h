@@ -42,12 +42,16 @@ struct WideFinder {
   int nf, cf, ch;                // lane: whole m tiles; whole and short tiles before the entry, from this XCD's first one on
   uint32_t inv;                  // what tile_div divides by nf with
   int b, n, x, base, tn, all_f, all_h;
-  bool split;
   __device__ __forceinline__ void init(const TokenSched& s, int xcd, int n_tiles_n, bool big_only) {
     x = xcd; b = 0; base = 0; tn = n_tiles_n;
     n = as_const(s.len)[big_only ? kXcd + 1 + x : x];
-    split = as_const(s.len)[kXcd] != 0;
     load(s);
+    if (as_const(s.len)[kXcd] != 0) {   // every XCD's list is this one: at most seven groups, loaded once
+      const int at_f = tile_share_first(all_f, x), at_h = tile_share_first(all_h, kXcd - 1 - x);
+      all_f = tile_share_first(all_f, x + 1) - at_f;
+      all_h = tile_share_first(all_h, kXcd - x) - at_h;
+      cf -= at_f; ch -= at_h;
+    }
   }
   __device__ __forceinline__ int live() const {
     const int lane = threadIdx.x & 63;
@@ -65,12 +69,6 @@ struct WideFinder {
     all_f = __builtin_amdgcn_readlane(cf, 63);
     all_h = __builtin_amdgcn_readlane(ch, 63);
     cf -= f; ch -= h;
-    if (split) {
-      const int at_f = tile_share_first(all_f, x), at_h = tile_share_first(all_h, kXcd - 1 - x);
-      all_f = tile_share_first(all_f, x + 1) - at_f;
-      all_h = tile_share_first(all_h, kXcd - x) - at_h;
-      cf -= at_f; ch -= at_h;
-    }
   }
   // tile number `local` of the XCD: its first row, its n tile, and tc.g, tc.slot0, tc.aux = tc.Mrows = the group's rows;
   // false: there is none
