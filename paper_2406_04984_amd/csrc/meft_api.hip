@@ -927,10 +927,25 @@ bool dvdk_beside_rows(const meft_shape& s) {
 
 // The tokens' rows of out (W = V, coef = act) or dh (W = K, coef = ds) from the entries' partial rows and the pairs of
 // the small groups; `dv`: the dV / dK work of the small groups, or none.
+// Whether token_rows reads its partial rows, each of them once, past L2, out of the way of the next contraction's operands, by the
+// bytes of all partial rows.  us per pass through / past L2.
+//   From 60 MB on past it: 7757 tokens, 8 of 41 blocks of 144 x 1856 (230 MB) 936 / 889; 1289 tokens, 7 of 67 blocks of 416 x 5056
+// (91 MB) 711 / 671; 4079 tokens, 8 of 29 blocks of 224 x 2048 (134 MB) 406 / 388; unions within 1 %.  But where a contraction of
+// up to three k tiles has just written 60 to 190 MB, the reads that go through L2 are the faster ones by more than the contractions
+// gain: 2003 tokens, 8 of 64 blocks of 96 x 4096 (131 MB) 328 / 339; 4666 tokens, 6 of 230 blocks of 96 x 1664 (93 MB) 350 / 364
+// (more of the same: 4000 x 4096, 262 MB 600 / 594).
+//   Below, rows of up to 4 KB: 5823 tokens, 4 of 19 blocks of 912 x 704 (33 MB) 474 / 463; 777 tokens, 4 of 64 blocks of 1024 x 4096
+// (25 MB) 281 / 283.
+bool rows_past_l2(const meft_shape& s) {
+  const int64_t bytes = (int64_t)s.T * s.top_e * s.d * 2;
+  if (bytes < (60ll << 20)) return s.d <= 2048;
+  return bytes > (190ll << 20) || s.block_size > 3 * kTK;
+}
+
 void launch_token_rows(const char* name, const meft_shape& s, const uint16_t* part, const DispatchWs& w, const void* W,
                        const int32_t* idx, const float* coef, void* out, const SmallDvdk& dv, hipStream_t st) {
   const TokenRows a{part, w.sblk, w.slot_of_ent, idx, coef, static_cast<const bf16_t*>(W), s.d, s.top_e, s.top_k, s.N,
-                    s.block_size, static_cast<bf16_t*>(out)};
+                    s.block_size, static_cast<bf16_t*>(out), rows_past_l2(s)};
   const size_t lds = small_rows_of(s) ? (size_t)(s.top_k < kTokenRowsPairs ? s.top_k : kTokenRowsPairs) * sizeof(int2) : 0;
   const int chunks = (s.d + kSmallCols - 1) / kSmallCols;
   if (rows_split(s)) {

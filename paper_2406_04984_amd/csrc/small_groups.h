@@ -122,6 +122,7 @@ struct TokenRows {
   const bf16_t* W;
   int d, e, k, N, bs;
   bf16_t* out;
+  bool past_l2;   // how the partial rows are read (rows_past_l2)
 };
 
 // the token's blocks whose groups are small, into s_blk
@@ -170,25 +171,27 @@ __device__ __forceinline__ void token_rows_body(const TokenRows& a, int t, int2*
 #pragma unroll
     for (int c = 0; c < 8; ++c) acc[v][c] = 0.f;
   bool small = false;
-  for (int q = 0; q < a.e; ++q) {
-    if (a.sblk[(size_t)t * a.e + q] < 0) continue;
-    const int slot = a.slot_of_ent[(size_t)t * a.e + q];
-    if (slot < 0) { small = true; continue; }
-    // (read once.  Rows of up to 4 KB past L2, out of the way of the next contraction's operands: union of 1023 tokens, 16384 rows x
-    // 2048, 620 us per pass / 605; longer ones through it: 2003 tokens x 4096, 8 blocks each, 337 / 352 past it)
-    const bf16_t* row = reinterpret_cast<const bf16_t*>(a.part) + (size_t)slot * d;
+  auto sum_partial = [&](auto past_l2) {
+    for (int q = 0; q < a.e; ++q) {
+      if (a.sblk[(size_t)t * a.e + q] < 0) continue;
+      const int slot = a.slot_of_ent[(size_t)t * a.e + q];
+      if (slot < 0) { small = true; continue; }
+      const bf16_t* row = reinterpret_cast<const bf16_t*>(a.part) + (size_t)slot * d;
 #pragma unroll
-    for (int v = 0; v < NV; ++v) {
-      const int col = (tid + v * nthr) * 8;
-      if (col < d) {
-        float x[8];
-        if constexpr (NV == 1) Vec8<bf16_t>::load_once(row + col, x);
-        else Vec8<bf16_t>::load(row + col, x);
+      for (int v = 0; v < NV; ++v) {
+        const int col = (tid + v * nthr) * 8;
+        if (col < d) {
+          float x[8];
+          if constexpr (decltype(past_l2)::value) Vec8<bf16_t>::load_once(row + col, x);
+          else Vec8<bf16_t>::load(row + col, x);
 #pragma unroll
-        for (int c = 0; c < 8; ++c) acc[v][c] += x[c];
+          for (int c = 0; c < 8; ++c) acc[v][c] += x[c];
+        }
       }
     }
-  }
+  };
+  if (a.past_l2) sum_partial(std::true_type{});
+  else sum_partial(std::false_type{});
   if (small) {   // the same in every thread
     collect_small_blocks(a, t, s_blk);
     constexpr int U = NV == 1 ? 16 : NV == 2 ? 8 : NV == 4 ? 4 : 2;   // rows in flight
