@@ -780,7 +780,7 @@ bool wide_tiles(const meft_shape& s, int cols, int nk) {
     for (int z = 7; z <= 13; ++z) t.add(rows * z / 10, per);
     count({(t.whole + by - 1) / by, (t.shorts + by - 1) / by, (t.of128 + by - 1) / by});
   }
-  return cost_wide <= cost_128;
+  return cost_wide * 101 <= cost_128 * 100;   // (a tie: 28 blocks of 896 at 268 rows, 4992 columns 102 / 115)
 }
 
 // Launches a token-major policy that exists with buffer loads only, with the tiles that suit the problem.

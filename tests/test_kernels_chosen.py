@@ -80,6 +80,7 @@ TOKEN_TILES = [
     ("fwd", dict(T=4096, d=4096, n_blocks=256, block_size=1024, top_e=8, top_k=512), "ProbTokNC", True),
     ("fwd", dict(T=2928, d=2688, n_blocks=28, block_size=864, top_e=1, top_k=200), "ProbTokNC", False),
     ("fwd", dict(T=8008, d=1472, n_blocks=18, block_size=816, top_e=1, top_k=100), "ProbTokNC", False),
+    ("fwd", dict(T=2501, d=4992, n_blocks=28, block_size=896, top_e=3, top_k=99), "ProbTokNC", False),
     ("fwd", dict(T=138, d=3264, n_blocks=1, block_size=9984, top_e=1, top_k=100), "ProbTokKCILi0E", False),
     ("fwd", dict(T=137, d=2560, n_blocks=1, block_size=34560, top_e=1, top_k=100), "ProbTokKCILi0E", True),
     ("union_fwd", dict(T=879, d=1344, n_blocks=1, block_size=10240, top_e=1, top_k=64), "ProbTokNCRows", False),
