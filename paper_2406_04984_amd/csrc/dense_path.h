@@ -240,7 +240,7 @@ struct ProbTokNC {
 // come from a row of zeros that the workspace keeps in front of the activation matrices, those of X are any valid
 // rows.  Only rows whose neuron is touched are written.
 // TM = 256: for gemm_wide_kernel; TM = 128: 128 x 256 with four compute and four loader waves (measured: 0.425 -> 0.388 ms (dV)
-// against two).  The host takes the larger tile where it does not add rows beyond the block (neu_tile_rows).
+// against two).  The host takes the tile that suits the problem (wide_neu).
 template <int TM>
 struct ProbNeuTN {
   static constexpr int kTM = TM, kSA = 3, kSB = 3, kCW = 4;

@@ -977,9 +977,31 @@ void launch_bwd_head(const meft_shape& s, const int32_t* flag, int32_t* chunk_cn
               w ? w->tok_of_slot : nullptr, s.d, s.top_k, s.block_size, w ? w->ds32 : nullptr);
 }
 
-// Tile rows of the dV / dK contractions: 256 (gemm_wide_kernel) where that computes no more padded rows of the block than 128 would
-int neu_tile_rows(int block_rows) {
-  return (block_rows + 255) / 256 * 256 == (block_rows + 127) / 128 * 128 ? 256 : 128;
+// Whether the dV / dK contractions of s's groups run on tiles of 256 rows (gemm_wide_kernel) rather than of 128 (gemm_mfma_kernel):
+// where that computes no more padded rows of the block, and by what an XCD's 32 compute units take for a k tile (64 tokens) and for a
+// tile, as in wide_tiles: 256 rows 100 and 150, 128 rows 56 and 54, or 72 where most compute units have a tile of 256 rows and 40
+// tokens or more for it (then both wait for the stores of the rows).  Every group has the same tiles.  us per launch on 128 / 256 rows:
+// 64 blocks of 1024 x 4096, 512 tokens each 355 / 320; 256 unbalanced ones, 128 each on average 314 / 303; 64 blocks of 256 x 1024, 128
+// each 15.3 / 14.6; 72 blocks of 144 x 640, 21 each 7.8 / 9.4 (a tile's end takes longer than its k tile); 15 blocks of 1024 x 1280, 168
+// each 19 / 22; one block of 960 x 1216, 1328 tokens 19 / 33 (20 tiles of 256 rows).  Over 149 contractions of random layers and unions
+// this takes 3 % longer than the better form of each would, 256 rows always 30 %.
+//   Gradients of 96 MB and more go to 256 rows, whose stores pass the caches by: those of the 128 rows push K and V out of the
+// memory-side cache, from where the other contractions read them.  us per pass on 128 / 256 rows: 388 tokens, 4 of 120 blocks of 208 x
+// 4288 (214 MB) 418 / 381, of which dV and dK 104 / 111; 3579 tokens, 3 of 220 blocks of 224 x 3584 (353 MB) 710 / 645; 451 tokens, 6 of
+// 237 blocks of 208 x 1280 (126 MB) 265 / 245; 1437 tokens, 8 of 101 blocks of 720 x 576 (84 MB) 353 / 387.  Groups of up to four tokens
+// are summed pair by pair but for a few, and nothing is found sooner by fewer waves (70 blocks, one token each 3.8 / 2.2 per launch).
+bool wide_neu(const meft_shape& s) {
+  const int64_t n_ent = (int64_t)s.T * s.top_e, groups = s.n_blocks < n_ent ? s.n_blocks : n_ent, rows = n_ent / groups;
+  const int64_t tm256 = (s.block_size + 255) / 256, tm128 = (s.block_size + 127) / 128;
+  if (2 * tm256 != tm128) return false;
+  if (rows <= 4 || (int64_t)s.N * s.d * 2 >= (96ll << 20)) return true;
+  const int64_t nk = (rows + kTK - 1) / kTK, tn = (s.d + kTN - 1) / kTN, cu = kPersistentWgs / kXcd;
+  auto rounds = [&](int64_t tm) {   // lists of fewer groups than XCDs: each XCD takes a part of every group's tiles
+    const int64_t tiles = groups < kXcd ? (groups * tm * tn + kXcd - 1) / kXcd : (groups + kXcd - 1) / kXcd * tm * tn;
+    return (tiles + cu - 1) / cu;
+  };
+  const bool stores = 4 * groups * tm256 * tn >= 3 * kPersistentWgs && rows >= 40;
+  return rounds(tm256) * (nk * 100 + 150) <= rounds(tm128) * (nk * 56 + (stores ? 72 : 54));
 }
 
 // One weight-gradient contraction (dV: A = A', X = dOut; dK: A = DS', X = h) over the groups of a tile schedule
@@ -988,6 +1010,7 @@ struct NeuArgs {
   const int32_t *tok_of_slot, *flag;
   TokenSched sched;
   int big_only, n_groups, bs, bsp, d;
+  bool wide;
   uint64_t a_bytes, x_bytes;   // bytes readable from the lowest address of either operand
 };
 
@@ -1007,7 +1030,7 @@ void launch_neu(const char* name, const NeuArgs& a, hipStream_t st) {
     else launch_gemm_mfma(name, pn, bound, st);
     return true;
   };
-  if (neu_tile_rows(a.bs) == 256 && launch(P<256>{})) return;
+  if (a.wide && launch(P<256>{})) return;
   launch(P<128>{});
 }
 
@@ -1246,6 +1269,7 @@ static meft_status bwd_impl(const meft_shape& s, const void* h, const void* K, c
     NeuArgs pn{};
     pn.tok_of_slot = w.tok_of_slot; pn.flag = w.flag;
     pn.sched = sched; pn.big_only = big_only; pn.n_groups = s.n_blocks; pn.bs = s.block_size; pn.bsp = bsp; pn.d = s.d;
+    pn.wide = wide_neu(s);
     pn.a_bytes = (uint64_t)(1 + 2 * (uint64_t)n_ent) * bsp * 2; pn.x_bytes = (uint64_t)s.T * s.d * 2;
     // dV first: it needs neither K nor V (so it also runs while host-resident K, V are still on their way), and it
     // gathers the same dOut rows as the activation-gradient GEMM that follows it
@@ -1449,6 +1473,7 @@ meft_status meft_union_bwd(const meft_shape* shape, const void* h, const void* K
   NeuArgs pn{};
   pn.tok_of_slot = w.tok_of_slot; pn.flag = w.rowtag;
   pn.sched = sched; pn.big_only = 0; pn.n_groups = g.nvb; pn.bs = g.vbs; pn.bsp = g.vbs; pn.d = s.d;
+  pn.wide = wide_neu(g.vs);
   pn.a_bytes = (1 + 2 * (uint64_t)s.T * g.nvb) * g.vbs * 2; pn.x_bytes = (uint64_t)s.T * s.d * 2;
   // written to the rows of S directly: a pass over compacted gradients took 2 x 24 us at 16384 rows x 2048
   pn.A = w.Ap; pn.zrow = -1; pn.X = gg; pn.G = static_cast<uint16_t*>(dV);

@@ -92,3 +92,21 @@ TOKEN_TILES = [
 def test_rows_of_a_token_major_tile(call, kw, policy, wide):
     names = [n for n in _names([call], dtype="bf16", **kw) if _has([n], policy)]
     assert len(names) == 1 and _has(names, "gemm_wide_kernel" if wide else "gemm_mfma_kernel"), names
+
+
+# The same of the weight gradients: (shape, on tiles of 256 rows?)
+GRADIENT_TILES = [
+    (dict(T=8192, d=4096, n_blocks=64, block_size=1024, top_e=4, top_k=256), True),
+    (dict(T=4096, d=4096, n_blocks=256, block_size=1024, top_e=8, top_k=512), True),
+    (dict(T=2048, d=1024, n_blocks=64, block_size=256, top_e=4, top_k=128), True),
+    (dict(T=305, d=640, n_blocks=72, block_size=144, top_e=5, top_k=34), False),          # one k tile
+    (dict(T=3480, d=768, n_blocks=88, block_size=192, top_e=1, top_k=10), False),
+    (dict(T=1400, d=768, n_blocks=4, block_size=1024, top_e=1, top_k=64), False),         # 48 tiles of 256 rows
+    (dict(T=1536, d=4096, n_blocks=64, block_size=300, top_e=2, top_k=64), False),        # 512 rows for 300
+]
+
+
+@pytest.mark.parametrize("kw, wide", GRADIENT_TILES, ids=lambda v: f"T{v['T']}_d{v['d']}" if isinstance(v, dict) else str(v))
+def test_rows_of_a_weight_gradient_tile(kw, wide):
+    names = [n for n in _names(["bwd"], dtype="bf16", **kw) if _has([n], "ProbNeuTN")]
+    assert len(names) == 2 and all(_has([n], "gemm_wide_kernel" if wide else "gemm_mfma_kernel") for n in names), names
