@@ -8,7 +8,7 @@ pytestmark = pytest.mark.gpu
 
 GATHERED = [  # T, d, N, neurons in the union, top_k
     (1700, 512, 5000, 3111, 8), (2100, 1024, 4096, 4096, 4),
-    (8100, 960, 900, 801, 4), (2100, 960, 1500, 1025, 4), (8100, 448, 2000, 1999, 2),
+    (8100, 960, 900, 801, 4), (2100, 960, 1500, 1025, 4), (8100, 448, 2000, 1999, 2), (1100, 2048, 24576, 20001, 20),
 ]
 SMALL = [(1500, 4096, 2048, 1025, 16), (9000, 320, 1300, 1100, 3)]
 

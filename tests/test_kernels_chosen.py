@@ -7,7 +7,7 @@ from tests.test_gpu_not_finite import PAIRS
 from tests.test_gpu_pair_rows import ONE_KERNEL, TWO_KERNELS
 from tests.test_gpu_select_bound import CASES
 from tests.test_gpu_union_rows import GATHERED, SMALL
-from tests.test_gpu_wide_tiles import SPLIT
+from tests.test_gpu_wide_tiles import ALONE, EDGES, GRADIENTS, MASKED, SCORES, SPLIT, VALUES, group_sizes
 
 
 def _names(calls, flags=0, **kw):
@@ -58,6 +58,13 @@ def test_pairs_of_the_per_pair_backward():
             assert _has(names, kernel) and _has(names, "pair_one") == (T * k <= 20480), (T, d, nb, bs, k, names)
 
 
+def test_gathered_rows_on_tiles_of_256_rows_and_of_128():
+    names = [n for T, d, N, _, k in GATHERED
+             for n in _names(["union_fwd", "union_bwd"], T=T, d=d, n_blocks=1, block_size=N, top_e=1, top_k=k, dtype="bf16")]
+    for policy in ("TokKCRowsILi2E", "TokKCRowsILi1E", "TokNCRows", "NeuTNRows"):
+        assert all(any(_has([n], kernel) and _has([n], policy) for n in names) for kernel in ("gemm_wide_kernel", "gemm_mfma_kernel")), policy
+
+
 @pytest.mark.parametrize("call", ["union_fwd", "union_bwd"])
 def test_rows_of_the_batch_union(call):
     for cases, gathered in ((GATHERED, True), (SMALL, False)):
@@ -66,10 +73,14 @@ def test_rows_of_the_batch_union(call):
             assert _has(names, "gather_rows") != gathered and _has(names, "NCRows") == gathered, (T, d, N, k, names)
 
 
-def test_lists_that_every_xcd_holds_on_tiles_of_256_rows():
+def test_tiles_of_256_rows():
+    for sizes, kw, wide in EDGES:
+        names = _names(["fwd", "bwd"], T=sum(group_sizes(sizes, kw["n_blocks"])), top_e=1, dtype="bf16", **kw)
+        got = {p for p in (SCORES, MASKED, VALUES, GRADIENTS, ALONE) for n in names if _has([n], "gemm_wide_kernel") and _has([n], p)}
+        assert got == set(wide), (kw, names)
     for kw in SPLIT:
-        wide = [n for n in _names(["fwd", "bwd"], dtype="bf16", **kw) if _has([n], "gemm_wide_kernel")]
-        assert kw["n_blocks"] < 8 and all(_has(wide, p) for p in ("ProbTokKCILi3E", "ProbTokKCILi1E", "ProbTokNC")), (kw, wide)
+        names = [n for n in _names(["fwd", "bwd"], dtype="bf16", **kw) if _has([n], "gemm_wide_kernel")]
+        assert kw["n_blocks"] < 8 and all(_has(names, p) for p in (SCORES, MASKED, VALUES)), (kw, names)
 
 
 # Forms of a token-major contraction, where the rounds of tiles decide: (call, shape, policy, on tiles of 256 rows?)
