@@ -149,14 +149,15 @@ struct ProbTokKC {
     if (n >= bsp) return;   // bsp is even: n + 1 < bsp
     *reinterpret_cast<uint32_t*>(DS + at) = keep(pk, n, mk);
   }
-  // Nontemporal, here and in the other problems' store16: the next kernel reads it, which is larger than L2 or finds it in the
-  // memory-side cache; the lines that L2 keeps are the operands'.  us per step, plain / nontemporal: 8192 tokens, 64 blocks of
-  // 1024 x 4096 2126 / 2078; 1500 tokens, 64 of 512, top 8 708 / 676; 6000, 64 of 512 x 1024 368 / 359.
-  // the same for 16 bytes of a row: four columns of fp32, or eight of bf16 (bsp % 64 == 0: all of them inside)
+  // the same for 16 bytes of a row: eight columns of bf16 (bsp % 64 == 0: all of them inside)
   __device__ u32x4 load_aux16(const TileCoord& tc, int m, int n) const {
     const int mm = m < tc.Mrows ? m : tc.Mrows - 1, nn = n < bsp ? n : bsp - 8;
     return *reinterpret_cast<const u32x4_dw*>(Ap + (size_t)(tc.slot0 + mm) * bsp + nn);
   }
+  // 16 bytes: four columns of fp32, or eight of bf16.  Nontemporal, in the other problems' store16 too: the next kernel reads it, which
+  // is larger than L2 or finds it in the memory-side cache; the lines that L2 keeps are the operands'.  us per step, plain /
+  // nontemporal: 8192 tokens, 64 blocks of 1024 x 4096 2126 / 2078; 1500 tokens, 64 of 512, top 8 708 / 676; 6000, 64 of 512 x 1024
+  // 368 / 359.  (The last columns of a row whose length is no multiple of four are stored one by one, through L2.)
   __device__ void store16(size_t at, int n, u32x4 v, u32x4 mk) const {
     if constexpr (tok_fp32_out(MODE)) {
       if (n + 4 <= bs) {

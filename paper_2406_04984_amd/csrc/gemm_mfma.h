@@ -145,14 +145,21 @@ struct TileCoord {
 //   static constexpr bool kAux;  true: __device__ uint32_t load_aux(const TileCoord&, int m, int n) const;   a word
 //                the policy wants next to the two values of (m, n), e.g. a mask; called for every position of the
 //                tile, stored or not, so the policy clamps m and n to valid ones
+// and for gemm_wide_kernel (kTM 256) instead of the last three
+//   __device__ void store16(size_t at, int n, u32x4 v, u32x4 aux) const;   16 bytes of a row at element offset `at` (= row_off + n):
+//                eight columns of bf16 (n a multiple of 8) or four of fp32 (a multiple of 4).  The first column of the 64 (fp32: 32)
+//                that n is among is below out_cols; the policy checks the rest where out_cols is no multiple of that.  `at` is
+//                aligned to four bytes where rows may have an odd length
+//   __device__ u32x4 load_aux16(const TileCoord&, int m, int n) const;   (kAux) 16 bytes next to the eight values from (m, n) on, also
+//                outside the group and the output, so the policy clamps m and n
 
 // Workgroup barrier of a compute wave: it first waits for its own LDS traffic.  (A loader wave waits for the
 // operand loads that have to have landed instead.)
 #define MEFT_BARRIER_LDS() asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory")
 
 // P::kCW compute waves (the first waves of the workgroup) and P::kLoaders loader waves (two, or four where the
-// loaders' own instruction stream paces the loads: row numbers to look up, an address to form per load; none where
-// the compute waves load).  Measured on gfx950 the operand path, not the matrix cores or LDS latency, bounds these
+// loaders' own instruction stream paces the loads: row numbers to look up, an address to form per load).  Measured on gfx950 the
+// operand path, not the matrix cores or LDS latency, bounds these
 // contractions (a compute unit keeps about a hundred 128-byte read requests in flight on average), and with four
 // compute waves a wave that both requests operands and issues MFMAs keeps neither queue full.  The workgroup is persistent: it works through tiles wg, wg + gridDim.x, ...
 // (gridDim.x is a multiple of 8, so it stays on one XCD's list).
@@ -188,7 +195,7 @@ __global__ __launch_bounds__(gemm_threads<P>(), 1) void gemm_mfma_kernel(P p, in
   // ---------------------------------------------------------------------- operand requests
   // (state and steps of a loader wave; dead code in the compute waves)
     const int lw = wave - kCW;
-    constexpr int LA = TM / 8 / kLoaders;    // A wave-loads (1 KB each) per loader and slot: 12, 8, 6 or 4
+    constexpr int LA = TM / 8 / kLoaders;    // A wave-loads (1 KB each) per loader and slot: 8 or 4
     constexpr int LB = kTN / 8 / kLoaders;   // B wave-loads (1 KB each) per loader and slot: 16 or 8
     constexpr int DA = SA - 1;               // positions ahead of the barrier at which they are requested
     constexpr int kAhead = (DA - 1) * (LA + LB);   // loads that may still be in flight at a barrier
@@ -212,8 +219,7 @@ __global__ __launch_bounds__(gemm_threads<P>(), 1) void gemm_mfma_kernel(P p, in
     // A, k-contiguous: a wave-load covers 8 rows (m) x 128 bytes; fixed row pointers per tile, advanced by k.
     // A, m-contiguous, 128 rows: a wave-load covers 4 rows (k) x 256 bytes; lane l fetches the 16-byte chunk
     //   (l & 15) ^ (4 * (row & 3)) of its row (the LDS swizzle; row & 3 == (l >> 4) & 3 for every load), so one
-    //   column offset per tile serves all the loads.  With 256 rows the slot has the shape of an n-contiguous B slot
-    //   and is filled the same way.
+    //   column offset per tile serves all the loads.
     // B, k-contiguous: like A, 8 rows (n) x 128 bytes.
     // B, n-contiguous: a wave-load covers two k rows (lanes 0..31 the even one, lanes 32..63 the odd one), 512 bytes
     //   of each; lane l fetches the chunk (l & 31) ^ (2 * (row & 7)); row & 7 only depends on i & 3, so four
