@@ -78,12 +78,15 @@ def kernel_models(cfg, n_touched):
 
 # profiler name of the kernel behind each stage label (the rocprofv3 summaries list kernels by symbol)
 STAGE_SYMBOL = {
-    "router_gemm": "gemm_mfma_kernel<ProbRouter, true>", "score_gemm": ("gemm_mfma_kernel<ProbTokKC<3>, true>", "gemm_mfma_kernel<ProbTokKC<0>, true>"),
-    "dact_gemm": "gemm_mfma_kernel<ProbTokKC<1>, true>", "value_gemm": "gemm_mfma_kernel<ProbTokNC, true>",
-    "dh_gemm": "gemm_mfma_kernel<ProbTokNC, true>",
-    # dV / dK: the tile height is chosen per shape (256 rows where the block fills them, else 128)
-    "dV_gemm": ("gemm_mfma_kernel<ProbNeuTN<256>, true>", "gemm_mfma_kernel<ProbNeuTN<128>, true>"),
-    "dK_gemm": ("gemm_mfma_kernel<ProbNeuTN<256>, true>", "gemm_mfma_kernel<ProbNeuTN<128>, true>"),
+    "router_gemm": "gemm_mfma_kernel<ProbRouter, true>",
+    # the contractions: 256-row tiles where the problem fills them, else 128-row ones
+    "score_gemm": ("gemm_wide_kernel<WideTok<ProbTokKC<3> > >", "gemm_wide_kernel<WideTok<ProbTokKC<0> > >",
+                   "gemm_mfma_kernel<ProbTokKC<3>, true>", "gemm_mfma_kernel<ProbTokKC<0>, true>"),
+    "dact_gemm": ("gemm_wide_kernel<WideTok<ProbTokKC<1> > >", "gemm_mfma_kernel<ProbTokKC<1>, true>"),
+    "value_gemm": ("gemm_wide_kernel<WideTok<ProbTokNC> >", "gemm_mfma_kernel<ProbTokNC, true>"),
+    "dh_gemm": ("gemm_wide_kernel<WideTok<ProbTokNC> >", "gemm_mfma_kernel<ProbTokNC, true>"),
+    "dV_gemm": ("gemm_wide_kernel<ProbNeuTN<256> >", "gemm_mfma_kernel<ProbNeuTN<128>, true>"),
+    "dK_gemm": ("gemm_wide_kernel<ProbNeuTN<256> >", "gemm_mfma_kernel<ProbNeuTN<128>, true>"),
     "topk_select": ("topk_select_reg_kernel<16, true>", "topk_select_reg_kernel<32, true>", "topk_select_reg_kernel<4, true>"),
     "out_rows": "token_rows_kernel<2, false, true>", "dh_rows": "token_rows_kernel<2, false, true>",
 }
