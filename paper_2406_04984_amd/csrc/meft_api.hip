@@ -985,16 +985,17 @@ void launch_bwd_head(const meft_shape& s, const int32_t* flag, int32_t* chunk_cn
 // each 15.3 / 14.6; 72 blocks of 144 x 640, 21 each 7.8 / 9.4 (a tile's end takes longer than its k tile); 15 blocks of 1024 x 1280, 168
 // each 19 / 22; one block of 960 x 1216, 1328 tokens 19 / 33 (20 tiles of 256 rows).  Over 149 contractions of random layers and unions
 // this takes 3 % longer than the better form of each would, 256 rows always 30 %.
-//   Gradients of 96 MB and more go to 256 rows, whose stores pass the caches by: those of the 128 rows push K and V out of the
-// memory-side cache, from where the other contractions read them.  us per pass on 128 / 256 rows: 388 tokens, 4 of 120 blocks of 208 x
-// 4288 (214 MB) 418 / 381, of which dV and dK 104 / 111; 3579 tokens, 3 of 220 blocks of 224 x 3584 (353 MB) 710 / 645; 451 tokens, 6 of
-// 237 blocks of 208 x 1280 (126 MB) 265 / 245; 1437 tokens, 8 of 101 blocks of 720 x 576 (84 MB) 353 / 387.  Groups of up to four tokens
-// are summed pair by pair but for a few, and nothing is found sooner by fewer waves (70 blocks, one token each 3.8 / 2.2 per launch).
+//   Gradients of 48 MB and more each go to 256 rows, whose stores pass the caches by: those of the 128 rows push K and V out of the
+// memory-side cache (256 MB), from where the other contractions read them.  us per pass on 128 / 256 rows: 388 tokens, 4 of 120 blocks
+// of 208 x 4288 (214 MB) 418 / 381, of which dV and dK 104 / 111; 3579 tokens, 3 of 220 blocks of 224 x 3584 (353 MB) 710 / 645; 448
+// tokens, 6 of 236 blocks of 192 x 640 (58 MB) 171 / 166; 808 tokens, 2 of 40 blocks of 720 x 768 (44 MB) 128 / 127.  Groups of up to
+// four tokens are summed pair by pair but for a few, and nothing is found sooner by fewer waves (70 blocks, one token each 3.8 / 2.2
+// per launch).
 bool wide_neu(const meft_shape& s) {
   const int64_t n_ent = (int64_t)s.T * s.top_e, groups = s.n_blocks < n_ent ? s.n_blocks : n_ent, rows = n_ent / groups;
   const int64_t tm256 = (s.block_size + 255) / 256, tm128 = (s.block_size + 127) / 128;
   if (2 * tm256 != tm128) return false;
-  if (rows <= 4 || (int64_t)s.N * s.d * 2 >= (96ll << 20)) return true;
+  if (rows <= 4 || (int64_t)s.N * s.d * 2 >= (48ll << 20)) return true;
   const int64_t nk = (rows + kTK - 1) / kTK, tn = (s.d + kTN - 1) / kTN, cu = kPersistentWgs / kXcd;
   auto rounds = [&](int64_t tm) {   // lists of fewer groups than XCDs: each XCD takes a part of every group's tiles
     const int64_t tiles = groups < kXcd ? (groups * tm * tn + kXcd - 1) / kXcd : (groups + kXcd - 1) / kXcd * tm * tn;

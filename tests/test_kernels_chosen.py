@@ -110,6 +110,8 @@ GRADIENT_TILES = [
     (dict(T=8192, d=4096, n_blocks=64, block_size=1024, top_e=4, top_k=256), True),
     (dict(T=4096, d=4096, n_blocks=256, block_size=1024, top_e=8, top_k=512), True),
     (dict(T=2048, d=1024, n_blocks=64, block_size=256, top_e=4, top_k=128), True),
+    (dict(T=448, d=640, n_blocks=236, block_size=192, top_e=6, top_k=194), True),         # 58 MB
+    (dict(T=808, d=768, n_blocks=40, block_size=720, top_e=2, top_k=56), False),          # 44 MB
     (dict(T=305, d=640, n_blocks=72, block_size=144, top_e=5, top_k=34), False),          # one k tile
     (dict(T=3480, d=768, n_blocks=88, block_size=192, top_e=1, top_k=10), False),
     (dict(T=1400, d=768, n_blocks=4, block_size=1024, top_e=1, top_k=64), False),         # 48 tiles of 256 rows
