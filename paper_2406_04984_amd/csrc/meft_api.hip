@@ -983,8 +983,8 @@ void launch_bwd_head(const meft_shape& s, const int32_t* flag, int32_t* chunk_cn
 // tokens or more for it (then both wait for the stores of the rows).  Every group has the same tiles.  us per launch on 128 / 256 rows:
 // 64 blocks of 1024 x 4096, 512 tokens each 355 / 320; 256 unbalanced ones, 128 each on average 314 / 303; 64 blocks of 256 x 1024, 128
 // each 15.3 / 14.6; 72 blocks of 144 x 640, 21 each 7.8 / 9.4 (a tile's end takes longer than its k tile); 15 blocks of 1024 x 1280, 168
-// each 19 / 22; one block of 960 x 1216, 1328 tokens 19 / 33 (20 tiles of 256 rows).  Over 149 contractions of random layers and unions
-// this takes 3 % longer than the better form of each would, 256 rows always 30 %.
+// each 19 / 22; one block of 960 x 1216, 1328 tokens 19 / 33 (20 tiles of 256 rows).  Over 111 contractions of random layers and unions
+// with smaller gradients this takes 1 % longer than the better form of each would, 256 rows always 34 %.
 //   Gradients of 48 MB and more each go to 256 rows, whose stores pass the caches by: those of the 128 rows push K and V out of the
 // memory-side cache (256 MB), from where the other contractions read them.  us per pass on 128 / 256 rows: 388 tokens, 4 of 120 blocks
 // of 208 x 4288 (214 MB) 418 / 381, of which dV and dK 104 / 111; 3579 tokens, 3 of 220 blocks of 224 x 3584 (353 MB) 710 / 645; 448
